@@ -57,6 +57,21 @@ static void dfree(T*& ptr) {
   ptr = nullptr;
 }
 
+// (c, tau) of e^{2 pi i m / 4096}, c = cos rounded to FP32 and tau such that c tau is sin
+// to one rounding; where cos vanishes c is 2^-30 (block_fft.h).
+static int upload_tangents(float2** ct) {
+  std::vector<float2> h(4096);
+  for (int m = 0; m < 4096; ++m) {
+    const double a = 2.0 * M_PI * m / 4096.0;
+    const float c = m % 2048 == 1024 ? 0x1p-30f : (float)cos(a);
+    h[m] = make_float2(c, (float)(sin(a) / (double)c));
+  }
+  int rc = dalloc(ct, h.size());
+  if (rc) return rc;
+  RFD_HIP(hipMemcpy(*ct, h.data(), h.size() * sizeof(float2), hipMemcpyHostToDevice));
+  return RFD_OK;
+}
+
 static bool is_pow2(int64_t x) { return x > 0 && (x & (x - 1)) == 0; }
 
 static int upload_table(Plan& p, int64_t len, int64_t step, int64_t den, float2** t32, double2** t64) {
@@ -144,7 +159,7 @@ static void plan_free(Plan& p) {
   dfree(p.work64b); dfree(p.dref_sig2); dfree(p.dref_scale); dfree(p.dref_part);
   dfree(p.zref); dfree(p.zbf_hi); dfree(p.zbf_lo); dfree(p.zh_hi); dfree(p.zh_lo);
   dfree(p.slots); dfree(p.counts); dfree(p.total); dfree(p.fc_work); dfree(p.counter);
-  dfree(p.ols_tw32); dfree(p.ols_tw64);
+  dfree(p.ols_tw32); dfree(p.ols_tw64); dfree(p.ols_ct32);
   for (auto& z : p.zband) dfree(z);
 }
 
@@ -343,6 +358,7 @@ int rfd_plan_create(const double* psd, int64_t n_psd, double f_low, double fs, i
   TRY(upload_table(p, p.n1, 1, p.n1, &p.tw32_n1, &p.tw64_n1));
   TRY(upload_table(p, p.n2, 1, p.n2, &p.tw32_n2, &p.tw64_n2));
   TRY(upload_table(p, 4096, 1, 4096, &p.ols_tw32, &p.ols_tw64));
+  TRY(upload_tangents(&p.ols_ct32));
   TRY(dalloc(&p.stilde64, nb));
   TRY(dalloc(&p.stilde, nb));
   TRY(dalloc(&p.work64, n));

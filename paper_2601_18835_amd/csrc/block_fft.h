@@ -37,19 +37,114 @@ __device__ __forceinline__ void dft4_prod(float2& a, float2& b, float2& c, float
   d = csub(s1, s3);
 }
 
-// Second half of the 16-point DFT (after the first radix-4 layer over n2).
+// A twiddle w = c (1 + i tau) in the form the butterflies below take: (c, tau).
+// Where Re w = 0 the table holds a c of 2^-30 (see ols_ct32): the product with
+// w is then off by 2^-30, below FP32 rounding.
+//
+// a +- w b as t = b (1 + i tau), a +- c t: six fused multiply-adds instead of the
+// eight operations of a complex product and two sums, with one rounding of
+// the product instead of two.
+__device__ __forceinline__ void bf_tw(float2& a, float2& b, float2 w) {
+  const float2 t = make_float2(fmaf(-w.y, b.y, b.x), fmaf(w.y, b.x, b.y));
+  b = make_float2(fmaf(-w.x, t.x, a.x), fmaf(-w.x, t.y, a.y));
+  a = make_float2(fmaf(w.x, t.x, a.x), fmaf(w.x, t.y, a.y));
+}
+// the same with the twiddle s i w (s = +-1)
+__device__ __forceinline__ void bf_tw_si(float2& a, float2& b, float2 w, int s) {
+  const float2 t = make_float2(fmaf(-w.y, b.y, b.x), fmaf(w.y, b.x, b.y));
+  const float c = s > 0 ? w.x : -w.x;
+  b = make_float2(fmaf(c, t.y, a.x), fmaf(-c, t.x, a.y));
+  a = make_float2(fmaf(-c, t.y, a.x), fmaf(c, t.x, a.y));
+}
+// 4-point DFT of (a, w b, w^2 c, w^3 d) from the twiddles w2 = w^2 and w
+__device__ __forceinline__ void dft4_tw(float2& a, float2& b, float2& c, float2& d, float2 w2, float2 w, int sign) {
+  bf_tw(a, c, w2);
+  bf_tw(b, d, w2);
+  bf_tw(a, b, w);              // outputs 0 and 2
+  bf_tw_si(c, d, w, sign);     // outputs 1 and 3
+  const float2 x2 = b;
+  b = c;
+  c = x2;
+}
+// ... with the twiddles s i w2 and w
+__device__ __forceinline__ void dft4_tw_i(float2& a, float2& b, float2& c, float2& d, float2 w2, float2 w, int sign) {
+  bf_tw_si(a, c, w2, sign);
+  bf_tw_si(b, d, w2, sign);
+  bf_tw(a, b, w);
+  bf_tw_si(c, d, w, sign);
+  const float2 x2 = b;
+  b = c;
+  c = x2;
+}
+
+// Second half of the 16-point DFT (after the first radix-4 layer over n2):
+// for each k the 4-point DFT of v[4 k + n1] w_16^(n1 k).
 template <int SIGN>
 __device__ __forceinline__ void dft16_rest(float2 (&v)[16]) {
+  constexpr float c1 = 0.92387953251128674f, t1 = 0.41421356237309503f;   // cos, tan of pi / 8
+  constexpr float c3 = 0.38268343236508977f, t3 = 2.41421356237309515f;   // of 3 pi / 8
+  constexpr float r = 0.70710678118654752f;
+  dft4(v[0], v[1], v[2], v[3], SIGN);
+  dft4_tw(v[4], v[5], v[6], v[7], make_float2(r, SIGN), make_float2(c1, SIGN * t1), SIGN);
+  {                                                     // k = 2: w^2 is a quarter turn
+    float2 s0 = v[8], s1 = v[9];
+    const float2 c = cmul_si(v[10], SIGN), d = cmul_si(v[11], SIGN);
+    float2 m0 = csub(s0, c), m1 = csub(s1, d);
+    s0 = cadd(s0, c);
+    s1 = cadd(s1, d);
+    bf_tw(s0, s1, make_float2(r, SIGN));
+    bf_tw_si(m0, m1, make_float2(r, SIGN), SIGN);
+    v[8] = s0;
+    v[9] = m0;
+    v[10] = s1;
+    v[11] = m1;
+  }
+  dft4_tw_i(v[12], v[13], v[14], v[15], make_float2(r, SIGN), make_float2(c3, SIGN * t3), SIGN);
+}
+
+// Twiddles of a 16-point DFT of x[q] w^q (w any unit complex number), as (c, tau):
+// w^8, w^4, w^2, w^2 w_8, w, w w_16, w w_16^2, w w_16^3: the other factors that its
+// radix-2 layers need are quarter turns of these.  Of an 8-point one: w^4,
+// w^2, w, w w_8; of a 4-point one: w^2, w.
+// Taking the inter-stage twiddles inside the butterflies like this costs
+// 192 operations per 16 points, against 60 for 15 products and 160 for a plain
+// DFT after them.
+constexpr int kTw16 = 8;
+// entry i of those of an R-point DFT at w = e^{2 pi i m / 4096}: its exponent over 4096
+template <int R>
+__device__ __forceinline__ constexpr int tw_exponent(int i, int m) {
+  if (R == 16) return (i == 0 ? 8 * m : i == 1 ? 4 * m : i < 4 ? 2 * m + 512 * (i - 2) : m + 256 * (i - 4)) & 4095;
+  if (R == 8) return (i == 0 ? 4 * m : i == 1 ? 2 * m : m + 512 * (i - 2)) & 4095;
+  return (i == 0 ? 2 * m : m) & 4095;
+}
+// DFTs (R = 4, 8, 16) of v[g R + u] w_g^u on consecutive groups of R slots; slot
+// order of the results as dft_r.  w(i): entry i of the 16 / R groups' twiddles, group by group.
+template <int R, int SIGN, typename W>
+__device__ __forceinline__ void dft_tw(float2 (&v)[16], const W& w) {
+  if constexpr (R == 16) {
+    const float2 w8 = w(0), w4 = w(1), w2 = w(2), w2b = w(3);
 #pragma unroll
-  for (int n1 = 1; n1 < 4; ++n1)
+    for (int n1 = 0; n1 < 4; ++n1) dft4_tw(v[n1], v[n1 + 4], v[n1 + 8], v[n1 + 12], w8, w4, SIGN);
+    dft4_tw(v[0], v[1], v[2], v[3], w2, w(4), SIGN);
+    dft4_tw(v[4], v[5], v[6], v[7], w2b, w(5), SIGN);
+    dft4_tw_i(v[8], v[9], v[10], v[11], w2, w(6), SIGN);
+    dft4_tw_i(v[12], v[13], v[14], v[15], w2b, w(7), SIGN);
+  } else if constexpr (R == 8) {
 #pragma unroll
-    for (int k = 1; k < 4; ++k) {
-      // a quarter turn is a swap (a product with the constant 0 would be kept)
-      const int p = n1 * k;
-      v[n1 + 4 * k] = p == 4 ? cmul_si(v[n1 + 4 * k], SIGN) : cmul(v[n1 + 4 * k], w16(p, SIGN));
+    for (int g = 0; g < 2; ++g) {
+      float2* u = v + 8 * g;
+      dft4_tw(u[0], u[2], u[4], u[6], w(4 * g), w(4 * g + 1), SIGN);
+      dft4_tw(u[1], u[3], u[5], u[7], w(4 * g), w(4 * g + 1), SIGN);
+      bf_tw(u[0], u[1], w(4 * g + 2));
+      bf_tw(u[2], u[3], w(4 * g + 3));
+      bf_tw_si(u[4], u[5], w(4 * g + 2), SIGN);
+      bf_tw_si(u[6], u[7], w(4 * g + 3), SIGN);
     }
+  } else {
 #pragma unroll
-  for (int k = 0; k < 4; ++k) dft4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3], SIGN);
+    for (int g = 0; g < 4; ++g)
+      dft4_tw(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3], w(2 * g), w(2 * g + 1), SIGN);
+  }
 }
 
 // 16-point DFT in registers, V[k] = sum_n v[n] e^{sign 2 pi i n k / 16}.
@@ -135,63 +230,43 @@ struct BlockFft {
   static constexpr int LDS = X1 > X2 ? X1 : X2;      // float2 per FFT
 };
 
-// Per-thread twiddles: stage A  W_K^(t k1), stage B  W_K^(16 u k2), k = 1..15.
+// Twiddles of the transform.  With m = t + NTf r, t = u + R q and the output index
+// k1 + 16 k2 + 256 k3, stage A's DFT over r needs none, stage B's over q takes
+// w = e^{2 pi i k1 / 256} and stage C's over u takes w = e^{2 pi i (k1 + 16 k2) / K}; each
+// stage takes its w inside its butterflies (dft_tw).  A thread keeps the eight of stage C
+// in registers (16 / R groups of k2); stage B's depend on k1 only, so a workgroup
+// table of 16 rows in LDS serves every thread.
+constexpr int kTwbStride = 9;    // row stride of the table: the rows' reads meet distinct banks
+constexpr int kTwbSize = 16 * kTwbStride;
 template <int K>
 struct BlockFftTw {
-  float2 a[16], b[16];
+  float2 c[kTw16];
+  const float2* b;    // LDS row of this thread's k1
 };
-template <int K, int SIGN>
-__device__ __forceinline__ void block_fft_twiddles(BlockFftTw<K>& w, const float2* __restrict__ tw, int t) {
-  using S = BlockFft<K>;
-  constexpr int step = 4096 / K;
-  const int u = t % S::R;
-#pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    float2 x = tw[((t * k) % K) * step];
-    float2 y = tw[((16 * u * k) % K) * step];
-    if (SIGN < 0) { x.y = -x.y; y.y = -y.y; }
-    w.a[k] = x;
-    w.b[k] = y;
-  }
-}
-
-// The same twiddles with stage B's taken from a workgroup table in LDS: they
-// depend on u = t % R only, so R x 16 values serve every thread, and the 32
-// registers they would hold stay free (for the next operands in flight).
-template <int K>
-struct BlockFftTwL {
-  float2 a[16];
-  const float2* bl;   // LDS row of this thread's u: bl[k] = W_K^(16 u k)
-};
-constexpr int kTwbStride = 17;   // odd row stride: the R rows' reads meet distinct banks
-template <int K>
-__host__ __device__ constexpr int block_fft_twb_size() { return (K / 256) * kTwbStride; }
 // Fills the table (every thread of the workgroup calls it; a barrier must
-// follow before the first block_fft) and this thread's stage-A twiddles.
+// follow before the first block_fft) and this thread's stage-C twiddles.
+// ct: the (c, tau) of e^{2 pi i m / 4096}, m < 4096.
 template <int K, int SIGN>
-__device__ __forceinline__ void block_fft_twiddles_lds(BlockFftTwL<K>& w, const float2* __restrict__ tw, int t,
-                                                       float2* table) {
+__device__ __forceinline__ void block_fft_twiddles(BlockFftTw<K>& w, const float2* __restrict__ ct, int t,
+                                                   float2* table) {
   using S = BlockFft<K>;
-  constexpr int step = 4096 / K;
-  for (int e = threadIdx.x; e < S::R * 16; e += 256) {
-    const int u = e / 16, k = e % 16;
-    float2 y = tw[((16 * u * k) % K) * step];
-    if (SIGN < 0) y.y = -y.y;
-    table[u * kTwbStride + k] = y;
-  }
-#pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    float2 x = tw[((t * k) % K) * step];
+  if (threadIdx.x < 16 * kTw16) {
+    const int k1 = threadIdx.x / kTw16, i = threadIdx.x % kTw16;
+    float2 x = ct[tw_exponent<16>(i, 16 * k1)];
     if (SIGN < 0) x.y = -x.y;
-    w.a[k] = x;
+    table[k1 * kTwbStride + i] = x;
   }
-  w.bl = table + (t % S::R) * kTwbStride;
+  const int k1 = t / S::R, g = t % S::R;
+  constexpr int per = kTw16 * S::R / 16;      // entries per group
+#pragma unroll
+  for (int i = 0; i < kTw16; ++i) {
+    const int m = (k1 + 16 * (g * S::G + i / per)) * (4096 / K);
+    float2 x = ct[tw_exponent<S::R>(i % per, m)];
+    if (SIGN < 0) x.y = -x.y;
+    w.c[i] = x;
+  }
+  w.b = table + k1 * kTwbStride;
 }
-// stage-B twiddle W_K^(16 u k) of either form
-template <int K>
-__device__ __forceinline__ float2 twb(const BlockFftTw<K>& w, int k) { return w.b[k]; }
-template <int K>
-__device__ __forceinline__ float2 twb(const BlockFftTwL<K>& w, int k) { return w.bl[k]; }
 
 // Exchange barrier: one wave per FFT (K = 1024) needs only wave-level
 // ordering of its LDS traffic, so the workgroup's four FFTs run
@@ -210,41 +285,38 @@ __device__ __forceinline__ void block_fft_sync() {
 // K-point DFT of v (thread t of its FFT holds x[t + NTf r] in v[r]) with
 // sign SIGN.  On return v[e * R + s] holds X[out_index(t, e, s)].  All
 // threads of the workgroup call it together (it synchronises).
-template <int K, int SIGN, typename TW>
-__device__ __forceinline__ void block_fft_after_a(float2 (&v)[16], float2* buf, int t, const TW& w);
+template <int K, int SIGN>
+__device__ __forceinline__ void block_fft_after_a(float2 (&v)[16], float2* buf, int t, const BlockFftTw<K>& w);
 
-template <int K, int SIGN, typename TW>
-__device__ __forceinline__ void block_fft(float2 (&v)[16], float2* buf, int t, const TW& w) {
+template <int K, int SIGN>
+__device__ __forceinline__ void block_fft(float2 (&v)[16], float2* buf, int t, const BlockFftTw<K>& w) {
   dft16<SIGN>(v);      // stage A: radix 16 over r
   block_fft_after_a<K, SIGN>(v, buf, t, w);
 }
 // The rest of block_fft once stage A's radix-16 DFT is in v (a caller can
 // form that DFT itself, e.g. with dft16_prod).
-template <int K, int SIGN, typename TW>
-__device__ __forceinline__ void block_fft_after_a(float2 (&v)[16], float2* buf, int t, const TW& w) {
+template <int K, int SIGN>
+__device__ __forceinline__ void block_fft_after_a(float2 (&v)[16], float2* buf, int t, const BlockFftTw<K>& w) {
   using S = BlockFft<K>;
   constexpr int NTf = S::NTf, R = S::R;
 #pragma unroll
-  for (int s = 0; s < 16; ++s) {
-    const int k1 = dft16_freq(s);
-    buf[k1 * S::S1 + t] = k1 ? cmul(v[s], w.a[k1]) : v[s];
-  }
+  for (int s = 0; s < 16; ++s) buf[dft16_freq(s) * S::S1 + t] = v[s];
   block_fft_sync<NTf>();
-  // stage B: thread (k1, u) = (t / R, t % R), radix 16 over v of t' = u + R v
+  // stage B: thread (k1, u) = (t / R, t % R), radix 16 over q of t' = u + R q
   {
     const int k1 = t / R, u = t % R;
 #pragma unroll
     for (int q = 0; q < 16; ++q) v[q] = buf[k1 * S::S1 + u + R * q];
   }
   block_fft_sync<NTf>();
-  dft16<SIGN>(v);
+  dft_tw<16, SIGN>(v, [&](int i) { return w.b[i]; });
   {
     const int k1 = t / R, u = t % R;
     float2* row = buf + k1 * R + u;
 #pragma unroll
     for (int s = 0; s < 16; ++s) {
       const int k2 = dft16_freq(s);
-      row[k2 * 16 * R + k2 / S::G] = k2 ? cmul(v[s], twb(w, k2)) : v[s];
+      row[k2 * 16 * R + k2 / S::G] = v[s];
     }
   }
   block_fft_sync<NTf>();
@@ -259,7 +331,7 @@ __device__ __forceinline__ void block_fft_after_a(float2 (&v)[16], float2* buf, 
     }
   }
   block_fft_sync<NTf>();
-  dft_r<R, SIGN>(v);
+  dft_tw<R, SIGN>(v, [&](int i) { return w.c[i]; });
 }
 
 // Output index of slot e * R + s of thread t after block_fft.
@@ -269,6 +341,11 @@ __device__ __forceinline__ int block_fft_out(int t, int e, int s) {
   const int k1 = t / S::R, g = t % S::R;
   const int k2 = g * (16 / S::R) + e;
   return k1 + 16 * k2 + 256 * dftr_freq<S::R>(s);
+}
+// ... as an offset from that of slot 0 (the same for every thread)
+template <int K>
+__device__ __forceinline__ constexpr int block_fft_step(int e, int s) {
+  return 16 * e + 256 * dftr_freq<BlockFft<K>::R>(s);
 }
 
 }  // namespace rfd

@@ -195,7 +195,7 @@ struct FcRowArgs {
   const float2* Y;           // [count][N2][N1] (pass A output), or
   const float2* s;           // with no pass A: data spectrum and filters
   const float2* filt;
-  const float2* tw;          // e^{+2 pi i m / 4096}
+  const float2* ct;          // (c, tau) of e^{+2 pi i m / 4096}
   unsigned long long* slots;
   int64_t i_low, i_high, n_band;
   int64_t N2, count, tmpl0, nwin, W;
@@ -217,8 +217,10 @@ __global__ __launch_bounds__(256) void k_fc_rows(FcRowArgs a) {
   __shared__ float2 lds[S::F * S::LDS];
   const int f = threadIdx.x / S::NTf, t = threadIdx.x % S::NTf;
   const int64_t npairs = a.count * a.N2;
+  __shared__ float2 twb_table[kTwbSize];
   BlockFftTw<N1> w;
-  block_fft_twiddles<N1, 1>(w, a.tw, t);
+  block_fft_twiddles<N1, 1>(w, a.ct, t, twb_table);
+  __syncthreads();     // the twiddle table is complete
   [[maybe_unused]] float2 sv[16];      // data values (one-pass form: the same for every template)
   [[maybe_unused]] int32_t off[16];
   if constexpr (DIRECT) {
@@ -348,7 +350,7 @@ int launch_findchirp(Plan& p, const float2* filt, int64_t n_templates, int64_t W
       }
       RFD_CHECK_LAUNCH();
     }
-    FcRowArgs ra{p.fc_work, p.stilde, fb, p.ols_tw32, p.slots, p.i_low, p.i_high, p.n_band,
+    FcRowArgs ra{p.fc_work, p.stilde, fb, p.ols_ct32, p.slots, p.i_low, p.i_high, p.n_band,
                  N2, nb, t0, nwin, W, threshold * threshold, 1};
     if (N2 > 1) {
       launch_rows<kFcN1, false>(p, ra);

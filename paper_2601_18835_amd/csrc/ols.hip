@@ -44,16 +44,17 @@ __device__ __forceinline__ unsigned long long umax64_ols(unsigned long long a, u
 template <int K>
 __device__ __forceinline__ void ols_x_body(const float2* __restrict__ z, int64_t n, int k0, int L, int64_t nB,
                                            int64_t org, const float2* __restrict__ tw, float2* __restrict__ X,
-                                           uint32_t bx, float2* lds) {
+                                           uint32_t bx, float2* lds, float2* twb_table) {
   using S = BlockFft<K>;
   const int f = threadIdx.x / S::NTf, t = threadIdx.x % S::NTf;
   const int64_t b = (int64_t)bx * S::F + f;     // row of X: the block whose outputs start at org + b L
   BlockFftTw<K> w;
-  block_fft_twiddles<K, -1>(w, tw, t);
+  block_fft_twiddles<K, -1>(w, tw, t, twb_table);
   float2 v[16];
   const int64_t start = org + b * L + k0;
 #pragma unroll
   for (int r = 0; r < 16; ++r) v[r] = b < nB ? z[(start + t + S::NTf * r) & (n - 1)] : make_float2(0.f, 0.f);
+  __syncthreads();     // the twiddle table is complete
   block_fft<K, -1>(v, lds + f * S::LDS, t, w);
   if (b >= nB) return;
   float2* xb = X + b * K;
@@ -67,7 +68,8 @@ template <int K>
 __global__ __launch_bounds__(256) void k_ols_x(const float2* __restrict__ z, int64_t n, int k0, int L, int64_t nB,
                                             int64_t org, const float2* __restrict__ tw, float2* __restrict__ X) {
   __shared__ float2 lds[BlockFft<K>::F * BlockFft<K>::LDS];
-  ols_x_body<K>(z, n, k0, L, nB, org, tw, X, blockIdx.x, lds);
+  __shared__ float2 twb_table[kTwbSize];
+  ols_x_body<K>(z, n, k0, L, nB, org, tw, X, blockIdx.x, lds, twb_table);
 }
 
 // --------------------------------------------------------- tap spectra (FP64)
@@ -102,7 +104,7 @@ __global__ __launch_bounds__(256) void k_ols_g(const float2* __restrict__ c32, i
 struct OlsArgs {
   const float2* X;           // [nB][K] block spectra of this sub-bank's series
   const float2* G;           // [count][K] tap spectra
-  const float2* tw;          // exp(+2 pi i m / 4096), m < 4096
+  const float2* tw;          // (c, tau) of exp(+2 pi i m / 4096), m < 4096
   unsigned long long* slots;
   int64_t n, count, tmpl0, nwin, W, nB;   // nB: blocks of this launch (rows of X)
   int64_t org;               // first output sample of X's row 0 (block b: [org + b L, org + b L + L))
@@ -157,32 +159,37 @@ __device__ __forceinline__ OlsTile ols_tile() {
   return OlsTile{x0 + r % w, r / w};
 }
 
-// One workgroup's (block group bx, template group by) of a sub-bank.
+// One workgroup's (block group bx, template group by) of a sub-bank.  Sample
+// numbers fit 32 bits here (N <= 2^22).
 template <int K, int NF>
 __device__ __forceinline__ void ols_body(const OlsArgs& a, uint32_t bx, uint32_t by, float2* lds,
                                          float2* twb_table) {
   using S = BlockFft<K>;
-  const int f = threadIdx.x / S::NTf, t = threadIdx.x % S::NTf;
-  const int64_t b = (int64_t)bx * S::F + f;
+  const int t = threadIdx.x % S::NTf;
+  const int f = __builtin_amdgcn_readfirstlane(threadIdx.x / S::NTf);      // an FFT takes whole waves
+  const int b = (int)bx * S::F + f;
   const bool bvalid = b < a.nB;
-  BlockFftTwL<K> w;
-  block_fft_twiddles_lds<K, 1>(w, a.tw, t, twb_table);
+  BlockFftTw<K> w;
+  block_fft_twiddles<K, 1>(w, a.tw, t, twb_table);
   float2 xb[16];
-  const float2* Xb = a.X + (bvalid ? b : 0) * K;
+  const float2* Xb = a.X + (int64_t)(bvalid ? b : 0) * K;
 #pragma unroll
   for (int r = 0; r < 16; ++r) xb[r] = Xb[t + S::NTf * r];
   __syncthreads();     // the twiddle table is complete
   // this block's output samples and their windows (uniform per FFT)
-  const int64_t n0 = a.org + b * a.L;
-  const int64_t nbeg = std::max<int64_t>(n0, a.n_lo);
-  const int64_t nend = std::min<int64_t>(std::min<int64_t>(n0 + a.L, a.n), a.n_hi);
+  const int W = (int)a.W;
+  const int n0 = (int)a.org + b * a.L;
+  const int nbeg = std::max(n0, (int)a.n_lo);
+  const int nend = std::min(std::min(n0 + a.L, (int)a.n), (int)a.n_hi);
   const bool has_out = bvalid && nend > nbeg;
   // every kept slot is an output of the launch: no per-sample range test
   const bool whole = NF > 0 && has_out && nbeg == n0 && nend == n0 + a.L;
-  const int64_t q0 = has_out ? nbeg / a.W : 0, q1 = has_out ? (nend - 1) / a.W : 0;
+  const int q0 = has_out ? nbeg / W : 0, q1 = has_out ? (nend - 1) / W : 0;
   const int64_t j0 = (int64_t)by * a.J;
   const int64_t j1 = std::min<int64_t>(j0 + a.J, a.count);
   const bool lead = (threadIdx.x & 63) == 0;
+  // output offset of slot 0 within the block; slot (e, s) sits block_fft_step(e, s) further
+  const int out0 = block_fft_out<K>(t, 0, 0);
   // the next template's tap spectrum is fetched while the current one is
   // transformed (its loads would otherwise stall all waves of the FFT)
   float2 gn[16];
@@ -198,69 +205,60 @@ __device__ __forceinline__ void ols_body(const OlsArgs& a, uint32_t bx, uint32_t
     fetch_g(j + 1);     // unconditional (the last one rereads j0's): no merge of old and new registers
     block_fft_after_a<K, 1>(v, lds + f * S::LDS, t, w);
     if (!has_out) continue;
+    // the sample numbers of a thread's slots are formed anew for each template
+    // where they are needed (the empty statement hides that they repeat):
+    // carried through the loop they would take 32 registers
+    int o = out0;
+    asm volatile("" : "+v"(o));
+    // index of slot (e, s) past `from`: below `len` exactly when it lies in [from, from + len)
+    auto past = [&](int e, int s, int from) { return (uint32_t)(o + block_fft_step<K>(e, s) + n0 - from); };
     unsigned long long* slot = a.slots + (a.tmpl0 + j) * a.nwin;
     float r2[16];
+    // rho^2 of every kept slot, formed once ahead of the two branches below (the
+    // compiler otherwise keeps a copy per branch: 0.928 -> 0.887 ms at K = 4096).
+#pragma unroll
+    for (int e = 0; e < 16 / S::R; ++e)
+#pragma unroll
+      for (int s = 0; s < S::R; ++s) {
+        if (!ols_slot_kept<K, NF>(s)) continue;
+        const float2 y = v[e * S::R + s];
+        r2[e * S::R + s] = y.x * y.x + y.y * y.y;
+      }
     // maximum of the kept samples' rho^2 as bit patterns (non-negative floats
     // order as their bits).  The discarded outputs stay out: where the block's
     // correlation wraps, taps that cancel only against the series' own
     // correlations lose that cancellation and would cross the threshold.
     uint32_t r2max = 0u;
-    // rho^2 of every kept slot, then its maximum with or without the range
-    // test.  Where the FFT spans waves, rho^2 is formed once ahead of the two
-    // branches (the compiler otherwise keeps a copy per branch: 0.928 -> 0.887
-    // ms at K = 4096); the one-wave K = 1024 transform runs as fast or a little
-    // faster with it formed inside each branch (2.53 against 2.54 ms on one GPU).
-    constexpr bool kAhead = S::NTf > 64;
-    auto rho2 = [&](int i) {
-      if constexpr (kAhead) return r2[i];
-      const float2 y = v[i];
-      return r2[i] = y.x * y.x + y.y * y.y;
-    };
-    if constexpr (kAhead) {
-#pragma unroll
-      for (int e = 0; e < 16 / S::R; ++e)
-#pragma unroll
-        for (int s = 0; s < S::R; ++s) {
-          if (!ols_slot_kept<K, NF>(s)) continue;
-          const float2 y = v[e * S::R + s];
-          r2[e * S::R + s] = y.x * y.x + y.y * y.y;
-        }
-    }
     if (whole) {
 #pragma unroll
       for (int e = 0; e < 16 / S::R; ++e)
 #pragma unroll
-        for (int s = 0; s < S::R; ++s) {
-          if (!ols_slot_kept<K, NF>(s)) continue;
-          r2max = max(r2max, __float_as_uint(rho2(e * S::R + s)));
-        }
+        for (int s = 0; s < S::R; ++s)
+          if (ols_slot_kept<K, NF>(s)) r2max = max(r2max, __float_as_uint(r2[e * S::R + s]));
     } else {
 #pragma unroll
       for (int e = 0; e < 16 / S::R; ++e)
 #pragma unroll
-        for (int s = 0; s < S::R; ++s) {
-          if (!ols_slot_kept<K, NF>(s)) continue;
-          const float x = rho2(e * S::R + s);
-          const int64_t nn = n0 + block_fft_out<K>(t, e, s);
-          if (nn >= nbeg && nn < nend) r2max = max(r2max, __float_as_uint(x));
-        }
+        for (int s = 0; s < S::R; ++s)
+          if (ols_slot_kept<K, NF>(s) && past(e, s, nbeg) < (uint32_t)(nend - nbeg))
+            r2max = max(r2max, __float_as_uint(r2[e * S::R + s]));
     }
     // the compaction reports a window only if its peak exceeds thr2: a wave
     // with no sample above it cannot contribute a reported peak
     if (!__any(r2max > __float_as_uint(a.thr2))) continue;
     if (q1 - q0 < kOlsMaxWin) {
       // one reduction and one atomic per window the block touches
-      for (int64_t qw = q0; qw <= q1; ++qw) {
-        const int64_t wq = qw * a.W;
-        const int64_t ws = std::max<int64_t>(wq, nbeg), we = std::min<int64_t>(wq + a.W, nend);
+      for (int qw = q0; qw <= q1; ++qw) {
+        const int wq = qw * W;
+        const int ws = std::max(wq, nbeg), we = std::min(wq + W, nend);
         unsigned long long k = 0;
 #pragma unroll
         for (int e = 0; e < 16 / S::R; ++e)
 #pragma unroll
           for (int s = 0; s < S::R; ++s) {
             if (!ols_slot_kept<K, NF>(s)) continue;
-            const int64_t nn = n0 + block_fft_out<K>(t, e, s);
-            if (nn >= ws && nn < we) k = umax64_ols(k, offset_key_ols(r2[e * S::R + s], (uint32_t)(nn - wq)));
+            if (past(e, s, ws) < (uint32_t)(we - ws))
+              k = umax64_ols(k, offset_key_ols(r2[e * S::R + s], past(e, s, wq)));
           }
         k = ols_reduce<K>(k);
         if (lead) atomicMax(slot + qw, k);
@@ -272,20 +270,27 @@ __device__ __forceinline__ void ols_body(const OlsArgs& a, uint32_t bx, uint32_t
 #pragma unroll
         for (int s = 0; s < S::R; ++s) {
           if (!ols_slot_kept<K, NF>(s)) continue;
-          const int64_t nn = n0 + block_fft_out<K>(t, e, s);
-          if (nn >= nbeg && nn < nend) {
-            const int64_t q = nn / a.W;
-            atomicMax(slot + q, offset_key_ols(r2[e * S::R + s], (uint32_t)(nn - q * a.W)));
+          if (past(e, s, nbeg) < (uint32_t)(nend - nbeg)) {
+            const uint32_t q = past(e, s, 0) / (uint32_t)W;
+            atomicMax(slot + q, offset_key_ols(r2[e * S::R + s], past(e, s, (int)q * W)));
           }
         }
     }
   }
 }
 
+// Bound by VALU issue: 614 VALU instructions per wave and template at K = 4096 and
+// NF = 12 (four cycles each; 342 x 512 transforms on 256 CUs then take 0.70 ms at
+// 2.4 GHz, measured 0.73), 506 at K = 1024 and NF = 3.  With the twiddles taken as
+// products between the stages and the slots' sample numbers carried through the loop
+// in 64 bits it was 685 and 583, and 215 registers allowed two waves per SIMD; three
+// now fit (150 to 161 registers, none spilled).  Whole cases: 8 sub-banks of 512
+// templates, T = 1024, N = 2^20: 7.47 -> 6.25 ms; 4096 templates, T = 256, N = 2^19:
+// 2.73 -> 2.49 ms.
 template <int K, int NF>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_ols(OlsArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_ols(OlsArgs a) {
   __shared__ float2 lds[BlockFft<K>::F * BlockFft<K>::LDS];
-  __shared__ float2 twb_table[block_fft_twb_size<K>()];
+  __shared__ float2 twb_table[kTwbSize];
   const OlsTile wg = ols_tile();
   ols_body<K, NF>(a, wg.bx, wg.by, lds, twb_table);
 }
@@ -331,6 +336,7 @@ __device__ __forceinline__ int ols_multi_find(const OlsMultiArgs& m, uint32_t g)
 template <int K>
 __global__ __launch_bounds__(256) void k_ols_x_multi(OlsMultiArgs m) {
   __shared__ float2 lds[BlockFft<K>::F * BlockFft<K>::LDS];
+  __shared__ float2 twb_table[kTwbSize];
   const int s = ols_multi_find<true>(m, blockIdx.x);
   const float2* z = nullptr;
   float2* X = nullptr;
@@ -347,13 +353,13 @@ __global__ __launch_bounds__(256) void k_ols_x_multi(OlsMultiArgs m) {
       L = m.sb[i].L;
       wgx0 = m.sb[i].wgx0;
     }
-  ols_x_body<K>(z, m.n, k0, L, nB, m.n_lo, m.tw, X, blockIdx.x - wgx0, lds);
+  ols_x_body<K>(z, m.n, k0, L, nB, m.n_lo, m.tw, X, blockIdx.x - wgx0, lds, twb_table);
 }
 
 template <int K, int NF>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_ols_multi(OlsMultiArgs m) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_ols_multi(OlsMultiArgs m) {
   __shared__ float2 lds[BlockFft<K>::F * BlockFft<K>::LDS];
-  __shared__ float2 twb_table[block_fft_twb_size<K>()];
+  __shared__ float2 twb_table[kTwbSize];
   const int s = ols_multi_find<false>(m, blockIdx.x);
   OlsArgs a;
   a.tw = m.tw;
@@ -511,12 +517,12 @@ static int launch_ols_k(Plan& p, const Taps& t, const SubBankTaps& s, int64_t W,
   const int64_t nB = (n_hi - n_lo + s.ols_L - 1) / s.ols_L;      // <= s.ols_nB
   const unsigned gx = (unsigned)((nB + S::F - 1) / S::F);
   hipLaunchKernelGGL(k_ols_x<K>, dim3(gx), dim3(256), 0, p.stream, z, p.n, s.k0, s.ols_L, nB, n_lo,
-                     (const float2*)p.ols_tw32, X);
+                     (const float2*)p.ols_ct32, X);
   RFD_CHECK_LAUNCH();
   OlsArgs a;
   a.X = X;
   a.G = s.ols_g;
-  a.tw = p.ols_tw32;
+  a.tw = p.ols_ct32;
   a.slots = p.slots;
   a.n = p.n;
   a.count = s.count;
@@ -545,7 +551,7 @@ static int launch_ols_multi(Plan& p, const Taps& t, const int* sbs, int nsb, int
                             float threshold, int64_t n_lo, int64_t n_hi) {
   using S = BlockFft<K>;
   OlsMultiArgs m{};
-  m.tw = p.ols_tw32;
+  m.tw = p.ols_ct32;
   m.slots = p.slots;
   m.n = p.n;
   m.nwin = nwin;
