@@ -297,9 +297,7 @@ def main():
         return time.perf_counter() - t0, n, rfd.rfd_plan_get_timing(s.plan)
 
     def ols_block(T):
-        eff = {1024: 1.17, 2048: 1.0, 4096: 0.99}     # the library's block-size rule
-        cands = [K for K in (1024, 2048, 4096) if K > T]
-        return min(cands, key=lambda K: ((5 * np.log2(K) + 6) * K / (K - T + 1) / eff[K], K))
+        return rfd.rfd_ols_shape(s.plan, T)[0]
 
     def ols_flops_per_launch():
         """(5 log2 K + 6) K per (template, block) over one sub-bank's launch, averaged over the launches."""

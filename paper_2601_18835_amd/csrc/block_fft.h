@@ -348,4 +348,22 @@ __device__ __forceinline__ constexpr int block_fft_step(int e, int s) {
   return 16 * e + 256 * dftr_freq<BlockFft<K>::R>(s);
 }
 
+// Place of element m of a K-point row in the order that the threads of a transform load:
+// thread t takes m = t + NTf r, r < 16, two of them side by side per 16-byte load.
+template <int K>
+__device__ __forceinline__ constexpr int block_fft_place(int m) {
+  constexpr int NTf = BlockFft<K>::NTf;
+  const int t = m % NTf, r = m / NTf;
+  return (r >> 1) * 2 * NTf + 2 * t + (r & 1);
+}
+template <int K>
+__device__ __forceinline__ void block_fft_load(float2 (&v)[16], const float2* __restrict__ row, uint32_t t) {
+#pragma unroll
+  for (int p = 0; p < 8; ++p) {
+    const float4 x = (reinterpret_cast<const float4*>(row) + p * BlockFft<K>::NTf)[t];
+    v[2 * p] = make_float2(x.x, x.y);
+    v[2 * p + 1] = make_float2(x.z, x.w);
+  }
+}
+
 }  // namespace rfd

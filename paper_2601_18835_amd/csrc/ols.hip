@@ -61,7 +61,7 @@ __device__ __forceinline__ void ols_x_body(const float2* __restrict__ z, int64_t
 #pragma unroll
   for (int e = 0; e < 16 / S::R; ++e)
 #pragma unroll
-    for (int s = 0; s < S::R; ++s) xb[block_fft_out<K>(t, e, s)] = v[e * S::R + s];
+    for (int s = 0; s < S::R; ++s) xb[block_fft_place<K>(block_fft_out<K>(t, e, s))] = v[e * S::R + s];
 }
 
 template <int K>
@@ -96,14 +96,14 @@ __global__ __launch_bounds__(256) void k_ols_g(const float2* __restrict__ c32, i
   float2* gj = G + (int64_t)blockIdx.x * K;
   for (int f = threadIdx.x; f < K; f += 256) {
     const double2 v = buf[lpad(f)];
-    gj[f] = make_float2((float)(v.x * inv), (float)(v.y * inv));
+    gj[block_fft_place<K>(f)] = make_float2((float)(v.x * inv), (float)(v.y * inv));
   }
 }
 
 // -------------------------------------------------------------- main kernel
 struct OlsArgs {
-  const float2* X;           // [nB][K] block spectra of this sub-bank's series
-  const float2* G;           // [count][K] tap spectra
+  const float2* X;           // [nB][K] block spectra of this sub-bank's series (rows in block_fft_place order)
+  const float2* G;           // [count][K] tap spectra (likewise)
   const float2* tw;          // (c, tau) of exp(+2 pi i m / 4096), m < 4096
   unsigned long long* slots;
   int64_t n, count, tmpl0, nwin, W, nB;   // nB: blocks of this launch (rows of X)
@@ -111,6 +111,7 @@ struct OlsArgs {
   int64_t n_lo, n_hi;        // output samples kept: [n_lo, n_hi)
   int L, J;                  // valid outputs per block, templates per workgroup
   float thr2;                // threshold^2 of the compaction (a key <= it never fires)
+  float part;                // largest |Re z|, |Im z| that cannot exceed it (ols_part)
 };
 
 template <int K>
@@ -172,9 +173,7 @@ __device__ __forceinline__ void ols_body(const OlsArgs& a, uint32_t bx, uint32_t
   BlockFftTw<K> w;
   block_fft_twiddles<K, 1>(w, a.tw, t, twb_table);
   float2 xb[16];
-  const float2* Xb = a.X + (int64_t)(bvalid ? b : 0) * K;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) xb[r] = Xb[t + S::NTf * r];
+  block_fft_load<K>(xb, a.X + (int64_t)(bvalid ? b : 0) * K, t);
   __syncthreads();     // the twiddle table is complete
   // this block's output samples and their windows (uniform per FFT)
   const int W = (int)a.W;
@@ -182,8 +181,6 @@ __device__ __forceinline__ void ols_body(const OlsArgs& a, uint32_t bx, uint32_t
   const int nbeg = std::max(n0, (int)a.n_lo);
   const int nend = std::min(std::min(n0 + a.L, (int)a.n), (int)a.n_hi);
   const bool has_out = bvalid && nend > nbeg;
-  // every kept slot is an output of the launch: no per-sample range test
-  const bool whole = NF > 0 && has_out && nbeg == n0 && nend == n0 + a.L;
   const int q0 = has_out ? nbeg / W : 0, q1 = has_out ? (nend - 1) / W : 0;
   const int64_t j0 = (int64_t)by * a.J;
   const int64_t j1 = std::min<int64_t>(j0 + a.J, a.count);
@@ -193,11 +190,7 @@ __device__ __forceinline__ void ols_body(const OlsArgs& a, uint32_t bx, uint32_t
   // the next template's tap spectrum is fetched while the current one is
   // transformed (its loads would otherwise stall all waves of the FFT)
   float2 gn[16];
-  auto fetch_g = [&](int64_t j) {
-    const float2* gj = a.G + (j < j1 ? j : j0) * K;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) gn[r] = gj[t + S::NTf * r];
-  };
+  auto fetch_g = [&](int64_t j) { block_fft_load<K>(gn, a.G + (j < j1 ? j : j0) * K, t); };
   fetch_g(j0);
   for (int64_t j = j0; j < j1; ++j) {
     float2 v[16];
@@ -205,6 +198,20 @@ __device__ __forceinline__ void ols_body(const OlsArgs& a, uint32_t bx, uint32_t
     fetch_g(j + 1);     // unconditional (the last one rereads j0's): no merge of old and new registers
     block_fft_after_a<K, 1>(v, lds + f * S::LDS, t, w);
     if (!has_out) continue;
+    // A wave whose every sample has |Re z|, |Im z| <= thr / sqrt 2 (a.part, rounded down) has no
+    // rho^2 above thr^2 and nothing to report: one v_max3 per sample instead of the product, the
+    // sum and the maximum of rho^2.  The comparison is false for a NaN, and a NaN or infinity in
+    // a block's spectrum reaches every output of the block, so such waves take the exact path.
+    float part = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16 / S::R; ++e)
+#pragma unroll
+      for (int s = 0; s < S::R; ++s)
+        if (ols_slot_kept<K, NF>(s)) {
+          const float2 y = v[e * S::R + s];
+          part = e + s == 0 ? fmaxf(fabsf(y.x), fabsf(y.y)) : fmaxf(fmaxf(part, fabsf(y.x)), fabsf(y.y));
+        }
+    if (!__any(!(part <= a.part))) continue;
     // the sample numbers of a thread's slots are formed anew for each template
     // where they are needed (the empty statement hides that they repeat):
     // carried through the loop they would take 32 registers
@@ -214,35 +221,19 @@ __device__ __forceinline__ void ols_body(const OlsArgs& a, uint32_t bx, uint32_t
     auto past = [&](int e, int s, int from) { return (uint32_t)(o + block_fft_step<K>(e, s) + n0 - from); };
     unsigned long long* slot = a.slots + (a.tmpl0 + j) * a.nwin;
     float r2[16];
-    // rho^2 of every kept slot, formed once ahead of the two branches below (the
-    // compiler otherwise keeps a copy per branch: 0.928 -> 0.887 ms at K = 4096).
 #pragma unroll
-    for (int e = 0; e < 16 / S::R; ++e)
-#pragma unroll
-      for (int s = 0; s < S::R; ++s) {
-        if (!ols_slot_kept<K, NF>(s)) continue;
-        const float2 y = v[e * S::R + s];
-        r2[e * S::R + s] = y.x * y.x + y.y * y.y;
-      }
+    for (int i = 0; i < 16; ++i) r2[i] = v[i].x * v[i].x + v[i].y * v[i].y;
     // maximum of the kept samples' rho^2 as bit patterns (non-negative floats
     // order as their bits).  The discarded outputs stay out: where the block's
     // correlation wraps, taps that cancel only against the series' own
     // correlations lose that cancellation and would cross the threshold.
     uint32_t r2max = 0u;
-    if (whole) {
 #pragma unroll
-      for (int e = 0; e < 16 / S::R; ++e)
+    for (int e = 0; e < 16 / S::R; ++e)
 #pragma unroll
-        for (int s = 0; s < S::R; ++s)
-          if (ols_slot_kept<K, NF>(s)) r2max = max(r2max, __float_as_uint(r2[e * S::R + s]));
-    } else {
-#pragma unroll
-      for (int e = 0; e < 16 / S::R; ++e)
-#pragma unroll
-        for (int s = 0; s < S::R; ++s)
-          if (ols_slot_kept<K, NF>(s) && past(e, s, nbeg) < (uint32_t)(nend - nbeg))
-            r2max = max(r2max, __float_as_uint(r2[e * S::R + s]));
-    }
+      for (int s = 0; s < S::R; ++s)
+        if (ols_slot_kept<K, NF>(s) && past(e, s, nbeg) < (uint32_t)(nend - nbeg))
+          r2max = max(r2max, __float_as_uint(r2[e * S::R + s]));
     // the compaction reports a window only if its peak exceeds thr2: a wave
     // with no sample above it cannot contribute a reported peak
     if (!__any(r2max > __float_as_uint(a.thr2))) continue;
@@ -279,14 +270,16 @@ __device__ __forceinline__ void ols_body(const OlsArgs& a, uint32_t bx, uint32_t
   }
 }
 
-// Bound by VALU issue: 614 VALU instructions per wave and template at K = 4096 and
-// NF = 12 (four cycles each; 342 x 512 transforms on 256 CUs then take 0.70 ms at
-// 2.4 GHz, measured 0.73), 506 at K = 1024 and NF = 3.  With the twiddles taken as
-// products between the stages and the slots' sample numbers carried through the loop
-// in 64 bits it was 685 and 583, and 215 registers allowed two waves per SIMD; three
-// now fit (150 to 161 registers, none spilled).  Whole cases: 8 sub-banks of 512
-// templates, T = 1024, N = 2^20: 7.47 -> 6.25 ms; 4096 templates, T = 256, N = 2^19:
-// 2.73 -> 2.49 ms.
+// Bound by VALU issue: 596 VALU instructions per wave and template at K = 4096 and
+// NF = 12 (four cycles each; 342 x 512 transforms on 256 CUs then take 0.68 ms at
+// 2.4 GHz, measured 0.72), 552 at K = 2048 and NF = 7, 494 at K = 1024 and NF = 3.
+// With the twiddles taken as products between the stages and the slots' sample
+// numbers carried through the loop in 64 bits it was 685 at K = 4096 and 583 at 1024,
+// and 215 registers allowed two waves per SIMD; three now fit (143 to 161 registers,
+// none spilled).  Of the last steps, rho^2 formed only in waves that may fire and spectra in
+// the order of their 16-byte loads took 626 to 596.  Whole cases: 8 sub-banks of 512
+// templates, T = 1024, N = 2^20: 7.47 -> 5.99 ms; 4096 templates, T = 256, N = 2^19:
+// 2.73 -> 2.35 ms.
 template <int K, int NF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_ols(OlsArgs a) {
   __shared__ float2 lds[BlockFft<K>::F * BlockFft<K>::LDS];
@@ -317,7 +310,7 @@ struct OlsMultiArgs {
   const float2* tw;
   unsigned long long* slots;
   int64_t n, nwin, W, n_lo, n_hi;
-  float thr2;
+  float thr2, part;
   int nsb;
 };
 static_assert(sizeof(OlsMultiArgs) <= 4096, "the descriptors must fit the kernel argument segment");
@@ -371,6 +364,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   a.n_hi = m.n_hi;
   a.org = m.n_lo;
   a.thr2 = m.thr2;
+  a.part = m.part;
   uint32_t gx = 1, wg0 = 0;
 #pragma unroll
   for (int i = 0; i < kOlsMulti; ++i)
@@ -391,15 +385,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 
 // ------------------------------------------------------------------ host
 // Measured throughput of each block size per unit of FFT work, relative to
-// K = 2048 (MI355X: one-wave FFTs without workgroup barriers at 1024, a
-// whole-workgroup FFT at 4096).
-// (FFT flops per second of the whole-segment launches at T = 256 and 1024: 59.5,
-// 50.9 and 50.4-51.1 TFLOP/s).
-static double ols_efficiency(int K) { return K == 1024 ? 1.17 : (K == 2048 ? 1.0 : 0.99); }
-// ... and the gain of an aligned output length (L = 256 NF: the discarded
-// outputs are never computed, interior blocks skip per-sample range tests)
-// (measured 1.01 at K = 4096 and 1.036 at K = 1024 on equal block counts)
-constexpr double kOlsAlignedGain = 1.03;
+// K = 2048: the kernels run at the VALU issue limit, so it follows their
+// instructions per (5 log2 K + 6) K flops (70.1, 68.0 and 67.0 TFLOP/s at T = 256,
+// 67.0, 68.7 and 68.0 at T = 512, whole segments of 2^19 samples).
+static double ols_efficiency(int K) { return K == 1024 ? 1.02 : (K == 2048 ? 1.0 : 0.99); }
+// ... and the gain of an aligned output length (L = 256 NF): the discarded outputs
+// are never computed (12 of 608 instructions at K = 4096 and NF = 12).  With these
+// T = 256 takes K = 2048, L = 1792 (2.21 ms for 4096 templates; 2.29 at K = 1024, 2.26 at
+// 4096), T = 128 K = 1024 (2.14; 2.21, 2.36) and T = 400 K = 4096 (2.38; 2.48 at 2048).
+constexpr double kOlsAlignedGain = 1.02;
 
 // aligned output groups the kernels are built for, per block size
 static bool ols_nf_built(int K, int nf) {
@@ -438,6 +432,12 @@ OlsShape ols_shape(const Plan& p, int T) {
 }
 
 int ols_block_size(const Plan& p, int T) { return ols_shape(p, T).K; }
+
+// Largest p with p^2 + p^2 <= thr2 however the two operations round: sqrt(thr2 / 2) less 2^-20
+// of itself; 0 for a vanishing (or denormal) threshold, where every sample may fire.
+static float ols_part(float thr2) {
+  return thr2 > 1e-30f ? (float)(std::sqrt(0.5 * (double)thr2) * (1.0 - 0x1p-20)) : 0.f;
+}
 
 static int ols_templates_per_wg(int64_t nB, int F, int64_t count, int n_cu) {
   // enough workgroups to fill the chip several times, at least 4 templates each
@@ -536,6 +536,7 @@ static int launch_ols_k(Plan& p, const Taps& t, const SubBankTaps& s, int64_t W,
   a.L = s.ols_L;
   a.J = ols_templates_per_wg(nB, S::F, s.count, p.n_cu);
   a.thr2 = threshold * threshold;
+  a.part = ols_part(a.thr2);
   const unsigned gy = (unsigned)((s.count + a.J - 1) / a.J);
   int rc = stage_begin(p, kStFirKernel);
   if (rc) return rc;
@@ -559,6 +560,7 @@ static int launch_ols_multi(Plan& p, const Taps& t, const int* sbs, int nsb, int
   m.n_lo = n_lo;
   m.n_hi = n_hi;
   m.thr2 = threshold * threshold;
+  m.part = ols_part(m.thr2);
   m.nsb = nsb;
   for (int i = 0; i < nsb; ++i) {
     const SubBankTaps& s = t.sb[sbs[i]];
