@@ -34,6 +34,12 @@ namespace rfd {
 
 constexpr int kFcN1 = 4096;    // row length when N > 4096
 
+// A filter value: read once per call, so marked to pass the caches by and leave them to the
+// intermediate (250 templates at N = 2^20: 1407 -> 1328 us).
+__device__ __forceinline__ float2 load_once(const float2* p) {
+  return __builtin_bit_cast(float2, __builtin_nontemporal_load(reinterpret_cast<const double*>(p)));
+}
+
 // Small in-register DFTs on v[0..N) (N = 1, 2, 4, 8, 16), sign SIGN; slot s
 // then holds X[small_freq<N>(s)].
 template <int N, int SIGN>
@@ -151,7 +157,7 @@ __global__ __launch_bounds__(256) void k_fc_cols(FcColArgs a) {
   if (b0 < b1) {
     const float2* fb = a.filt + b0 * a.n_band;
 #pragma unroll
-    for (int r = 0; r < V; ++r) fv[r] = off[r] >= 0 ? fb[off[r]] : make_float2(0.f, 0.f);
+    for (int r = 0; r < V; ++r) fv[r] = off[r] >= 0 ? load_once(fb + off[r]) : make_float2(0.f, 0.f);
   }
   [[maybe_unused]] __shared__ float2 lds[M2 > 1 ? 16 * M2 * CW : 1];
   for (int64_t b = b0; b < b1; ++b) {
@@ -161,7 +167,7 @@ __global__ __launch_bounds__(256) void k_fc_cols(FcColArgs a) {
     if (b + 1 < b1) {
       const float2* fb = a.filt + (b + 1) * a.n_band;
 #pragma unroll
-      for (int r = 0; r < V; ++r) fv[r] = off[r] >= 0 ? fb[off[r]] : make_float2(0.f, 0.f);
+      for (int r = 0; r < V; ++r) fv[r] = off[r] >= 0 ? load_once(fb + off[r]) : make_float2(0.f, 0.f);
     }
     float2* Yb = a.Y + b * N2 * N1;
     if constexpr (M2 == 1) {
@@ -283,20 +289,21 @@ __global__ __launch_bounds__(256) void k_fc_rows(FcRowArgs a) {
   }
 }
 
-// Items per workgroup so that a launch holds about kFcWgPerCu workgroups per
-// compute unit (at least one item each, at most 16).  Measured on MI355X at
-// N = 2^19: two workgroups per CU with up to 16 items beat one per item by
-// 1.5x (the prefetch hides the loads) and beat one per CU by 1.2x.
-constexpr int kFcWgPerCu = 2;
-static int fc_items_per_wg(int64_t wgs_at_one, int n_cu) {
-  int64_t j = wgs_at_one / ((int64_t)kFcWgPerCu * n_cu);
+// Items per workgroup so that a launch holds about `per_cu` workgroups per compute unit (at
+// least one item each, at most 16): few enough that each amortises its twiddles and fetches
+// ahead.  Two in pass A: at N = 2^19 1.5x faster than one item each and 1.2x than one workgroup
+// per CU.  Six in pass B, whose last wave of workgroups is then shorter (250 templates at
+// N = 2^20: 1328 -> 1305 us; 1371 at three, 1321 at eight).
+constexpr int kFcColsPerCu = 2, kFcRowsPerCu = 6;
+static int fc_items_per_wg(int64_t wgs_at_one, int n_cu, int per_cu) {
+  int64_t j = wgs_at_one / ((int64_t)per_cu * n_cu);
   return (int)std::max<int64_t>(1, std::min<int64_t>(16, j));
 }
 
 template <int N2>
 static void launch_cols(Plan& p, FcColArgs a) {
   const int64_t gx = kFcN1 / FcCols<N2>::CW;
-  a.JT = fc_items_per_wg(gx * a.count, p.n_cu);
+  a.JT = fc_items_per_wg(gx * a.count, p.n_cu, kFcColsPerCu);
   const unsigned gy = (unsigned)((a.count + a.JT - 1) / a.JT);
   hipLaunchKernelGGL((k_fc_cols<kFcN1, N2>), dim3((unsigned)gx, gy), dim3(256), 0, p.stream, a);
 }
@@ -305,13 +312,16 @@ template <int N1, bool DIRECT>
 static void launch_rows(Plan& p, FcRowArgs a) {
   const int64_t F = BlockFft<N1>::F;
   const int64_t slots = (a.count * a.N2 + F - 1) / F;
-  a.JR = fc_items_per_wg(slots, p.n_cu);
+  a.JR = fc_items_per_wg(slots, p.n_cu, kFcRowsPerCu);
   const unsigned gx = (unsigned)((slots + a.JR - 1) / a.JR);
   hipLaunchKernelGGL((k_fc_rows<N1, DIRECT>), dim3(gx), dim3(256), 0, p.stream, a);
 }
 
 int findchirp_batch_size(const Plan& p) {
-  // pass-A output of a batch: up to 256 MiB (64 templates at N = 2^19)
+  // pass-A output of a batch: up to 256 MiB (64 templates at N = 2^19), the size of the
+  // last-level cache that pass B then finds much of it in.  Smaller batches pay more launches
+  // (128 MiB: 1420 us for 250 templates at N = 2^20, 64 MiB: 1620), larger ones go to memory
+  // (512 MiB: 1523); 256 MiB: 1328.
   int64_t b = ((int64_t)256 << 20) / (p.n * (int64_t)sizeof(float2));
   if (b < 1) b = 1;
   if (b > 64) b = 64;

@@ -228,39 +228,61 @@ __global__ __launch_bounds__(256) void k_fc_z(rfd_trigger* __restrict__ out, con
 
 // ... or, for long segments, kZParts blocks per trigger over contiguous bin
 // ranges (grid-stride over the triggers), their partial sums then added in
-// a fixed order by one thread per trigger.
+// a fixed order by one thread per trigger.  A thread's bins are 256 apart, so
+// its factor e^{2 pi i bin n / N} turns by the same angle from each bin to the next: an
+// FP64 rotation, rounded to FP32 per bin (at most N / 2 / kZParts / 256 turns, far below
+// FP32 rounding).  Bound by reading the filters, with kZU bins' loads in flight
+// per thread: 250 triggers at N = 2^20 408 -> 215 us (one bin at a time, its factor from two
+// scattered FP32 table reads).
+constexpr int kZU = 8;
 __global__ __launch_bounds__(256) void k_fc_z_part(const rfd_trigger* __restrict__ out,
                                                  const long long* __restrict__ total, int64_t capacity,
                                                  const float2* __restrict__ s, const float2* __restrict__ filt,
                                                  int64_t i_low, int64_t n_band, int64_t n,
-                                                 const float2* __restrict__ coarse, const float2* __restrict__ fine,
+                                                 const double2* __restrict__ coarse, const double2* __restrict__ fine,
                                                  float2* __restrict__ part) {
-  __shared__ float red[2][256];
+  __shared__ float red[2][4];
   const int64_t lim = *total < capacity ? *total : capacity;
   const int64_t chunk = (n_band + kZParts - 1) / kZParts;
   const int64_t k0 = (int64_t)blockIdx.x * chunk, k1 = std::min<int64_t>(k0 + chunk, n_band);
+  const float2* sb = s + i_low;
   for (int64_t i = blockIdx.y; i < lim; i += gridDim.y) {
-    const rfd_trigger t = out[i];
-    const float2* f = filt + (int64_t)t.tmpl * n_band;
+    const int64_t sample = out[i].sample;
+    const float2* f = filt + (int64_t)out[i].tmpl * n_band;
+    double2 w = twiddle_n(coarse, fine, (uint32_t)(((k0 + threadIdx.x + i_low) * sample) & (n - 1)), +1);
+    const double2 step = twiddle_n(coarse, fine, (uint32_t)((256 * sample) & (n - 1)), +1);
     float re = 0.f, im = 0.f;
-    for (int64_t k = k0 + threadIdx.x; k < k1; k += 256) {
-      const int64_t bin = k + i_low;
-      const uint32_t p = (uint32_t)((bin * t.sample) & (n - 1));
-      const float2 v = cmul(cmul(s[bin], f[k]), twiddle_n(coarse, fine, p, +1));
+    auto add = [&](float2 x, float2 y) {
+      const float2 v = cmul(cmul(x, y), make_float2((float)w.x, (float)w.y));
       re += v.x;
       im += v.y;
-    }
-    red[0][threadIdx.x] = re;
-    red[1][threadIdx.x] = im;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-      if (threadIdx.x < o) {
-        red[0][threadIdx.x] += red[0][threadIdx.x + o];
-        red[1][threadIdx.x] += red[1][threadIdx.x + o];
+      w = cmul(w, step);
+    };
+    int64_t k = k0 + threadIdx.x;
+    for (; k + 256 * (kZU - 1) < k1; k += 256 * kZU) {
+      float2 x[kZU], y[kZU];
+#pragma unroll
+      for (int u = 0; u < kZU; ++u) {
+        x[u] = sb[k + 256 * u];
+        y[u] = f[k + 256 * u];
       }
-      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < kZU; ++u) add(x[u], y[u]);
     }
-    if (threadIdx.x == 0) part[i * kZParts + blockIdx.x] = make_float2(red[0][0], red[1][0]);
+    for (; k < k1; k += 256) add(sb[k], f[k]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      re += __shfl_xor(re, o);
+      im += __shfl_xor(im, o);
+    }
+    if ((threadIdx.x & 63) == 0) {
+      red[0][threadIdx.x >> 6] = re;
+      red[1][threadIdx.x >> 6] = im;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+      part[i * kZParts + blockIdx.x] = make_float2((red[0][0] + red[0][1]) + (red[0][2] + red[0][3]),
+                                                   (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]));
     __syncthreads();
   }
 }
@@ -370,8 +392,8 @@ int launch_findchirp_z(Plan& p, const float2* filt, rfd_trigger* out, int64_t ca
     // partial sums in FINDCHIRP's (now idle) intermediate buffer
     const unsigned gy = (unsigned)std::min<int64_t>(capacity, 256);
     hipLaunchKernelGGL(k_fc_z_part, dim3(kZParts, gy), dim3(256), 0, p.stream, (const rfd_trigger*)out,
-                       (const long long*)p.total, capacity, p.stilde, filt, p.i_low, p.n_band, p.n, p.tw32c, p.tw32f,
-                       p.fc_work);
+                       (const long long*)p.total, capacity, p.stilde, filt, p.i_low, p.n_band, p.n, (const double2*)p.tw64c,
+                       (const double2*)p.tw64f, p.fc_work);
     RFD_CHECK_LAUNCH();
     hipLaunchKernelGGL(k_fc_z_final, dim3((unsigned)((capacity + 255) / 256)), dim3(256), 0, p.stream, out,
                        (const long long*)p.total, capacity, (const float2*)p.fc_work);
