@@ -23,11 +23,19 @@
 
 namespace rfd {
 
-constexpr int kMaxBands = 64;
+template <typename T>
+static int calloc_dev(T** p, size_t n) {
+  *p = nullptr;
+  if (device_malloc((void**)p, std::max<size_t>(n, 1) * sizeof(T)) != hipSuccess) {
+    *p = nullptr;
+    (void)hipGetLastError();
+    return fail(RFD_E_NOMEM, "chi^2: hipMalloc failed");
+  }
+  return RFD_OK;
+}
 
-// Band edges from the host copy of u (the rule in the header comment).
-static int band_edges(Plan& p, const double* h_ref, int n_bands, std::vector<int64_t>& edges) {
-  if (n_bands < 2 || n_bands > kMaxBands) return fail(RFD_E_INVALID, "n_bands must be in [2, 64]");
+// Band edges (the rule in the header comment) from the host copy of u, in sequence.
+static int band_edges_host(Plan& p, const double* h_ref, int n_bands, std::vector<int64_t>& edges) {
   const int64_t lo = p.i_low, hi = p.i_high, cnt = hi - lo + 1;
   std::vector<double> w(cnt);
   std::vector<double2> h(cnt);
@@ -51,6 +59,154 @@ static int band_edges(Plan& p, const double* h_ref, int n_bands, std::vector<int
     edges.push_back(lo + k);
   }
   edges.push_back(hi + 1);
+  return RFD_OK;
+}
+
+// The same edges from sums in another order.  Chunks of kBandChunk bins are added by
+// one workgroup each; one workgroup per edge then finds the chunk and the bin where
+// the prefix sum reaches its share, and how far the sums on both sides of the edge
+// are from the share.  25 us for 15 edges of 2^18 bins; the copies of w and h to the host and
+// the sums there took 0.8 ms per reference.
+constexpr int kBandChunk = 1024;
+constexpr int kBandMaxChunks = (1 << 21) / kBandChunk;      // N <= 2^22
+struct BandSplit {
+  double total;
+  double margin[kMaxBands];
+  int64_t bin[kMaxBands];       // bins before the edge, counted from the first of the band
+};
+
+__device__ __forceinline__ double band_power(const double* __restrict__ w, const double2* __restrict__ h, int64_t i) {
+  const double2 x = h[i];
+  return w[i] * (x.x * x.x + x.y * x.y);
+}
+
+// inclusive sums of one value per thread (256 threads), in LDS
+__device__ __forceinline__ void scan256(double* s) {
+  for (int o = 1; o < 256; o <<= 1) {
+    const double x = (int)threadIdx.x >= o ? s[threadIdx.x - o] : 0.0;
+    __syncthreads();
+    s[threadIdx.x] += x;
+    __syncthreads();
+  }
+}
+
+__global__ __launch_bounds__(256) void k_band_chunks(const double* __restrict__ w, const double2* __restrict__ h,
+                                                   int64_t cnt, double* __restrict__ sums) {
+  __shared__ double red[256];
+  const int64_t i0 = (int64_t)blockIdx.x * kBandChunk;
+  double acc = 0.0;
+#pragma unroll
+  for (int e = 0; e < kBandChunk / 256; ++e) {
+    const int64_t i = i0 + threadIdx.x + 256 * e;
+    if (i < cnt) acc += band_power(w, h, i);
+  }
+  red[threadIdx.x] = acc;
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) sums[blockIdx.x] = red[0];
+}
+
+__global__ __launch_bounds__(256) void k_band_edge(const double* __restrict__ w, const double2* __restrict__ h,
+                                                 int64_t cnt, const double* __restrict__ sums, int n_chunks,
+                                                 int n_bands, BandSplit* __restrict__ out) {
+  constexpr int kPer = kBandMaxChunks / 256, kIn = kBandChunk / 256;
+  __shared__ double s[256];
+  __shared__ double chunk_end[kBandMaxChunks], bin_end[kBandChunk];
+  __shared__ int at;
+  const int b = blockIdx.x + 1, t = threadIdx.x;
+  double v[kPer], run = 0.0;
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    const int c = t * kPer + e;
+    v[e] = c < n_chunks ? sums[c] : 0.0;
+    run += v[e];
+  }
+  s[t] = run;
+  if (t == 0) at = n_chunks - 1;
+  __syncthreads();
+  scan256(s);
+  const double total = s[255], thr = (total * b) / n_bands;
+  double before = t ? s[t - 1] : 0.0;
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    before += v[e];
+    chunk_end[t * kPer + e] = before;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    const int c = t * kPer + e;
+    if (c < n_chunks && chunk_end[c] >= thr) atomicMin(&at, c);
+  }
+  __syncthreads();
+  const int c = at;
+  const double start = c ? chunk_end[c - 1] : 0.0;
+  __syncthreads();
+  if (t == 0) at = kBandChunk - 1;
+  double u[kIn];
+  run = 0.0;
+#pragma unroll
+  for (int e = 0; e < kIn; ++e) {
+    const int64_t i = (int64_t)c * kBandChunk + t * kIn + e;
+    u[e] = i < cnt ? band_power(w, h, i) : 0.0;
+    run += u[e];
+  }
+  s[t] = run;
+  __syncthreads();
+  scan256(s);
+  before = start + (t ? s[t - 1] : 0.0);
+#pragma unroll
+  for (int e = 0; e < kIn; ++e) {
+    before += u[e];
+    bin_end[t * kIn + e] = before;
+    if (before >= thr) atomicMin(&at, t * kIn + e);
+  }
+  __syncthreads();
+  if (t == 0) {
+    const int i = at;
+    out->bin[b] = (int64_t)c * kBandChunk + i + 1;
+    out->margin[b] = fmin(bin_end[i] - thr, thr - (i ? bin_end[i - 1] : start));
+    if (b == 1) out->total = total;
+  }
+}
+
+// Band edges of h_ref.  The rule adds u in sequence; its sums differ from those of
+// any other order by at most cnt 2^-52 of the total (positive terms), so an edge whose
+// margins are above twice that is the same in both, and the host's sequence decides
+// where one is not (or the sums are not finite).
+static int band_edges(Plan& p, const double* h_ref, int n_bands, std::vector<int64_t>& edges) {
+  if (n_bands < 2 || n_bands > kMaxBands) return fail(RFD_E_INVALID, "n_bands must be in [2, 64]");
+  const int64_t lo = p.i_low, cnt = p.i_high - lo + 1;
+  const int chunks = (int)((cnt + kBandChunk - 1) / kBandChunk);
+  if (!p.band_sums) {
+    int rc = calloc_dev(&p.band_sums, kBandMaxChunks + sizeof(BandSplit) / sizeof(double));
+    if (rc) return rc;
+  }
+  BandSplit* split = reinterpret_cast<BandSplit*>(p.band_sums + kBandMaxChunks);
+  const double2* h = reinterpret_cast<const double2*>(h_ref) + lo;
+  hipLaunchKernelGGL(k_band_chunks, dim3((unsigned)chunks), dim3(256), 0, p.stream, (const double*)p.w + lo, h, cnt,
+                     p.band_sums);
+  RFD_CHECK_LAUNCH();
+  hipLaunchKernelGGL(k_band_edge, dim3((unsigned)(n_bands - 1)), dim3(256), 0, p.stream, (const double*)p.w + lo, h,
+                     cnt, (const double*)p.band_sums, chunks, n_bands, split);
+  RFD_CHECK_LAUNCH();
+  BandSplit got;
+  RFD_HIP(hipMemcpyAsync(&got, split, sizeof(got), hipMemcpyDeviceToHost, p.stream));
+  RFD_HIP(hipStreamSynchronize(p.stream));
+  const double tol = 2.0 * (double)cnt * 0x1p-52 * got.total;
+  bool clear = got.total > 0.0;
+  for (int b = 1; b < n_bands && clear; ++b) clear = got.margin[b] > tol;
+  if (clear) {
+    edges.assign(1, lo);
+    for (int b = 1; b < n_bands; ++b) edges.push_back(lo + got.bin[b]);
+    edges.push_back(p.i_high + 1);
+  } else {
+    int rc = band_edges_host(p, h_ref, n_bands, edges);
+    if (rc) return rc;
+  }
   for (int b = 0; b < n_bands; ++b)
     if (edges[b + 1] <= edges[b]) return fail(RFD_E_INVALID, "band split produced an empty band; use fewer bands");
   return RFD_OK;
@@ -109,15 +265,16 @@ struct ChisqSub {
   const float* f;
 };
 
-// One wave per trigger: the band SNRs at the trigger sample, then chi^2.
-__global__ __launch_bounds__(64) void k_chisq(const rfd_trigger* __restrict__ trig, int64_t n_trig,
+// One workgroup per trigger: the band SNRs at the trigger sample, its four waves taking
+// the bands in turn, then chi^2 (84 triggers of 16 bands at T = 256 in a wave each: 31 us, now 12).
+__global__ __launch_bounds__(256) void k_chisq(const rfd_trigger* __restrict__ trig, int64_t n_trig,
                                             const ChisqSub* __restrict__ subs, int nsb,
                                             const float2* const* __restrict__ bands, int p, int64_t n,
                                             const float2* __restrict__ c32, const int32_t* __restrict__ shift,
                                             float* __restrict__ out) {
   const int64_t t = blockIdx.x;
   if (t >= n_trig) return;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const rfd_trigger tr = trig[t];
   const int sb = tr.subbank;
   bool ok = sb >= 0 && sb < nsb && tr.sample >= 0 && tr.sample < n;
@@ -127,7 +284,7 @@ __global__ __launch_bounds__(64) void k_chisq(const rfd_trigger* __restrict__ tr
     ok = tr.tmpl >= s.first && tr.tmpl < s.first + s.count && bands[s.ref_id] != nullptr && s.f != nullptr;
   }
   if (!ok) {
-    if (lane == 0) out[t] = __int_as_float(0x7fc00000);   // NaN for a trigger outside the bank
+    if (threadIdx.x == 0) out[t] = __int_as_float(0x7fc00000);   // NaN for a trigger outside the bank
     return;
   }
   const int64_t j = tr.tmpl - s.first;
@@ -135,7 +292,7 @@ __global__ __launch_bounds__(64) void k_chisq(const rfd_trigger* __restrict__ tr
   const float2* zb = bands[s.ref_id];
   __shared__ float2 zs[kMaxBands];
   const int64_t base = tr.sample + s.k0 + shift[tr.tmpl];   // the template's own lag window
-  for (int b = 0; b < p; ++b) {
+  for (int b = wave; b < p; b += 4) {
     const float2* z = zb + (int64_t)b * n;
     float re = 0.f, im = 0.f;
     for (int k = lane; k < s.T; k += 64) {
@@ -152,7 +309,7 @@ __global__ __launch_bounds__(64) void k_chisq(const rfd_trigger* __restrict__ tr
     if (lane == 0) zs[b] = make_float2(re, im);
   }
   __syncthreads();
-  if (lane == 0) {
+  if (threadIdx.x == 0) {
     float2 z = make_float2(0.f, 0.f);
     for (int b = 0; b < p; ++b) z = cadd(z, zs[b]);
     const float* f = s.f + j * p;
@@ -164,17 +321,6 @@ __global__ __launch_bounds__(64) void k_chisq(const rfd_trigger* __restrict__ tr
     }
     out[t] = x;
   }
-}
-
-template <typename T>
-static int calloc_dev(T** p, size_t n) {
-  *p = nullptr;
-  if (device_malloc((void**)p, std::max<size_t>(n, 1) * sizeof(T)) != hipSuccess) {
-    *p = nullptr;
-    (void)hipGetLastError();
-    return fail(RFD_E_NOMEM, "chi^2: hipMalloc failed");
-  }
-  return RFD_OK;
 }
 
 }  // namespace rfd
@@ -202,7 +348,17 @@ int rfd_dechirp_bands(rfd_plan* plan, const double* h_ref, int32_t ref_id, int32
     p.zband_cap[ref_id] = need;
     ++p.res_gen;
   }
-  rc = launch_dechirp_bands(p, h_ref, edges.data(), n_bands, p.zband[ref_id]);
+  // up to 128 MiB of intermediates, or the plan's one-band buffer where they cannot be had
+  int batch = (int)std::max<int64_t>(1, std::min<int64_t>(n_bands, ((int64_t)128 << 20) / (p.n * 16)));
+  if (batch > 1 && p.band_work_cap < (size_t)batch * p.n) {
+    RFD_HIP(hipStreamSynchronize(p.stream));
+    if (p.band_work) (void)hipFree(p.band_work);
+    p.band_work_cap = 0;
+    if (calloc_dev(&p.band_work, (size_t)batch * p.n) == RFD_OK) p.band_work_cap = (size_t)batch * p.n;
+    else batch = 1;
+  }
+  rc = launch_dechirp_bands(p, h_ref, edges.data(), n_bands, p.zband[ref_id], batch > 1 ? p.band_work : p.work64,
+                            batch);
   if (rc) return rc;
   p.zband_edges[ref_id] = edges;
   p.zband_gen[ref_id] = p.seg_gen;
@@ -304,28 +460,38 @@ int rfd_chisq(rfd_plan* plan, const rfd_taps* taps, const rfd_trigger* triggers,
       return fail(RFD_E_STATE, "sub-bank " + std::to_string(b) + ": band series and shares use different bands");
   }
   if (pb < 0) return fail(RFD_E_STATE, "bank is empty");
-  ChisqSub* dsubs = nullptr;
-  const float2** dbands = nullptr;
-  int rc = calloc_dev(&dsubs, subs.size());
-  if (!rc) rc = calloc_dev(&dbands, (size_t)p.max_refs);
-  std::vector<const float2*> hb(p.max_refs);
-  for (int r = 0; r < p.max_refs; ++r) hb[r] = p.zband_gen[r] == p.seg_gen ? p.zband[r] : nullptr;
-  if (!rc && hipMemcpyAsync(dsubs, subs.data(), subs.size() * sizeof(ChisqSub), hipMemcpyHostToDevice, p.stream) !=
-                 hipSuccess)
+  // sub-bank table and band pointers in one upload, into memory that the plan keeps
+  const size_t sub_bytes = subs.size() * sizeof(ChisqSub), ptr_bytes = (size_t)p.max_refs * sizeof(float2*);
+  if (p.chi_meta_cap < sub_bytes + ptr_bytes) {
+    RFD_HIP(hipStreamSynchronize(p.stream));
+    if (p.chi_meta) (void)hipFree(p.chi_meta);
+    p.chi_meta_cap = 0;
+    unsigned char* mem = nullptr;
+    int rc = calloc_dev(&mem, sub_bytes + ptr_bytes);
+    p.chi_meta = mem;
+    if (rc) return rc;
+    p.chi_meta_cap = sub_bytes + ptr_bytes;
+  }
+  std::vector<unsigned char> meta(sub_bytes + ptr_bytes);
+  memcpy(meta.data(), subs.data(), sub_bytes);
+  for (int r = 0; r < p.max_refs; ++r) {
+    const float2* z = p.zband_gen[r] == p.seg_gen ? p.zband[r] : nullptr;
+    memcpy(meta.data() + sub_bytes + r * sizeof(z), &z, sizeof(z));
+  }
+  const ChisqSub* dsubs = static_cast<const ChisqSub*>(p.chi_meta);
+  const float2* const* dbands =
+      reinterpret_cast<const float2* const*>(static_cast<unsigned char*>(p.chi_meta) + sub_bytes);
+  int rc = RFD_OK;
+  if (hipMemcpyAsync(p.chi_meta, meta.data(), meta.size(), hipMemcpyHostToDevice, p.stream) != hipSuccess)
     rc = fail(RFD_E_DEVICE, "chi^2 metadata upload failed");
-  if (!rc && hipMemcpyAsync(dbands, hb.data(), hb.size() * sizeof(float2*), hipMemcpyHostToDevice, p.stream) !=
-                 hipSuccess)
-    rc = fail(RFD_E_DEVICE, "chi^2 metadata upload failed");
-  for (int64_t t0 = 0; !rc && t0 < n; t0 += 1 << 30) {
-    const int64_t cnt = std::min<int64_t>(n - t0, (int64_t)1 << 30);
-    hipLaunchKernelGGL(k_chisq, dim3((unsigned)cnt), dim3(64), 0, p.stream, triggers + t0, cnt,
-                       (const ChisqSub*)dsubs, (int)subs.size(), (const float2* const*)dbands, pb, p.n,
+  for (int64_t t0 = 0; !rc && t0 < n; t0 += 1 << 22) {
+    const int64_t cnt = std::min<int64_t>(n - t0, (int64_t)1 << 22);
+    hipLaunchKernelGGL(k_chisq, dim3((unsigned)cnt), dim3(256), 0, p.stream, triggers + t0, cnt, dsubs,
+                       (int)subs.size(), dbands, pb, p.n,
                        (const float2*)t.c32, (const int32_t*)t.d_shift, chisq_out + t0);
     if (hipGetLastError() != hipSuccess) rc = fail(RFD_E_DEVICE, "chi^2 launch failed");
   }
   (void)hipStreamSynchronize(p.stream);
-  if (dsubs) (void)hipFree(dsubs);
-  if (dbands) (void)hipFree(dbands);
   return rc;
 }
 

@@ -37,13 +37,6 @@ struct LoadData64 {        // real FP64 series, scaled, FP64 complex
   const double* x; double scale;
   __device__ double2 operator()(int, int64_t i) const { return make_double2(x[i] * scale, 0.0); }
 };
-struct LoadDechirp64 {     // s_i * F_ref,i over the band, FP64 (Eq. 1 integrand)
-  const double2* s; const double2* f; int64_t i_low, i_high;
-  __device__ double2 operator()(int, int64_t i) const {
-    if (i < i_low || i > i_high) return make_double2(0.0, 0.0);
-    return cmul(s[i], f[i]);
-  }
-};
 // References of one batched dechirp, carried by value in the kernel arguments
 // (so eager launches and captured graphs need no pointer table in memory).
 struct DechirpRefs {
@@ -82,6 +75,26 @@ struct LoadDechirpRefs32 { // the same integrand, formed in FP64 and rounded onc
     return make_float2((float)v.x, (float)v.y);
   }
   __device__ float2 operator()(int b, int64_t i) const { return make(b, i, fetch(b, i)); }
+};
+struct LoadBands {         // the integrand of one reference on bins [e[b], e[b + 1]), FP64
+  const double2* s; const double* w; const double2* h; const double* scale;
+  int32_t e[kMaxBands + 1];
+  struct Raw { double2 h, s; double w; };
+  __device__ Raw fetch(int b, int64_t i) const {
+    const bool in = i >= e[b] && i < e[b + 1];
+    const int64_t k = in ? i : e[b];
+    Raw x;
+    x.h = h[k];
+    x.s = s[k];
+    x.w = w[k];
+    if (!in) x.w = 0.0;
+    return x;
+  }
+  __device__ double2 make(int b, int64_t, const Raw& x) const {
+    const double f = x.w * scale[0];
+    return cmul(x.s, make_double2(f * x.h.x, -f * x.h.y));
+  }
+  __device__ double2 operator()(int b, int64_t i) const { return make(b, i, fetch(b, i)); }
 };
 struct LoadFindchirp {     // s_i * F_j,i with F_j stored over band bins
   const float2* s; const float2* f; int64_t i_low, i_high, n_band;
@@ -155,9 +168,11 @@ struct StoreRefSlots32 {   // FP32 series into the slot of batch entry b
   float2* z; int64_t n; DechirpRefs r;
   __device__ void operator()(int b, int64_t m, float2 v) const { z[(int64_t)r.slot[b] * n + m] = v; }
 };
-struct StoreBand {         // FP64 series -> FP32 band series
-  float2* z;
-  __device__ void operator()(int, int64_t n, double2 v) const { z[n] = make_float2((float)v.x, (float)v.y); }
+struct StoreBand {         // FP64 series -> FP32 band series [b][n]
+  float2* z; int64_t n;
+  __device__ void operator()(int b, int64_t m, double2 v) const {
+    z[(int64_t)b * n + m] = make_float2((float)v.x, (float)v.y);
+  }
 };
 
 // ------------------------------------------------------------------ passes
@@ -524,17 +539,6 @@ __global__ void k_build_filter(const double* __restrict__ w, const double2* __re
   }
 }
 
-// F[i] = w_i conj(h_i) / (sigma * alpha) kept in FP64 (reference filter).
-__global__ void k_build_filter64(const double* __restrict__ w, const double2* __restrict__ h, int64_t nb,
-                                 const double* __restrict__ sigma_sq, double inv_alpha, double2* __restrict__ out) {
-  const double s = inv_alpha / sqrt(sigma_sq[0]);
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nb; i += (int64_t)gridDim.x * blockDim.x) {
-    double2 v = h[i];
-    double f = w[i] * s;
-    out[i] = make_double2(f * v.x, -f * v.y);
-  }
-}
-
 __global__ void k_sqrt_to(const double* __restrict__ in, double* __restrict__ out, int64_t n) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) out[i] = sqrt(in[i]);
@@ -610,19 +614,25 @@ int launch_dechirp_refs(Plan& p, int n_refs, const int32_t* ref_ids, const doubl
 
 // Band series of one reference: the dechirp integrand restricted to bins
 // [edges[b], edges[b+1]) and transformed, for every band (FP32 out, [p][N]).
-int launch_dechirp_bands(Plan& p, const double* h_ref, const int64_t* edges, int n_bands, float2* out) {
-  double* sig = p.dscratch + 16;
-  hipLaunchKernelGGL(k_sigma_sq, dim3(1), dim3(1024), 0, p.stream, p.w, (const double2*)h_ref, p.nb, p.nb, sig);
+// `batch` bands per pair of launches, through `work` (batch N values): one band's passes
+// are 128 to 256 workgroups, half a wave of the chip, and 12 us each (16 bands of a 2^19
+// segment: 390 us one by one, 150 us together).
+int launch_dechirp_bands(Plan& p, const double* h_ref, const int64_t* edges, int n_bands, float2* out, double2* work,
+                         int batch) {
+  DechirpRefs one{};
+  one.h[0] = reinterpret_cast<const double2*>(h_ref);
+  hipLaunchKernelGGL(k_sigma_part, dim3(kSigParts, 1), dim3(256), 0, p.stream, p.w, one, p.nb, p.dref_part);
   RFD_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_build_filter64, dim3(256), dim3(256), 0, p.stream, p.w, (const double2*)h_ref, p.nb,
-                     (const double*)sig, 1.0 / p.data_scale, p.fref64);
+  hipLaunchKernelGGL(k_sigma_final, dim3(1), dim3(kDechirpBatch), 0, p.stream, one, 1, (const double*)p.dref_part,
+                     p.dscratch + 16, p.dref_scale, 1.0 / p.data_scale);
   RFD_CHECK_LAUNCH();
-  for (int b = 0; b < n_bands; ++b) {
-    LoadDechirp64 ld{p.stilde64, p.fref64, edges[b], edges[b + 1] - 1};
-    int rc = run_pass_a<double2>(p, ld, p.work64, p.tw64c, p.tw64f, p.tw64_n2, 1, +1);
+  for (int b0 = 0; b0 < n_bands; b0 += batch) {
+    const int nb = std::min(batch, n_bands - b0);
+    LoadBands ld{p.stilde64, p.w, one.h[0], p.dref_scale, {}};
+    for (int b = 0; b <= nb; ++b) ld.e[b] = (int32_t)edges[b0 + b];
+    int rc = run_pass_a<double2>(p, ld, work, p.tw64c, p.tw64f, p.tw64_n2, nb, +1);
     if (rc) return rc;
-    StoreBand st{out + (int64_t)b * p.n};
-    rc = run_pass_b<double2>(p, p.work64, st, p.tw64_n1, 1, +1);
+    rc = run_pass_b<double2>(p, work, StoreBand{out + (int64_t)b0 * p.n, p.n}, p.tw64_n1, nb, +1);
     if (rc) return rc;
   }
   return RFD_OK;

@@ -32,6 +32,7 @@ constexpr int kDechirpBatch = 32;               // references per batched dechir
 constexpr int kMaxRefSlots = 4096;              // reference-series slots of a plan, at most
 constexpr int kSigParts = 64;                   // partial sums per reference norm
 constexpr int kZParts = 32;                     // partial sums per FINDCHIRP trigger z
+constexpr int kMaxBands = 64;                   // bands of the chi^2 test, at most
 
 // ------------------------------------------------------------- plan state
 struct Plan {
@@ -57,7 +58,6 @@ struct Plan {
   double* dref_sig2 = nullptr;    // sigma_ref^2 by reference slot [max_refs]
   double* dref_scale = nullptr;   // 1 / (sigma alpha) of a dechirp batch [kDechirpBatch]
   double* dref_part = nullptr;    // partial sums of their norms [kDechirpBatch][kSigParts]
-  double2* fref64 = nullptr;  // reference filter scratch [nb]
   double* dscratch = nullptr; // small FP64 scratch (sigma etc.)  [64]
   // reference series store, slot-major [max_refs][n]
   float2* zref = nullptr;
@@ -104,6 +104,9 @@ struct Plan {
   std::vector<int64_t> zband_cap;
   std::vector<std::vector<int64_t>> zband_edges;
   std::vector<int64_t> zband_gen;
+  double2* band_work = nullptr; size_t band_work_cap = 0;   // FP64 intermediates of several bands (grown)
+  double* band_sums = nullptr;    // power of the band split's chunks, then its result (chisq.hip)
+  void* chi_meta = nullptr; size_t chi_meta_cap = 0;        // sub-bank table of a chi^2 call (grown)
 
   // objects that keep a pointer to this plan (graphs, streams): destroy refuses while > 0
   int users = 0;
@@ -220,7 +223,8 @@ constexpr int kPeakParts = 64;   // chunks per template in the peak-lag reductio
 int launch_corr_peak(Plan& p, Taps& tp, const double* h_r, const double* h_t, int64_t batch, int T, int k0_sb,
                      double* pw, int32_t* k0_out, int32_t* d_out);
 // band series [n_bands][N] (FP32, normalised by sigma_ref) of one reference
-int launch_dechirp_bands(Plan& p, const double* h_ref, const int64_t* edges, int n_bands, float2* out);
+int launch_dechirp_bands(Plan& p, const double* h_ref, const int64_t* edges, int n_bands, float2* out, double2* work,
+                         int batch);
 
 // ---------------------------------------------------- launchers (taps.hip)
 int taps_prepare_subbank(Plan& p, Taps& tp, int b, const double* h_ref, double eps);

@@ -232,7 +232,7 @@ __global__ __launch_bounds__(256) void k_fc_z(rfd_trigger* __restrict__ out, con
 // its factor e^{2 pi i bin n / N} turns by the same angle from each bin to the next: an
 // FP64 rotation, rounded to FP32 per bin (at most N / 2 / kZParts / 256 turns, far below
 // FP32 rounding).  Bound by reading the filters, with kZU bins' loads in flight
-// per thread: 250 triggers at N = 2^20 408 -> 215 us (one bin at a time, its factor from two
+// per thread: 250 triggers at N = 2^20 408 -> 237 us (one bin at a time, its factor from two
 // scattered FP32 table reads).
 constexpr int kZU = 8;
 __global__ __launch_bounds__(256) void k_fc_z_part(const rfd_trigger* __restrict__ out,
