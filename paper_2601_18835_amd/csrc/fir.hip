@@ -441,11 +441,17 @@ static int launch_ref_planes(Plan& p, int precision, int ref, int64_t start, int
 
 // Tiles per workgroup: one workgroup covers a whole cluster window when W is
 // a multiple of 256 (so each (template, window) peak gets one update), capped
-// at 8 tiles; otherwise 4 tiles.
-static int tiles_per_block(int64_t n, int64_t W, int cols, int smax_cfg) {
+// at 2048 samples; otherwise half of that.  Fewer where the launch would then hold less
+// than `want` workgroups (rows of them: `rows` template tiles): a short segment or a small
+// bank would leave most of the chip idle behind a few long sweeps.  want = 8 per CU for
+// the launches per sub-bank (FP32, N = 2^17, 16 templates, T = 64: 91 us in 64 workgroups, 28 in
+// 1024; BF16, 250 templates at N = 2^18, T = 48: 81 us in 1024, 79 in 2048), 1 per CU for the
+// persistent form, whose workgroups pay a queue step per item (64 templates, N = 2^17,
+// T = 128: 64 us in 128 items, 47 in 256, 52 in 2048).
+static int tiles_per_block(int64_t n, int64_t W, int cols, int smax_cfg, int64_t rows, int64_t want) {
   const int smax = std::max(1, std::min(2048 / cols, smax_cfg));
   int S = (W % cols == 0) ? (int)std::min<int64_t>(W / cols, smax) : std::max(1, smax / 2);
-  while (S > 1 && (n % ((int64_t)S * cols)) != 0) S >>= 1;
+  while (S > 1 && (n % ((int64_t)S * cols) != 0 || n / ((int64_t)S * cols) * rows < want)) S >>= 1;
   return S < 1 ? 1 : S;
 }
 
@@ -484,7 +490,7 @@ int launch_fir(Plan& p, const Taps& tp, int b, int precision, int64_t W, int64_t
     n_start = 0;
     n_len = p.n;
   }
-  a.S = tiles_per_block(n_len, W, cols, p.fir_smax);
+  a.S = tiles_per_block(n_len, W, cols, p.fir_smax, (s.count + kTmplTile - 1) / kTmplTile, (int64_t)8 * p.n_cu);
   while (a.S > 1 && n_start % ((int64_t)a.S * cols) != 0) a.S >>= 1;
   a.m_off = n_start;
   dim3 grid((unsigned)(n_len / ((int64_t)a.S * cols)), (unsigned)((s.count + kTmplTile - 1) / kTmplTile));
@@ -545,9 +551,11 @@ int prepare_fir_items(Plan& p, Taps& tp, int precision, int64_t W) {
   std::vector<int64_t> off(m + 1, 0), nsg(std::max(m, 1), 0);
   std::vector<int32_t> S(std::max(m, 1), 1), sbv(std::max(m, 1), 0);
   size_t lds = 0;
+  int64_t rows = 0;
+  for (int b : order) rows += (tp.sb[b].count + kTmplTile - 1) / kTmplTile;
   for (int j = 0; j < m; ++j) {
     const SubBankTaps& s = tp.sb[order[j]];
-    S[j] = tiles_per_block(p.n, W, cols, p.fir_smax);
+    S[j] = tiles_per_block(p.n, W, cols, p.fir_smax, rows, p.n_cu);
     nsg[j] = p.n / ((int64_t)S[j] * cols);
     sbv[j] = order[j];
     off[j + 1] = off[j] + nsg[j] * ((s.count + kTmplTile - 1) / kTmplTile);
