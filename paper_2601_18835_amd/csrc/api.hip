@@ -162,6 +162,7 @@ static void plan_free(Plan& p) {
   dfree(p.ols_tw32); dfree(p.ols_tw64); dfree(p.ols_ct32);
   for (auto& z : p.zband) dfree(z);
   dfree(p.band_work); dfree(p.band_sums);
+  if (p.total_host) (void)hipHostFree(p.total_host);
   if (p.chi_meta) (void)hipFree(p.chi_meta);
 }
 
@@ -220,9 +221,8 @@ static int check_filter_args(const Plan& p, float threshold, int64_t W, const rf
 }
 
 int finish_triggers(Plan& p, int64_t capacity, int64_t* n_out) {
-  long long tot = 0;
-  RFD_HIP(hipMemcpyAsync(&tot, p.total, sizeof(long long), hipMemcpyDeviceToHost, p.stream));
   RFD_HIP(hipStreamSynchronize(p.stream));
+  const long long tot = *(volatile long long*)p.total_host;
   *n_out = tot;
   if (tot > capacity)
     return fail(RFD_E_OVERFLOW, "trigger capacity " + std::to_string(capacity) + " < " + std::to_string(tot));
@@ -377,6 +377,11 @@ int rfd_plan_create(const double* psd, int64_t n_psd, double f_low, double fs, i
     if (p.n_cu < 1) p.n_cu = 1;
   }
   TRY(dalloc(&p.total, 1));
+  if (hipHostMalloc((void**)&p.total_host, sizeof(long long), hipHostMallocDefault) != hipSuccess) {
+    p.total_host = nullptr;
+    (void)hipGetLastError();
+    TRY(fail(RFD_E_NOMEM, "host allocation failed"));
+  }
   TRY(dalloc(&p.zref, (size_t)max_refs * n));
   TRY(dalloc(&p.zbf_hi, (size_t)max_refs * n));
   TRY(dalloc(&p.zbf_lo, (size_t)max_refs * n));

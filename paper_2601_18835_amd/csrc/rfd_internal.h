@@ -70,6 +70,7 @@ struct Plan {
   unsigned long long* slots = nullptr; size_t slots_cap = 0;
   long long* counts = nullptr; size_t counts_cap = 0;
   long long* total = nullptr;
+  long long* total_host = nullptr;   // the same count in pinned host memory, for the call that waits for it
 
   // FINDCHIRP batch intermediates (grown on demand)
   float2* fc_work = nullptr; size_t fc_work_cap = 0;

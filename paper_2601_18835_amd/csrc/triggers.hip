@@ -17,7 +17,9 @@ constexpr int kSeg = kSegThreads * kSegPer;   // slots per compaction block
 // ascending slot order.
 
 __device__ __forceinline__ int64_t map_slot(const WinMap& m, int64_t v) {
-  const int64_t t = v / m.nq, qi = v - t * m.nq;
+  // (a 64-bit division costs tens of instructions: 32 bits serve nearly every call)
+  const int64_t t = v <= 0xFFFFFFFFll ? (int64_t)((uint32_t)v / (uint32_t)m.nq) : v / m.nq;
+  const int64_t qi = v - t * m.nq;
   const int64_t q = qi < m.cnt0 ? m.lo0 + qi : m.lo1 + (qi - m.cnt0);
   return t * m.nwin + q;
 }
@@ -78,7 +80,7 @@ __global__ __launch_bounds__(kSegThreads) void k_count(const unsigned long long*
 
 // single-workgroup exclusive scan of the block counts; total at counts[nblk]
 __global__ __launch_bounds__(1024) void k_scan(long long* __restrict__ counts, int64_t nblk,
-                                             long long* __restrict__ total) {
+                                             long long* __restrict__ total, long long* __restrict__ total_host) {
   __shared__ long long sh[1024];
   __shared__ long long carry;
   if (threadIdx.x == 0) carry = 0;
@@ -100,7 +102,10 @@ __global__ __launch_bounds__(1024) void k_scan(long long* __restrict__ counts, i
     if (threadIdx.x == 0) carry += add;
     __syncthreads();
   }
-  if (threadIdx.x == 0) *total = carry;
+  if (threadIdx.x == 0) {
+    *total = carry;
+    *total_host = carry;
+  }
 }
 
 __device__ __forceinline__ int find_subbank(const int64_t* first, int nsb, int64_t t) {
@@ -112,20 +117,48 @@ __device__ __forceinline__ int find_subbank(const int64_t* first, int nsb, int64
   return lo;
 }
 
+// counts: the blocks' trigger counts, or with SCANNED their exclusive sums.  Without, each
+// block adds the counts before its own (few enough, see launch_compact_impl) and the last
+// one stores the total, on the device and in the plan's host word.
+template <bool SCANNED>
 __global__ __launch_bounds__(kSegThreads) void k_write(const unsigned long long* __restrict__ slots, int64_t n,
-                                                     float thr2, const long long* __restrict__ offs, int64_t nwin,
+                                                     float thr2, const long long* __restrict__ counts, int64_t nwin,
                                                      int64_t W, rfd_trigger* __restrict__ out, int64_t capacity,
                                                      const int64_t* __restrict__ sb_first, int nsb, WinMap m,
-                                                     const int32_t* __restrict__ shift, int64_t nseg) {
+                                                     const int32_t* __restrict__ shift, int64_t nseg,
+                                                     long long* __restrict__ total, long long* __restrict__ total_host) {
   __shared__ int wc[kSegThreads / 64];
+  __shared__ long long part[kSegThreads / 64];
   const int wave = threadIdx.x >> 6;
   const int64_t base = (int64_t)blockIdx.x * kSeg + (int64_t)wave * 64 * kSegPer;
+  long long before = 0;
+  if constexpr (!SCANNED) {
+    for (int64_t i = threadIdx.x; i < (int64_t)blockIdx.x; i += kSegThreads) before += counts[i];
+  }
   WaveSlots w;
   wave_slots(w, slots, n, thr2, m, base);
-  if ((threadIdx.x & 63) == 0) wc[wave] = w.count;
+  if constexpr (!SCANNED) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    wc[wave] = w.count;
+    part[wave] = before;
+  }
   __syncthreads();
+  int64_t pos = 0;
+  if constexpr (SCANNED) {
+    pos = counts[blockIdx.x];
+  } else {
+    for (int i = 0; i < kSegThreads / 64; ++i) pos += part[i];
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+      long long all = pos;
+      for (int i = 0; i < kSegThreads / 64; ++i) all += wc[i];
+      *total = all;
+      *total_host = all;
+    }
+  }
   if (w.count == 0) return;     // wave-uniform; no barrier follows
-  int64_t pos = offs[blockIdx.x];
   for (int i = 0; i < wave; ++i) pos += wc[i];
   const bool ident = map_identity(m);
   const int lane = threadIdx.x & 63;
@@ -350,13 +383,27 @@ int launch_compact_impl(Plan& p, int64_t n_slots, int64_t nwin, int64_t W, float
   int64_t nblk = (n_slots + kSeg - 1) / kSeg;
   if ((size_t)nblk > p.counts_cap) return fail(RFD_E_INVALID, "compaction scratch too small");
   float thr2 = threshold * threshold;
-  hipLaunchKernelGGL(k_count, dim3((unsigned)nblk), dim3(kSegThreads), 0, p.stream, p.slots, n_slots, thr2,
-                     p.counts, m);
+  // One block needs no counts.  Up to 4096 blocks (16.8 million slots) each add the counts before
+  // them in place of the single-workgroup scan between the two passes (at 2 to 2048
+  // blocks 5 us of the chain's 20 to 30).  Beyond that the sums would be more
+  // work than the scan.
+  if (nblk > 1) {
+    hipLaunchKernelGGL(k_count, dim3((unsigned)nblk), dim3(kSegThreads), 0, p.stream, p.slots, n_slots, thr2,
+                       p.counts, m);
+    RFD_CHECK_LAUNCH();
+  }
+  if (nblk <= 4096) {
+    hipLaunchKernelGGL(k_write<false>, dim3((unsigned)nblk), dim3(kSegThreads), 0, p.stream,
+                       p.slots, n_slots, thr2, (const long long*)p.counts, nwin, W, out, capacity, sb_first, nsb, m,
+                       shift, p.n, p.total, p.total_host);
+    RFD_CHECK_LAUNCH();
+    return RFD_OK;
+  }
+  hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, p.stream, p.counts, nblk, p.total, p.total_host);
   RFD_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, p.stream, p.counts, nblk, p.total);
-  RFD_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_write, dim3((unsigned)nblk), dim3(kSegThreads), 0, p.stream, p.slots, n_slots, thr2,
-                     p.counts, nwin, W, out, capacity, sb_first, nsb, m, shift, p.n);
+  hipLaunchKernelGGL(k_write<true>, dim3((unsigned)nblk), dim3(kSegThreads), 0, p.stream, p.slots, n_slots, thr2,
+                     (const long long*)p.counts, nwin, W, out, capacity, sb_first, nsb, m, shift, p.n, p.total,
+                     p.total_host);
   RFD_CHECK_LAUNCH();
   return RFD_OK;
 }
