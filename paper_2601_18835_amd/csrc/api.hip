@@ -57,19 +57,17 @@ static void dfree(T*& ptr) {
   ptr = nullptr;
 }
 
-// (c, tau) of e^{2 pi i m / 4096}, c = cos rounded to FP32 and tau such that c tau is sin
-// to one rounding; where cos vanishes c is 2^-30 (block_fft.h).
-static int upload_tangents(float2** ct) {
-  std::vector<float2> h(4096);
-  for (int m = 0; m < 4096; ++m) {
-    const double a = 2.0 * M_PI * m / 4096.0;
-    const float c = m % 2048 == 1024 ? 0x1p-30f : (float)cos(a);
-    h[m] = make_float2(c, (float)(sin(a) / (double)c));
-  }
-  int rc = dalloc(ct, h.size());
-  if (rc) return rc;
-  RFD_HIP(hipMemcpy(*ct, h.data(), h.size() * sizeof(float2), hipMemcpyHostToDevice));
-  return RFD_OK;
+// (c, tau) of e^{2 pi i m / 4096} (block_fft.h) from its FP64 table: c = cos rounded to the
+// type and tau such that c tau is sin to one rounding; where cos vanishes c is 2^-30
+// (FP32) or 2^-60.
+__global__ void k_tangents(const double2* __restrict__ tw, float2* __restrict__ ct32, double2* __restrict__ ct64) {
+  const int m = blockIdx.x * 256 + threadIdx.x;
+  const bool quarter = m % 2048 == 1024;
+  const double2 w = tw[m];
+  const float c32 = quarter ? 0x1p-30f : (float)w.x;
+  const double c64 = quarter ? 0x1p-60 : w.x;
+  ct32[m] = make_float2(c32, (float)(w.y / (double)c32));
+  ct64[m] = make_double2(c64, w.y / c64);
 }
 
 static bool is_pow2(int64_t x) { return x > 0 && (x & (x - 1)) == 0; }
@@ -159,7 +157,7 @@ static void plan_free(Plan& p) {
   dfree(p.work64b); dfree(p.dref_sig2); dfree(p.dref_scale); dfree(p.dref_part);
   dfree(p.zref); dfree(p.zbf_hi); dfree(p.zbf_lo); dfree(p.zh_hi); dfree(p.zh_lo);
   dfree(p.slots); dfree(p.counts); dfree(p.total); dfree(p.fc_work); dfree(p.counter);
-  dfree(p.ols_tw32); dfree(p.ols_tw64); dfree(p.ols_ct32);
+  dfree(p.ols_tw32); dfree(p.ols_tw64); dfree(p.ols_ct32); dfree(p.ct64);
   for (auto& z : p.zband) dfree(z);
   dfree(p.band_work); dfree(p.band_sums);
   if (p.total_host) (void)hipHostFree(p.total_host);
@@ -360,7 +358,11 @@ int rfd_plan_create(const double* psd, int64_t n_psd, double f_low, double fs, i
   TRY(upload_table(p, p.n1, 1, p.n1, &p.tw32_n1, &p.tw64_n1));
   TRY(upload_table(p, p.n2, 1, p.n2, &p.tw32_n2, &p.tw64_n2));
   TRY(upload_table(p, 4096, 1, 4096, &p.ols_tw32, &p.ols_tw64));
-  TRY(upload_tangents(&p.ols_ct32));
+  TRY(dalloc(&p.ols_ct32, 4096));
+  TRY(dalloc(&p.ct64, 4096));
+  hipLaunchKernelGGL(k_tangents, dim3(4096 / 256), dim3(256), 0, p.stream, (const double2*)p.ols_tw64, p.ols_ct32,
+                     p.ct64);
+  if (hipGetLastError() != hipSuccess) TRY(fail(RFD_E_DEVICE, "twiddle table launch failed"));
   TRY(dalloc(&p.stilde64, nb));
   TRY(dalloc(&p.stilde, nb));
   TRY(dalloc(&p.work64, n));
@@ -387,6 +389,8 @@ int rfd_plan_create(const double* psd, int64_t n_psd, double f_low, double fs, i
   TRY(dalloc(&p.zbf_lo, (size_t)max_refs * n));
   TRY(dalloc(&p.zh_hi, (size_t)max_refs * n));
   TRY(dalloc(&p.zh_lo, (size_t)max_refs * n));
+  // (the tables are complete before a call on another stream reads them)
+  if (hipStreamSynchronize(p.stream) != hipSuccess) TRY(fail(RFD_E_DEVICE, "twiddle table kernel failed"));
 #undef TRY
   *out = h;
   return RFD_OK;

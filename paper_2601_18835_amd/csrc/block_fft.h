@@ -37,69 +37,84 @@ __device__ __forceinline__ void dft4_prod(float2& a, float2& b, float2& c, float
   d = csub(s1, s3);
 }
 
+// The scalar of a complex type and the fused multiply-add of either precision.
+template <typename V> struct ScalarOf;
+template <> struct ScalarOf<float2> { typedef float type; };
+template <> struct ScalarOf<double2> { typedef double type; };
+template <typename V> using scalar_t = typename ScalarOf<V>::type;
+__device__ __forceinline__ float fma_s(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double fma_s(double a, double b, double c) { return fma(a, b, c); }
+template <typename V>
+__device__ __forceinline__ V make_c(scalar_t<V> x, scalar_t<V> y) { V v; v.x = x; v.y = y; return v; }
+
 // A twiddle w = c (1 + i tau) in the form the butterflies below take: (c, tau).
-// Where Re w = 0 the table holds a c of 2^-30 (see ols_ct32): the product with
-// w is then off by 2^-30, below FP32 rounding.
+// Where Re w = 0 the tables hold a c of 2^-30 (FP64: 2^-60): the product with
+// w is then off by as much, below the type's rounding.
 //
 // a +- w b as t = b (1 + i tau), a +- c t: six fused multiply-adds instead of the
 // eight operations of a complex product and two sums, with one rounding of
 // the product instead of two.
-__device__ __forceinline__ void bf_tw(float2& a, float2& b, float2 w) {
-  const float2 t = make_float2(fmaf(-w.y, b.y, b.x), fmaf(w.y, b.x, b.y));
-  b = make_float2(fmaf(-w.x, t.x, a.x), fmaf(-w.x, t.y, a.y));
-  a = make_float2(fmaf(w.x, t.x, a.x), fmaf(w.x, t.y, a.y));
+template <typename V>
+__device__ __forceinline__ void bf_tw(V& a, V& b, V w) {
+  const V t = make_c<V>(fma_s(-w.y, b.y, b.x), fma_s(w.y, b.x, b.y));
+  b = make_c<V>(fma_s(-w.x, t.x, a.x), fma_s(-w.x, t.y, a.y));
+  a = make_c<V>(fma_s(w.x, t.x, a.x), fma_s(w.x, t.y, a.y));
 }
 // the same with the twiddle s i w (s = +-1)
-__device__ __forceinline__ void bf_tw_si(float2& a, float2& b, float2 w, int s) {
-  const float2 t = make_float2(fmaf(-w.y, b.y, b.x), fmaf(w.y, b.x, b.y));
-  const float c = s > 0 ? w.x : -w.x;
-  b = make_float2(fmaf(c, t.y, a.x), fmaf(-c, t.x, a.y));
-  a = make_float2(fmaf(-c, t.y, a.x), fmaf(c, t.x, a.y));
+template <typename V>
+__device__ __forceinline__ void bf_tw_si(V& a, V& b, V w, int s) {
+  const V t = make_c<V>(fma_s(-w.y, b.y, b.x), fma_s(w.y, b.x, b.y));
+  const scalar_t<V> c = s > 0 ? w.x : -w.x;
+  b = make_c<V>(fma_s(c, t.y, a.x), fma_s(-c, t.x, a.y));
+  a = make_c<V>(fma_s(-c, t.y, a.x), fma_s(c, t.x, a.y));
 }
 // 4-point DFT of (a, w b, w^2 c, w^3 d) from the twiddles w2 = w^2 and w
-__device__ __forceinline__ void dft4_tw(float2& a, float2& b, float2& c, float2& d, float2 w2, float2 w, int sign) {
+template <typename V>
+__device__ __forceinline__ void dft4_tw(V& a, V& b, V& c, V& d, V w2, V w, int sign) {
   bf_tw(a, c, w2);
   bf_tw(b, d, w2);
   bf_tw(a, b, w);              // outputs 0 and 2
   bf_tw_si(c, d, w, sign);     // outputs 1 and 3
-  const float2 x2 = b;
+  const V x2 = b;
   b = c;
   c = x2;
 }
 // ... with the twiddles s i w2 and w
-__device__ __forceinline__ void dft4_tw_i(float2& a, float2& b, float2& c, float2& d, float2 w2, float2 w, int sign) {
+template <typename V>
+__device__ __forceinline__ void dft4_tw_i(V& a, V& b, V& c, V& d, V w2, V w, int sign) {
   bf_tw_si(a, c, w2, sign);
   bf_tw_si(b, d, w2, sign);
   bf_tw(a, b, w);
   bf_tw_si(c, d, w, sign);
-  const float2 x2 = b;
+  const V x2 = b;
   b = c;
   c = x2;
 }
 
 // Second half of the 16-point DFT (after the first radix-4 layer over n2):
 // for each k the 4-point DFT of v[4 k + n1] w_16^(n1 k).
-template <int SIGN>
-__device__ __forceinline__ void dft16_rest(float2 (&v)[16]) {
-  constexpr float c1 = 0.92387953251128674f, t1 = 0.41421356237309503f;   // cos, tan of pi / 8
-  constexpr float c3 = 0.38268343236508977f, t3 = 2.41421356237309515f;   // of 3 pi / 8
-  constexpr float r = 0.70710678118654752f;
+template <int SIGN, typename V>
+__device__ __forceinline__ void dft16_rest(V (&v)[16]) {
+  using S = scalar_t<V>;
+  constexpr S c1 = (S)0.92387953251128674, t1 = (S)0.41421356237309503;   // cos, tan of pi / 8
+  constexpr S c3 = (S)0.38268343236508977, t3 = (S)2.41421356237309515;   // of 3 pi / 8
+  constexpr S r = (S)0.70710678118654752, sg = (S)SIGN;
   dft4(v[0], v[1], v[2], v[3], SIGN);
-  dft4_tw(v[4], v[5], v[6], v[7], make_float2(r, SIGN), make_float2(c1, SIGN * t1), SIGN);
+  dft4_tw(v[4], v[5], v[6], v[7], make_c<V>(r, sg), make_c<V>(c1, sg * t1), SIGN);
   {                                                     // k = 2: w^2 is a quarter turn
-    float2 s0 = v[8], s1 = v[9];
-    const float2 c = cmul_si(v[10], SIGN), d = cmul_si(v[11], SIGN);
-    float2 m0 = csub(s0, c), m1 = csub(s1, d);
+    V s0 = v[8], s1 = v[9];
+    const V c = cmul_si(v[10], SIGN), d = cmul_si(v[11], SIGN);
+    V m0 = csub(s0, c), m1 = csub(s1, d);
     s0 = cadd(s0, c);
     s1 = cadd(s1, d);
-    bf_tw(s0, s1, make_float2(r, SIGN));
-    bf_tw_si(m0, m1, make_float2(r, SIGN), SIGN);
+    bf_tw(s0, s1, make_c<V>(r, sg));
+    bf_tw_si(m0, m1, make_c<V>(r, sg), SIGN);
     v[8] = s0;
     v[9] = m0;
     v[10] = s1;
     v[11] = m1;
   }
-  dft4_tw_i(v[12], v[13], v[14], v[15], make_float2(r, SIGN), make_float2(c3, SIGN * t3), SIGN);
+  dft4_tw_i(v[12], v[13], v[14], v[15], make_c<V>(r, sg), make_c<V>(c3, sg * t3), SIGN);
 }
 
 // Twiddles of a 16-point DFT of x[q] w^q (w any unit complex number), as (c, tau):
@@ -115,14 +130,15 @@ template <int R>
 __device__ __forceinline__ constexpr int tw_exponent(int i, int m) {
   if (R == 16) return (i == 0 ? 8 * m : i == 1 ? 4 * m : i < 4 ? 2 * m + 512 * (i - 2) : m + 256 * (i - 4)) & 4095;
   if (R == 8) return (i == 0 ? 4 * m : i == 1 ? 2 * m : m + 512 * (i - 2)) & 4095;
-  return (i == 0 ? 2 * m : m) & 4095;
+  if (R == 4) return (i == 0 ? 2 * m : m) & 4095;
+  return m & 4095;
 }
-// DFTs (R = 4, 8, 16) of v[g R + u] w_g^u on consecutive groups of R slots; slot
+// DFTs (R = 2, 4, 8, 16) of v[g R + u] w_g^u on consecutive groups of R slots; slot
 // order of the results as dft_r.  w(i): entry i of the 16 / R groups' twiddles, group by group.
-template <int R, int SIGN, typename W>
-__device__ __forceinline__ void dft_tw(float2 (&v)[16], const W& w) {
+template <int R, int SIGN, typename V, typename W>
+__device__ __forceinline__ void dft_tw(V (&v)[16], const W& w) {
   if constexpr (R == 16) {
-    const float2 w8 = w(0), w4 = w(1), w2 = w(2), w2b = w(3);
+    const V w8 = w(0), w4 = w(1), w2 = w(2), w2b = w(3);
 #pragma unroll
     for (int n1 = 0; n1 < 4; ++n1) dft4_tw(v[n1], v[n1 + 4], v[n1 + 8], v[n1 + 12], w8, w4, SIGN);
     dft4_tw(v[0], v[1], v[2], v[3], w2, w(4), SIGN);
@@ -132,7 +148,7 @@ __device__ __forceinline__ void dft_tw(float2 (&v)[16], const W& w) {
   } else if constexpr (R == 8) {
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
-      float2* u = v + 8 * g;
+      V* u = v + 8 * g;
       dft4_tw(u[0], u[2], u[4], u[6], w(4 * g), w(4 * g + 1), SIGN);
       dft4_tw(u[1], u[3], u[5], u[7], w(4 * g), w(4 * g + 1), SIGN);
       bf_tw(u[0], u[1], w(4 * g + 2));
@@ -140,6 +156,9 @@ __device__ __forceinline__ void dft_tw(float2 (&v)[16], const W& w) {
       bf_tw_si(u[4], u[5], w(4 * g + 2), SIGN);
       bf_tw_si(u[6], u[7], w(4 * g + 3), SIGN);
     }
+  } else if constexpr (R == 2) {
+#pragma unroll
+    for (int g = 0; g < 8; ++g) bf_tw(v[2 * g], v[2 * g + 1], w(g));
   } else {
 #pragma unroll
     for (int g = 0; g < 4; ++g)
@@ -149,10 +168,23 @@ __device__ __forceinline__ void dft_tw(float2 (&v)[16], const W& w) {
 
 // 16-point DFT in registers, V[k] = sum_n v[n] e^{sign 2 pi i n k / 16}.
 // On return slot s holds V[(s >> 2) + 4 (s & 3)].
-template <int SIGN>
-__device__ __forceinline__ void dft16(float2 (&v)[16]) {
+template <int SIGN, typename V>
+__device__ __forceinline__ void dft16(V (&v)[16]) {
 #pragma unroll
   for (int n1 = 0; n1 < 4; ++n1) dft4(v[n1], v[n1 + 4], v[n1 + 8], v[n1 + 12], SIGN);
+  dft16_rest<SIGN>(v);
+}
+// The same DFT where v[8..16) is zero (and not read).
+template <int SIGN, typename V>
+__device__ __forceinline__ void dft16_half(V (&v)[16]) {
+#pragma unroll
+  for (int n1 = 0; n1 < 4; ++n1) {
+    const V a = v[n1], b = v[n1 + 4], ib = cmul_si(b, SIGN);
+    v[n1] = cadd(a, b);
+    v[n1 + 4] = cadd(a, ib);
+    v[n1 + 8] = csub(a, b);
+    v[n1 + 12] = csub(a, ib);
+  }
   dft16_rest<SIGN>(v);
 }
 // The same DFT of the products x[n] g[n].

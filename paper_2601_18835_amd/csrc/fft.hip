@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "col_fft.h"
 #include "dev_common.h"
 #include "rfd_internal.h"
 
@@ -33,7 +34,19 @@ template <typename V, int L, int C>
 constexpr size_t lds_bytes() { return (size_t)C * lds_col<L>() * sizeof(V) + (size_t)(L + L / 16) * sizeof(V); }
 
 // ---------------------------------------------------------------- loaders
+__device__ __forceinline__ uint32_t clamp_bin(int i, int64_t lo, int64_t hi) {
+  return (uint32_t)std::min<int>(std::max<int>(i, (int)lo), (int)hi);
+}
+// For the transforms of col_fft.h a loader gives each element as an operand that every batch entry
+// shares (fixed: read once per thread) and one of the entry (var: the load alone), joined by join.
+// kHalf: elements past bin N / 2 - 1 vanish.  Bins outside the band carry a zero in `fixed` and
+// read the first bin of the band, so that what a caller keeps there is never met.
 struct LoadData64 {        // real FP64 series, scaled, FP64 complex
+  static constexpr bool kHalf = false;
+  typedef double Fixed; typedef double Var;
+  __device__ double fixed(int) const { return scale; }
+  __device__ double var(int, int i) const { return x[i]; }
+  __device__ double2 join(int, int, double s, double v) const { return make_double2(v * s, 0.0); }
   const double* x; double scale;
   __device__ double2 operator()(int, int64_t i) const { return make_double2(x[i] * scale, 0.0); }
 };
@@ -49,6 +62,18 @@ struct DechirpRefs {
 // in flight before it combines any (see gather_columns).
 struct LoadDechirpRefs {   // s_i w_i conj(h_b,i) / (sigma_b alpha) over the band, FP64
   const double2* s; const double* w; DechirpRefs r; const double* scale; int64_t i_low, i_high;
+  static constexpr bool kHalf = true;
+  typedef double2 Fixed; typedef double2 Var;
+  __device__ double2 fixed(int i) const {
+    if (i < i_low || i > i_high) return make_double2(0.0, 0.0);
+    const double2 x = s[i];
+    return make_double2(w[i] * x.x, w[i] * x.y);
+  }
+  __device__ double2 var(int b, int i) const { return r.h[b][clamp_bin(i, i_low, i_high)]; }
+  __device__ double2 join(int b, int, double2 f, double2 h) const {
+    const double2 v = cmul(f, cconj(h));
+    return make_double2(v.x * scale[b], v.y * scale[b]);
+  }
   struct Raw { double2 h, s; double w; };
   __device__ Raw fetch(int b, int64_t i) const {
     const bool in = i >= i_low && i <= i_high;
@@ -68,6 +93,14 @@ struct LoadDechirpRefs {   // s_i w_i conj(h_b,i) / (sigma_b alpha) over the ban
 };
 struct LoadDechirpRefs32 { // the same integrand, formed in FP64 and rounded once to FP32
   LoadDechirpRefs d;
+  static constexpr bool kHalf = true;
+  typedef double2 Fixed; typedef double2 Var;
+  __device__ double2 fixed(int i) const { return d.fixed(i); }
+  __device__ double2 var(int b, int i) const { return d.var(b, i); }
+  __device__ float2 join(int b, int i, double2 f, double2 h) const {
+    const double2 v = d.join(b, i, f, h);
+    return make_float2((float)v.x, (float)v.y);
+  }
   using Raw = LoadDechirpRefs::Raw;
   __device__ Raw fetch(int b, int64_t i) const { return d.fetch(b, i); }
   __device__ float2 make(int b, int64_t i, const Raw& x) const {
@@ -79,6 +112,19 @@ struct LoadDechirpRefs32 { // the same integrand, formed in FP64 and rounded onc
 struct LoadBands {         // the integrand of one reference on bins [e[b], e[b + 1]), FP64
   const double2* s; const double* w; const double2* h; const double* scale;
   int32_t e[kMaxBands + 1];
+  int32_t last;              // the last edge of the batch
+  static constexpr bool kHalf = true;
+  typedef double2 Fixed; typedef char Var;     // (nothing differs between bands but the range)
+  __device__ double2 fixed(int i) const {
+    if (i < e[0] || i >= last) return make_double2(0.0, 0.0);
+    const double f = w[i] * scale[0];
+    const double2 x = h[i];
+    return cmul(s[i], make_double2(f * x.x, -f * x.y));
+  }
+  __device__ char var(int, int) const { return 0; }
+  __device__ double2 join(int b, int i, double2 f, char) const {
+    return i >= e[b] && i < e[b + 1] ? f : make_double2(0.0, 0.0);
+  }
   struct Raw { double2 h, s; double w; };
   __device__ Raw fetch(int b, int64_t i) const {
     const bool in = i >= e[b] && i < e[b + 1];
@@ -106,6 +152,22 @@ struct LoadFindchirp {     // s_i * F_j,i with F_j stored over band bins
 struct LoadCorr64 {        // FP64 correlation integrands (tap construction, streaming series)
   const double* w; const double2* hr; const double2* ht; int64_t nb, i_low, i_high; int mode;
   const double* bscale;    // mode 0: per-member factor folded into the integrand (nullptr: none)
+  static constexpr bool kHalf = true;
+  typedef double2 Fixed; typedef double2 Var;
+  __device__ double2 fixed(int i) const {
+    if (i < i_low || i > i_high) return make_double2(0.0, 0.0);
+    const double2 r = hr[i];
+    const double rr = r.x * r.x + r.y * r.y;
+    if (mode == 1) return make_double2(w[i] * rr, 0.0);
+    if (mode == 0) return make_double2(w[i] * r.x, -w[i] * r.y);
+    return w[i] * rr > 0.0 ? make_double2(r.x / rr, -r.y / rr) : make_double2(0.0, 0.0);
+  }
+  __device__ double2 var(int b, int i) const { return (ht + (int64_t)b * nb)[clamp_bin(i, i_low, i_high)]; }
+  __device__ double2 join(int b, int, double2 f, double2 t) const {
+    if (mode == 1) return f;
+    const double2 v = cmul(f, t);
+    return bscale ? make_double2(v.x * bscale[b], v.y * bscale[b]) : v;
+  }
   struct Raw { double2 r, t; double w; };
   __device__ Raw fetch(int b, int64_t i) const {
     const bool in = i >= i_low && i <= i_high;
@@ -137,6 +199,14 @@ struct LoadCorr64 {        // FP64 correlation integrands (tap construction, str
 // streaming series use 1 / (sigma_ref alpha), as the FP32 dechirp passes do).
 struct LoadCorr32 {
   LoadCorr64 d;
+  static constexpr bool kHalf = true;
+  typedef double2 Fixed; typedef double2 Var;
+  __device__ double2 fixed(int i) const { return d.fixed(i); }
+  __device__ double2 var(int b, int i) const { return d.var(b, i); }
+  __device__ float2 join(int b, int i, double2 f, double2 t) const {
+    const double2 v = d.join(b, i, f, t);
+    return make_float2((float)v.x, (float)v.y);
+  }
   using Raw = LoadCorr64::Raw;
   __device__ Raw fetch(int b, int64_t i) const { return d.fetch(b, i); }
   __device__ float2 make(int b, int64_t i, const Raw& x) const {
@@ -303,9 +373,151 @@ __global__ __launch_bounds__(kNT) void k_pass_b(const V* __restrict__ Y, ST st, 
   }
 }
 
+
+// ------------------------------------------- passes with register transforms
+// Columns per workgroup: 512 to 1024 threads per CU with two to four workgroups' LDS, and runs of
+// 64 to 256 contiguous bytes in every global access.
+template <typename V, int L> struct ColsOf;
+template <int L> struct ColsOf<float2, L> { static constexpr int value = L == 256 ? 16 : (L == 2048 ? 4 : 8); };
+template <int L> struct ColsOf<double2, L> { static constexpr int value = L == 256 ? 16 : (L == 512 ? 8 : 4); };
+template <typename V, int L> using Fft = ColFft<V, L, ColsOf<V, L>::value>;
+
+__device__ __forceinline__ double2 to_v(double2 v, double2) { return v; }
+__device__ __forceinline__ float2 to_v(double2 v, float2) { return make_float2((float)v.x, (float)v.y); }
+
+// A thread's first-stage inputs x[j + J r] of column i1 for batch entry b.
+template <class F, class LD>
+struct ColInput {
+  static constexpr int NR = LD::kHalf ? 8 : 16;
+  typename LD::Fixed f[NR];
+  typename LD::Var x[NR];
+  int i0, step;
+  __device__ __forceinline__ void init(const LD& ld, int i1, int j, int n1) {
+    i0 = i1 + n1 * j;
+    step = n1 * F::J;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) f[r] = ld.fixed(i0 + step * r);
+  }
+  __device__ __forceinline__ void fetch(const LD& ld, int b) {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) x[r] = ld.var(b, i0 + step * r);
+  }
+  template <int SIGN>
+  __device__ __forceinline__ void first_stage(const LD& ld, int b, typename F::V (&v)[16]) {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) v[r] = ld.join(b, i0 + step * r, f[r], x[r]);
+    if constexpr (LD::kHalf) dft16_half<SIGN>(v);
+    else dft16<SIGN>(v);
+  }
+};
+
+// Pass A (as k_pass_a): columns [g C, (g + 1) C) of batch entries [y JT, (y + 1) JT), the next entry's
+// operands fetched during the current transform.  The inter-pass factor w_N^(i1 n2) of a
+// thread's outputs turns by constant angles from one to the next: FP64 rotations from three table
+// values, rounded to V.  Neighbouring column groups, whose runs share cache lines, go to one XCD.
+// Bound by memory where the batch is large: 16 FP64 correlations at N = 2^20 read 134 MB and write
+// 268 MB in 96 us (325 us with the radix-4 transform in LDS, k_pass_a, which the lengths
+// below 256 keep); 8 FP32 reference integrands 66 -> 36 us; the data transform 24 -> 13 us.
+template <class F, int SIGN, class LD>
+__global__ __launch_bounds__(F::NT) __attribute__((amdgpu_waves_per_eu(2))) void k_cols(LD ld, typename F::V* __restrict__ Y,
+                                               const double2* __restrict__ coarse, const double2* __restrict__ fine,
+                                               const typename F::V* __restrict__ ct, int n1, int count, int JT,
+                                               int row_lo, int row_cnt) {
+  typedef typename F::V V;
+  extern __shared__ __align__(16) unsigned char smem[];
+  V* buf = reinterpret_cast<V*>(smem);
+  const int c = threadIdx.x % F::C, j = threadIdx.x / F::C;
+  const int i1 = (int)xcd_contiguous(blockIdx.x, gridDim.x) * F::C + c;
+  ColTw<F, SIGN> tw;
+  tw.load(ct, buf + F::LDS, j);
+  const int b0 = blockIdx.y * JT, b1 = min(b0 + JT, count);
+  ColInput<F, LD> in;
+  in.init(ld, i1, j, n1);
+  in.fetch(ld, b0);
+  const uint32_t nmask = (uint32_t)n1 * F::L - 1;
+  const double2 base = twiddle_n(coarse, fine, (uint32_t)i1 * (uint32_t)j & nmask, SIGN);
+  const double2 turn_g = twiddle_n(coarse, fine, (uint32_t)i1 * (uint32_t)F::J & nmask, SIGN);
+  const double2 turn_f = twiddle_n(coarse, fine, (uint32_t)i1 * (F::R3 == 1 ? 16u : 256u) & nmask, SIGN);
+  __syncthreads();       // the twiddle table is complete
+  for (int b = b0; b < b1; ++b) {
+    V v[16];
+    in.template first_stage<SIGN>(ld, b, v);
+    in.fetch(ld, min(b + 1, b1 - 1));
+    col_fft_rest<F, SIGN>(v, buf, tw, c, j, c, j);
+    V* Yb = Y + (int64_t)b * n1 * F::L;
+    int jo = j;                                      // formed anew: 16 row addresses carried through
+    asm volatile("" : "+v"(jo));                     // the loop would take 32 registers
+    constexpr int RF = F::R3 == 1 ? 16 : F::R3;      // outputs per group, turn_f apart
+    double2 wg = base;                               // (likewise: 16 factors would take 64)
+    asm volatile("" : "+v"(wg.x), "+v"(wg.y));
+#pragma unroll
+    for (int g = 0; g < 16 / RF; ++g) {
+      double2 w = wg;
+#pragma unroll
+      for (int f = 0; f < RF; ++f) {
+        int q = g * RF;                              // slot of the group's frequency f
+#pragma unroll
+        for (int s = 0; s < RF; ++s)
+          if ((F::R3 == 1 ? dft16_freq(s) : dftr_freq<F::R3>(s)) == f) q = g * RF + s;
+        const int n2 = jo + col_fft_step<F>(q);
+        if (((n2 - row_lo) & (F::L - 1)) < row_cnt) Yb[(uint32_t)(n2 * n1 + i1)] = cmul(v[q], to_v(w, V{}));
+        if (f + 1 < RF) w = cmul(w, turn_f);
+      }
+      if (g + 1 < 16 / RF) wg = cmul(wg, turn_g);
+    }
+  }
+}
+
+// Pass B (as k_pass_b): rows [x C, (x + 1) C) of batch entries [y JT, (y + 1) JT).  The first stage's
+// threads run along a row, the last one's across the rows.  (8 FP32 series at N = 2^20: 41 -> 30 us; 16 FP64
+// ones to |b|^2 193 -> 119; 16 chi^2 bands at 2^19 94 -> 41.)
+template <class F, int SIGN, class ST>
+__global__ __launch_bounds__(F::NT) __attribute__((amdgpu_waves_per_eu(2))) void k_rows(const typename F::V* __restrict__ Y, ST st,
+                                               const typename F::V* __restrict__ ct, int n2, int count, int JT) {
+  typedef typename F::V V;
+  extern __shared__ __align__(16) unsigned char smem[];
+  V* buf = reinterpret_cast<V*>(smem);
+  const int j0 = threadIdx.x % F::J, c0 = threadIdx.x / F::J;
+  const int c = threadIdx.x % F::C, j = threadIdx.x / F::C;
+  const int r0 = (int)xcd_contiguous(blockIdx.x, gridDim.x) * F::C;
+  ColTw<F, SIGN> tw;
+  tw.load(ct, buf + F::LDS, j);
+  const int b0 = blockIdx.y * JT, b1 = min(b0 + JT, count);
+  const int64_t n = (int64_t)n2 * F::L;
+  const V* row = Y + (int64_t)(r0 + c0) * F::L + j0;
+  V nx[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) nx[r] = row[b0 * n + r * F::J];
+  __syncthreads();       // the twiddle table is complete
+  for (int b = b0; b < b1; ++b) {
+    V v[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[r] = nx[r];
+    const int bn = min(b + 1, b1 - 1);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) nx[r] = row[bn * n + r * F::J];
+    dft16<SIGN>(v);
+    col_fft_rest<F, SIGN>(v, buf, tw, c0, j0, c, j);
+    int jo = j;                                      // (as in k_cols)
+    asm volatile("" : "+v"(jo));
+#pragma unroll
+    for (int q = 0; q < 16; ++q) st(b, r0 + c + n2 * (jo + col_fft_step<F>(q)), v[q]);
+  }
+}
+
+// Batch entries per workgroup: enough workgroups for `per_cu` on every CU first, then as many entries
+// as share a thread's tables and operands, up to 8.
+static int entries_per_wg(int64_t groups, int count, int n_cu, int per_cu) {
+  int jt = 1;
+  while (jt < 8 && groups * ((count + 2 * jt - 1) / (2 * jt)) >= (int64_t)per_cu * n_cu) jt *= 2;
+  return jt;
+}
+static const float2* tangents(const Plan& p, float2) { return p.ols_ct32; }
+static const double2* tangents(const Plan& p, double2) { return p.ct64; }
+
 // -------------------------------------------------------------- dispatch
-template <typename V, class LD>
-static int run_pass_a(Plan& p, LD ld, V* Y, const V* coarse, const V* fine, const V* tab2, int batch, int sign,
+template <int SIGN, typename V, class LD>
+static int run_pass_a(Plan& p, LD ld, V* Y, const V* coarse, const V* fine, const V* tab2, int batch,
                       int row_lo = 0, int row_cnt = 1 << 30) {
   dim3 blk(kNT);
   switch (p.n2) {
@@ -314,19 +526,31 @@ static int run_pass_a(Plan& p, LD ld, V* Y, const V* coarse, const V* fine, cons
     constexpr int C = Cols<V>::value(LL);                                                  \
     size_t sh = lds_bytes<V, LL, C>();                                                     \
     hipLaunchKernelGGL((k_pass_a<V, LL, LD>), dim3(p.n1 / C, batch), blk, sh, p.stream, ld, Y, coarse, \
-                       fine, tab2, p.n1, sign, 1, row_lo & (LL - 1), std::min(row_cnt, LL));  \
+                       fine, tab2, p.n1, SIGN, 1, row_lo & (LL - 1), std::min(row_cnt, LL));  \
     break;                                                                                 \
   }
-    CASE_A(32) CASE_A(64) CASE_A(128) CASE_A(256) CASE_A(512) CASE_A(1024) CASE_A(2048)
+#define CASE_R(LL)                                                                                        \
+  case LL: {                                                                                              \
+    using F = Fft<V, LL>;                                                                                 \
+    const int groups = p.n1 / F::C, jt = entries_per_wg(groups, batch, p.n_cu, 2);                         \
+    const dim3 grid((unsigned)groups, (unsigned)((batch + jt - 1) / jt));                                  \
+    const int lo = row_lo & (LL - 1), cnt = std::min(row_cnt, LL);                                         \
+    hipLaunchKernelGGL((k_cols<F, SIGN, LD>), grid, dim3(F::NT), F::lds_bytes, p.stream, ld, Y,             \
+                         (const double2*)p.tw64c, (const double2*)p.tw64f, tangents(p, V{}), p.n1, batch, jt, lo, cnt); \
+    break;                                                                                                \
+  }
+    CASE_A(32) CASE_A(64) CASE_A(128)
+    CASE_R(256) CASE_R(512) CASE_R(1024) CASE_R(2048)
 #undef CASE_A
+#undef CASE_R
     default: return fail(RFD_E_UNSUPPORTED, "fft: unsupported N2");
   }
   RFD_CHECK_LAUNCH();
   return RFD_OK;
 }
 
-template <typename V, class ST>
-static int run_pass_b(Plan& p, const V* Y, ST st, const V* tab1, int batch, int sign) {
+template <int SIGN, typename V, class ST>
+static int run_pass_b(Plan& p, const V* Y, ST st, const V* tab1, int batch) {
   dim3 blk(kNT);
   switch (p.n1) {
 #define CASE_B(LL)                                                                          \
@@ -334,11 +558,22 @@ static int run_pass_b(Plan& p, const V* Y, ST st, const V* tab1, int batch, int 
     constexpr int C = Cols<V>::value(LL);                                                   \
     size_t sh = lds_bytes<V, LL, C>();                                                      \
     hipLaunchKernelGGL((k_pass_b<V, LL, ST>), dim3(p.n2 / C, batch), blk, sh, p.stream, Y, st, tab1, \
-                       p.n2, sign);                                                         \
+                       p.n2, SIGN);                                                         \
     break;                                                                                  \
   }
-    CASE_B(32) CASE_B(64) CASE_B(128) CASE_B(256) CASE_B(512) CASE_B(1024) CASE_B(2048)
+#define CASE_R(LL)                                                                                       \
+  case LL: {                                                                                             \
+    using F = Fft<V, LL>;                                                                                \
+    const int groups = p.n2 / F::C, jt = entries_per_wg(groups, batch, p.n_cu, 2);                        \
+    const dim3 grid((unsigned)groups, (unsigned)((batch + jt - 1) / jt));                                 \
+    hipLaunchKernelGGL((k_rows<F, SIGN, ST>), grid, dim3(F::NT), F::lds_bytes, p.stream, Y, st, tangents(p, V{}), \
+                         p.n2, batch, jt);                                                               \
+    break;                                                                                               \
+  }
+    CASE_B(32) CASE_B(64) CASE_B(128)
+    CASE_R(256) CASE_R(512) CASE_R(1024) CASE_R(2048)
 #undef CASE_B
+#undef CASE_R
     default: return fail(RFD_E_UNSUPPORTED, "fft: unsupported N1");
   }
   RFD_CHECK_LAUNCH();
@@ -550,10 +785,10 @@ __global__ void k_sqrt_to(const double* __restrict__ in, double* __restrict__ ou
 // white rounding noise in the reference series by its out-of-band gain.
 int launch_data_fft(Plan& p, const double* data) {
   LoadData64 ld{data, p.data_scale / p.fs};
-  int rc = run_pass_a<double2>(p, ld, p.work64, p.tw64c, p.tw64f, p.tw64_n2, 1, -1);
+  int rc = run_pass_a<-1, double2>(p, ld, p.work64, p.tw64c, p.tw64f, p.tw64_n2, 1);
   if (rc) return rc;
   StoreSpectrum64 st{p.stilde64, p.stilde, p.n / 2};
-  return run_pass_b<double2>(p, p.work64, st, p.tw64_n1, 1, -1);
+  return run_pass_b<-1, double2>(p, p.work64, st, p.tw64_n1, 1);
 }
 
 int dechirp_batch_size(const Plan& p) {
@@ -594,18 +829,18 @@ int launch_dechirp_refs(Plan& p, int n_refs, const int32_t* ref_ids, const doubl
     LoadDechirpRefs ld{p.stilde64, p.w, refs, p.dref_scale, p.i_low, p.i_high};
     int rc;
     if (p.dechirp_fp64) {
-      rc = run_pass_a<double2>(p, ld, work, p.tw64c, p.tw64f, p.tw64_n2, nr, +1);
+      rc = run_pass_a<1, double2>(p, ld, work, p.tw64c, p.tw64f, p.tw64_n2, nr);
       if (rc) return rc;
       StoreRefSlots st{p.zref, p.n, refs};
-      rc = run_pass_b<double2>(p, work, st, p.tw64_n1, nr, +1);
+      rc = run_pass_b<1, double2>(p, work, st, p.tw64_n1, nr);
     } else {
       // the integrand (and the reference norm) in FP64, both transform passes in
       // FP32 with twiddles rounded once from FP64
       float2* w32 = reinterpret_cast<float2*>(work);
-      rc = run_pass_a<float2>(p, LoadDechirpRefs32{ld}, w32, p.tw32c, p.tw32f, p.tw32_n2, nr, +1);
+      rc = run_pass_a<1, float2>(p, LoadDechirpRefs32{ld}, w32, p.tw32c, p.tw32f, p.tw32_n2, nr);
       if (rc) return rc;
       StoreRefSlots32 st{p.zref, p.n, refs};
-      rc = run_pass_b<float2>(p, w32, st, p.tw32_n1, nr, +1);
+      rc = run_pass_b<1, float2>(p, w32, st, p.tw32_n1, nr);
     }
     if (rc) return rc;
   }
@@ -628,11 +863,11 @@ int launch_dechirp_bands(Plan& p, const double* h_ref, const int64_t* edges, int
   RFD_CHECK_LAUNCH();
   for (int b0 = 0; b0 < n_bands; b0 += batch) {
     const int nb = std::min(batch, n_bands - b0);
-    LoadBands ld{p.stilde64, p.w, one.h[0], p.dref_scale, {}};
+    LoadBands ld{p.stilde64, p.w, one.h[0], p.dref_scale, {}, (int32_t)edges[b0 + nb]};
     for (int b = 0; b <= nb; ++b) ld.e[b] = (int32_t)edges[b0 + b];
-    int rc = run_pass_a<double2>(p, ld, work, p.tw64c, p.tw64f, p.tw64_n2, nb, +1);
+    int rc = run_pass_a<1, double2>(p, ld, work, p.tw64c, p.tw64f, p.tw64_n2, nb);
     if (rc) return rc;
-    rc = run_pass_b<double2>(p, work, StoreBand{out + (int64_t)b0 * p.n, p.n}, p.tw64_n1, nb, +1);
+    rc = run_pass_b<1, double2>(p, work, StoreBand{out + (int64_t)b0 * p.n, p.n}, p.tw64_n1, nb);
     if (rc) return rc;
   }
   return RFD_OK;
@@ -728,7 +963,7 @@ int launch_corr64(Plan& p, Taps& tp, int mode, const double* h_r, const double* 
   // k_lags_direct reads the pass-A rows (k0 + l) mod N2, l < T (every row
   // when the lag window differs per template)
   const int row_lo = k0s ? 0 : (int)(((int64_t)k0 % p.n2 + p.n2) % p.n2);
-  int rc = run_pass_a<double2>(p, ld, tp.work64, p.tw64c, p.tw64f, p.tw64_n2, (int)batch, +1, row_lo,
+  int rc = run_pass_a<1, double2>(p, ld, tp.work64, p.tw64c, p.tw64f, p.tw64_n2, (int)batch, row_lo,
                                k0s ? p.n2 : T);
   if (rc) return rc;
   hipLaunchKernelGGL(k_lags_direct, dim3((unsigned)((T + 3) / 4), (unsigned)batch), dim3(256), 0, p.stream,
@@ -812,9 +1047,9 @@ int launch_corr_peak(Plan& p, Taps& tp, const double* h_r, const double* h_t, in
   if (tp.peak_cap < (size_t)batch * p.n || tp.peak_parts_cap < (size_t)batch * kPeakParts || p.n < 1024)
     return fail(RFD_E_INVALID, "corr peak: scratch too small");
   LoadCorr64 ld{p.w, (const double2*)h_r, (const double2*)h_t, p.nb, p.i_low, p.i_high, 0, nullptr};
-  int rc = run_pass_a<double2>(p, ld, tp.work64, p.tw64c, p.tw64f, p.tw64_n2, (int)batch, +1);
+  int rc = run_pass_a<1, double2>(p, ld, tp.work64, p.tw64c, p.tw64f, p.tw64_n2, (int)batch);
   if (rc) return rc;
-  rc = run_pass_b<double2>(p, (const double2*)tp.work64, StorePow{pw, p.n}, p.tw64_n1, (int)batch, +1);
+  rc = run_pass_b<1, double2>(p, (const double2*)tp.work64, StorePow{pw, p.n}, p.tw64_n1, (int)batch);
   if (rc) return rc;
   hipLaunchKernelGGL(k_peak_part, dim3(kPeakParts, (unsigned)batch), dim3(256), 0, p.stream, (const double*)pw,
                      p.n, tp.peak_part, tp.peak_idx);

@@ -97,8 +97,9 @@ struct Plan {
   bool dechirp_fp64 = false;   // reference transforms in FP64 (default: FP32 passes, FP64 integrand)
   float2* ols_tw32 = nullptr;
   double2* ols_tw64 = nullptr;
-  // the same points e^{i a} as (cos a, tan a), |cos a| at least 2^-30: the twiddles of block_fft.h
+  // the same points e^{i a} as (cos a, tan a): the twiddles of block_fft.h and col_fft.h
   float2* ols_ct32 = nullptr;
+  double2* ct64 = nullptr;
   // chi^2 band series per reference slot: [n_bands][n] FP32, the band edges
   // they were made with and the segment generation
   std::vector<float2*> zband;
