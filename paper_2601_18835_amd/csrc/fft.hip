@@ -676,6 +676,61 @@ __global__ __launch_bounds__(kNT) void k_corr_part(LD ld, V* __restrict__ part, 
   }
 }
 
+// The same shares with the transforms of col_fft.h: the workgroup's columns pass through their
+// stages in registers (as k_cols, batch entries [y JT, (y + 1) JT) in turn) and return to LDS in
+// natural order, where each lag finds its row.  (16 FP64 correlations at N = 2^20, T = 1024: 208 -> 73 us
+// against k_corr_part; 32 FP32 stretches of 3072 lags: 252 -> 161 us.)
+template <class F, class LD>
+__global__ __launch_bounds__(F::NT) __attribute__((amdgpu_waves_per_eu(2))) void k_col_lags(
+    LD ld, typename F::V* __restrict__ part, const double2* __restrict__ coarse, const double2* __restrict__ fine,
+    const typename F::V* __restrict__ ct, int n1, int k0, const int32_t* __restrict__ k0s, int T, int count, int JT) {
+  typedef typename F::V V;
+  extern __shared__ __align__(16) unsigned char smem[];
+  V* buf = reinterpret_cast<V*>(smem);
+  const int c = threadIdx.x % F::C, j = threadIdx.x / F::C;
+  const int g = (int)xcd_contiguous(blockIdx.x, gridDim.x);
+  const int c0 = g * F::C;
+  ColTw<F, 1> tw;
+  tw.load(ct, buf + F::LDS, j);
+  const int b0 = blockIdx.y * JT, b1 = min(b0 + JT, count);
+  ColInput<F, LD> in;
+  in.init(ld, c0 + c, j, n1);
+  in.fetch(ld, b0);
+  const uint32_t nmask = (uint32_t)n1 * F::L - 1;
+  const double2 adv = twiddle_n(coarse, fine, (uint32_t)c0 * (uint32_t)F::NT & nmask, +1);
+  __syncthreads();       // the twiddle table is complete
+  for (int b = b0; b < b1; ++b) {
+    V v[16];
+    in.template first_stage<1>(ld, b, v);
+    in.fetch(ld, min(b + 1, b1 - 1));
+    col_fft_rest<F, 1>(v, buf, tw, c, j, c, j);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) buf[c * F::LP + lpad(j + col_fft_step<F>(q))] = v[q];
+    __syncthreads();
+    if (k0s) k0 = k0s[b];                  // per-template lag window
+    V* pb = part + ((int64_t)b * gridDim.x + g) * T;
+    // share of lag m = k0 + l: sum_c Y_c[m mod L] e^{+2 pi i (c0 + c) m / N}, the factors as in k_corr_part
+    double2 base = twiddle_n(coarse, fine, (uint32_t)c0 * (uint32_t)(k0 + (int)threadIdx.x) & nmask, +1);
+    for (int l = threadIdx.x; l < T; l += F::NT) {
+      const uint32_t m = (uint32_t)(k0 + l) & nmask;
+      const V* row = buf + lpad(m % F::L);
+      const double2 step = twiddle_n(coarse, fine, m, +1);
+      double2 f = base;
+      double re = 0.0, im = 0.0;
+#pragma unroll
+      for (int k = 0; k < F::C; ++k) {
+        const V y = row[k * F::LP];
+        re += (double)y.x * f.x - (double)y.y * f.y;
+        im += (double)y.x * f.y + (double)y.y * f.x;
+        if (k + 1 < F::C) f = cmul(f, step);
+      }
+      pb[l] = to_v(make_double2(re, im), V{});
+      base = cmul(base, adv);
+    }
+    __syncthreads();                       // the next entry's first stage overwrites the rows
+  }
+}
+
 // 32 lags per workgroup; 8 slices of the groups per lag (slice s adds groups
 // s, s + 8, ...), then the slices in order: a fixed summation order.
 template <typename V>
@@ -914,6 +969,18 @@ int launch_fc_cols_lds(Plan& p, const float2* filt, int nb, float2* Y, int n1, i
   return RFD_OK;
 }
 
+// columns per workgroup of the lag shares at column length n2
+template <typename V>
+static int corr_columns(int n2) {
+  switch (n2) {
+    case 256: return Fft<V, 256>::C;
+    case 512: return Fft<V, 512>::C;
+    case 1024: return Fft<V, 1024>::C;
+    case 2048: return Fft<V, 2048>::C;
+    default: return Cols<V>::value(n2);
+  }
+}
+
 int launch_corr64(Plan& p, Taps& tp, int mode, const double* h_r, const double* h_t, int64_t batch, int T,
                   int k0, double2* out, int64_t out_stride, int64_t lo, int64_t hi, const int32_t* k0s, bool fp32,
                   const double* bscale) {
@@ -926,10 +993,11 @@ int launch_corr64(Plan& p, Taps& tp, int mode, const double* h_r, const double* 
                 lo >= 0 ? lo : p.i_low, hi >= 0 ? hi : p.i_high, mode, mode == 0 ? bscale : nullptr};
   const double scale = mode == 2 ? 1.0 / (double)p.n : 1.0;
   // fused form: per-workgroup lag shares in the work buffer, then their sums
-  const int C = fp32 ? Cols<float2>::value(p.n2) : Cols<double2>::value(p.n2);
-  const int groups = p.n1 / C;
+  const int groups = p.n1 / (fp32 ? corr_columns<float2>(p.n2) : corr_columns<double2>(p.n2));
   if ((int64_t)groups * T <= p.n) {
     dim3 blk(kNT);
+    const int jt = entries_per_wg(groups, (int)batch, p.n_cu, 2);
+    const dim3 grid_r((unsigned)groups, (unsigned)((batch + jt - 1) / jt));
     switch (p.n2) {
 #define CASE_C(LL)                                                                                       \
   case LL: {                                                                                             \
@@ -946,8 +1014,25 @@ int launch_corr64(Plan& p, Taps& tp, int mode, const double* h_r, const double* 
     }                                                                                                    \
     break;                                                                                               \
   }
-      CASE_C(32) CASE_C(64) CASE_C(128) CASE_C(256) CASE_C(512) CASE_C(1024) CASE_C(2048)
+#define CASE_R(LL)                                                                                       \
+  case LL: {                                                                                             \
+    if (fp32) {                                                                                          \
+      using F = Fft<float2, LL>;                                                                         \
+      hipLaunchKernelGGL((k_col_lags<F, LoadCorr32>), grid_r, dim3(F::NT), F::lds_bytes, p.stream,        \
+                         LoadCorr32{ld}, (float2*)tp.work64, (const double2*)p.tw64c,                       \
+                         (const double2*)p.tw64f, (const float2*)p.ols_ct32, p.n1, k0, k0s, T, (int)batch, jt); \
+    } else {                                                                                             \
+      using F = Fft<double2, LL>;                                                                        \
+      hipLaunchKernelGGL((k_col_lags<F, LoadCorr64>), grid_r, dim3(F::NT), F::lds_bytes, p.stream, ld,    \
+                         tp.work64, (const double2*)p.tw64c, (const double2*)p.tw64f,                       \
+                         (const double2*)p.ct64, p.n1, k0, k0s, T, (int)batch, jt);                         \
+    }                                                                                                    \
+    break;                                                                                               \
+  }
+      CASE_C(32) CASE_C(64) CASE_C(128)
+      CASE_R(256) CASE_R(512) CASE_R(1024) CASE_R(2048)
 #undef CASE_C
+#undef CASE_R
       default: return fail(RFD_E_UNSUPPORTED, "fft: unsupported N2");
     }
     RFD_CHECK_LAUNCH();
