@@ -709,22 +709,21 @@ __global__ __launch_bounds__(F::NT) __attribute__((amdgpu_waves_per_eu(2))) void
     __syncthreads();
     if (k0s) k0 = k0s[b];                  // per-template lag window
     V* pb = part + ((int64_t)b * gridDim.x + g) * T;
-    // share of lag m = k0 + l: sum_c Y_c[m mod L] e^{+2 pi i (c0 + c) m / N}, the factors as in k_corr_part
+    // share of lag m = k0 + l: e^{+2 pi i c0 m / N} sum_c Y_c[m mod L] (e^{+2 pi i m / N})^c, the sum by Horner's
+    // rule and the factor before it turning from one of the thread's lags to its next, in FP64
     double2 base = twiddle_n(coarse, fine, (uint32_t)c0 * (uint32_t)(k0 + (int)threadIdx.x) & nmask, +1);
     for (int l = threadIdx.x; l < T; l += F::NT) {
       const uint32_t m = (uint32_t)(k0 + l) & nmask;
       const V* row = buf + lpad(m % F::L);
       const double2 step = twiddle_n(coarse, fine, m, +1);
-      double2 f = base;
-      double re = 0.0, im = 0.0;
+      double2 acc = make_double2(row[(F::C - 1) * F::LP].x, row[(F::C - 1) * F::LP].y);
 #pragma unroll
-      for (int k = 0; k < F::C; ++k) {
+      for (int k = F::C - 2; k >= 0; --k) {
         const V y = row[k * F::LP];
-        re += (double)y.x * f.x - (double)y.y * f.y;
-        im += (double)y.x * f.y + (double)y.y * f.x;
-        if (k + 1 < F::C) f = cmul(f, step);
+        acc = make_double2(fma(acc.x, step.x, fma(-acc.y, step.y, (double)y.x)),
+                           fma(acc.x, step.y, fma(acc.y, step.x, (double)y.y)));
       }
-      pb[l] = to_v(make_double2(re, im), V{});
+      pb[l] = to_v(cmul(acc, base), V{});
       base = cmul(base, adv);
     }
     __syncthreads();                       // the next entry's first stage overwrites the rows
