@@ -27,7 +27,7 @@ struct ColFft {
   // the third stage's twiddles: 8 per thread in registers, or in FP64, where they would take 32
   // registers beside the 64 of the values, the 256 butterflies' own in LDS
   static constexpr int PER = R3 > 1 ? kTw16 * R3 / 16 : 0;    // per butterfly
-  static constexpr bool TW3_LDS = sizeof(V) == 16;
+  static constexpr bool TW3_LDS = true;
   static constexpr int TW3 = TW3_LDS ? 256 * PER : 0;
   static constexpr size_t lds_bytes = (size_t)(LDS + TWB + TW3) * sizeof(V);
   static_assert(C <= G && G % C == 0, "columns of a workgroup");

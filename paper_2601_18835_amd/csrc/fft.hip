@@ -679,9 +679,13 @@ __global__ __launch_bounds__(kNT) void k_corr_part(LD ld, V* __restrict__ part, 
 // The same shares with the transforms of col_fft.h: the workgroup's columns pass through their
 // stages in registers (as k_cols, batch entries [y JT, (y + 1) JT) in turn) and return to LDS in
 // natural order, where each lag finds its row.  (16 FP64 correlations at N = 2^20, T = 1024: 208 -> 73 us
-// against k_corr_part; 32 FP32 stretches of 3072 lags: 252 -> 161 us.)
+// against k_corr_part; 32 FP32 stretches of 3072 lags: 252 -> 122 us.)
+// FP32 columns of 512 and 1024 points do without the fetch ahead: two workgroups then fit a CU
+// (128 registers) and the one's loads pass under the other's lag sums (148 -> 122 us for those
+// stretches).  The other lengths would spill.
+template <class F> constexpr bool kLagAhead = sizeof(typename F::V) == 16 || F::L == 256 || F::L == 2048;
 template <class F, class LD>
-__global__ __launch_bounds__(F::NT) __attribute__((amdgpu_waves_per_eu(2))) void k_col_lags(
+__global__ __launch_bounds__(F::NT) __attribute__((amdgpu_waves_per_eu(kLagAhead<F> ? 2 : 4))) void k_col_lags(
     LD ld, typename F::V* __restrict__ part, const double2* __restrict__ coarse, const double2* __restrict__ fine,
     const typename F::V* __restrict__ ct, int n1, int k0, const int32_t* __restrict__ k0s, int T, int count, int JT) {
   typedef typename F::V V;
@@ -695,14 +699,15 @@ __global__ __launch_bounds__(F::NT) __attribute__((amdgpu_waves_per_eu(2))) void
   const int b0 = blockIdx.y * JT, b1 = min(b0 + JT, count);
   ColInput<F, LD> in;
   in.init(ld, c0 + c, j, n1);
-  in.fetch(ld, b0);
+  if constexpr (kLagAhead<F>) in.fetch(ld, b0);
   const uint32_t nmask = (uint32_t)n1 * F::L - 1;
   const double2 adv = twiddle_n(coarse, fine, (uint32_t)c0 * (uint32_t)F::NT & nmask, +1);
   __syncthreads();       // the twiddle table is complete
   for (int b = b0; b < b1; ++b) {
     V v[16];
+    if constexpr (!kLagAhead<F>) in.fetch(ld, b);
     in.template first_stage<1>(ld, b, v);
-    in.fetch(ld, min(b + 1, b1 - 1));
+    if constexpr (kLagAhead<F>) in.fetch(ld, min(b + 1, b1 - 1));
     col_fft_rest<F, 1>(v, buf, tw, c, j, c, j);
 #pragma unroll
     for (int q = 0; q < 16; ++q) buf[c * F::LP + lpad(j + col_fft_step<F>(q))] = v[q];
@@ -781,7 +786,7 @@ __global__ __launch_bounds__(1024) void k_sigma_sq(const double* __restrict__ w,
 
 // sigma^2 of each reference of a batch in two steps of fixed order:
 // kSigParts workgroups per reference reduce contiguous bin ranges to
-// partial sums, then one thread per reference adds its partials in order and
+// partial sums, then one wave per reference adds its partials and
 // stores sigma^2 by slot and the filter scale 1 / (sigma alpha).
 __global__ __launch_bounds__(256) void k_sigma_part(const double* __restrict__ w, DechirpRefs r, int64_t nb,
                                                    double* __restrict__ part) {
@@ -790,10 +795,19 @@ __global__ __launch_bounds__(256) void k_sigma_part(const double* __restrict__ w
   const int64_t chunk = (nb + kSigParts - 1) / kSigParts;
   const int64_t i0 = (int64_t)blockIdx.x * chunk, i1 = std::min<int64_t>(i0 + chunk, nb);
   double acc = 0.0;
-  for (int64_t i = i0 + threadIdx.x; i < i1; i += 256) {
-    const double2 v = hb[i];
-    acc += w[i] * (v.x * v.x + v.y * v.y);
+  int64_t i = i0 + threadIdx.x;
+  for (; i + 256 * 7 < i1; i += 256 * 8) {       // eight bins' loads in flight (one at a time: 24 us for
+    double2 v[8];                                // 8 references at N = 2^20)
+    double u[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      v[k] = hb[i + 256 * k];
+      u[k] = w[i + 256 * k];
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc += u[k] * (v[k].x * v[k].x + v[k].y * v[k].y);
   }
+  for (; i < i1; i += 256) acc += w[i] * (hb[i].x * hb[i].x + hb[i].y * hb[i].y);
   red[threadIdx.x] = acc;
   __syncthreads();
   for (int o = 128; o > 0; o >>= 1) {
@@ -802,14 +816,17 @@ __global__ __launch_bounds__(256) void k_sigma_part(const double* __restrict__ w
   }
   if (threadIdx.x == 0) part[blockIdx.y * kSigParts + blockIdx.x] = red[0];
 }
-__global__ void k_sigma_final(DechirpRefs r, int nr, const double* __restrict__ part,
-                              double* __restrict__ sig2_by_slot, double* __restrict__ scale, double inv_alpha) {
-  const int b = threadIdx.x;
-  if (b >= nr) return;
-  double s2 = 0.0;
-  for (int k = 0; k < kSigParts; ++k) s2 += part[b * kSigParts + k];
-  sig2_by_slot[r.slot[b]] = s2;
-  scale[b] = inv_alpha / sqrt(s2);
+__global__ __launch_bounds__(kSigParts) void k_sigma_final(DechirpRefs r, const double* __restrict__ part,
+                                                         double* __restrict__ sig2_by_slot,
+                                                         double* __restrict__ scale, double inv_alpha) {
+  const int b = blockIdx.x;
+  double s2 = part[b * kSigParts + threadIdx.x];
+#pragma unroll
+  for (int o = kSigParts / 2; o > 0; o >>= 1) s2 += __shfl_xor(s2, o);
+  if (threadIdx.x == 0) {
+    sig2_by_slot[r.slot[b]] = s2;
+    scale[b] = inv_alpha / sqrt(s2);
+  }
 }
 
 // F[i] = w_i conj(h_i) / (sigma * alpha), FP64 then rounded to FP32.
@@ -846,12 +863,13 @@ int launch_data_fft(Plan& p, const double* data) {
 }
 
 int dechirp_batch_size(const Plan& p) {
-  // intermediates of a batch (FP32 or FP64 complex): at most 64 MiB and
-  // kDechirpBatch references.  A batch's pass-A output then stays small
-  // beside the 256 MB last-level cache when pass B reads it back (0.61 ->
-  // 0.56 ms for 32 references at N = 2^20 against 256 MiB batches)
+  // intermediates of a batch (FP32 or FP64 complex): at most 128 MiB and
+  // kDechirpBatch references.  A batch's pass-A output then stays within
+  // the 256 MB last-level cache when pass B reads it back, and its four launches
+  // are few (32 references at N = 2^20, with the copies out: 651 us at 64 MiB, 619 at 128,
+  // 596 at 256)
   const int64_t elem = p.dechirp_fp64 ? (int64_t)sizeof(double2) : (int64_t)sizeof(float2);
-  int64_t b = ((int64_t)64 << 20) / (p.n * elem);
+  int64_t b = ((int64_t)128 << 20) / (p.n * elem);
   return (int)std::max<int64_t>(1, std::min<int64_t>(b, kDechirpBatch));
 }
 
@@ -877,7 +895,7 @@ int launch_dechirp_refs(Plan& p, int n_refs, const int32_t* ref_ids, const doubl
     hipLaunchKernelGGL(k_sigma_part, dim3(kSigParts, (unsigned)nr), dim3(256), 0, p.stream, p.w, refs, p.nb,
                        p.dref_part);
     RFD_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_sigma_final, dim3(1), dim3(kDechirpBatch), 0, p.stream, refs, nr,
+    hipLaunchKernelGGL(k_sigma_final, dim3((unsigned)nr), dim3(kSigParts), 0, p.stream, refs,
                        (const double*)p.dref_part, p.dref_sig2, p.dref_scale, 1.0 / p.data_scale);
     RFD_CHECK_LAUNCH();
     LoadDechirpRefs ld{p.stilde64, p.w, refs, p.dref_scale, p.i_low, p.i_high};
@@ -912,7 +930,7 @@ int launch_dechirp_bands(Plan& p, const double* h_ref, const int64_t* edges, int
   one.h[0] = reinterpret_cast<const double2*>(h_ref);
   hipLaunchKernelGGL(k_sigma_part, dim3(kSigParts, 1), dim3(256), 0, p.stream, p.w, one, p.nb, p.dref_part);
   RFD_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_sigma_final, dim3(1), dim3(kDechirpBatch), 0, p.stream, one, 1, (const double*)p.dref_part,
+  hipLaunchKernelGGL(k_sigma_final, dim3(1), dim3(kSigParts), 0, p.stream, one, (const double*)p.dref_part,
                      p.dscratch + 16, p.dref_scale, 1.0 / p.data_scale);
   RFD_CHECK_LAUNCH();
   for (int b0 = 0; b0 < n_bands; b0 += batch) {
