@@ -766,7 +766,7 @@ static void taps_free(Taps& t) {
   dfree(t.d_first); dfree(t.d_meta); dfree(t.d_abase); dfree(t.work64); dfree(t.bvec);
   dfree(t.d_p16); dfree(t.d_p32); dfree(t.d_count);
   dfree(t.d_it_off); dfree(t.d_it_sb); dfree(t.d_it_S); dfree(t.d_it_nsg);
-  dfree(t.d_shift); dfree(t.peak_pw); dfree(t.k0buf); dfree(t.peak_part); dfree(t.peak_idx);
+  dfree(t.d_shift); dfree(t.peak_z); dfree(t.k0buf); dfree(t.peak_part); dfree(t.peak_idx);
 }
 
 int rfd_taps_create(rfd_plan* plan, int32_t n_subbanks, const int64_t* offsets, const int32_t* ref_id,
@@ -878,6 +878,7 @@ int rfd_make_taps(rfd_plan* plan, rfd_taps* taps, int32_t subbank, const double*
   // FFT scratch for a chunk of templates (<= 256 MiB)
   int64_t chunk = std::max<int64_t>(1, ((int64_t)256 << 20) / (p.n * (int64_t)sizeof(double2)));
   chunk = std::min<int64_t>(chunk, 64);
+  if (centre) chunk = std::max<int64_t>(1, chunk / 2);     // as much again for the full correlations
   chunk = std::min<int64_t>(chunk, count);
   size_t need_w = (size_t)std::max<int64_t>(chunk, 1) * p.n;
   if (t.work64_cap < need_w) {
@@ -919,9 +920,9 @@ int rfd_make_taps(rfd_plan* plan, rfd_taps* taps, int32_t subbank, const double*
     const size_t need_p = (size_t)chunk * p.n;
     if (t.peak_cap < need_p) {
       RFD_HIP(hipStreamSynchronize(p.stream));
-      dfree(t.peak_pw);
+      dfree(t.peak_z);
       t.peak_cap = 0;
-      int rc = dalloc(&t.peak_pw, need_p);
+      int rc = dalloc(&t.peak_z, need_p);
       if (rc) return rc;
       t.peak_cap = need_p;
     }
@@ -959,9 +960,11 @@ int rfd_make_taps(rfd_plan* plan, rfd_taps* taps, int32_t subbank, const double*
     int64_t cn = std::min(chunk, count - c0);
     const int32_t* k0s = nullptr;
     if (centre) {
-      int rc = launch_corr_peak(p, t, h_ref, h_tmpl + 2 * c0 * p.nb, cn, T, s.k0, t.peak_pw, t.k0buf + c0,
-                                dsh + c0);
+      const bool ls = method == RFD_TAPS_LS;
+      int rc = launch_corr_peak(p, t, h_ref, h_tmpl + 2 * c0 * p.nb, cn, T, s.k0, t.peak_z, t.k0buf + c0, dsh + c0,
+                                ls ? t.bvec + c0 * T : nullptr);
       if (rc) return rc;
+      if (ls) continue;
       k0s = t.k0buf + c0;
     }
     int rc = launch_corr64(p, t, method == RFD_TAPS_LS ? 0 : 2, h_ref, h_tmpl + 2 * c0 * p.nb, cn, T, s.k0,

@@ -353,6 +353,10 @@ __device__ void pass_b_load(const V* __restrict__ Yb, V* buf, V* twl, const V* _
   __syncthreads();
 }
 
+// storers that also reduce over a workgroup's outputs
+template <class ST, class = void> struct HasDone : std::false_type {};
+template <class ST> struct HasDone<ST, std::void_t<decltype(&ST::done)>> : std::true_type {};
+
 // pass B: L = N1-point transforms of C rows, generic storer
 template <typename V, int L, class ST>
 __global__ __launch_bounds__(kNT) void k_pass_b(const V* __restrict__ Y, ST st, const V* __restrict__ tabL,
@@ -371,6 +375,7 @@ __global__ __launch_bounds__(kNT) void k_pass_b(const V* __restrict__ Y, ST st, 
     int c = e % C, n1 = e / C;
     st(b, (int64_t)(r0 + c) + (int64_t)n2 * n1, buf[c * LP + lpad(n1)]);
   }
+  if constexpr (HasDone<ST>::value) st.done(b, blockIdx.x, gridDim.x);
 }
 
 
@@ -502,6 +507,7 @@ __global__ __launch_bounds__(F::NT) __attribute__((amdgpu_waves_per_eu(2))) void
     asm volatile("" : "+v"(jo));
 #pragma unroll
     for (int q = 0; q < 16; ++q) st(b, r0 + c + n2 * (jo + col_fft_step<F>(q)), v[q]);
+    if constexpr (HasDone<ST>::value) st.done(b, blockIdx.x, gridDim.x);
   }
 }
 
@@ -1077,87 +1083,107 @@ int launch_corr64(Plan& p, Taps& tp, int mode, const double* h_r, const double* 
 
 
 // ------------------------------------------------- lag of the correlation peak
-// |b|^2 of pass B's output (natural order) for the peak search
-struct StorePow {
-  double* pw;
+// Pass B's output b (natural order) and the largest |b|^2 of each workgroup's outputs with its
+// index, the lowest on exact ties.
+struct StorePeak {
+  double2* z;
   int64_t n;
-  __device__ void operator()(int b, int64_t idx, double2 v) const { pw[(int64_t)b * n + idx] = v.x * v.x + v.y * v.y; }
+  double* pv;        // [batch][groups]
+  int32_t* pi;
+  double best = -1.0;
+  int at = 0;
+  __device__ __forceinline__ void take(double v, int i) {
+    if (v > best || (v == best && i < at)) {
+      best = v;
+      at = i;
+    }
+  }
+  __device__ __forceinline__ void operator()(int b, int64_t i, double2 v) {
+    z[(int64_t)b * n + i] = v;
+    take(v.x * v.x + v.y * v.y, (int)i);
+  }
+  __device__ __forceinline__ void done(int b, int group, int groups) {
+    __shared__ double sv[16];
+    __shared__ int si[16];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) take(__shfl_xor(best, o), __shfl_xor(at, o));
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+      sv[wave] = best;
+      si[wave] = at;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int k = 1; k < (int)(blockDim.x >> 6); ++k) take(sv[k], si[k]);
+      pv[(int64_t)b * groups + group] = best;
+      pi[(int64_t)b * groups + group] = at;
+    }
+    __syncthreads();
+    best = -1.0;
+    at = 0;
+  }
 };
 
 // Per template: the lag of the largest |b[l]|^2 over all N lags (lowest
-// index 0..N-1 on exact ties), mapped into (-N/2, N/2]; the lag window
-// k0_j = peak - floor(T/2) and its offset from the sub-bank's k0.  Two
-// stages: kPeakParts workgroups per template each reduce one contiguous
-// chunk to (value, index), then one thread per template takes the chunks
-// in index order (a strict > keeps the lowest index).
-__global__ __launch_bounds__(256) void k_peak_part(const double* __restrict__ pw, int64_t n,
-                                                 double* __restrict__ pv, int64_t* __restrict__ pi) {
-  __shared__ double bv[256];
-  __shared__ int64_t bi[256];
-  const int64_t chunk = n / kPeakParts;              // n is a power of two >= 1024
-  const double* row = pw + (int64_t)blockIdx.y * n + (int64_t)blockIdx.x * chunk;
-  double best = -1.0;
-  int64_t idx = 0;
-  for (int64_t i = threadIdx.x; i < chunk; i += 256) {
-    const double v = row[i];
-    if (v > best) {          // increasing i: the first maximum stays
-      best = v;
-      idx = i;
-    }
-  }
-  bv[threadIdx.x] = best;
-  bi[threadIdx.x] = idx;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) {
-      const double v = bv[threadIdx.x + o];
-      const int64_t j = bi[threadIdx.x + o];
-      if (v > bv[threadIdx.x] || (v == bv[threadIdx.x] && j < bi[threadIdx.x])) {
-        bv[threadIdx.x] = v;
-        bi[threadIdx.x] = j;
-      }
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    pv[(int64_t)blockIdx.y * kPeakParts + blockIdx.x] = bv[0];
-    pi[(int64_t)blockIdx.y * kPeakParts + blockIdx.x] = (int64_t)blockIdx.x * chunk + bi[0];
-  }
-}
-__global__ void k_peak_lag(const double* __restrict__ pv, const int64_t* __restrict__ pi, int64_t batch, int64_t n,
-                           int T, int k0_sb, int32_t* __restrict__ k0_out, int32_t* __restrict__ d_out) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= batch) return;
-  double best = -1.0;
-  int64_t i = 0;
-  for (int c = 0; c < kPeakParts; ++c) {
-    const double v = pv[t * kPeakParts + c];
-    if (v > best) {
-      best = v;
-      i = pi[t * kPeakParts + c];
-    }
-  }
-  const int lag = (int)(i <= n / 2 ? i : i - n);
-  const int k0 = lag - T / 2;
-  k0_out[t] = k0;
-  if (d_out) d_out[t] = k0 - k0_sb;
+// index 0..N-1 on exact ties) from its workgroups' maxima, mapped into
+// (-N/2, N/2]; the lag window k0_j = peak - floor(T/2) and its offset from the
+// sub-bank's k0.  One wave per template.
+__global__ __launch_bounds__(64) void k_peak_lag(const double* __restrict__ pv, const int32_t* __restrict__ pi,
+                                               int groups, int64_t n, int T, int k0_sb, int32_t* __restrict__ k0_out,
+                                               int32_t* __restrict__ d_out) {
+  StorePeak m{nullptr, 0, nullptr, nullptr};
+  for (int c = threadIdx.x; c < groups; c += 64)
+    m.take(pv[(int64_t)blockIdx.x * groups + c], pi[(int64_t)blockIdx.x * groups + c]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m.take(__shfl_xor(m.best, o), __shfl_xor(m.at, o));
+  if (threadIdx.x) return;
+  const int lag = (int)(m.at <= n / 2 ? m.at : m.at - n);
+  k0_out[blockIdx.x] = lag - T / 2;
+  if (d_out) d_out[blockIdx.x] = lag - T / 2 - k0_sb;
 }
 
+// The T lags k0_t + l of each template's full correlation.
+__global__ __launch_bounds__(256) void k_peak_window(const double2* __restrict__ z, int64_t n,
+                                                   const int32_t* __restrict__ k0s, int T, double2* __restrict__ out) {
+  const int l = blockIdx.x * 256 + threadIdx.x;
+  if (l >= T) return;
+  const int64_t t = blockIdx.y;
+  out[t * T + l] = z[t * n + (((int64_t)k0s[t] + l) & (n - 1))];
+}
+
+// workgroups per template of the FP64 row pass
+static int row_groups(const Plan& p) {
+  switch (p.n1) {
+    case 256: return p.n2 / Fft<double2, 256>::C;
+    case 512: return p.n2 / Fft<double2, 512>::C;
+    case 1024: return p.n2 / Fft<double2, 1024>::C;
+    case 2048: return p.n2 / Fft<double2, 2048>::C;
+    default: return p.n2 / Cols<double2>::value(p.n1);
+  }
+}
+
+// The correlations stay in z [batch][N]: with the lag windows chosen, least squares reads its right-hand sides from
+// them (out, may be NULL) instead of transforming the templates again.  16 templates at
+// N = 2^20, T = 1024: 365 us while the row pass kept |b|^2 alone, a second pass searched it and the kept lags were
+// summed from a second column transform.
 int launch_corr_peak(Plan& p, Taps& tp, const double* h_r, const double* h_t, int64_t batch, int T, int k0_sb,
-                     double* pw, int32_t* k0_out, int32_t* d_out) {
+                     double2* z, int32_t* k0_out, int32_t* d_out, double2* out) {
   if (tp.work64_cap < (size_t)batch * p.n) return fail(RFD_E_INVALID, "corr peak: work buffer too small");
-  if (tp.peak_cap < (size_t)batch * p.n || tp.peak_parts_cap < (size_t)batch * kPeakParts || p.n < 1024)
+  const int groups = row_groups(p);
+  if (tp.peak_cap < (size_t)batch * p.n || tp.peak_parts_cap < (size_t)batch * kPeakParts || groups > kPeakParts)
     return fail(RFD_E_INVALID, "corr peak: scratch too small");
   LoadCorr64 ld{p.w, (const double2*)h_r, (const double2*)h_t, p.nb, p.i_low, p.i_high, 0, nullptr};
   int rc = run_pass_a<1, double2>(p, ld, tp.work64, p.tw64c, p.tw64f, p.tw64_n2, (int)batch);
   if (rc) return rc;
-  rc = run_pass_b<1, double2>(p, (const double2*)tp.work64, StorePow{pw, p.n}, p.tw64_n1, (int)batch);
+  rc = run_pass_b<1, double2>(p, (const double2*)tp.work64, StorePeak{z, p.n, tp.peak_part, tp.peak_idx}, p.tw64_n1,
+                              (int)batch);
   if (rc) return rc;
-  hipLaunchKernelGGL(k_peak_part, dim3(kPeakParts, (unsigned)batch), dim3(256), 0, p.stream, (const double*)pw,
-                     p.n, tp.peak_part, tp.peak_idx);
+  hipLaunchKernelGGL(k_peak_lag, dim3((unsigned)batch), dim3(64), 0, p.stream, (const double*)tp.peak_part,
+                     (const int32_t*)tp.peak_idx, groups, p.n, T, k0_sb, k0_out, d_out);
   RFD_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_peak_lag, dim3((unsigned)((batch + 63) / 64)), dim3(64), 0, p.stream,
-                     (const double*)tp.peak_part, (const int64_t*)tp.peak_idx, batch, p.n, T, k0_sb, k0_out, d_out);
+  if (!out) return RFD_OK;
+  hipLaunchKernelGGL(k_peak_window, dim3((unsigned)((T + 255) / 256), (unsigned)batch), dim3(256), 0, p.stream,
+                     (const double2*)z, p.n, (const int32_t*)k0_out, T, out);
   RFD_CHECK_LAUNCH();
   return RFD_OK;
 }

@@ -188,8 +188,8 @@ struct Taps {
   // scratch for tap construction
   double2* work64 = nullptr; size_t work64_cap = 0;
   double2* bvec = nullptr; size_t bvec_cap = 0;
-  double* peak_pw = nullptr; size_t peak_cap = 0;      // |b|^2 of the full correlations (centring)
-  double* peak_part = nullptr; int64_t* peak_idx = nullptr; size_t peak_parts_cap = 0;   // chunk maxima
+  double2* peak_z = nullptr; size_t peak_cap = 0;      // the full correlations (centring)
+  double* peak_part = nullptr; int32_t* peak_idx = nullptr; size_t peak_parts_cap = 0;   // workgroup maxima
   int32_t* k0buf = nullptr; size_t k0buf_cap = 0;      // per-template k0 of one make_taps call
 };
 
@@ -218,12 +218,13 @@ int launch_fc_cols_lds(Plan& p, const float2* filt, int nb, float2* Y, int n1, i
 int launch_corr64(Plan& p, Taps& tp, int mode, const double* h_r, const double* h_t, int64_t batch,
                   int T, int k0, double2* out, int64_t out_stride, int64_t lo = -1, int64_t hi = -1,
                   const int32_t* k0s = nullptr, bool fp32 = false, const double* bscale = nullptr);
-constexpr int kPeakParts = 64;   // chunks per template in the peak-lag reduction
+constexpr int kPeakParts = 512;  // workgroups per template of the row pass, at most
 // Per-template lag centring: the full weighted cross-correlation b (mode 0)
-// of each batch entry, |b|^2 into pw [batch][N], and its peak lag l in
+// of each batch entry into z [batch][N], and its peak lag l in
 // (-N/2, N/2]: k0_out[t] = l - floor(T/2), d_out[t] = k0_out[t] - k0_sb.
+// out (may be NULL) [batch][T]: b at the lags k0_out[t] + l, l < T.
 int launch_corr_peak(Plan& p, Taps& tp, const double* h_r, const double* h_t, int64_t batch, int T, int k0_sb,
-                     double* pw, int32_t* k0_out, int32_t* d_out);
+                     double2* z, int32_t* k0_out, int32_t* d_out, double2* out);
 // band series [n_bands][N] (FP32, normalised by sigma_ref) of one reference
 int launch_dechirp_bands(Plan& p, const double* h_ref, const int64_t* edges, int n_bands, float2* out, double2* work,
                          int batch);
