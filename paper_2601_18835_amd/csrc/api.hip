@@ -757,6 +757,7 @@ static void taps_free(Taps& t) {
   for (auto& s : t.sb) {
     dfree(s.L);
     dfree(s.U);
+    dfree(s.Dinv);
     dfree(s.g);
     dfree(s.ols_x);
     dfree(s.ols_g);
@@ -901,13 +902,12 @@ int rfd_make_taps(rfd_plan* plan, rfd_taps* taps, int32_t subbank, const double*
   // reference autocorrelation g (always) and the Cholesky factor (LS)
   const double eps = method == RFD_TAPS_LS ? ridge_eps : -1.0;
   if (method == RFD_TAPS_LS && (!s.L || s.eps != ridge_eps)) {
-    if (!s.L) {
-      int rc = dalloc(&s.L, (size_t)T * T);
-      if (rc) return rc;
-      rc = dalloc(&s.U, (size_t)T * T);
-      if (rc) return rc;
-    }
-    int rc = taps_prepare_subbank(p, t, subbank, h_ref, eps);
+    int rc = RFD_OK;      // (each on its own: an earlier call may have stopped between them)
+    if (!s.L) rc = dalloc(&s.L, (size_t)T * T);
+    if (!rc && !s.U) rc = dalloc(&s.U, (size_t)T * T);
+    if (!rc && !s.Dinv) rc = dalloc(&s.Dinv, (size_t)round_up(T, 64) * 64);
+    if (rc) return rc;
+    rc = taps_prepare_subbank(p, t, subbank, h_ref, eps);
     if (rc) return rc;
   } else {
     // g is cheap; refresh it so sigma_fit always uses this reference

@@ -139,6 +139,7 @@ struct SubBankTaps {
   int64_t p32_base = 0;             // offset (float4) into packed fp32 array
   double2* L = nullptr;             // Cholesky factor, column-major T x T
   double2* U = nullptr;             // L^H, column-major
+  double2* Dinv = nullptr;          // inverses of L's 64 x 64 diagonal blocks, column-major
   double2* g = nullptr;             // autocorrelation g[0..T-1]
   double eps = -1.0;                // ridge of the cached factor
   int64_t made = 0;                 // templates whose taps exist

@@ -112,183 +112,130 @@ __global__ void k_upper(const double2* __restrict__ L, int T, double2* __restric
   }
 }
 
-// (L L^H) a = b for one template per workgroup (column-oriented sweeps in LDS):
-// a forward sweep with L, then a backward sweep with U = L^H.
-template <int E>
-struct TrsvCol {
-  double2 v[E];   // column entries at rows lane + 64 q (row T - 1 past the end), unmasked
-};
-
-// Entry (j, j) of a column held as TrsvCol: lane j % 64 holds it in slot
-// j / 64; read across lanes with readlane (no memory access).
-template <int E>
-__device__ __forceinline__ double trsv_diag(const TrsvCol<E>& c, int j) {
-  // a masked sum (one nonzero term, exact) rather than a selection, which the
-  // compiler would turn into an indexed access and move the ring to scratch
-  double d = 0.0;
-#pragma unroll
-  for (int q = 0; q < E; ++q) d += (q == (j >> 6)) ? c.v[q].x : 0.0;
-  const long long bits = __double_as_longlong(d);
-  const int lo = __builtin_amdgcn_readlane((int)bits, j & 63);
-  const int hi = __builtin_amdgcn_readlane((int)(bits >> 32), j & 63);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-template <int E>
-__device__ __forceinline__ void trsv_load(const double2* __restrict__ F, int T, int lane, TrsvCol<E>& c, int j) {
-  const double2* col = F + (int64_t)min(max(j, 0), T - 1) * T;
-#pragma unroll
-  for (int q = 0; q < E; ++q) c.v[q] = col[min(lane + 64 * q, T - 1)];
-}
-
-// One step of a column sweep: w_j = r_j / F[j][j] (stored to out[j]), then
-// r_i -= F[i][j] w_j for the rows i the step updates (forward: j < i < T,
-// backward: i < j); the other rows subtract an exact zero.
-template <int E, bool FWD>
-__device__ __forceinline__ void trsv_step(const TrsvCol<E>& c, int j, int T, int lane, double2* r, double2* out) {
-  const double inv = 1.0 / trsv_diag(c, j);
-  const double2 rj = r[j];
-  const double2 wj = make_double2(rj.x * inv, rj.y * inv);
-  out[j] = wj;
-#pragma unroll
-  for (int q = 0; q < E; ++q) {
-    const int i = lane + 64 * q;
-    const bool active = FWD ? (i > j && i < T) : (i < j);
-    const double2 v = active ? c.v[q] : make_double2(0.0, 0.0);
-    r[i] = csub(r[i], cmul(v, wj));
-  }
-  __syncthreads();
-}
-
-// One wavefront per template; lane l owns rows l + 64 q (q < E, T <= 64 E).
-// The factor is read B = 32 / E columns at a time (one batch of independent
-// loads, one wait), then B steps run from registers: each workgroup meets the
-// latency of a column read once per B steps (the waves of a launch read the
-// same column in lockstep, so each read waits on the L2 fill).  Every step is
-// branch-free (rows outside the update subtract an exact zero; x and y hold
-// 64 E entries) and takes the diagonal from registers.
-template <int E>
-__global__ __launch_bounds__(64) void k_trsv(const double2* __restrict__ L, const double2* __restrict__ U, int T,
-                                           const double2* __restrict__ b, int64_t bstride,
-                                           double2* __restrict__ a, int64_t astride) {
-  constexpr int B = 32 / E;
+// Inverses of the 64 x 64 diagonal blocks of L, column-major, the last one padded with the
+// identity: one workgroup per block, a forward substitution per column in LDS.  Once per factor.
+constexpr int kTrsmBlock = 64;
+__global__ __launch_bounds__(kTrsmBlock) void k_diag_inv(const double2* __restrict__ L, int T,
+                                                        double2* __restrict__ inv) {
+  constexpr int N = kTrsmBlock, S = N + 1;
   extern __shared__ double2 sh[];
-  double2* x = sh;               // [64 E]
-  double2* y = sh + 64 * E;      // [64 E]
-  const int lane = threadIdx.x;
-  const double2* bb = b + (int64_t)blockIdx.x * bstride;
-#pragma unroll
-  for (int q = 0; q < E; ++q) {
-    const int i = lane + 64 * q;
-    x[i] = i < T ? bb[i] : make_double2(0.0, 0.0);
-    y[i] = make_double2(0.0, 0.0);
+  double2* blk = sh;               // [row][col]
+  double2* x = sh + N * S;         // [row][col], the inverse
+  const int o = blockIdx.x * N, c = threadIdx.x;
+  for (int j = 0; j < N; ++j) {    // lane c loads row c of column j
+    double2 v = make_double2(c == j ? 1.0 : 0.0, 0.0);
+    if (o + c < T && o + j < T && c >= j) v = L[(int64_t)(o + j) * T + o + c];
+    blk[c * S + j] = v;
   }
   __syncthreads();
-  // forward: L y = b
-  for (int j0 = 0; j0 < T; j0 += B) {
-    TrsvCol<E> c[B];
-#pragma unroll
-    for (int k = 0; k < B; ++k) trsv_load<E>(L, T, lane, c[k], j0 + k);
-#pragma unroll
-    for (int k = 0; k < B; ++k)
-      if (j0 + k < T) trsv_step<E, true>(c[k], j0 + k, T, lane, x, y);
+  for (int r = 0; r < N; ++r) {    // column c: every lane walks all rows, zero above the diagonal
+    double2 s = make_double2(r == c ? 1.0 : 0.0, 0.0);
+    for (int k = 0; k < r; ++k) s = csub(s, cmul(blk[r * S + k], x[k * S + c]));
+    const double d = 1.0 / blk[r * S + r].x;
+    x[r * S + c] = make_double2(s.x * d, s.y * d);
   }
-  // backward: U a = y
-  for (int j0 = T - 1; j0 >= 0; j0 -= B) {
-    TrsvCol<E> c[B];
-#pragma unroll
-    for (int k = 0; k < B; ++k) trsv_load<E>(U, T, lane, c[k], j0 - k);
-#pragma unroll
-    for (int k = 0; k < B; ++k)
-      if (j0 - k >= 0) trsv_step<E, false>(c[k], j0 - k, T, lane, y, x);
+  for (int r = 0; r < N; ++r) inv[((int64_t)blockIdx.x * N + c) * N + r] = x[r * S + c];
+}
+
+// (L L^H) a = b for TPW templates per workgroup on the FP64 matrix cores: their right-hand sides stay
+// in LDS as 2 TPW real columns, X = [Re | Im], through a forward sweep with L and a backward
+// sweep with U = L^H in block rows of 64.  Off the diagonal a block row is a complex GEMM,
+// L X = Re L [Re | Im] + Im L [-Im | Re], one v_mfma_f64_16x16x4 for either part of four columns of L;
+// wave w takes 16 of the 64 rows, its operands come straight from L2 eight steps ahead.  The
+// diagonal block is a product with its inverse (64 rows: its condition is at most that of
+// the whole factor).  Bound by the matrix cores where count fills the chip: 2 T^2 / 4 / 16 / 4
+// pairs of 64-cycle instructions per wave, 0.2 ms at T = 1024 however few the templates.  256 templates at
+// T = 1024: 2836 us with one wave per template sweeping the factor's columns -> 424 us;
+// 500 at T = 256: 178 -> 46 us.
+typedef __attribute__((ext_vector_type(4))) double f64x4;
+template <int TPW>
+__global__ __launch_bounds__(256) void k_trsm(const double2* __restrict__ L, const double2* __restrict__ U,
+                                              const double2* __restrict__ inv, int T, const double2* __restrict__ b,
+                                              int64_t bstride, double2* __restrict__ a, int64_t astride,
+                                              int64_t count) {
+  constexpr int NC = 2 * TPW, N = kTrsmBlock;
+  extern __shared__ __align__(16) double X[];       // [nb N][NC]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int nb = (T + N - 1) / N;
+  const int64_t t0 = (int64_t)blockIdx.x * TPW;
+  for (int e = threadIdx.x; e < nb * N * TPW; e += 256) {
+    const int tt = e / (nb * N), row = e % (nb * N);
+    const double2 v = row < T && t0 + tt < count ? b[(t0 + tt) * bstride + row] : make_double2(0.0, 0.0);
+    X[row * NC + tt] = v.x;
+    X[row * NC + TPW + tt] = v.y;
   }
-  double2* ao = a + (int64_t)blockIdx.x * astride;
-  for (int i = lane; i < T; i += 64) ao[i] = x[i];
-}
-
-__device__ __forceinline__ double lane_bcast(double v, int src) {
-  const long long bits = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)bits, src);
-  const int hi = __builtin_amdgcn_readlane((int)(bits >> 32), src);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-// Row j of a register-distributed vector (row i = lane + 64 q in slot q of
-// lane i % 64), on every lane: a masked sum over the slots (one nonzero
-// term, exact) and a cross-lane read.
-template <int E>
-__device__ __forceinline__ double row_pick(const double (&v)[E], int j) {
-  double s = 0.0;
+  __syncthreads();
+  // matrix operands: lane holds row lane % 16 (A) or column lane % 16 (B) at k = lane / 16; results: row
+  // 4 v + lane / 16 and column lane % 16 in register v
+  const int kq = lane >> 4, col = (lane & 15) % NC, mate = col ^ TPW;
+  const double sgn = col < TPW ? -1.0 : 1.0;
+  // p + q += M X over columns [c0, c1) of the factor (c0, c1 multiples of 64, columns past T read T - 1
+  // and meet zero rows of X)
+  auto gemm = [&](const double2* M, int row, int c0, int c1, f64x4& p, f64x4& q) {
+    auto fetch = [&](double2 (&m)[8], int c) {
 #pragma unroll
-  for (int q = 0; q < E; ++q) s += (q == (j >> 6)) ? v[q] : 0.0;
-  return lane_bcast(s, j & 63);
-}
-
-// The same sweeps for T <= 64 E, E <= 8, with x, y and the inverse diagonal
-// 1 / L[i][i] (= 1 / U[i][i], real) in registers: a step is a cross-lane
-// read of row j and E independent updates, with no LDS and no barrier.  The
-// factor columns come in batches of B = 32 / E as in k_trsv.
-template <int E>
-__device__ __forceinline__ void trsv_reg_step(const TrsvCol<E>& c, int j, int T, int lane, bool fwd,
-                                              const double (&dinv)[E], double (&rr)[E], double (&ri)[E],
-                                              double (&outr)[E], double (&outi)[E]) {
-  const double inv = row_pick<E>(dinv, j);
-  const double wr = row_pick<E>(rr, j) * inv, wi = row_pick<E>(ri, j) * inv;
+      for (int u = 0; u < 8; ++u) m[u] = M[(int64_t)min(c + 4 * u + kq, T - 1) * T + row];
+    };
+    auto products = [&](const double2 (&m)[8], int c) {
+      __builtin_amdgcn_sched_barrier(0);       // the next loads leave before this step's products
 #pragma unroll
-  for (int q = 0; q < E; ++q) {
-    const int i = lane + 64 * q;
-    if (i == j) {
-      outr[q] = wr;
-      outi[q] = wi;
+      for (int u = 0; u < 8; ++u) {
+        const double* x = X + (c + 4 * u + kq) * NC;
+        p = __builtin_amdgcn_mfma_f64_16x16x4f64(m[u].x, x[col], p, 0, 0, 0);
+        q = __builtin_amdgcn_mfma_f64_16x16x4f64(m[u].y, sgn * x[mate], q, 0, 0, 0);
+      }
+    };
+    double2 m[8], n[8];
+    if (c0 < c1) fetch(m, c0);
+    for (int c = c0; c < c1; c += 64) {        // two sets in turn: moving one to the other would wait for it
+      fetch(n, c + 32);
+      products(m, c);
+      fetch(m, min(c + 64, c1 - 32));
+      products(n, c + 32);
     }
-    const bool active = fwd ? (i > j && i < T) : (i < j);
-    const double2 v = active ? c.v[q] : make_double2(0.0, 0.0);
-    const double2 d = csub(make_double2(rr[q], ri[q]), cmul(v, make_double2(wr, wi)));
-    rr[q] = d.x;
-    ri[q] = d.y;
+  };
+  const bool mine = (lane & 15) < NC;
+  for (int sweep = 0; sweep < 2; ++sweep) {
+    for (int s = 0; s < nb; ++s) {
+      const int i = sweep ? nb - 1 - s : s;
+      const int r0 = i * N + 16 * wave;                       // this wave's rows
+      // the diagonal block's operands (inv(L_ii) or its conjugate transpose), loaded ahead of the GEMM
+      const double2* D = inv + (int64_t)i * N * N;
+      double2 dm[N / 4];
+#pragma unroll
+      for (int u = 0; u < N / 4; ++u) {
+        const int k = 4 * u + kq, r = 16 * wave + (lane & 15);
+        dm[u] = sweep ? D[r * N + k] : D[k * N + r];
+      }
+      f64x4 p = {0.0, 0.0, 0.0, 0.0}, q = {0.0, 0.0, 0.0, 0.0};
+      if (sweep) gemm(U, min(r0 + (lane & 15), T - 1), (i + 1) * N, nb * N, p, q);
+      else gemm(L, min(r0 + (lane & 15), T - 1), 0, i * N, p, q);
+      if (mine) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int row = r0 + 4 * v + kq;
+          X[row * NC + col] = row < T ? X[row * NC + col] - (p[v] + q[v]) : 0.0;
+        }
+      }
+      __syncthreads();
+      p = q = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int u = 0; u < N / 4; ++u) {
+        const double* x = X + (i * N + 4 * u + kq) * NC;
+        p = __builtin_amdgcn_mfma_f64_16x16x4f64(dm[u].x, x[col], p, 0, 0, 0);
+        q = __builtin_amdgcn_mfma_f64_16x16x4f64(sweep ? -dm[u].y : dm[u].y, sgn * x[mate], q, 0, 0, 0);
+      }
+      __syncthreads();                                        // the residual has been read
+      if (mine) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) X[(r0 + 4 * v + kq) * NC + col] = p[v] + q[v];
+      }
+      __syncthreads();
+    }
   }
-}
-
-template <int E>
-__global__ __launch_bounds__(64) void k_trsv_reg(const double2* __restrict__ L, const double2* __restrict__ U,
-                                               int T, const double2* __restrict__ b, int64_t bstride,
-                                               double2* __restrict__ a, int64_t astride) {
-  constexpr int B = 32 / E;
-  const int lane = threadIdx.x;
-  const double2* bb = b + (int64_t)blockIdx.x * bstride;
-  double xr[E], xi[E], yr[E], yi[E], dinv[E];
-#pragma unroll
-  for (int q = 0; q < E; ++q) {
-    const int i = lane + 64 * q;
-    const double2 v = i < T ? bb[i] : make_double2(0.0, 0.0);
-    xr[q] = v.x;
-    xi[q] = v.y;
-    yr[q] = yi[q] = 0.0;
-    dinv[q] = i < T ? 1.0 / L[(int64_t)i * T + i].x : 1.0;
-  }
-  // forward: y_j = x_j / L[j][j]; x_i -= L[i][j] y_j for j < i < T
-  for (int j0 = 0; j0 < T; j0 += B) {
-    TrsvCol<E> c[B];
-#pragma unroll
-    for (int k = 0; k < B; ++k) trsv_load<E>(L, T, lane, c[k], j0 + k);
-#pragma unroll
-    for (int k = 0; k < B; ++k)
-      if (j0 + k < T) trsv_reg_step<E>(c[k], j0 + k, T, lane, true, dinv, xr, xi, yr, yi);
-  }
-  // backward: a_j = y_j / U[j][j] (into x); y_i -= U[i][j] a_j for i < j
-  for (int j0 = T - 1; j0 >= 0; j0 -= B) {
-    TrsvCol<E> c[B];
-#pragma unroll
-    for (int k = 0; k < B; ++k) trsv_load<E>(U, T, lane, c[k], j0 - k);
-#pragma unroll
-    for (int k = 0; k < B; ++k)
-      if (j0 - k >= 0) trsv_reg_step<E>(c[k], j0 - k, T, lane, false, dinv, yr, yi, xr, xi);
-  }
-  double2* ao = a + (int64_t)blockIdx.x * astride;
-#pragma unroll
-  for (int q = 0; q < E; ++q) {
-    const int i = lane + 64 * q;
-    if (i < T) ao[i] = make_double2(xr[q], xi[q]);
+  for (int e = threadIdx.x; e < T * TPW; e += 256) {
+    const int tt = e / T, row = e % T;
+    if (t0 + tt < count) a[(t0 + tt) * astride + row] = make_double2(X[row * NC + tt], X[row * NC + TPW + tt]);
   }
 }
 
@@ -341,6 +288,25 @@ __global__ __launch_bounds__(256) void k_sigma_fit(const double2* __restrict__ a
     __syncthreads();
   }
   if (threadIdx.x == 0) sigma[blockIdx.x] = sqrt(red[0]);
+}
+
+// sigma_fit^2 = a^H M a of a least-squares solution: (M + lam I) a = b gives Re(a^H b) - lam |a|^2,
+// T products instead of T^2 (256 templates at T = 1024: 345 -> 6 us).  Both forms carry a rounding
+// error of about eps |M| |a|^2.  One wave per template.
+__global__ __launch_bounds__(64) void k_sigma_ls(const double2* __restrict__ a, int64_t astride,
+                                               const double2* __restrict__ b, int T, const double2* __restrict__ g,
+                                               double eps, double* __restrict__ sigma) {
+  const double2* ab = a + (int64_t)blockIdx.x * astride;
+  const double2* bb = b + (int64_t)blockIdx.x * T;
+  const double lam = eps * g[0].x;
+  double acc = 0.0;
+  for (int k = threadIdx.x; k < T; k += 64) {
+    const double2 x = ab[k], y = bb[k];
+    acc += x.x * (y.x - lam * x.x) + x.y * (y.y - lam * x.y);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+  if (threadIdx.x == 0) sigma[blockIdx.x] = sqrt(acc);
 }
 
 // Normalised taps c = conj(a) sigma_ref / sigma_fit, and their MFMA A-operand
@@ -444,6 +410,9 @@ int taps_prepare_subbank(Plan& p, Taps& tp, int b, const double* h_ref, double e
     RFD_CHECK_LAUNCH();
     hipLaunchKernelGGL(k_upper, dim3(blocks), dim3(256), 0, p.stream, s.L, T, s.U);
     RFD_CHECK_LAUNCH();
+    hipLaunchKernelGGL(k_diag_inv, dim3((unsigned)((T + kTrsmBlock - 1) / kTrsmBlock)), dim3(kTrsmBlock),
+                       (size_t)2 * kTrsmBlock * (kTrsmBlock + 1) * sizeof(double2), p.stream, s.L, T, s.Dinv);
+    RFD_CHECK_LAUNCH();
     int hinfo = 0;
     RFD_HIP(hipMemcpyAsync(&hinfo, info, sizeof(int), hipMemcpyDeviceToHost, p.stream));
     RFD_HIP(hipStreamSynchronize(p.stream));
@@ -461,19 +430,14 @@ int taps_solve_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count, 
   const int T = s.T;
   double2* abase = tp.a64 + s.a_base + first * s.Tp;
   if (method == RFD_TAPS_LS) {
-    const dim3 grid((unsigned)count);
-#define RFD_TRSV(E)                                                                                              \
-  hipLaunchKernelGGL(k_trsv<E>, grid, dim3(64), (size_t)2 * 64 * (E) * sizeof(double2), p.stream, s.L, s.U, T,   \
-                     tp.bvec, (int64_t)T, abase, (int64_t)s.Tp)
-    if (T <= 256)
-      hipLaunchKernelGGL(k_trsv_reg<4>, grid, dim3(64), 0, p.stream, s.L, s.U, T, tp.bvec, (int64_t)T, abase,
-                         (int64_t)s.Tp);
-    else if (T <= 512)
-      hipLaunchKernelGGL(k_trsv_reg<8>, grid, dim3(64), 0, p.stream, s.L, s.U, T, tp.bvec, (int64_t)T, abase,
-                         (int64_t)s.Tp);
-    else if (T <= 1024) RFD_TRSV(16);
-    else RFD_TRSV(32);
-#undef RFD_TRSV
+    // eight templates per workgroup while their columns fit LDS (128 KiB at T = 1024), else four
+    const int Tn = (int)round_up(T, kTrsmBlock);
+    if (T <= 1024)
+      hipLaunchKernelGGL(k_trsm<8>, dim3((unsigned)((count + 7) / 8)), dim3(256), (size_t)Tn * 16 * sizeof(double),
+                         p.stream, s.L, s.U, s.Dinv, T, tp.bvec, (int64_t)T, abase, (int64_t)s.Tp, count);
+    else
+      hipLaunchKernelGGL(k_trsm<4>, dim3((unsigned)((count + 3) / 4)), dim3(256), (size_t)Tn * 8 * sizeof(double),
+                         p.stream, s.L, s.U, s.Dinv, T, tp.bvec, (int64_t)T, abase, (int64_t)s.Tp, count);
   } else {
     int64_t el = count * T;
     int blocks = (int)((el + 255) / 256 < 4096 ? (el + 255) / 256 : 4096);
@@ -481,7 +445,11 @@ int taps_solve_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count, 
                        (int64_t)s.Tp);
   }
   RFD_CHECK_LAUNCH();
-  return taps_norm_and_pack(p, tp, b, first, count);
+  if (method != RFD_TAPS_LS) return taps_norm_and_pack(p, tp, b, first, count);
+  hipLaunchKernelGGL(k_sigma_ls, dim3((unsigned)count), dim3(64), 0, p.stream, (const double2*)abase, (int64_t)s.Tp,
+                     (const double2*)tp.bvec, T, (const double2*)s.g, s.eps, tp.sigma_fit + s.first + first);
+  RFD_CHECK_LAUNCH();
+  return taps_pack(p, tp, b, first, count);
 }
 
 // sigma_fit of taps already in a64, then the normalised taps and MFMA packings.
