@@ -111,6 +111,12 @@ struct Bf16Parts<uint16_t> {
 };
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+// Sums over more than kGemmChunk rows (the weight gradients of batches beyond 256) are cut into chunks of
+// that many, a workgroup each, whose results are added in order afterwards: their output tiles
+// alone leave most CUs idle behind a long sweep (1024 rows, 256 x 256 weights: 64 workgroups of 32
+// steps, 34 us).  The cut depends on the row count only, so a network's arithmetic is the
+// same alone and in a group.
+constexpr int kGemmChunk = 256;
 constexpr int kMfmaLdsRow = 40;   // 32 K values + 8 of padding (80 B rows: 16 B aligned)
 
 template <int P>
@@ -129,17 +135,19 @@ __device__ __forceinline__ float ld_f(const float* p, int64_t i) { return p[i]; 
 __device__ __forceinline__ float ld_f(const uint16_t* p, int64_t i) { return bf16_to_float(p[i]); }
 
 template <int TM, typename TA, typename TB>
-__global__ __launch_bounds__(256) void k_gemm_mfma(int M, int N, int K, int lda, int ta, int ldb, int tb, int ldc,
-                                                 int accumulate, int mode, GemmOps<TA, TB> ops) {
+__global__ __launch_bounds__(256) void k_gemm_mfma(int M, int N, int Kall, int lda, int ta, int ldb, int tb, int ldc,
+                                                 int accumulate, int mode, int nsplit, int64_t split_stride,
+                                                 GemmOps<TA, TB> ops) {
   constexpr int PA = Bf16Parts<TA>::n, PB = Bf16Parts<TB>::n;
   constexpr int R = TM * 32 / 256;       // tile elements per thread and operand
   constexpr int BW = TM / 32;            // 16 x 16 blocks per wave along each dimension
   __shared__ __align__(16) uint16_t As[PA][TM][kMfmaLdsRow];
   __shared__ __align__(16) uint16_t Bs[PB][TM][kMfmaLdsRow];
-  const int z = blockIdx.z;
+  const int z = blockIdx.z / nsplit, sp = blockIdx.z % nsplit;
+  const int kbeg = sp * kGemmChunk, K = nsplit > 1 ? min(Kall, kbeg + kGemmChunk) : Kall;
   const TA* __restrict__ A = ops.A.p[z];
   const TB* __restrict__ B = ops.B.p[z];
-  float* __restrict__ C = ops.C.p[z];
+  float* __restrict__ C = ops.C.p[z] + sp * split_stride;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wm = w >> 1, wn = w & 1;
   const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TM;
@@ -162,9 +170,9 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(int M, int N, int K, int lda,
       rb[r] = (gn < N && gk < K) ? (tb ? ld_f(B, (int64_t)gn * ldb + gk) : ld_f(B, (int64_t)gk * ldb + gn)) : 0.f;
     }
   };
-  fetch(0);
+  fetch(kbeg);
   const int r16 = lane & 15, kq = (lane >> 4) * 8;
-  for (int k0 = 0; k0 < K; k0 += 32) {
+  for (int k0 = kbeg; k0 < K; k0 += 32) {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       int kk, mm;
@@ -232,17 +240,17 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(int M, int N, int K, int lda,
 // the same GEMM shape for nz networks at once
 template <typename TA, typename TB>
 static int gemm_n(hipStream_t st, int nz, int M, int N, int K, const GemmOps<TA, TB>& ops, int lda, int ta, int ldb,
-                  int tb, int ldc, int accumulate = 0, int mode = kStore) {
+                  int tb, int ldc, int accumulate = 0, int mode = kStore, int nsplit = 1, int64_t split_stride = 0) {
   if (M <= 0 || N <= 0 || nz <= 0) return RFD_OK;
   // 32-wide tiles when 64-wide ones would leave most of the 256 CUs idle
-  if ((int64_t)((N + 63) / 64) * ((M + 63) / 64) * nz < 512) {
-    dim3 grid((N + 31) / 32, (M + 31) / 32, nz);
+  if ((int64_t)((N + 63) / 64) * ((M + 63) / 64) * nz * nsplit < 512) {
+    dim3 grid((N + 31) / 32, (M + 31) / 32, nz * nsplit);
     hipLaunchKernelGGL((k_gemm_mfma<32, TA, TB>), grid, dim3(256), 0, st, M, N, K, lda, ta, ldb, tb, ldc,
-                       accumulate, mode, ops);
+                       accumulate, mode, nsplit, split_stride, ops);
   } else {
-    dim3 grid((N + 63) / 64, (M + 63) / 64, nz);
+    dim3 grid((N + 63) / 64, (M + 63) / 64, nz * nsplit);
     hipLaunchKernelGGL((k_gemm_mfma<64, TA, TB>), grid, dim3(256), 0, st, M, N, K, lda, ta, ldb, tb, ldc,
-                       accumulate, mode, ops);
+                       accumulate, mode, nsplit, split_stride, ops);
   }
   RFD_CHECK_LAUNCH();
   return RFD_OK;
@@ -288,37 +296,54 @@ __global__ __launch_bounds__(256) void k_loss(PerNet<const float*> Ys, PerNet<co
 
 // accumulate: the flag, or when acc_from is given, whether acc_from[0] > 0
 // (a training step after the epoch's first)
-__global__ void k_sum_partials(PerNet<const double*> parts, int n, double scale, PerNet<double*> outs,
-                               int accumulate, PerNet<const int64_t*> acc_from) {
-  if (threadIdx.x != 0) return;
+__global__ __launch_bounds__(64) void k_sum_partials(PerNet<const double*> parts, int n, double scale,
+                                                   PerNet<double*> outs, int accumulate,
+                                                   PerNet<const int64_t*> acc_from) {
   const int z = blockIdx.x;
   const double* __restrict__ partial = parts.p[z];
   if (acc_from.p[z]) accumulate = acc_from.p[z][0] > 0;
   double s = 0.0;
-  for (int i = 0; i < n; ++i) s += partial[i];
+  for (int i = threadIdx.x; i < n; i += 64) s += partial[i];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if (threadIdx.x != 0) return;
   s *= scale;
   double* out = outs.p[z];
   *out = accumulate ? *out + s : s;
 }
 
 // out[j] = sum_i X[i][j]: 64 columns per workgroup, 16 row groups (rows
-// g, g + 16, ...) added in LDS in a fixed order.
-__global__ __launch_bounds__(1024) void k_colsum(PerNet<const float*> Xs, int64_t n, int H, PerNet<float*> outs) {
+// g, g + 16, ...) added in LDS in a fixed order; blockIdx.z takes a chunk of kGemmChunk rows
+// (all rows when there is one) to its own copy of the gradients, split_stride further on.
+__global__ __launch_bounds__(1024) void k_colsum(PerNet<const float*> Xs, int64_t nall, int H, PerNet<float*> outs,
+                                               int64_t split_stride) {
   __shared__ float red[16][64];
   const float* __restrict__ X = Xs.p[blockIdx.y];
   const int c = threadIdx.x & 63, g = threadIdx.x >> 6;
   const int j = blockIdx.x * 64 + c;
+  const int64_t beg = (int64_t)blockIdx.z * kGemmChunk;
+  const int64_t n = gridDim.z > 1 ? min(nall, beg + kGemmChunk) : nall;
   float s = 0.f;
   if (j < H)
-    for (int64_t i = g; i < n; i += 16) s += X[i * H + j];
+    for (int64_t i = beg + g; i < n; i += 16) s += X[i * H + j];
   red[g][c] = s;
   __syncthreads();
   if (g == 0 && j < H) {
     float t = 0.f;
 #pragma unroll
     for (int q = 0; q < 16; ++q) t += red[q][c];
-    outs.p[blockIdx.y][j] = t;
+    outs.p[blockIdx.y][blockIdx.z * split_stride + j] = t;
   }
+}
+
+// g[i] = sum of the chunks' copies part[s][i], in order
+__global__ void k_sum_chunks(PerNet<const float*> parts, int nsplit, int64_t np, PerNet<float*> gs) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= np) return;
+  const float* __restrict__ part = parts.p[blockIdx.y];
+  float v = part[i];
+  for (int s = 1; s < nsplit; ++s) v += part[s * np + i];
+  gs.p[blockIdx.y][i] = v;
 }
 
 // Training step state on the device, so every step of an epoch is the same
@@ -686,6 +711,7 @@ struct Surrogate {
   float *Pb = nullptr, *Cb = nullptr, *Z1 = nullptr, *H1 = nullptr, *Z2 = nullptr, *H2 = nullptr, *Y = nullptr,
         *dY = nullptr, *dA = nullptr, *dB = nullptr;
   int32_t* idx = nullptr;
+  float* gpart = nullptr;              // gradient copies of row chunks [kSurMaxBatch / kGemmChunk][np]
   double* partial = nullptr;
   double* epart = nullptr;             // [nb x tap blocks x 2] expansion norm partials
   double* loss = nullptr;
@@ -716,7 +742,7 @@ static void sfree(T*& p) {
 static void sur_free(Surrogate& s) {
   sfree(s.X); sfree(s.Weff); sfree(s.Bt); sfree(s.C); sfree(s.Q2); sfree(s.w); sfree(s.g); sfree(s.m); sfree(s.v); sfree(s.wbf);
   sfree(s.Pb); sfree(s.Cb); sfree(s.Z1); sfree(s.H1); sfree(s.Z2); sfree(s.H2); sfree(s.Y); sfree(s.dY);
-  sfree(s.dA); sfree(s.dB); sfree(s.idx); sfree(s.partial); sfree(s.epart); sfree(s.loss); sfree(s.tstate);
+  sfree(s.dA); sfree(s.dB); sfree(s.idx); sfree(s.partial); sfree(s.gpart); sfree(s.epart); sfree(s.loss); sfree(s.tstate);
   sfree(s.frange);
 }
 
@@ -871,18 +897,28 @@ static int backward(const NetGroup& g, hipStream_t st, const PerNet<const float*
   hipLaunchKernelGGL(k_loss, dim3(nblk, g.n), dim3(256), 0, st, PER(const float*, s.Y), Cb, PER(float*, s.dY), ny,
                      1.f / n, PER(double*, s.partial));
   RFD_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_sum_partials, dim3(g.n), dim3(1), 0, st, PER(const double*, s.partial), nblk, loss_scale,
+  hipLaunchKernelGGL(k_sum_partials, dim3(g.n), dim3(64), 0, st, PER(const double*, s.partial), nblk, loss_scale,
                      PER(double*, s.loss), accumulate_loss,
                      PER(const int64_t*, state_acc ? s.tstate : nullptr));
   RFD_CHECK_LAUNCH();
+  // gradients of weights and biases: in place, or by chunks of rows into copies that are added last
+  const int nsplit = (n + kGemmChunk - 1) / kGemmChunk;
+  const int64_t np = g.s[0]->np;
+  const PerNet<float*> gr = PER(float*, nsplit > 1 ? s.gpart : s.g);
+  const auto at = [&](int64_t off) {
+    PerNet<float*> r = gr;
+    for (int i = 0; i < g.n; ++i) r.p[i] += off;
+    return r;
+  };
+  const Surrogate& s0 = *g.s[0];
   // layer 3
   GemmOps<float, float> wg{};
   wg.A = PER(const float*, s.dY);
   wg.B = PER(const float*, s.H2);
-  wg.C = PER(float*, s.g + s.oW3);
-  if ((rc = gemm_n(st, g.n, K, H, n, wg, K, 1, H, 0, H))) return rc;
-  hipLaunchKernelGGL(k_colsum, dim3((K + 63) / 64, g.n), dim3(1024), 0, st, PER(const float*, s.dY), (int64_t)n, K,
-                     PER(float*, s.g + s.ob3));
+  wg.C = at(s0.oW3);
+  if ((rc = gemm_n(st, g.n, K, H, n, wg, K, 1, H, 0, H, 0, kStore, nsplit, np))) return rc;
+  hipLaunchKernelGGL(k_colsum, dim3((K + 63) / 64, g.n, nsplit), dim3(1024), 0, st, PER(const float*, s.dY), (int64_t)n, K,
+                     at(s0.ob3), np);
   RFD_CHECK_LAUNCH();
   GemmOps<float, uint16_t> ag{};
   ag.A = PER(const float*, s.dY);
@@ -893,10 +929,10 @@ static int backward(const NetGroup& g, hipStream_t st, const PerNet<const float*
   // layer 2
   wg.A = PER(const float*, s.dA);
   wg.B = PER(const float*, s.H1);
-  wg.C = PER(float*, s.g + s.oW2);
-  if ((rc = gemm_n(st, g.n, H, H, n, wg, H, 1, H, 0, H))) return rc;
-  hipLaunchKernelGGL(k_colsum, dim3((H + 63) / 64, g.n), dim3(1024), 0, st, PER(const float*, s.dA), (int64_t)n, H,
-                     PER(float*, s.g + s.ob2));
+  wg.C = at(s0.oW2);
+  if ((rc = gemm_n(st, g.n, H, H, n, wg, H, 1, H, 0, H, 0, kStore, nsplit, np))) return rc;
+  hipLaunchKernelGGL(k_colsum, dim3((H + 63) / 64, g.n, nsplit), dim3(1024), 0, st, PER(const float*, s.dA), (int64_t)n, H,
+                     at(s0.ob2), np);
   RFD_CHECK_LAUNCH();
   ag.A = PER(const float*, s.dA);
   ag.B = PER(const uint16_t*, s.wbf + s.oW2);
@@ -906,11 +942,16 @@ static int backward(const NetGroup& g, hipStream_t st, const PerNet<const float*
   // layer 1
   wg.A = PER(const float*, s.dB);
   wg.B = P;
-  wg.C = PER(float*, s.g + s.oW1);
-  if ((rc = gemm_n(st, g.n, H, 4, n, wg, H, 1, 4, 0, 4))) return rc;
-  hipLaunchKernelGGL(k_colsum, dim3((H + 63) / 64, g.n), dim3(1024), 0, st, PER(const float*, s.dB), (int64_t)n, H,
-                     PER(float*, s.g + s.ob1));
+  wg.C = at(s0.oW1);
+  if ((rc = gemm_n(st, g.n, H, 4, n, wg, H, 1, 4, 0, 4, 0, kStore, nsplit, np))) return rc;
+  hipLaunchKernelGGL(k_colsum, dim3((H + 63) / 64, g.n, nsplit), dim3(1024), 0, st, PER(const float*, s.dB), (int64_t)n, H,
+                     at(s0.ob1), np);
   RFD_CHECK_LAUNCH();
+  if (nsplit > 1) {
+    hipLaunchKernelGGL(k_sum_chunks, dim3((unsigned)((np + 255) / 256), g.n), dim3(256), 0, st,
+                       PER(const float*, s.gpart), nsplit, np, PER(float*, s.g));
+    RFD_CHECK_LAUNCH();
+  }
   return RFD_OK;
 }
 
@@ -1121,6 +1162,7 @@ int rfd_surrogate_create(rfd_plan* plan, rfd_taps* taps, int32_t subbank, int32_
   TRY(salloc(&s.dB, (size_t)s.nb * H));
   TRY(salloc(&s.idx, (size_t)s.nb));
   TRY(salloc(&s.partial, 256));
+  TRY(salloc(&s.gpart, (size_t)(kSurMaxBatch / kGemmChunk) * s.np));
   TRY(salloc(&s.epart, (size_t)s.nb * ((s.T + 255) / 256) * 2));
   TRY(salloc(&s.loss, 1));
   TRY(salloc(&s.frange, 8));
@@ -1190,7 +1232,7 @@ int rfd_surrogate_fit_basis(rfd_surrogate* sur, int32_t iters, double* captured_
     if ((rc = salloc(&dummy, (size_t)ny))) return rc;
     hipLaunchKernelGGL(k_loss, dim3(nblk), dim3(256), 0, st, one_net<const float*>(s.C), one_net<const float*>(zeros),
                        one_net(dummy), ny, 1.f, one_net(s.partial));
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(1), 0, st, one_net<const double*>(s.partial), nblk, 1.0 / n,
+    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(64), 0, st, one_net<const double*>(s.partial), nblk, 1.0 / n,
                        one_net(s.loss), 0, one_net<const int64_t*>(nullptr));
     double v = 0;
     RFD_HIP(hipMemcpyAsync(&v, s.loss, sizeof(double), hipMemcpyDeviceToHost, st));
