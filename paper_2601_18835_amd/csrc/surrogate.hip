@@ -114,7 +114,7 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 // Sums over more than kGemmChunk rows (the weight gradients of batches beyond 256) are cut into chunks of
 // that many, a workgroup each, whose results are added in order afterwards: their output tiles
 // alone leave most CUs idle behind a long sweep (1024 rows, 256 x 256 weights: 64 workgroups of 32
-// steps, 34 us).  The cut depends on the row count only, so a network's arithmetic is the
+// steps, 34 us; cut, 11 us).  The cut depends on the row count only, so a network's arithmetic is the
 // same alone and in a group.
 constexpr int kGemmChunk = 256;
 constexpr int kMfmaLdsRow = 40;   // 32 K values + 8 of padding (80 B rows: 16 B aligned)
@@ -294,14 +294,13 @@ __global__ __launch_bounds__(256) void k_loss(PerNet<const float*> Ys, PerNet<co
   if (threadIdx.x == 0) parts.p[z][blockIdx.x] = red[0];
 }
 
-// accumulate: the flag, or when acc_from is given, whether acc_from[0] > 0
-// (a training step after the epoch's first)
+// out = scale sum(parts), added to what is there when acc_from[0] > 0 (a training step after the
+// epoch's first); out_host (pinned, or NULL) gets it too
 __global__ __launch_bounds__(64) void k_sum_partials(PerNet<const double*> parts, int n, double scale,
-                                                   PerNet<double*> outs, int accumulate,
+                                                   PerNet<double*> outs, double* out_host,
                                                    PerNet<const int64_t*> acc_from) {
   const int z = blockIdx.x;
   const double* __restrict__ partial = parts.p[z];
-  if (acc_from.p[z]) accumulate = acc_from.p[z][0] > 0;
   double s = 0.0;
   for (int i = threadIdx.x; i < n; i += 64) s += partial[i];
 #pragma unroll
@@ -309,7 +308,9 @@ __global__ __launch_bounds__(64) void k_sum_partials(PerNet<const double*> parts
   if (threadIdx.x != 0) return;
   s *= scale;
   double* out = outs.p[z];
-  *out = accumulate ? *out + s : s;
+  if (acc_from.p[z] && acc_from.p[z][0] > 0) s = *out + s;
+  *out = s;
+  if (out_host) *out_host = s;
 }
 
 // out[j] = sum_i X[i][j]: 64 columns per workgroup, 16 row groups (rows
@@ -344,6 +345,484 @@ __global__ void k_sum_chunks(PerNet<const float*> parts, int nsplit, int64_t np,
   float v = part[i];
   for (int s = 1; s < nsplit; ++s) v += part[s * np + i];
   gs.p[blockIdx.y][i] = v;
+}
+
+// ------------------------------------------------- network in one pass
+// Rows are independent through every layer of the network, forward and backward, so a workgroup
+// takes kNetRows of them from the parameters to the gradient at the first layer's output
+// in one launch; the layer-wise GEMMs needed a launch per layer (seven, with 3-4 us between
+// dependent ones and 9-15 us in each, mostly the latency of staging tiles through LDS for a
+// handful of K steps).  Activations stay in LDS as the three BF16 parts of Bf16Parts, weights
+// go from L2 straight into MFMA operands, and a wave keeps the 32 output columns it owns (2c and 2c + 1
+// of a strip for lane column c) in every hidden layer, so z1 and z2 wait in registers for
+// the backward half.  The columns come in pairs because the backward products read
+// the weights transposed: one dword holds the same K row of both.  K steps, parts
+// and their order are those of k_gemm_mfma, so every activation keeps its bits.
+// What bounds it is the latency of five dependent layers (weight loads of a layer do not
+// depend on the one before).  loss_grad, 1024 rows, 256 hidden, 64 coefficients: 24 us here and 6 each in
+// k_net_wgrad and k_net_sums, against 116 us in 14 kernels (the call: 195 -> 78 us).
+constexpr int kNetRows = 16;
+constexpr int kNetWaves = 8;
+constexpr int kNetMaxWidth = 512;      // LDS: 3 parts x 16 rows x (512 + 8) x 2 B = 50 KB
+
+// What the weight gradients contract over the rows is kept as [part][row / 8][column][row % 8]:
+// 8 consecutive rows of a column are one lane's MFMA operand (k_net writes, k_net_wgrad reads).
+constexpr int kNetGroups = 1024 / 8;   // row groups of the largest gradient batch
+
+struct NetArgs {
+  PerNet<const float*> P;              // [n][4] parameters
+  PerNet<const float*> Cb;             // [n][K] targets
+  PerNet<const float*> w;              // FP32 parameters (biases)
+  PerNet<const uint16_t*> wbf;         // BF16 weights
+  PerNet<float*> Y;                    // [n][K] outputs (forward only)
+  PerNet<uint16_t*> H1, H2, dA, dY;    // operand parts for the weight gradients
+  PerNet<float*> part;                 // [workgroup][6 H + K] sums over its rows: W1, b1, b2, b3
+  PerNet<double*> loss;                // [workgroup] sums of squares
+};
+
+__device__ __forceinline__ bf16x8 as_frag(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
+
+// v[t][e]: row 4 (lane >> 4) + e, column 2 (lane & 15) + t of strip s: as parts into the LDS rows
+template <typename V>
+__device__ __forceinline__ void net_to_lds(uint16_t* act, int pitch, int lane, int s, const V& v) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    uint16_t q0[3], q1[3];
+    to_parts<3>(v[0][e], q0);
+    to_parts<3>(v[1][e], q1);
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+      *reinterpret_cast<uint32_t*>(act + ((int64_t)p * kNetRows + 4 * (lane >> 4) + e) * pitch + 32 * s +
+                                   2 * (lane & 15)) = (uint32_t)q0[p] | (uint32_t)q1[p] << 16;
+  }
+}
+// the same values as operand parts; rows past n are zero
+template <typename V>
+__device__ __forceinline__ void net_to_parts(uint16_t* out, int cols, int lane, int s, int row0, int n, const V& v) {
+  const int q = lane >> 4, g = row0 / 8 + (q >> 1);
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    uint16_t h[4][3];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) to_parts<3>(row0 + 4 * q + e < n ? v[t][e] : 0.f, h[e]);
+    const int col = 32 * s + 2 * (lane & 15) + t;
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+      *reinterpret_cast<uint2*>(out + (((int64_t)p * kNetGroups + g) * cols + col) * 8 + 4 * (q & 1)) =
+          make_uint2((uint32_t)h[0][p] | (uint32_t)h[1][p] << 16, (uint32_t)h[2][p] | (uint32_t)h[3][p] << 16);
+  }
+}
+// sum over the workgroup's rows, in every lane of the column
+__device__ __forceinline__ float net_rows(float x) {
+  x += __shfl_xor(x, 16);
+  return x + __shfl_xor(x, 32);
+}
+
+// A K steps of net_fwd, all their weights loaded before the first product
+template <int A>
+__device__ __forceinline__ void net_fwd_steps(const uint16_t* act, int pitch, const uint16_t* w0, const uint16_t* w1,
+                                              f32x4 (&acc)[2]) {
+  uint4 b0[A], b1[A];
+#pragma unroll
+  for (int i = 0; i < A; ++i) {
+    b0[i] = *reinterpret_cast<const uint4*>(w0 + 32 * i);
+    b1[i] = *reinterpret_cast<const uint4*>(w1 + 32 * i);
+  }
+#pragma unroll
+  for (int i = 0; i < A; ++i)
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const uint4 a = *reinterpret_cast<const uint4*>(act + p * kNetRows * pitch + 32 * i);
+      acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(a), as_frag(b0[i]), acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(a), as_frag(b1[i]), acc[1], 0, 0, 0);
+    }
+}
+// acc[t] += act W^T for columns 2c + t of strip s: W [cols][K], K a multiple of 32 (16 B aligned rows)
+__device__ __forceinline__ void net_fwd(const uint16_t* act, int pitch, int lane, int s, const uint16_t* W, int K,
+                                        int cols, f32x4 (&acc)[2]) {
+  const int c = lane & 15, kq = 8 * (lane >> 4);
+  const int n0 = 32 * s + 2 * c;
+  const uint16_t* w0 = W + (int64_t)min(n0, cols - 1) * K + kq;
+  const uint16_t* w1 = W + (int64_t)min(n0 + 1, cols - 1) * K + kq;
+  act += c * pitch + kq;
+  int k = 0;
+  for (; k + 256 <= K; k += 256) net_fwd_steps<8>(act + k, pitch, w0 + k, w1 + k, acc);
+  for (; k + 64 <= K; k += 64) net_fwd_steps<2>(act + k, pitch, w0 + k, w1 + k, acc);
+  if (k < K) net_fwd_steps<1>(act + k, pitch, w0 + k, w1 + k, acc);
+}
+// A K steps of net_bwd from weight row r on; rows past the last count as zero
+template <int A>
+__device__ __forceinline__ void net_bwd_steps(const uint16_t* act, int pitch, const uint16_t* w, int r, int rows, int H,
+                                              f32x4 (&acc)[2]) {
+  uint32_t d[A][8];
+#pragma unroll
+  for (int i = 0; i < A; ++i)
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      d[i][j] = *reinterpret_cast<const uint32_t*>(w + (int64_t)min(r + 32 * i + j, rows - 1) * H);
+#pragma unroll
+  for (int i = 0; i < A; ++i) {
+    uint32_t lo[4], hi[4];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (r + 32 * i + j >= rows) d[i][j] = 0u;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      lo[j] = (d[i][2 * j] & 0xFFFFu) | d[i][2 * j + 1] << 16;
+      hi[j] = d[i][2 * j] >> 16 | (d[i][2 * j + 1] & 0xFFFF0000u);
+    }
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const uint4 a = *reinterpret_cast<const uint4*>(act + p * kNetRows * pitch + 32 * i);
+      acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(a), as_frag(make_uint4(lo[0], lo[1], lo[2], lo[3])),
+                                                       acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(a), as_frag(make_uint4(hi[0], hi[1], hi[2], hi[3])),
+                                                       acc[1], 0, 0, 0);
+    }
+  }
+}
+// acc[t] += act W for columns 2c + t of strip s: W [rows][H], H even
+__device__ __forceinline__ void net_bwd(const uint16_t* act, int pitch, int lane, int s, const uint16_t* W, int rows,
+                                        int H, f32x4 (&acc)[2]) {
+  const int c = lane & 15, kq = 8 * (lane >> 4);
+  const uint16_t* w = W + 32 * s + 2 * c;
+  act += c * pitch + kq;
+  int k = 0;
+  for (; k + 256 <= rows; k += 256) net_bwd_steps<8>(act + k, pitch, w, k + kq, rows, H, acc);
+  for (; k + 32 < rows; k += 64) net_bwd_steps<2>(act + k, pitch, w, k + kq, rows, H, acc);
+  if (k < rows) net_bwd_steps<1>(act + k, pitch, w, k + kq, rows, H, acc);
+}
+
+// NS strips of 32 columns per wave (widths up to 256 NS).  BWD: loss, operand parts and row sums for n <= 1024
+// rows; otherwise the outputs Y of any n.
+template <int NS, bool BWD>
+__global__ __launch_bounds__(64 * kNetWaves) void k_net(int n, int H, int K, int64_t oW2, int64_t oW3, float scale,
+                                                       NetArgs a) {
+  __shared__ __align__(16) uint16_t act[3 * kNetRows * (256 * NS + 8)];
+  __shared__ double red[kNetWaves];
+  const int z = blockIdx.y, row0 = blockIdx.x * kNetRows;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, c = lane & 15, q = lane >> 4;
+  const int Kp = (K + 31) & ~31, pitch = max(H, Kp) + 8;
+  const int sh = H / 32, sk = Kp / 32;
+  const float* __restrict__ w = a.w.p[z];
+  const uint16_t* __restrict__ W1 = a.wbf.p[z];
+  const uint16_t* __restrict__ W2 = W1 + oW2;
+  const uint16_t* __restrict__ W3 = W1 + oW3;
+  const float* __restrict__ b1 = w + 4 * H;
+  const float* __restrict__ b2 = w + oW2 + (int64_t)H * H;
+  const float* __restrict__ b3 = w + oW3 + (int64_t)K * H;
+  const float* __restrict__ P = a.P.p[z];
+  f32x4 z1[NS][2], z2[NS][2], acc[NS][2];
+  const auto zero = [&]() {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+
+  // layer 1: K = 4, held by the first quarter of the lanes
+  uint4 pa[3];
+  {
+    float x[4] = {0.f, 0.f, 0.f, 0.f};
+    if (q == 0 && row0 + c < n)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[j] = P[(int64_t)(row0 + c) * 4 + j];
+    uint16_t h[4][3];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) to_parts<3>(x[j], h[j]);
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+      pa[p] = make_uint4((uint32_t)h[0][p] | (uint32_t)h[1][p] << 16, (uint32_t)h[2][p] | (uint32_t)h[3][p] << 16, 0, 0);
+  }
+  zero();
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    const int s = wv + kNetWaves * i;
+    if (s >= sh) break;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int col = 32 * s + 2 * c + t;
+      uint4 b = make_uint4(0, 0, 0, 0);
+      if (q == 0) {
+        const uint2 w1 = *reinterpret_cast<const uint2*>(W1 + 4 * col);
+        b = make_uint4(w1.x, w1.y, 0, 0);
+      }
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(pa[p]), as_frag(b), acc[i][t], 0, 0, 0);
+      const float bias = b1[col];
+      f32x4 h;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        z1[i][t][e] = acc[i][t][e] + bias;
+        h[e] = silu_f(z1[i][t][e]);
+      }
+      acc[i][t] = h;
+    }
+    net_to_lds(act, pitch, lane, s, acc[i]);
+    if (BWD) net_to_parts(a.H1.p[z], H, lane, s, row0, n, acc[i]);
+  }
+  __syncthreads();
+
+  // layer 2
+  zero();
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    const int s = wv + kNetWaves * i;
+    if (s >= sh) break;
+    net_fwd(act, pitch, lane, s, W2, H, H, acc[i]);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const float bias = b2[32 * s + 2 * c + t];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        z2[i][t][e] = acc[i][t][e] + bias;
+        acc[i][t][e] = silu_f(z2[i][t][e]);
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    const int s = wv + kNetWaves * i;
+    if (s >= sh) break;
+    net_to_lds(act, pitch, lane, s, acc[i]);
+    if (BWD) net_to_parts(a.H2.p[z], H, lane, s, row0, n, acc[i]);
+  }
+  __syncthreads();
+
+  // layer 3
+  zero();
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    const int s = wv + kNetWaves * i;
+    if (s >= sk) break;
+    net_fwd(act, pitch, lane, s, W3, H, K, acc[i]);
+  }
+  if constexpr (!BWD) {
+    float* __restrict__ Y = a.Y.p[z];
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int col = 32 * (wv + kNetWaves * i) + 2 * c + t;
+        if (col >= K) continue;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int row = row0 + 4 * q + e;
+          if (row < n) Y[(int64_t)row * K + col] = acc[i][t][e] + b3[col];
+        }
+      }
+  } else {
+    // loss and dY = 2 (y - c) / n
+    float* __restrict__ part = a.part.p[z] + (int64_t)blockIdx.x * (6 * H + K);
+    const float* __restrict__ Cb = a.Cb.p[z];
+    double sq = 0.0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      const int s = wv + kNetWaves * i;
+      if (s >= sk) break;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int col = 32 * s + 2 * c + t;
+        float sum = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int row = row0 + 4 * q + e;
+          float d = 0.f;
+          if (row < n && col < K) {
+            const float r = acc[i][t][e] + b3[col] - Cb[(int64_t)row * K + col];
+            d = 2.f * r * scale;
+            sq += (double)r * r;
+          }
+          acc[i][t][e] = d;
+          sum += d;
+        }
+        sum = net_rows(sum);
+        if (q == 0 && col < K) part[6 * H + col] = sum;
+      }
+      net_to_lds(act, pitch, lane, s, acc[i]);
+      net_to_parts(a.dY.p[z], Kp, lane, s, row0, n, acc[i]);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+    if (lane == 0) red[wv] = sq;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double l = 0.0;
+#pragma unroll
+      for (int i = 0; i < kNetWaves; ++i) l += red[i];
+      a.loss.p[z][blockIdx.x] = l;
+    }
+
+    // dA = (dY W3) silu'(z2)
+    zero();
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      const int s = wv + kNetWaves * i;
+      if (s >= sh) break;
+      net_bwd(act, pitch, lane, s, W3, K, H, acc[i]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      const int s = wv + kNetWaves * i;
+      if (s >= sh) break;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        float sum = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          acc[i][t][e] *= silu_g(z2[i][t][e]);
+          sum += row0 + 4 * q + e < n ? acc[i][t][e] : 0.f;
+        }
+        sum = net_rows(sum);
+        if (q == 0) part[5 * H + 32 * s + 2 * c + t] = sum;
+      }
+      net_to_lds(act, pitch, lane, s, acc[i]);
+      net_to_parts(a.dA.p[z], H, lane, s, row0, n, acc[i]);
+    }
+    __syncthreads();
+
+    // dB = (dA W2) silu'(z1), needed only for its products with the parameters and its sums
+    float x[4][4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        x[e][j] = row0 + 4 * q + e < n ? P[(int64_t)(row0 + 4 * q + e) * 4 + j] : 0.f;
+    zero();
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      const int s = wv + kNetWaves * i;
+      if (s >= sh) break;
+      net_bwd(act, pitch, lane, s, W2, H, H, acc[i]);
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int col = 32 * s + 2 * c + t;
+        float sum = 0.f, g[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float d = row0 + 4 * q + e < n ? acc[i][t][e] * silu_g(z1[i][t][e]) : 0.f;
+          sum += d;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) g[j] = fmaf(d, x[e][j], g[j]);
+        }
+        sum = net_rows(sum);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) g[j] = net_rows(g[j]);
+        if (q == 0) {
+          part[4 * H + col] = sum;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) part[4 * col + j] = g[j];
+        }
+      }
+    }
+  }
+}
+
+// Weight gradients of layers 2 and 3, W2 = dA^T H1 [H x H] and W3 = dY^T H2 [K x H]: one launch, a
+// workgroup per 32 x 32 tile (blockIdx.x: those of W2, then those of W3) and kGemmChunk rows (blockIdx.y), each of
+// the four waves a quarter of the rows with all its operands loaded at once as k_net
+// left them: no LDS staging, no conversion, one memory latency instead of one per K step.
+__global__ __launch_bounds__(256) void k_net_wgrad(int n, int H, int K, int64_t oW2, int64_t oW3, int64_t split_stride,
+                                                 NetArgs a, PerNet<float*> outs) {
+  __shared__ float red[4][32][33];
+  const int z = blockIdx.z, lane = threadIdx.x & 63, wv = threadIdx.x >> 6, c = lane & 15, q = lane >> 4;
+  const int th = H / 32, Kp = (K + 31) & ~31;
+  const bool second = (int)blockIdx.x < th * th;
+  const int tile = second ? blockIdx.x : blockIdx.x - th * th;
+  const int m0 = tile / th * 32, n0 = tile % th * 32;
+  const int ca = second ? H : Kp, rows = second ? H : K;
+  const uint16_t* __restrict__ A = second ? a.dA.p[z] : a.dY.p[z];
+  const uint16_t* __restrict__ B = second ? a.H1.p[z] : a.H2.p[z];
+  const int groups = (n + kNetRows - 1) / kNetRows * (kNetRows / 8);   // the ones that k_net wrote
+  const int g0 = blockIdx.y * (kGemmChunk / 8) + wv * (kGemmChunk / 32);
+  f32x4 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  uint4 fa[kGemmChunk / 128][2][3], fb[kGemmChunk / 128][2][3];
+#pragma unroll
+  for (int ks = 0; ks < kGemmChunk / 128; ++ks) {
+    const int g = g0 + 4 * ks + q;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        const int64_t r = (int64_t)p * kNetGroups + g;
+        fa[ks][i][p] = fb[ks][i][p] = make_uint4(0, 0, 0, 0);
+        if (g < groups) {
+          fa[ks][i][p] = *reinterpret_cast<const uint4*>(A + (r * ca + m0 + 16 * i + c) * 8);
+          fb[ks][i][p] = *reinterpret_cast<const uint4*>(B + (r * H + n0 + 16 * i + c) * 8);
+        }
+      }
+  }
+#pragma unroll
+  for (int ks = 0; ks < kGemmChunk / 128; ++ks)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+#pragma unroll
+          for (int r = 0; p + r <= 2; ++r)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(fa[ks][i][p]), as_frag(fb[ks][j][r]),
+                                                                acc[i][j], 0, 0, 0);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) red[wv][16 * i + 4 * q + e][16 * j + c] = acc[i][j][e];
+  __syncthreads();
+  float* __restrict__ out = outs.p[z] + blockIdx.y * split_stride + (second ? oW2 : oW3);
+#pragma unroll
+  for (int e = threadIdx.x; e < 1024; e += 256) {
+    const int m = e >> 5, k = e & 31;
+    if (m0 + m < rows)
+      out[(int64_t)(m0 + m) * H + n0 + k] = red[0][m][k] + red[1][m][k] + red[2][m][k] + red[3][m][k];
+  }
+}
+
+// Gradients from their parts, in order: W1 and the biases from the nblk row blocks of k_net, W2 and
+// W3 from the nsplit chunks of k_net_wgrad (in place already when there is one).  The last
+// workgroup adds the loss: out (+)= scale sum(parts), see k_sum_partials.
+__global__ __launch_bounds__(256) void k_net_sums(int nblk, int nsplit, int H, int K, int64_t np, int64_t oW2, int64_t oW3,
+                                                NetArgs a, PerNet<const float*> chunks, PerNet<float*> gs,
+                                                double scale, PerNet<double*> losses, double* loss_host,
+                                                PerNet<const int64_t*> acc_from) {
+  const int z = blockIdx.y;
+  if (blockIdx.x == gridDim.x - 1) {
+    if (threadIdx.x >= 64) return;
+    double s = 0.0;
+    for (int i = threadIdx.x; i < nblk; i += 64) s += a.loss.p[z][i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if (threadIdx.x != 0) return;
+    s *= scale;
+    if (acc_from.p[z] && acc_from.p[z][0] > 0) s = *losses.p[z] + s;
+    *losses.p[z] = s;
+    if (loss_host) *loss_host = s;
+    return;
+  }
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= np) return;
+  const int64_t ob2 = oW2 + (int64_t)H * H, ob3 = oW3 + (int64_t)K * H;
+  const bool w2 = i >= oW2 && i < ob2, w3 = i >= oW3 && i < ob3;
+  if (w2 || w3) {
+    if (nsplit == 1) return;
+    const float* __restrict__ src = chunks.p[z] + i;
+    float v = src[0];
+    for (int s = 1; s < nsplit; ++s) v += src[s * np];
+    gs.p[z][i] = v;
+    return;
+  }
+  const int64_t bw = 6 * H + K;
+  const float* __restrict__ src = a.part.p[z] + (i < oW2 ? i : i < oW3 ? i - ob2 + 5 * H : i - ob3 + 6 * H);
+  float v = src[0];
+#pragma unroll 16
+  for (int b = 1; b < nblk; ++b) v += src[b * bw];
+  gs.p[z][i] = v;
 }
 
 // Training step state on the device, so every step of an epoch is the same
@@ -692,6 +1171,7 @@ __global__ __launch_bounds__(256) void k_match(const double2* __restrict__ A, co
 // ------------------------------------------------------------- state
 constexpr int kSurMaxBatch = 1024;    // training batch and loss_grad rows
 constexpr int kSurChunk = 4096;       // inference templates per forward pass and expansion
+static_assert(kNetGroups * 8 == kSurMaxBatch, "operand parts hold the largest batch");
 struct Surrogate {
   Plan* plan = nullptr;
   Taps* taps = nullptr;
@@ -712,6 +1192,10 @@ struct Surrogate {
         *dY = nullptr, *dA = nullptr, *dB = nullptr;
   int32_t* idx = nullptr;
   float* gpart = nullptr;              // gradient copies of row chunks [kSurMaxBatch / kGemmChunk][np]
+  // networks that run in one pass (net_fused): operand parts [3][kSurMaxBatch / 8][H or K up to 32s][8], row sums
+  uint16_t *pH1 = nullptr, *pH2 = nullptr, *pdA = nullptr, *pdY = nullptr;
+  float* rowpart = nullptr;            // [kSurMaxBatch / kNetRows][6 H + K]
+  double* loss_host = nullptr;         // pinned
   double* partial = nullptr;
   double* epart = nullptr;             // [nb x tap blocks x 2] expansion norm partials
   double* loss = nullptr;
@@ -744,7 +1228,14 @@ static void sur_free(Surrogate& s) {
   sfree(s.Pb); sfree(s.Cb); sfree(s.Z1); sfree(s.H1); sfree(s.Z2); sfree(s.H2); sfree(s.Y); sfree(s.dY);
   sfree(s.dA); sfree(s.dB); sfree(s.idx); sfree(s.partial); sfree(s.gpart); sfree(s.epart); sfree(s.loss); sfree(s.tstate);
   sfree(s.frange);
+  sfree(s.pH1); sfree(s.pH2); sfree(s.pdA); sfree(s.pdY); sfree(s.rowpart);
+  if (s.loss_host) (void)hipHostFree(s.loss_host);
+  s.loss_host = nullptr;
 }
+
+// One pass needs whole 16 B rows of weights (hidden width in 32s) and activations that fit its LDS; other
+// widths go layer by layer (195 against 78 us for the gradients of 1024 rows at a width of 256).
+static bool net_fused(const Surrogate& s) { return s.H % 32 == 0 && s.H <= kNetMaxWidth && s.K <= kNetMaxWidth; }
 
 // Network inputs from physical parameters (m1, m2, chi, e0): chirp mass
 // M eta^(3/5), symmetric mass ratio eta = m1 m2 / M^2, chi and e0 (the same
@@ -859,8 +1350,36 @@ static int refresh_bf16(const NetGroup& g, hipStream_t st) {
   return RFD_OK;
 }
 
+template <bool BWD>
+static int net_pass(const NetGroup& g, hipStream_t st, const PerNet<const float*>& P, const PerNet<const float*>& Cb,
+                    int n, NetArgs& a) {
+  const Surrogate& s0 = *g.s[0];
+  a.P = P;
+  a.Cb = Cb;
+  a.w = PER(const float*, s.w);
+  a.wbf = PER(const uint16_t*, s.wbf);
+  a.Y = PER(float*, s.Y);
+  a.H1 = PER(uint16_t*, s.pH1);
+  a.H2 = PER(uint16_t*, s.pH2);
+  a.dA = PER(uint16_t*, s.pdA);
+  a.dY = PER(uint16_t*, s.pdY);
+  a.part = PER(float*, s.rowpart);
+  a.loss = PER(double*, s.partial);
+  const dim3 grid((unsigned)((n + kNetRows - 1) / kNetRows), g.n);
+  if (std::max(s0.H, s0.K) <= 256)
+    hipLaunchKernelGGL((k_net<1, BWD>), grid, dim3(64 * kNetWaves), 0, st, n, s0.H, s0.K, s0.oW2, s0.oW3, 1.f / n, a);
+  else
+    hipLaunchKernelGGL((k_net<2, BWD>), grid, dim3(64 * kNetWaves), 0, st, n, s0.H, s0.K, s0.oW2, s0.oW3, 1.f / n, a);
+  RFD_CHECK_LAUNCH();
+  return RFD_OK;
+}
+
 // forward pass for n rows (n <= nb) of parameters P -> Y (and the activations)
 static int forward(const NetGroup& g, hipStream_t st, const PerNet<const float*>& P, int n) {
+  if (net_fused(*g.s[0])) {
+    NetArgs a{};
+    return net_pass<false>(g, st, P, PerNet<const float*>{}, n, a);
+  }
   int rc;
   const int H = g.s[0]->H, K = g.s[0]->K;
   // biases and activations in the GEMM epilogues
@@ -885,26 +1404,40 @@ static int forward(const NetGroup& g, hipStream_t st, const PerNet<const float*>
   return RFD_OK;
 }
 
-// loss (added to *s.loss when accumulate) and gradients into s.g for n rows
-// (P, Cb); with state_acc the loss accumulates after an epoch's first step
-static int backward(const NetGroup& g, hipStream_t st, const PerNet<const float*>& P,
-                    const PerNet<const float*>& Cb, int n, int accumulate_loss, double loss_scale,
-                    bool state_acc = false) {
+// loss and gradients gs for n rows (P, Cb); with state_acc the loss is added to *s.loss after an
+// epoch's first step.  loss_host (pinned, or NULL; one network): gets the loss too.
+static int loss_grads(const NetGroup& g, hipStream_t st, const PerNet<const float*>& P,
+                      const PerNet<const float*>& Cb, int n, double loss_scale, const PerNet<float*>& gs,
+                      double* loss_host, bool state_acc) {
   int rc;
   const int H = g.s[0]->H, K = g.s[0]->K;
+  // sums over rows: in place, or by chunks of rows into copies that are added last
+  const int nsplit = (n + kGemmChunk - 1) / kGemmChunk;
+  const int64_t np = g.s[0]->np;
+  const PerNet<float*> gr = nsplit > 1 ? PER(float*, s.gpart) : gs;
+  const PerNet<const int64_t*> acc_from = PER(const int64_t*, state_acc ? s.tstate : nullptr);
+  if (net_fused(*g.s[0])) {
+    const Surrogate& s0 = *g.s[0];
+    NetArgs a{};
+    if ((rc = net_pass<true>(g, st, P, Cb, n, a))) return rc;
+    const unsigned tiles = (unsigned)((H / 32) * (H / 32) + (K + 31) / 32 * (H / 32));
+    hipLaunchKernelGGL(k_net_wgrad, dim3(tiles, nsplit, g.n), dim3(256), 0, st, n, H, K, s0.oW2, s0.oW3, np, a, gr);
+    RFD_CHECK_LAUNCH();
+    hipLaunchKernelGGL(k_net_sums, dim3((unsigned)((np + 255) / 256 + 1), g.n), dim3(256), 0, st,
+                       (n + kNetRows - 1) / kNetRows, nsplit, H, K, np, s0.oW2, s0.oW3, a,
+                       PER(const float*, s.gpart), gs, loss_scale, PER(double*, s.loss), loss_host, acc_from);
+    RFD_CHECK_LAUNCH();
+    return RFD_OK;
+  }
+  if ((rc = forward(g, st, P, n))) return rc;
   const int64_t ny = (int64_t)n * K;
   const int nblk = std::min<int>(grid_for(ny), 256);
   hipLaunchKernelGGL(k_loss, dim3(nblk, g.n), dim3(256), 0, st, PER(const float*, s.Y), Cb, PER(float*, s.dY), ny,
                      1.f / n, PER(double*, s.partial));
   RFD_CHECK_LAUNCH();
   hipLaunchKernelGGL(k_sum_partials, dim3(g.n), dim3(64), 0, st, PER(const double*, s.partial), nblk, loss_scale,
-                     PER(double*, s.loss), accumulate_loss,
-                     PER(const int64_t*, state_acc ? s.tstate : nullptr));
+                     PER(double*, s.loss), loss_host, acc_from);
   RFD_CHECK_LAUNCH();
-  // gradients of weights and biases: in place, or by chunks of rows into copies that are added last
-  const int nsplit = (n + kGemmChunk - 1) / kGemmChunk;
-  const int64_t np = g.s[0]->np;
-  const PerNet<float*> gr = PER(float*, nsplit > 1 ? s.gpart : s.g);
   const auto at = [&](int64_t off) {
     PerNet<float*> r = gr;
     for (int i = 0; i < g.n; ++i) r.p[i] += off;
@@ -949,7 +1482,7 @@ static int backward(const NetGroup& g, hipStream_t st, const PerNet<const float*
   RFD_CHECK_LAUNCH();
   if (nsplit > 1) {
     hipLaunchKernelGGL(k_sum_chunks, dim3((unsigned)((np + 255) / 256), g.n), dim3(256), 0, st,
-                       PER(const float*, s.gpart), nsplit, np, PER(float*, s.g));
+                       PER(const float*, s.gpart), nsplit, np, gs);
     RFD_CHECK_LAUNCH();
   }
   return RFD_OK;
@@ -1011,8 +1544,7 @@ static int train_group(const NetGroup& g, const PerNet<const float*>& params, in
     hipLaunchKernelGGL(k_gather, dim3(grid_for((int64_t)batch * (4 + K)), g.n), dim3(256), 0, q, params,
                        PER(const float*, s.C), dp, tst, batch, K, PER(float*, s.Pb), PER(float*, s.Cb));
     if (hipGetLastError() != hipSuccess) return fail(RFD_E_DEVICE, "gather launch failed");
-    int r = forward(g, q, Pb, batch);
-    if (!r) r = backward(g, q, Pb, Cb, batch, 0, loss_scale, true);
+    const int r = loss_grads(g, q, Pb, Cb, batch, loss_scale, PER(float*, s.g), nullptr, true);
     if (r) return r;
     hipLaunchKernelGGL(k_adam_step, dim3(grid_for(s0.np), g.n), dim3(256), 0, q, PER(float*, s.w),
                        PER(const float*, s.g), PER(float*, s.m), PER(float*, s.v), PER(uint16_t*, s.wbf), s0.np, lr,
@@ -1152,14 +1684,28 @@ int rfd_surrogate_create(rfd_plan* plan, rfd_taps* taps, int32_t subbank, int32_
   TRY(salloc(&s.wbf, (size_t)s.np));
   TRY(salloc(&s.Pb, (size_t)s.nb * 4));
   TRY(salloc(&s.Cb, (size_t)s.nb * K));
-  TRY(salloc(&s.Z1, (size_t)s.nb * H));
-  TRY(salloc(&s.H1, (size_t)s.nb * H));
-  TRY(salloc(&s.Z2, (size_t)s.nb * H));
-  TRY(salloc(&s.H2, (size_t)s.nb * H));
   TRY(salloc(&s.Y, (size_t)s.nb * K));
-  TRY(salloc(&s.dY, (size_t)s.nb * K));
-  TRY(salloc(&s.dA, (size_t)s.nb * H));
-  TRY(salloc(&s.dB, (size_t)s.nb * H));
+  if (net_fused(s)) {
+    const size_t cols = (size_t)3 * kSurMaxBatch;
+    TRY(salloc(&s.pH1, cols * H));
+    TRY(salloc(&s.pH2, cols * H));
+    TRY(salloc(&s.pdA, cols * H));
+    TRY(salloc(&s.pdY, cols * ((K + 31) & ~31)));
+    TRY(salloc(&s.rowpart, (size_t)(kSurMaxBatch / kNetRows) * (6 * H + K)));
+  } else {
+    TRY(salloc(&s.Z1, (size_t)s.nb * H));
+    TRY(salloc(&s.H1, (size_t)s.nb * H));
+    TRY(salloc(&s.Z2, (size_t)s.nb * H));
+    TRY(salloc(&s.H2, (size_t)s.nb * H));
+    TRY(salloc(&s.dY, (size_t)s.nb * K));
+    TRY(salloc(&s.dA, (size_t)s.nb * H));
+    TRY(salloc(&s.dB, (size_t)s.nb * H));
+  }
+  if (hipHostMalloc((void**)&s.loss_host, sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    s.loss_host = nullptr;
+    (void)hipGetLastError();
+    TRY(fail(RFD_E_NOMEM, "surrogate: hipHostMalloc failed"));
+  }
   TRY(salloc(&s.idx, (size_t)s.nb));
   TRY(salloc(&s.partial, 256));
   TRY(salloc(&s.gpart, (size_t)(kSurMaxBatch / kGemmChunk) * s.np));
@@ -1233,7 +1779,7 @@ int rfd_surrogate_fit_basis(rfd_surrogate* sur, int32_t iters, double* captured_
     hipLaunchKernelGGL(k_loss, dim3(nblk), dim3(256), 0, st, one_net<const float*>(s.C), one_net<const float*>(zeros),
                        one_net(dummy), ny, 1.f, one_net(s.partial));
     hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(64), 0, st, one_net<const double*>(s.partial), nblk, 1.0 / n,
-                       one_net(s.loss), 0, one_net<const int64_t*>(nullptr));
+                       one_net(s.loss), (double*)nullptr, one_net<const int64_t*>(nullptr));
     double v = 0;
     RFD_HIP(hipMemcpyAsync(&v, s.loss, sizeof(double), hipMemcpyDeviceToHost, st));
     RFD_HIP(hipStreamSynchronize(st));
@@ -1312,16 +1858,12 @@ int rfd_surrogate_loss_grad(rfd_surrogate* sur, const float* params, const float
   if (n < 1 || n > kSurMaxBatch) return fail(RFD_E_INVALID, "n out of range");
   hipStream_t st = s.plan->stream;
   const float* Cb = targets ? targets : s.C;
-  const NetGroup g = one_group(s);
-  int rc = forward(g, st, one_net(params), n);
-  if (!rc) rc = backward(g, st, one_net(params), one_net<const float*>(Cb), n, 0, (double)1.0 / n);
+  const int rc = loss_grads(one_group(s), st, one_net(params), one_net<const float*>(Cb), n, 1.0 / n, one_net(grads),
+                            s.loss_host, false);
   if (rc) return rc;
-  RFD_HIP(hipMemcpyAsync(grads, s.g, s.np * sizeof(float), hipMemcpyDeviceToDevice, st));
   if (loss_out) {
-    double v = 0;
-    RFD_HIP(hipMemcpyAsync(&v, s.loss, sizeof(double), hipMemcpyDeviceToHost, st));
     RFD_HIP(hipStreamSynchronize(st));
-    *loss_out = v;         // mean over rows of ||y - c||^2
+    *loss_out = *s.loss_host;         // mean over rows of ||y - c||^2
   }
   return RFD_OK;
 }
