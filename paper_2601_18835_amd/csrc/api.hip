@@ -158,6 +158,7 @@ static void plan_free(Plan& p) {
   dfree(p.zref); dfree(p.zbf_hi); dfree(p.zbf_lo); dfree(p.zh_hi); dfree(p.zh_lo);
   dfree(p.slots); dfree(p.counts); dfree(p.total); dfree(p.fc_work); dfree(p.counter);
   dfree(p.ols_tw32); dfree(p.ols_tw64); dfree(p.ols_ct32); dfree(p.ct64);
+  dfree(p.fcz_list); dfree(p.fcz_count);
   for (auto& z : p.zband) dfree(z);
   dfree(p.band_work); dfree(p.band_sums);
   if (p.total_host) (void)hipHostFree(p.total_host);
@@ -370,6 +371,8 @@ int rfd_plan_create(const double* psd, int64_t n_psd, double f_low, double fs, i
   TRY(dalloc(&p.dref_sig2, (size_t)max_refs));
   TRY(dalloc(&p.dref_scale, (size_t)kDechirpBatch));
   TRY(dalloc(&p.dref_part, (size_t)kDechirpBatch * kSigParts));
+  TRY(dalloc(&p.fcz_list, (size_t)kFcZList));
+  TRY(dalloc(&p.fcz_count, (size_t)1));
   TRY(dalloc(&p.counter, 1));
   {
     int dev = 0, ncu = 0;
@@ -1176,7 +1179,8 @@ int findchirp_filter(rfd_plan* plan, const double* data, const float* filt, int6
   if (rc) return rc;
   rc = launch_compact(p, n_slots, nwin, cluster_window, threshold, out, capacity);
   if (rc) return rc;
-  rc = launch_findchirp_z(p, reinterpret_cast<const float2*>(filt), out, std::min<int64_t>(capacity, 4096));
+  rc = launch_findchirp_z(p, reinterpret_cast<const float2*>(filt), n_templates, out,
+                          std::min<int64_t>(capacity, kFcZList), cluster_window, nwin);
   if (!rc) rc = stage_end(p);
   if (rc) return rc;
   return finish_triggers(p, capacity, n_out);

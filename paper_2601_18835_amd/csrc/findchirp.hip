@@ -373,6 +373,8 @@ int launch_findchirp(Plan& p, const float2* filt, int64_t n_templates, int64_t W
       }
     }
     RFD_CHECK_LAUNCH();
+    const int rc = launch_findchirp_z_batch(p, n_templates, t0, nb, N1, N2, W, nwin, threshold * threshold);
+    if (rc) return rc;
   }
   return RFD_OK;
 }

@@ -32,6 +32,7 @@ constexpr int kDechirpBatch = 32;               // references per batched dechir
 constexpr int kMaxRefSlots = 4096;              // reference-series slots of a plan, at most
 constexpr int kSigParts = 64;                   // partial sums per reference norm
 constexpr int kZParts = 32;                     // partial sums per FINDCHIRP trigger z
+constexpr int kFcZList = 4096;                  // firing slots listed with their z by FINDCHIRP
 constexpr int kMaxBands = 64;                   // bands of the chi^2 test, at most
 
 // ------------------------------------------------------------- plan state
@@ -97,6 +98,8 @@ struct Plan {
   bool dechirp_fp64 = false;   // reference transforms in FP64 (default: FP32 passes, FP64 integrand)
   float2* ols_tw32 = nullptr;
   double2* ols_tw64 = nullptr;
+  double2* fcz_list = nullptr;               // [kFcZList] slot and z of FINDCHIRP's firing slots (16 B each)
+  unsigned long long* fcz_count = nullptr;   // how many fired
   // the same points e^{i a} as (cos a, tan a): the twiddles of block_fft.h and col_fft.h
   float2* ols_ct32 = nullptr;
   double2* ct64 = nullptr;
@@ -292,7 +295,10 @@ int compaction_blocks(int64_t n_slots);
 int findchirp_batch_size(const Plan& p);
 size_t findchirp_work_size(const Plan& p);
 int launch_fir_z(Plan& p, const Taps& tp, rfd_trigger* out, int64_t capacity);
-int launch_findchirp_z(Plan& p, const float2* filt, rfd_trigger* out, int64_t capacity);
+int launch_findchirp_z_batch(Plan& p, int64_t n_templates, int64_t tmpl0, int count, int64_t N1, int64_t N2, int64_t W,
+                             int64_t nwin, float thr2);
+int launch_findchirp_z(Plan& p, const float2* filt, int64_t n_templates, rfd_trigger* out, int64_t capacity, int64_t W,
+                       int64_t nwin);
 
 }  // namespace rfd
 

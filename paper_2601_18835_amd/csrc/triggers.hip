@@ -28,8 +28,9 @@ __device__ __forceinline__ bool map_identity(const WinMap& m) {
   return m.nq == m.nwin && m.cnt0 == m.nq && m.lo0 == 0;
 }
 
-__global__ void k_fill_u64(unsigned long long* __restrict__ p, int64_t n, WinMap m) {
+__global__ void k_fill_u64(unsigned long long* __restrict__ p, int64_t n, WinMap m, unsigned long long* also) {
   const bool ident = map_identity(m);
+  if (also && blockIdx.x == 0 && threadIdx.x == 0) *also = 0ull;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     p[ident ? i : map_slot(m, i)] = 0ull;
 }
@@ -259,7 +260,80 @@ __global__ __launch_bounds__(256) void k_fc_z(rfd_trigger* __restrict__ out, con
   }
 }
 
-// ... or, for long segments, kZParts blocks per trigger over contiguous bin
+// ... or, for long segments, from the rows of the intermediate [template][N2][N1] that pass B has just
+// transformed: z[m] = sum_i1 Y[m mod N2][i1] e^{2 pi i i1 (m div N2) / N1}, N1 terms (32 KB) per trigger in place of
+// the N / 2 of its filter (4 MB at N = 2^20; 250 triggers then read 1 GB again, 238 us).  Each batch
+// of templates lists its firing slots with their z, summed in FP64, in any order; k_fc_z_final gives them to the
+// triggers after compaction.  More than kFcZList firing slots (beyond what gets a z at all) are
+// left to the sums over the filters, all of them, so that no result depends on the order.
+constexpr int kFcZSlots = 32;            // slots per workgroup
+struct FcZ {
+  long long slot;
+  float2 z;
+};
+__global__ __launch_bounds__(256) void k_fc_z_rows(const unsigned long long* __restrict__ slots, int64_t tmpl0, int count,
+                                                 float thr2, int64_t nwin, int64_t W, const float2* __restrict__ Y,
+                                                 int64_t N1, int64_t N2, const double2* __restrict__ tab,
+                                                 FcZ* __restrict__ list, unsigned long long* __restrict__ listed) {
+  __shared__ unsigned long long base;
+  __shared__ double red[2][4];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  // a signal fires the same windows of every template: neighbouring workgroups, which run on
+  // different compute units, take the same windows of different templates
+  const int64_t b = blockIdx.x % (uint32_t)count, q0 = (int64_t)(blockIdx.x / (uint32_t)count) * kFcZSlots;
+  slots += (tmpl0 + b) * nwin + q0;
+  const unsigned long long k = lane < kFcZSlots && q0 + lane < nwin ? slots[lane] : 0ull;   // (in every wave)
+  unsigned long long mask = __ballot(slot_fires(k, thr2));
+  if (mask == 0) return;
+  if (threadIdx.x == 0) base = atomicAdd(listed, (unsigned long long)__popcll(mask));
+  __syncthreads();
+  for (unsigned long long e = base; mask != 0 && e < (unsigned long long)kFcZList; ++e, mask &= mask - 1) {
+    const int at = __ffsll(mask) - 1;
+    const uint32_t off = 0xFFFFFFFFu - (uint32_t)__shfl((int)(uint32_t)(k & 0xFFFFFFFFull), at);
+    const int64_t q = q0 + at, m = q * W + (int64_t)off;
+    const float2* __restrict__ row = Y + (b * N2 + (m & (N2 - 1))) * N1;
+    const uint32_t turn = (uint32_t)(m / N2);                     // of N1 (powers of two, at most 4096)
+    double re = 0.0, im = 0.0;
+#pragma unroll 16
+    for (uint32_t i = threadIdx.x; i < (uint32_t)N1; i += 256) {
+      const float2 y = row[i];
+      const double2 w = tab[i * turn & (uint32_t)(N1 - 1)];
+      re += (double)y.x * w.x - (double)y.y * w.y;
+      im += (double)y.x * w.y + (double)y.y * w.x;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      re += __shfl_xor(re, o);
+      im += __shfl_xor(im, o);
+    }
+    if (lane == 0) {
+      red[0][wv] = re;
+      red[1][wv] = im;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+      list[e] = FcZ{(long long)((tmpl0 + b) * nwin + q), make_float2((float)((red[0][0] + red[0][1]) + (red[0][2] + red[0][3])),
+                                                               (float)((red[1][0] + red[1][1]) + (red[1][2] + red[1][3])))};
+    __syncthreads();
+  }
+}
+// the z of list entry x to its trigger, unless that lies beyond the first lim
+__device__ __forceinline__ void fc_z_match(rfd_trigger* __restrict__ out, int64_t lim, int64_t nwin, int64_t W,
+                                           const FcZ& x) {
+  const int64_t tmpl = x.slot / nwin, first = (x.slot - tmpl * nwin) * W;
+  int64_t lo = 0, hi = lim;                // triggers are in slot order
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) >> 1;
+    const int64_t t = out[mid].tmpl;
+    if (t < tmpl || (t == tmpl && out[mid].sample < first)) lo = mid + 1; else hi = mid;
+  }
+  if (lo >= lim || out[lo].tmpl != tmpl || out[lo].sample < first || out[lo].sample >= first + W) return;
+  out[lo].z_re = x.z.x;
+  out[lo].z_im = x.z.y;
+  out[lo].flags = 0u;
+}
+
+// ... or, where those lists do not serve, kZParts blocks per trigger over contiguous bin
 // ranges (grid-stride over the triggers), their partial sums then added in
 // a fixed order by one thread per trigger.  A thread's bins are 256 apart, so
 // its factor e^{2 pi i bin n / N} turns by the same angle from each bin to the next: an
@@ -273,8 +347,10 @@ __global__ __launch_bounds__(256) void k_fc_z_part(const rfd_trigger* __restrict
                                                  const float2* __restrict__ s, const float2* __restrict__ filt,
                                                  int64_t i_low, int64_t n_band, int64_t n,
                                                  const double2* __restrict__ coarse, const double2* __restrict__ fine,
-                                                 float2* __restrict__ part) {
+                                                 float2* __restrict__ part,
+                                                 const unsigned long long* __restrict__ listed) {
   __shared__ float red[2][4];
+  if (listed && *listed <= (unsigned long long)kFcZList) return;
   const int64_t lim = *total < capacity ? *total : capacity;
   const int64_t chunk = (n_band + kZParts - 1) / kZParts;
   const int64_t k0 = (int64_t)blockIdx.x * chunk, k1 = std::min<int64_t>(k0 + chunk, n_band);
@@ -320,9 +396,16 @@ __global__ __launch_bounds__(256) void k_fc_z_part(const rfd_trigger* __restrict
   }
 }
 __global__ __launch_bounds__(256) void k_fc_z_final(rfd_trigger* __restrict__ out, const long long* __restrict__ total,
-                                                  int64_t capacity, const float2* __restrict__ part) {
+                                                  int64_t capacity, const float2* __restrict__ part,
+                                                  const FcZ* __restrict__ list,
+                                                  const unsigned long long* __restrict__ listed, int64_t nwin,
+                                                  int64_t W) {
   const int64_t lim = *total < capacity ? *total : capacity;
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (listed && *listed <= (unsigned long long)kFcZList) {
+    if ((unsigned long long)i < *listed) fc_z_match(out, lim, nwin, W, list[i]);
+    return;
+  }
   if (i >= lim) return;
   float re = 0.f, im = 0.f;
   for (int k = 0; k < kZParts; ++k) {
@@ -363,19 +446,22 @@ bool win_map_range(int64_t nwin, int64_t W, int pieces, const int64_t* lo, const
   return true;
 }
 
-int launch_slots_clear(Plan& p, int64_t n_slots) {
-  // every slot: templates x windows, identity order
-  return launch_slots_clear_map(p, n_slots, win_map_all(std::max<int64_t>(n_slots, 1)));
-}
-
-int launch_slots_clear_map(Plan& p, int64_t n_visit, const WinMap& m) {
+// also: a counter to clear with them, or NULL
+static int slots_clear(Plan& p, int64_t n_visit, const WinMap& m, unsigned long long* also) {
   int64_t blocks = (n_visit + 255) / 256;
   if (blocks > 65536) blocks = 65536;
   if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(k_fill_u64, dim3((unsigned)blocks), dim3(256), 0, p.stream, p.slots, n_visit, m);
+  hipLaunchKernelGGL(k_fill_u64, dim3((unsigned)blocks), dim3(256), 0, p.stream, p.slots, n_visit, m, also);
   RFD_CHECK_LAUNCH();
   return RFD_OK;
 }
+
+int launch_slots_clear(Plan& p, int64_t n_slots) {
+  // every slot: templates x windows, identity order
+  return slots_clear(p, n_slots, win_map_all(std::max<int64_t>(n_slots, 1)), p.fcz_count);
+}
+
+int launch_slots_clear_map(Plan& p, int64_t n_visit, const WinMap& m) { return slots_clear(p, n_visit, m, nullptr); }
 
 int launch_compact_impl(Plan& p, int64_t n_slots, int64_t nwin, int64_t W, float threshold, rfd_trigger* out,
                         int64_t capacity, const int64_t* sb_first, int nsb, const WinMap& m,
@@ -433,17 +519,39 @@ int launch_fir_z(Plan& p, const Taps& tp, rfd_trigger* out, int64_t capacity) {
   return RFD_OK;
 }
 
-int launch_findchirp_z(Plan& p, const float2* filt, rfd_trigger* out, int64_t capacity) {
+// The lists pay where a call's filters are much to read again and its slots few against its
+// intermediates.  250 templates of 2^20 samples, one trigger each and windows of 2048: 1260 -> 1103 us
+// (no trigger at all: 1020 -> 1034); windows of 64: 1267 -> 1142 (1033 -> 1092), of 16: 1376 -> 1332 (1091 -> 1293).
+// 64 templates of 2^20: 384 -> 339; 250 of 2^18: 415 -> 379; 64 of 2^18: 147 -> 143 (119 -> 123); 8 of 2^20: 107 -> 110.
+static bool fc_z_lists(const Plan& p, int64_t n_templates, int64_t W) {
+  return W >= 256 && n_templates * p.n >= (int64_t)1 << 25 && p.n > 4096;
+}
+
+int launch_findchirp_z_batch(Plan& p, int64_t n_templates, int64_t tmpl0, int count, int64_t N1, int64_t N2, int64_t W,
+                             int64_t nwin, float thr2) {
+  if (!fc_z_lists(p, n_templates, W)) return RFD_OK;
+  hipLaunchKernelGGL(k_fc_z_rows, dim3((unsigned)((nwin + kFcZSlots - 1) / kFcZSlots * count)), dim3(256), 0, p.stream,
+                     (const unsigned long long*)p.slots, tmpl0, count, thr2, nwin, W, (const float2*)p.fc_work, N1, N2,
+                     (const double2*)p.ols_tw64, (FcZ*)p.fcz_list, p.fcz_count);
+  RFD_CHECK_LAUNCH();
+  return RFD_OK;
+}
+
+int launch_findchirp_z(Plan& p, const float2* filt, int64_t n_templates, rfd_trigger* out, int64_t capacity, int64_t W,
+                       int64_t nwin) {
   if (capacity <= 0) return RFD_OK;
+  const unsigned long long* listed = fc_z_lists(p, n_templates, W) ? p.fcz_count : nullptr;
   if (p.fc_work && p.fc_work_cap >= (size_t)capacity * kZParts) {
     // partial sums in FINDCHIRP's (now idle) intermediate buffer
     const unsigned gy = (unsigned)std::min<int64_t>(capacity, 256);
     hipLaunchKernelGGL(k_fc_z_part, dim3(kZParts, gy), dim3(256), 0, p.stream, (const rfd_trigger*)out,
                        (const long long*)p.total, capacity, p.stilde, filt, p.i_low, p.n_band, p.n, (const double2*)p.tw64c,
-                       (const double2*)p.tw64f, p.fc_work);
+                       (const double2*)p.tw64f, p.fc_work, listed);
     RFD_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_fc_z_final, dim3((unsigned)((capacity + 255) / 256)), dim3(256), 0, p.stream, out,
-                       (const long long*)p.total, capacity, (const float2*)p.fc_work);
+    const int64_t items = listed ? std::max<int64_t>(capacity, kFcZList) : capacity;
+    hipLaunchKernelGGL(k_fc_z_final, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, p.stream, out,
+                       (const long long*)p.total, capacity, (const float2*)p.fc_work, (const FcZ*)p.fcz_list, listed,
+                       nwin, W);
     RFD_CHECK_LAUNCH();
     return RFD_OK;
   }
