@@ -16,12 +16,19 @@ constexpr int kSeg = kSegThreads * kSegPer;   // slots per compaction block
 // blocks follow each other in slot order, so the triggers come out in
 // ascending slot order.
 
+// template and window of visit v (a 64-bit division costs tens of instructions: 32 bits serve
+// nearly every call)
+__device__ __forceinline__ void map_visit(const WinMap& m, int64_t v, int64_t& t, int64_t& qi) {
+  t = v <= 0xFFFFFFFFll ? (int64_t)((uint32_t)v / (uint32_t)m.nq) : v / m.nq;
+  qi = v - t * m.nq;
+}
+__device__ __forceinline__ int64_t map_window(const WinMap& m, int64_t qi) {
+  return qi < m.cnt0 ? m.lo0 + qi : m.lo1 + (qi - m.cnt0);
+}
 __device__ __forceinline__ int64_t map_slot(const WinMap& m, int64_t v) {
-  // (a 64-bit division costs tens of instructions: 32 bits serve nearly every call)
-  const int64_t t = v <= 0xFFFFFFFFll ? (int64_t)((uint32_t)v / (uint32_t)m.nq) : v / m.nq;
-  const int64_t qi = v - t * m.nq;
-  const int64_t q = qi < m.cnt0 ? m.lo0 + qi : m.lo1 + (qi - m.cnt0);
-  return t * m.nwin + q;
+  int64_t t, qi;
+  map_visit(m, v, t, qi);
+  return t * m.nwin + map_window(m, qi);
 }
 // every window of every template, in order: slot index = visit index
 __device__ __forceinline__ bool map_identity(const WinMap& m) {
@@ -44,7 +51,11 @@ __device__ __forceinline__ int lanes_below(unsigned long long mask) {
   return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// The wave's keys and firing masks over its kSegPer rounds.
+// The wave's keys and firing masks over its kSegPer rounds.  The visits of a lane are 64 apart, so
+// its template and window follow from the round before by an addition: one division per
+// lane, not one per slot (unrolled, those were most of 19 KB of code in k_count and, with those
+// of the triggers, 58 KB in k_write, which a launch reads into cold instruction caches: one
+// block 12 -> 4 us, a stream's 4096 slots 22 -> 10, 256 blocks 10 -> 5).
 struct WaveSlots {
   unsigned long long key[kSegPer];
   unsigned long long fire[kSegPer];
@@ -52,13 +63,32 @@ struct WaveSlots {
 };
 __device__ __forceinline__ void wave_slots(WaveSlots& w, const unsigned long long* __restrict__ slots, int64_t n,
                                            float thr2, const WinMap& m, int64_t base) {
-  const int lane = threadIdx.x & 63;
-  const bool ident = map_identity(m);
+  const int64_t v0 = base + (threadIdx.x & 63);
+  const int left = (int)min(n - v0, (int64_t)64 * kSegPer);
+  if (map_identity(m)) {
+    slots += v0;
+#pragma unroll
+    for (int r = 0; r < kSegPer; ++r) w.key[r] = 64 * r < left ? slots[64 * r] : 0ull;
+  } else {
+    const int nq = (int)m.nq, dt = 64 / nq, dq = 64 % nq;          // (windows are at most N)
+    int64_t t0, q0;
+    map_visit(m, v0, t0, q0);
+    slots += t0 * m.nwin;
+    int qi = (int)q0;
+#pragma unroll
+    for (int r = 0; r < kSegPer; ++r) {
+      w.key[r] = 64 * r < left ? slots[map_window(m, qi)] : 0ull;
+      qi += dq;
+      slots += dt * m.nwin;
+      if (qi >= nq) {
+        qi -= nq;
+        slots += m.nwin;
+      }
+    }
+  }
   w.count = 0;
 #pragma unroll
   for (int r = 0; r < kSegPer; ++r) {
-    const int64_t v = base + 64 * r + lane;
-    w.key[r] = v < n ? slots[ident ? v : map_slot(m, v)] : 0ull;
     w.fire[r] = __ballot(slot_fires(w.key[r], thr2));
     w.count += __popcll(w.fire[r]);
   }
@@ -123,58 +153,63 @@ __device__ __forceinline__ int find_subbank(const int64_t* first, int nsb, int64
 // one stores the total, on the device and in the plan's host word.
 template <bool SCANNED>
 __global__ __launch_bounds__(kSegThreads) void k_write(const unsigned long long* __restrict__ slots, int64_t n,
-                                                     float thr2, const long long* __restrict__ counts, int64_t nwin,
-                                                     int64_t W, rfd_trigger* __restrict__ out, int64_t capacity,
+                                                     float thr2, const long long* __restrict__ counts, int64_t W,
+                                                     rfd_trigger* __restrict__ out, int64_t capacity,
                                                      const int64_t* __restrict__ sb_first, int nsb, WinMap m,
                                                      const int32_t* __restrict__ shift, int64_t nseg,
                                                      long long* __restrict__ total, long long* __restrict__ total_host) {
   __shared__ int wc[kSegThreads / 64];
   __shared__ long long part[kSegThreads / 64];
-  const int wave = threadIdx.x >> 6;
-  const int64_t base = (int64_t)blockIdx.x * kSeg + (int64_t)wave * 64 * kSegPer;
+  __shared__ unsigned long long keys[kSeg];      // the block's firing slots, in order
+  __shared__ uint16_t at[kSeg];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t base = (int64_t)blockIdx.x * kSeg;
   long long before = 0;
   if constexpr (!SCANNED) {
     for (int64_t i = threadIdx.x; i < (int64_t)blockIdx.x; i += kSegThreads) before += counts[i];
   }
   WaveSlots w;
-  wave_slots(w, slots, n, thr2, m, base);
+  wave_slots(w, slots, n, thr2, m, base + wave * 64 * kSegPer);
   if constexpr (!SCANNED) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o);
   }
-  if ((threadIdx.x & 63) == 0) {
+  if (lane == 0) {
     wc[wave] = w.count;
     part[wave] = before;
   }
   __syncthreads();
   int64_t pos = 0;
+  int fired = 0;
+  for (int i = 0; i < kSegThreads / 64; ++i) fired += wc[i];
   if constexpr (SCANNED) {
     pos = counts[blockIdx.x];
   } else {
     for (int i = 0; i < kSegThreads / 64; ++i) pos += part[i];
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-      long long all = pos;
-      for (int i = 0; i < kSegThreads / 64; ++i) all += wc[i];
-      *total = all;
-      *total_host = all;
+      *total = pos + fired;
+      *total_host = pos + fired;
     }
   }
-  if (w.count == 0) return;     // wave-uniform; no barrier follows
-  for (int i = 0; i < wave; ++i) pos += wc[i];
-  const bool ident = map_identity(m);
-  const int lane = threadIdx.x & 63;
+  int e = 0;
+  for (int i = 0; i < wave; ++i) e += wc[i];
 #pragma unroll
   for (int r = 0; r < kSegPer; ++r) {
-    const unsigned long long k = w.key[r];
-    const int64_t at = pos + lanes_below(w.fire[r]);
-    pos += __popcll(w.fire[r]);
-    if (!((w.fire[r] >> lane) & 1ull) || at >= capacity) continue;
-    const int64_t v = base + 64 * r + lane;
-    const int64_t si = ident ? v : map_slot(m, v);
-    const int64_t tmpl = si / nwin, q = si - tmpl * nwin;
+    if ((w.fire[r] >> lane) & 1ull) {
+      const int k = e + lanes_below(w.fire[r]);
+      keys[k] = w.key[r];
+      at[k] = (uint16_t)(wave * 64 * kSegPer + 64 * r + lane);
+    }
+    e += __popcll(w.fire[r]);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < fired && pos + i < capacity; i += kSegThreads) {
+    const unsigned long long k = keys[i];
+    int64_t tmpl, qi;
+    map_visit(m, base + at[i], tmpl, qi);
     rfd_trigger t;
     // filter index m of the peak; sample n = m - d (mod N) under lag centring
-    t.sample = q * W + (int64_t)(0xFFFFFFFFu - (uint32_t)(k & 0xFFFFFFFFull));
+    t.sample = map_window(m, qi) * W + (int64_t)(0xFFFFFFFFu - (uint32_t)(k & 0xFFFFFFFFull));
     if (shift) t.sample = (t.sample - shift[tmpl]) & (nseg - 1);
     t.tmpl = (int32_t)tmpl;
     t.subbank = sb_first ? find_subbank(sb_first, nsb, tmpl) : 0;
@@ -182,7 +217,7 @@ __global__ __launch_bounds__(kSegThreads) void k_write(const unsigned long long*
     t.z_re = 0.f;
     t.z_im = 0.f;
     t.flags = 1u;       // complex SNR not yet evaluated
-    out[at] = t;
+    out[pos + i] = t;
   }
 }
 
@@ -463,8 +498,8 @@ int launch_slots_clear(Plan& p, int64_t n_slots) {
 
 int launch_slots_clear_map(Plan& p, int64_t n_visit, const WinMap& m) { return slots_clear(p, n_visit, m, nullptr); }
 
-int launch_compact_impl(Plan& p, int64_t n_slots, int64_t nwin, int64_t W, float threshold, rfd_trigger* out,
-                        int64_t capacity, const int64_t* sb_first, int nsb, const WinMap& m,
+int launch_compact_impl(Plan& p, int64_t n_slots, int64_t W, float threshold, rfd_trigger* out, int64_t capacity,
+                        const int64_t* sb_first, int nsb, const WinMap& m,
                         const int32_t* shift = nullptr) {
   int64_t nblk = (n_slots + kSeg - 1) / kSeg;
   if ((size_t)nblk > p.counts_cap) return fail(RFD_E_INVALID, "compaction scratch too small");
@@ -480,7 +515,7 @@ int launch_compact_impl(Plan& p, int64_t n_slots, int64_t nwin, int64_t W, float
   }
   if (nblk <= 4096) {
     hipLaunchKernelGGL(k_write<false>, dim3((unsigned)nblk), dim3(kSegThreads), 0, p.stream,
-                       p.slots, n_slots, thr2, (const long long*)p.counts, nwin, W, out, capacity, sb_first, nsb, m,
+                       p.slots, n_slots, thr2, (const long long*)p.counts, W, out, capacity, sb_first, nsb, m,
                        shift, p.n, p.total, p.total_host);
     RFD_CHECK_LAUNCH();
     return RFD_OK;
@@ -488,7 +523,7 @@ int launch_compact_impl(Plan& p, int64_t n_slots, int64_t nwin, int64_t W, float
   hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, p.stream, p.counts, nblk, p.total, p.total_host);
   RFD_CHECK_LAUNCH();
   hipLaunchKernelGGL(k_write<true>, dim3((unsigned)nblk), dim3(kSegThreads), 0, p.stream, p.slots, n_slots, thr2,
-                     (const long long*)p.counts, nwin, W, out, capacity, sb_first, nsb, m, shift, p.n, p.total,
+                     (const long long*)p.counts, W, out, capacity, sb_first, nsb, m, shift, p.n, p.total,
                      p.total_host);
   RFD_CHECK_LAUNCH();
   return RFD_OK;
@@ -496,7 +531,7 @@ int launch_compact_impl(Plan& p, int64_t n_slots, int64_t nwin, int64_t W, float
 
 int launch_compact(Plan& p, int64_t n_slots, int64_t nwin, int64_t W, float threshold, rfd_trigger* out,
                    int64_t capacity) {
-  return launch_compact_impl(p, n_slots, nwin, W, threshold, out, capacity, nullptr, 1, win_map_all(nwin));
+  return launch_compact_impl(p, n_slots, W, threshold, out, capacity, nullptr, 1, win_map_all(nwin));
 }
 
 int compaction_blocks(int64_t n_slots) { return (int)((n_slots + kSeg - 1) / kSeg); }
@@ -506,7 +541,7 @@ int launch_compact_bank(Plan& p, const Taps& tp, int64_t n_slots, int64_t nwin, 
   // the lag offsets are always read (zero where a template is not centred), so
   // a captured graph stays right when taps are later re-made with or without
   // centring
-  return launch_compact_impl(p, n_slots, nwin, W, threshold, out, capacity, tp.d_first, (int)tp.sb.size(),
+  return launch_compact_impl(p, n_slots, W, threshold, out, capacity, tp.d_first, (int)tp.sb.size(),
                              m ? *m : win_map_all(nwin), tp.d_shift);
 }
 
