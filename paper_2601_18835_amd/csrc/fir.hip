@@ -60,12 +60,6 @@ struct FirArgs {
   uint32_t thr2_bits = 0;   // bits of threshold^2: keys at or below it never fire, so are not written
 };
 
-__device__ __forceinline__ unsigned long long peak_key(float r2, int64_t n, int64_t W, int64_t& q) {
-  q = n / W;
-  return ((unsigned long long)__float_as_uint(r2) << 32) |
-         (unsigned long long)(0xFFFFFFFFu - (uint32_t)(n - q * W));
-}
-
 __device__ __forceinline__ unsigned long long umax64(unsigned long long a, unsigned long long b) {
   return a > b ? a : b;
 }
@@ -91,46 +85,60 @@ __device__ __forceinline__ unsigned long long offset_key(float r2, uint32_t off)
   return ((unsigned long long)__float_as_uint(r2) << 32) | (unsigned long long)(0xFFFFFFFFu - off);
 }
 
+// A tile without a value above the threshold, nearly every one in a search, ends after the maximum
+// of its squared moduli.  For the others window and offset follow from block to block in 32 bits (windows are
+// at most N): 64-bit divisions and reductions for every block took longer than the products
+// where a workgroup met more than one window (250 templates, T = 48, N = 2^18, windows of 3000
+// at a threshold of 6: 193 -> 96 us; of 2048: 110 -> 94; 16 FP32 templates, T = 64, N = 2^17: 48 -> 40,
+// the code being 11 KB and not 26).
 template <int NB>
 __device__ __forceinline__ void fir_tile_epilogue(const f32x4 (&acc)[NB], const FirArgs& a, int64_t m0, int64_t tb,
                                                   PeakState& ps) {
   const int lane = threadIdx.x & 63;
   const int n = lane & 15, g = lane >> 4;
-  const int64_t ta = tb * 8 + 2 * g;          // templates ta, ta+1 (within the sub-bank)
-  const int64_t W = a.W;
+  float r2a[NB], r2b[NB];
+  uint32_t top = 0;                           // (squares: their bits order as they do, NaN above all)
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    r2a[nb] = acc[nb][0] * acc[nb][0] + acc[nb][1] * acc[nb][1];
+    r2b[nb] = acc[nb][2] * acc[nb][2] + acc[nb][3] * acc[nb][3];
+    top = max(top, max(__float_as_uint(r2a[nb]), __float_as_uint(r2b[nb])));
+  }
+  if (!__any(top > a.thr2_bits)) return;
   if (ps.one_window) {
     const uint32_t base = (uint32_t)(m0 - ps.qW) + (uint32_t)n;   // offset within the window
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      float r2a = acc[nb][0] * acc[nb][0] + acc[nb][1] * acc[nb][1];
-      float r2b = acc[nb][2] * acc[nb][2] + acc[nb][3] * acc[nb][3];
-      ps.ka = umax64(ps.ka, offset_key(r2a, base + 16u * nb));
-      ps.kb = umax64(ps.kb, offset_key(r2b, base + 16u * nb));
+      ps.ka = umax64(ps.ka, offset_key(r2a[nb], base + 16u * nb));
+      ps.kb = umax64(ps.kb, offset_key(r2b[nb], base + 16u * nb));
     }
     return;
   }
+  const int64_t ta = tb * 8 + 2 * g;          // templates ta, ta+1 (within the sub-bank)
   const bool va = ta < a.count, vb = ta + 1 < a.count;
+  const uint32_t W = (uint32_t)a.W;
+  uint32_t q = (uint32_t)m0 / W, off = (uint32_t)m0 - q * W;      // of the block's first sample
   unsigned long long* sa = a.slots + (a.tmpl0 + ta) * a.nwin;
   unsigned long long* sb = sa + a.nwin;
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
-    const int64_t c0 = m0 + 16 * nb;
-    const int64_t s = c0 + n;
-    float r2a = acc[nb][0] * acc[nb][0] + acc[nb][1] * acc[nb][1];
-    float r2b = acc[nb][2] * acc[nb][2] + acc[nb][3] * acc[nb][3];
-    int64_t q;
-    unsigned long long ka = peak_key(r2a, s, W, q);
-    unsigned long long kb = peak_key(r2b, s, W, q);
-    if (c0 / W == (c0 + 15) / W) {
-      ka = reduce16(ka);
-      kb = reduce16(kb);
+    if (off + 15 < W) {
+      const unsigned long long ka = reduce16(offset_key(r2a[nb], off + n));
+      const unsigned long long kb = reduce16(offset_key(r2b[nb], off + n));
       if (n == 0) {
         if (va && (uint32_t)(ka >> 32) > a.thr2_bits) atomicMax(sa + q, ka);
         if (vb && (uint32_t)(kb >> 32) > a.thr2_bits) atomicMax(sb + q, kb);
       }
     } else {
-      if (va && (uint32_t)(ka >> 32) > a.thr2_bits) atomicMax(sa + q, ka);
-      if (vb && (uint32_t)(kb >> 32) > a.thr2_bits) atomicMax(sb + q, kb);
+      const uint32_t dq = (off + n) / W, o = off + n - dq * W;
+      if (va && __float_as_uint(r2a[nb]) > a.thr2_bits) atomicMax(sa + q + dq, offset_key(r2a[nb], o));
+      if (vb && __float_as_uint(r2b[nb]) > a.thr2_bits) atomicMax(sb + q + dq, offset_key(r2b[nb], o));
+    }
+    off += 16;
+    if (off >= W) {
+      const uint32_t dq = off / W;
+      q += dq;
+      off -= dq * W;
     }
   }
 }
