@@ -161,6 +161,10 @@ static void plan_free(Plan& p) {
   dfree(p.fcz_list); dfree(p.fcz_count);
   for (auto& z : p.zband) dfree(z);
   dfree(p.band_work); dfree(p.band_sums);
+  if (p.band_host) (void)hipHostFree(p.band_host);
+  if (p.band_event) (void)hipEventDestroy(p.band_event);
+  p.band_host = nullptr;
+  p.band_event = nullptr;
   if (p.total_host) (void)hipHostFree(p.total_host);
   if (p.chi_meta) (void)hipFree(p.chi_meta);
 }

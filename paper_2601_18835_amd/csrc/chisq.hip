@@ -65,14 +65,14 @@ static int band_edges_host(Plan& p, const double* h_ref, int n_bands, std::vecto
 // The same edges from sums in another order.  Chunks of kBandChunk bins are added by
 // one workgroup each; one workgroup per edge then finds the chunk and the bin where
 // the prefix sum reaches its share, and how far the sums on both sides of the edge
-// are from the share.  25 us for 15 edges of 2^18 bins; the copies of w and h to the host and
-// the sums there took 0.8 ms per reference.
+// are from the share.  Bound by the latency of its loads and scans: 10 us for 15 edges of 2^18 bins (25 with scans
+// and searches in LDS steps); the copies of w and h to the host and the sums there took 0.8 ms per reference.
 constexpr int kBandChunk = 1024;
 constexpr int kBandMaxChunks = (1 << 21) / kBandChunk;      // N <= 2^22
 struct BandSplit {
   double total;
   double margin[kMaxBands];
-  int64_t bin[kMaxBands];       // bins before the edge, counted from the first of the band
+  int32_t edge[kMaxBands + 1];
 };
 
 __device__ __forceinline__ double band_power(const double* __restrict__ w, const double2* __restrict__ h, int64_t i) {
@@ -80,14 +80,18 @@ __device__ __forceinline__ double band_power(const double* __restrict__ w, const
   return w[i] * (x.x * x.x + x.y * x.y);
 }
 
-// inclusive sums of one value per thread (256 threads), in LDS
-__device__ __forceinline__ void scan256(double* s) {
-  for (int o = 1; o < 256; o <<= 1) {
-    const double x = (int)threadIdx.x >= o ? s[threadIdx.x - o] : 0.0;
-    __syncthreads();
-    s[threadIdx.x] += x;
-    __syncthreads();
+// inclusive sum of one value per thread (256 threads); wave_sum: LDS of the four waves' sums
+__device__ __forceinline__ double scan256(double x, double* wave_sum) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const double y = __shfl_up(x, o);
+    if (lane >= o) x += y;
   }
+  if (lane == 63) wave_sum[wave] = x;
+  __syncthreads();
+  for (int i = 0; i < wave; ++i) x += wave_sum[i];
+  return x;
 }
 
 __global__ __launch_bounds__(256) void k_band_chunks(const double* __restrict__ w, const double2* __restrict__ h,
@@ -109,14 +113,17 @@ __global__ __launch_bounds__(256) void k_band_chunks(const double* __restrict__ 
   if (threadIdx.x == 0) sums[blockIdx.x] = red[0];
 }
 
+// out and host (pinned): the same result; scale: 1 / (sigma_ref alpha), the norm being the band's sum, or NULL
 __global__ __launch_bounds__(256) void k_band_edge(const double* __restrict__ w, const double2* __restrict__ h,
                                                  int64_t cnt, const double* __restrict__ sums, int n_chunks,
-                                                 int n_bands, BandSplit* __restrict__ out) {
+                                                 int n_bands, int lo, BandSplit* __restrict__ out,
+                                                 BandSplit* __restrict__ host, double inv_alpha,
+                                                 double* __restrict__ scale) {
   constexpr int kPer = kBandMaxChunks / 256, kIn = kBandChunk / 256;
-  __shared__ double s[256];
-  __shared__ double chunk_end[kBandMaxChunks], bin_end[kBandChunk];
-  __shared__ int at;
+  __shared__ double wave_sum[2][4], total_s, chunk_start;
+  __shared__ int below[2];
   const int b = blockIdx.x + 1, t = threadIdx.x;
+  if (t < 2) below[t] = 0;
   double v[kPer], run = 0.0;
 #pragma unroll
   for (int e = 0; e < kPer; ++e) {
@@ -124,28 +131,27 @@ __global__ __launch_bounds__(256) void k_band_edge(const double* __restrict__ w,
     v[e] = c < n_chunks ? sums[c] : 0.0;
     run += v[e];
   }
-  s[t] = run;
-  if (t == 0) at = n_chunks - 1;
+  const double upto = scan256(run, wave_sum[0]);
+  if (t == 255) total_s = upto;
   __syncthreads();
-  scan256(s);
-  const double total = s[255], thr = (total * b) / n_bands;
-  double before = t ? s[t - 1] : 0.0;
+  const double total = total_s, thr = (total * b) / n_bands;
+  // sums only grow: the edge lies in the first chunk whose end reaches the share, after as many as do not
+  double end = upto - run;
+  int less = 0;
 #pragma unroll
   for (int e = 0; e < kPer; ++e) {
-    before += v[e];
-    chunk_end[t * kPer + e] = before;
+    end += v[e];
+    less += t * kPer + e < n_chunks - 1 && !(end >= thr);
   }
+  if (less) atomicAdd(&below[0], less);
   __syncthreads();
+  const int c = below[0];
+  end = upto - run;
 #pragma unroll
   for (int e = 0; e < kPer; ++e) {
-    const int c = t * kPer + e;
-    if (c < n_chunks && chunk_end[c] >= thr) atomicMin(&at, c);
+    if (t * kPer + e == c) chunk_start = end;
+    end += v[e];
   }
-  __syncthreads();
-  const int c = at;
-  const double start = c ? chunk_end[c - 1] : 0.0;
-  __syncthreads();
-  if (t == 0) at = kBandChunk - 1;
   double u[kIn];
   run = 0.0;
 #pragma unroll
@@ -154,22 +160,35 @@ __global__ __launch_bounds__(256) void k_band_edge(const double* __restrict__ w,
     u[e] = i < cnt ? band_power(w, h, i) : 0.0;
     run += u[e];
   }
-  s[t] = run;
-  __syncthreads();
-  scan256(s);
-  before = start + (t ? s[t - 1] : 0.0);
+  const double in = scan256(run, wave_sum[1]);
+  const double first = chunk_start + (in - run);
+  end = first;
+  less = 0;
 #pragma unroll
   for (int e = 0; e < kIn; ++e) {
-    before += u[e];
-    bin_end[t * kIn + e] = before;
-    if (before >= thr) atomicMin(&at, t * kIn + e);
+    end += u[e];
+    less += t * kIn + e < kBandChunk - 1 && !(end >= thr);
   }
+  if (less) atomicAdd(&below[1], less);
   __syncthreads();
-  if (t == 0) {
-    const int i = at;
-    out->bin[b] = (int64_t)c * kBandChunk + i + 1;
-    out->margin[b] = fmin(bin_end[i] - thr, thr - (i ? bin_end[i - 1] : start));
-    if (b == 1) out->total = total;
+  const int i = below[1];
+  end = first;
+#pragma unroll
+  for (int e = 0; e < kIn; ++e) {
+    const double start = end;
+    end += u[e];
+    if (t * kIn + e != i) continue;
+    // (the bins after the edge's last chunk are not bins: kept inside the band)
+    const int32_t edge = lo + (int32_t)min((int64_t)c * kBandChunk + i + 1, cnt);
+    const double margin = fmin(end - thr, thr - start);
+    out->edge[b] = edge;
+    host->edge[b] = edge;
+    host->margin[b] = margin;
+    if (b != 1) continue;
+    out->edge[0] = lo;
+    out->edge[n_bands] = lo + (int32_t)cnt;
+    host->total = total;
+    if (scale) *scale = inv_alpha / sqrt(total);
   }
 }
 
@@ -177,31 +196,54 @@ __global__ __launch_bounds__(256) void k_band_edge(const double* __restrict__ w,
 // any other order by at most cnt 2^-52 of the total (positive terms), so an edge whose
 // margins are above twice that is the same in both, and the host's sequence decides
 // where one is not (or the sums are not finite).
-static int band_edges(Plan& p, const double* h_ref, int n_bands, std::vector<int64_t>& edges) {
+// In two halves: band_edges_begin queues the device's, with a reference's scale if asked for, and
+// band_edges_end waits for them and decides (`device`: the ones in p.band_split stand).  Work between the two
+// may use p.band_split, whose edges lie in the band whatever the input.
+static BandSplit* band_split(const Plan& p) { return reinterpret_cast<BandSplit*>(p.band_sums + kBandMaxChunks); }
+
+static int band_edges_begin(Plan& p, const double* h_ref, int n_bands, double* scale) {
   if (n_bands < 2 || n_bands > kMaxBands) return fail(RFD_E_INVALID, "n_bands must be in [2, 64]");
   const int64_t lo = p.i_low, cnt = p.i_high - lo + 1;
   const int chunks = (int)((cnt + kBandChunk - 1) / kBandChunk);
   if (!p.band_sums) {
-    int rc = calloc_dev(&p.band_sums, kBandMaxChunks + sizeof(BandSplit) / sizeof(double));
+    int rc = calloc_dev(&p.band_sums, kBandMaxChunks + (sizeof(BandSplit) + 7) / sizeof(double));
     if (rc) return rc;
   }
-  BandSplit* split = reinterpret_cast<BandSplit*>(p.band_sums + kBandMaxChunks);
+  if (!p.band_host) {
+    if (hipHostMalloc(&p.band_host, sizeof(BandSplit), hipHostMallocDefault) != hipSuccess) {
+      p.band_host = nullptr;
+      (void)hipGetLastError();
+      return fail(RFD_E_NOMEM, "chi^2: hipHostMalloc failed");
+    }
+  }
+  if (!p.band_event) {
+    if (hipEventCreateWithFlags(&p.band_event, hipEventDisableTiming) != hipSuccess) {
+      p.band_event = nullptr;
+      return fail(RFD_E_DEVICE, "chi^2: hipEventCreate failed");
+    }
+  }
   const double2* h = reinterpret_cast<const double2*>(h_ref) + lo;
   hipLaunchKernelGGL(k_band_chunks, dim3((unsigned)chunks), dim3(256), 0, p.stream, (const double*)p.w + lo, h, cnt,
                      p.band_sums);
   RFD_CHECK_LAUNCH();
   hipLaunchKernelGGL(k_band_edge, dim3((unsigned)(n_bands - 1)), dim3(256), 0, p.stream, (const double*)p.w + lo, h,
-                     cnt, (const double*)p.band_sums, chunks, n_bands, split);
+                     cnt, (const double*)p.band_sums, chunks, n_bands, (int)lo, band_split(p),
+                     static_cast<BandSplit*>(p.band_host), 1.0 / p.data_scale, scale);
   RFD_CHECK_LAUNCH();
-  BandSplit got;
-  RFD_HIP(hipMemcpyAsync(&got, split, sizeof(got), hipMemcpyDeviceToHost, p.stream));
-  RFD_HIP(hipStreamSynchronize(p.stream));
+  RFD_HIP(hipEventRecord(p.band_event, p.stream));
+  return RFD_OK;
+}
+
+static int band_edges_end(Plan& p, const double* h_ref, int n_bands, std::vector<int64_t>& edges, bool& device) {
+  RFD_HIP(hipEventSynchronize(p.band_event));
+  const BandSplit& got = *static_cast<const BandSplit*>(p.band_host);
+  const int64_t cnt = p.i_high - p.i_low + 1;
   const double tol = 2.0 * (double)cnt * 0x1p-52 * got.total;
-  bool clear = got.total > 0.0;
-  for (int b = 1; b < n_bands && clear; ++b) clear = got.margin[b] > tol;
-  if (clear) {
-    edges.assign(1, lo);
-    for (int b = 1; b < n_bands; ++b) edges.push_back(lo + got.bin[b]);
+  device = got.total > 0.0;
+  for (int b = 1; b < n_bands && device; ++b) device = got.margin[b] > tol;
+  if (device) {
+    edges.assign(1, p.i_low);
+    for (int b = 1; b < n_bands; ++b) edges.push_back(got.edge[b]);
     edges.push_back(p.i_high + 1);
   } else {
     int rc = band_edges_host(p, h_ref, n_bands, edges);
@@ -210,6 +252,13 @@ static int band_edges(Plan& p, const double* h_ref, int n_bands, std::vector<int
   for (int b = 0; b < n_bands; ++b)
     if (edges[b + 1] <= edges[b]) return fail(RFD_E_INVALID, "band split produced an empty band; use fewer bands");
   return RFD_OK;
+}
+
+static int band_edges(Plan& p, const double* h_ref, int n_bands, std::vector<int64_t>& edges) {
+  bool device;
+  int rc = band_edges_begin(p, h_ref, n_bands, nullptr);
+  if (!rc) rc = band_edges_end(p, h_ref, n_bands, edges, device);
+  return rc;
 }
 
 // num[b][j] = a_j^H M_b a_j, one workgroup per (template, band)
@@ -334,8 +383,26 @@ int rfd_dechirp_bands(rfd_plan* plan, const double* h_ref, int32_t ref_id, int32
   Plan& p = plan->p;
   if (ref_id < 0 || ref_id >= p.max_refs) return fail(RFD_E_INVALID, "ref_id out of range");
   if (p.seg_gen == 0) return fail(RFD_E_STATE, "no segment transformed yet");
+  if (n_bands < 2 || n_bands > kMaxBands) return fail(RFD_E_INVALID, "n_bands must be in [2, 64]");
+  // up to 128 MiB of intermediates, or the plan's one-band buffer where they cannot be had
+  int batch = (int)std::max<int64_t>(1, std::min<int64_t>(n_bands, ((int64_t)128 << 20) / (p.n * 16)));
+  if (batch > 1 && p.band_work_cap < (size_t)batch * p.n) {
+    RFD_HIP(hipStreamSynchronize(p.stream));
+    if (p.band_work) (void)hipFree(p.band_work);
+    p.band_work_cap = 0;
+    if (calloc_dev(&p.band_work, (size_t)batch * p.n) == RFD_OK) p.band_work_cap = (size_t)batch * p.n;
+    else batch = 1;
+  }
+  double2* work = batch > 1 ? p.band_work : p.work64;
+  // The first batch's column pass runs on the device's edges while the host reads and checks
+  // them: waiting first left the device idle for 36 us per reference.  The row pass writes the slot's series, so
+  // it follows the check.
+  int rc = band_edges_begin(p, h_ref, n_bands, p.dref_scale);
+  if (!rc) rc = launch_band_cols(p, h_ref, band_split(p)->edge, 0, std::min(batch, n_bands), work);
+  if (rc) return rc;
   std::vector<int64_t> edges;
-  int rc = band_edges(p, h_ref, n_bands, edges);
+  bool device;
+  rc = band_edges_end(p, h_ref, n_bands, edges, device);
   if (rc) return rc;
   const int64_t need = (int64_t)n_bands * p.n;
   if (p.zband_cap[ref_id] < need) {
@@ -348,18 +415,21 @@ int rfd_dechirp_bands(rfd_plan* plan, const double* h_ref, int32_t ref_id, int32
     p.zband_cap[ref_id] = need;
     ++p.res_gen;
   }
-  // up to 128 MiB of intermediates, or the plan's one-band buffer where they cannot be had
-  int batch = (int)std::max<int64_t>(1, std::min<int64_t>(n_bands, ((int64_t)128 << 20) / (p.n * 16)));
-  if (batch > 1 && p.band_work_cap < (size_t)batch * p.n) {
+  if (!device) {
+    int32_t e32[kMaxBands + 1];
+    for (int b = 0; b <= n_bands; ++b) e32[b] = (int32_t)edges[b];
+    RFD_HIP(hipMemcpyAsync(band_split(p)->edge, e32, (n_bands + 1) * sizeof(int32_t), hipMemcpyHostToDevice, p.stream));
     RFD_HIP(hipStreamSynchronize(p.stream));
-    if (p.band_work) (void)hipFree(p.band_work);
-    p.band_work_cap = 0;
-    if (calloc_dev(&p.band_work, (size_t)batch * p.n) == RFD_OK) p.band_work_cap = (size_t)batch * p.n;
-    else batch = 1;
   }
-  rc = launch_dechirp_bands(p, h_ref, edges.data(), n_bands, p.zband[ref_id], batch > 1 ? p.band_work : p.work64,
-                            batch);
-  if (rc) return rc;
+  for (int b0 = 0; b0 < n_bands; b0 += batch) {
+    const int nb = std::min(batch, n_bands - b0);
+    if (b0 > 0 || !device) {
+      rc = launch_band_cols(p, h_ref, band_split(p)->edge, b0, nb, work);
+      if (rc) return rc;
+    }
+    rc = launch_band_rows(p, b0, nb, p.zband[ref_id], work);
+    if (rc) return rc;
+  }
   p.zband_edges[ref_id] = edges;
   p.zband_gen[ref_id] = p.seg_gen;
   if (edges_out) memcpy(edges_out, edges.data(), edges.size() * sizeof(int64_t));

@@ -111,19 +111,19 @@ struct LoadDechirpRefs32 { // the same integrand, formed in FP64 and rounded onc
 };
 struct LoadBands {         // the integrand of one reference on bins [e[b], e[b + 1]), FP64
   const double2* s; const double* w; const double2* h; const double* scale;
-  int32_t e[kMaxBands + 1];
-  int32_t last;              // the last edge of the batch
+  const int32_t* e;          // the batch's edges, on the device
+  int nb;                    // its bands
   static constexpr bool kHalf = true;
-  typedef double2 Fixed; typedef char Var;     // (nothing differs between bands but the range)
+  typedef double2 Fixed; typedef int2 Var;     // (nothing differs between bands but the range)
   __device__ double2 fixed(int i) const {
-    if (i < e[0] || i >= last) return make_double2(0.0, 0.0);
+    if (i < e[0] || i >= e[nb]) return make_double2(0.0, 0.0);
     const double f = w[i] * scale[0];
     const double2 x = h[i];
     return cmul(s[i], make_double2(f * x.x, -f * x.y));
   }
-  __device__ char var(int, int) const { return 0; }
-  __device__ double2 join(int b, int i, double2 f, char) const {
-    return i >= e[b] && i < e[b + 1] ? f : make_double2(0.0, 0.0);
+  __device__ int2 var(int b, int) const { return make_int2(e[b], e[b + 1]); }
+  __device__ double2 join(int, int i, double2 f, int2 range) const {
+    return i >= range.x && i < range.y ? f : make_double2(0.0, 0.0);
   }
   struct Raw { double2 h, s; double w; };
   __device__ Raw fetch(int b, int64_t i) const {
@@ -926,29 +926,17 @@ int launch_dechirp_refs(Plan& p, int n_refs, const int32_t* ref_ids, const doubl
 }
 
 // Band series of one reference: the dechirp integrand restricted to bins
-// [edges[b], edges[b+1]) and transformed, for every band (FP32 out, [p][N]).
-// `batch` bands per pair of launches, through `work` (batch N values): one band's passes
+// [edges[b], edges[b+1]) (on the device, as the reference's p.dref_scale is) and transformed, for bands
+// [b0, b0 + nb) (FP32 out, [band][N]) through `work` (nb N values): one band's passes
 // are 128 to 256 workgroups, half a wave of the chip, and 12 us each (16 bands of a 2^19
-// segment: 390 us one by one, 150 us together).
-int launch_dechirp_bands(Plan& p, const double* h_ref, const int64_t* edges, int n_bands, float2* out, double2* work,
-                         int batch) {
-  DechirpRefs one{};
-  one.h[0] = reinterpret_cast<const double2*>(h_ref);
-  hipLaunchKernelGGL(k_sigma_part, dim3(kSigParts, 1), dim3(256), 0, p.stream, p.w, one, p.nb, p.dref_part);
-  RFD_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_sigma_final, dim3(1), dim3(kSigParts), 0, p.stream, one, (const double*)p.dref_part,
-                     p.dscratch + 16, p.dref_scale, 1.0 / p.data_scale);
-  RFD_CHECK_LAUNCH();
-  for (int b0 = 0; b0 < n_bands; b0 += batch) {
-    const int nb = std::min(batch, n_bands - b0);
-    LoadBands ld{p.stilde64, p.w, one.h[0], p.dref_scale, {}, (int32_t)edges[b0 + nb]};
-    for (int b = 0; b <= nb; ++b) ld.e[b] = (int32_t)edges[b0 + b];
-    int rc = run_pass_a<1, double2>(p, ld, work, p.tw64c, p.tw64f, p.tw64_n2, nb);
-    if (rc) return rc;
-    rc = run_pass_b<1, double2>(p, work, StoreBand{out + (int64_t)b0 * p.n, p.n}, p.tw64_n1, nb);
-    if (rc) return rc;
-  }
-  return RFD_OK;
+// segment: 390 us one by one, 75 us together).
+int launch_band_cols(Plan& p, const double* h_ref, const int32_t* edges, int b0, int nb, double2* work) {
+  const LoadBands ld{p.stilde64, p.w, reinterpret_cast<const double2*>(h_ref), p.dref_scale, edges + b0, nb};
+  return run_pass_a<1, double2>(p, ld, work, p.tw64c, p.tw64f, p.tw64_n2, nb);
+}
+
+int launch_band_rows(Plan& p, int b0, int nb, float2* out, const double2* work) {
+  return run_pass_b<1, double2>(p, work, StoreBand{out + (int64_t)b0 * p.n, p.n}, p.tw64_n1, nb);
 }
 
 int launch_findchirp_prepare(Plan& p, const double* h, int64_t count, float2* filt, double* sigma) {

@@ -111,6 +111,8 @@ struct Plan {
   std::vector<int64_t> zband_gen;
   double2* band_work = nullptr; size_t band_work_cap = 0;   // FP64 intermediates of several bands (grown)
   double* band_sums = nullptr;    // power of the band split's chunks, then its result (chisq.hip)
+  void* band_host = nullptr;      // the result again, pinned, complete at band_event
+  hipEvent_t band_event = nullptr;
   void* chi_meta = nullptr; size_t chi_meta_cap = 0;        // sub-bank table of a chi^2 call (grown)
 
   // objects that keep a pointer to this plan (graphs, streams): destroy refuses while > 0
@@ -230,8 +232,8 @@ constexpr int kPeakParts = 512;  // workgroups per template of the row pass, at 
 int launch_corr_peak(Plan& p, Taps& tp, const double* h_r, const double* h_t, int64_t batch, int T, int k0_sb,
                      double2* z, int32_t* k0_out, int32_t* d_out, double2* out);
 // band series [n_bands][N] (FP32, normalised by sigma_ref) of one reference
-int launch_dechirp_bands(Plan& p, const double* h_ref, const int64_t* edges, int n_bands, float2* out, double2* work,
-                         int batch);
+int launch_band_cols(Plan& p, const double* h_ref, const int32_t* edges, int b0, int nb, double2* work);
+int launch_band_rows(Plan& p, int b0, int nb, float2* out, const double2* work);
 
 // ---------------------------------------------------- launchers (taps.hip)
 int taps_prepare_subbank(Plan& p, Taps& tp, int b, const double* h_ref, double eps);
