@@ -261,6 +261,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NB <= 8 ? 3
   fir16_block<BF16, NB>(a, a.m_off + (int64_t)blockIdx.x * a.S * 16 * NB, (int64_t)blockIdx.y * kWavesPerBlock, win);
 }
 
+// The template block and tiles of a wave of the FP32 form: a block of 8 templates each, or, where the bank has only one or
+// two left, all four waves on those and every fourth or second tile each (idle waves leave their SIMDs
+// idle: 16 FP32 templates, T = 64, N = 2^17: 38 -> 35 us).
+struct WaveTiles {
+  int64_t tb;
+  int first, step;
+};
+__device__ __forceinline__ WaveTiles wave_tiles(const FirArgs& a, int64_t tb0) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t left = a.count - tb0 * kTmplPerWave;
+  if (left <= kTmplPerWave) return {tb0, wave, 4};
+  if (left <= 2 * kTmplPerWave) return {tb0 + (wave & 1), wave >> 1, 2};
+  return {tb0 + wave, 0, 1};
+}
+
 // FP32: v_mfma_f32_16x16x4f32, K step = 2 complex taps; B read from LDS.
 template <int NB>
 __device__ __forceinline__ void fir32_block(const FirArgs& a, int64_t mbase, int64_t tb0, float2* wz) {
@@ -268,8 +283,9 @@ __device__ __forceinline__ void fir32_block(const FirArgs& a, int64_t mbase, int
   const int Lw = a.S * kColsPerTile + a.Tp;
   load_window(wz, a.z32, mbase + a.k0, Lw, a.n - 1);
   __syncthreads();
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t tb = tb0 + wave;
+  const int lane = threadIdx.x & 63;
+  const WaveTiles wt = wave_tiles(a, tb0);
+  const int64_t tb = wt.tb;
   if (tb * kTmplPerWave >= a.count) return;   // wave-uniform; no barrier follows
   const float4* A = a.pa32 + tb * (int64_t)(a.Tp / 8) * 64 + lane;
   const int KQ = a.Tp / 8;
@@ -278,7 +294,7 @@ __device__ __forceinline__ void fir32_block(const FirArgs& a, int64_t mbase, int
   ps.q = mbase / a.W;
   ps.qW = ps.q * a.W;
   ps.one_window = ps.q == ((mbase + (int64_t)a.S * kColsPerTile - 1) / a.W);
-  for (int t = 0; t < a.S; ++t) {
+  for (int t = wt.first; t < a.S; t += wt.step) {
     const float* wf = reinterpret_cast<const float*>(wz + t * kColsPerTile) + 2 * (lane & 15) + (lane >> 4);
     // The K sweep runs in chunks of kFir32Chunk tap groups (8 complex taps,
     // 16 real products each): every chunk accumulates from zero in the MFMA
@@ -447,6 +463,14 @@ static int launch_ref_planes(Plan& p, int precision, int ref, int64_t start, int
   return RFD_OK;
 }
 
+// Waves that share a template block of the FP32 form (wave_tiles), where a tile is long enough
+// to be worth a workgroup of several: 16 templates, N = 2^20, T = 64 134 -> 104 us, 8 at 2^17 33 -> 30; but 3 at 2^16,
+// T = 24 26 -> 27.  A 16-bit tile is an eighth of an FP32 one: 5 BF16 templates, N = 2^17, T = 40 29 -> 30.
+static int waves_per_block(int64_t count, int precision, int Tp) {
+  if (precision != RFD_FP32 || Tp < 48) return 1;
+  return count <= kTmplPerWave ? 4 : count <= 2 * kTmplPerWave ? 2 : 1;
+}
+
 // Tiles per workgroup: one workgroup covers a whole cluster window when W is
 // a multiple of 256 (so each (template, window) peak gets one update), capped
 // at 2048 samples; otherwise half of that.  Fewer where the launch would then hold less
@@ -455,11 +479,12 @@ static int launch_ref_planes(Plan& p, int precision, int ref, int64_t start, int
 // the launches per sub-bank (FP32, N = 2^17, 16 templates, T = 64: 91 us in 64 workgroups, 28 in
 // 1024; BF16, 250 templates at N = 2^18, T = 48: 81 us in 1024, 79 in 2048), 1 per CU for the
 // persistent form, whose workgroups pay a queue step per item (64 templates, N = 2^17,
-// T = 128: 64 us in 128 items, 47 in 256, 52 in 2048).
-static int tiles_per_block(int64_t n, int64_t W, int cols, int smax_cfg, int64_t rows, int64_t want) {
+// T = 128: 64 us in 128 items, 47 in 256, 52 in 2048).  At least `share` (waves_per_block).
+static int tiles_per_block(int64_t n, int64_t W, int cols, int smax_cfg, int share, int64_t rows, int64_t want) {
   const int smax = std::max(1, std::min(2048 / cols, smax_cfg));
   int S = (W % cols == 0) ? (int)std::min<int64_t>(W / cols, smax) : std::max(1, smax / 2);
   while (S > 1 && (n % ((int64_t)S * cols) != 0 || n / ((int64_t)S * cols) * rows < want)) S >>= 1;
+  while (S < share && 2 * S <= smax && n % ((int64_t)2 * S * cols) == 0) S *= 2;
   return S < 1 ? 1 : S;
 }
 
@@ -498,7 +523,8 @@ int launch_fir(Plan& p, const Taps& tp, int b, int precision, int64_t W, int64_t
     n_start = 0;
     n_len = p.n;
   }
-  a.S = tiles_per_block(n_len, W, cols, p.fir_smax, (s.count + kTmplTile - 1) / kTmplTile, (int64_t)8 * p.n_cu);
+  a.S = tiles_per_block(n_len, W, cols, p.fir_smax, waves_per_block(s.count, precision, s.Tp),
+                        (s.count + kTmplTile - 1) / kTmplTile, (int64_t)8 * p.n_cu);
   while (a.S > 1 && n_start % ((int64_t)a.S * cols) != 0) a.S >>= 1;
   a.m_off = n_start;
   dim3 grid((unsigned)(n_len / ((int64_t)a.S * cols)), (unsigned)((s.count + kTmplTile - 1) / kTmplTile));
@@ -563,7 +589,7 @@ int prepare_fir_items(Plan& p, Taps& tp, int precision, int64_t W) {
   for (int b : order) rows += (tp.sb[b].count + kTmplTile - 1) / kTmplTile;
   for (int j = 0; j < m; ++j) {
     const SubBankTaps& s = tp.sb[order[j]];
-    S[j] = tiles_per_block(p.n, W, cols, p.fir_smax, rows, p.n_cu);
+    S[j] = tiles_per_block(p.n, W, cols, p.fir_smax, waves_per_block(s.count, precision, s.Tp), rows, p.n_cu);
     nsg[j] = p.n / ((int64_t)S[j] * cols);
     sbv[j] = order[j];
     off[j + 1] = off[j] + nsg[j] * ((s.count + kTmplTile - 1) / kTmplTile);

@@ -14,12 +14,16 @@ def test_refused_split_keeps_the_series(rfd, n):
     from paper_2601_18835_amd.driver import RatioFilterSearch, SubBankSpec
     fs, f_low = 2048.0, 30.0
     h = synth.taylorf2(synth.WaveformParams(2.0, 1.8), n, fs, f_low)
-    loud = n // 16
-    h[loud] *= 1e3 * np.sqrt(n) * np.abs(h).max() / np.abs(h[loud])     # nearly all the power: three bands are too many
-    s = RatioFilterSearch(synth.psd_array(n, fs), f_low, fs, n, [SubBankSpec(0, 1, 0, 1)])
+    psd = synth.psd_array(n, fs)
+    s = RatioFilterSearch(psd, f_low, fs, n, [SubBankSpec(0, 1, 0, 1)])
+    band = slice(s.info["i_low"], s.info["i_high"] + 1)
+    power = np.abs(h) ** 2 / psd
+    loud = n // 16                                        # three fifths of the power: three bands are too many
+    h[loud] *= np.sqrt(1.5 * (power[band].sum() - power[loud]) / power[loud])
     s.set_reference(0, h)
     s.make_taps(0, h[None])
-    s.set_segment(np.random.default_rng(3).standard_normal(n))
+    w = synth.Workload("order", 9, n, fs, f_low, 0, 1, 0, "fp32", "nonspin")
+    s.set_segment(synth.spectrum_to_time(synth.make_noise_spectrum(w, np.random.default_rng(3)), n, fs))
     s.dechirp_all()
     edges = s.bands(2)[0]
     buf, k = s.filter("fp32", 0.0, n // 8, 8)
