@@ -154,7 +154,7 @@ static void plan_free(Plan& p) {
   dfree(p.tw32c); dfree(p.tw32f); dfree(p.tw64c); dfree(p.tw64f);
   dfree(p.tw32_n1); dfree(p.tw32_n2); dfree(p.tw64_n1); dfree(p.tw64_n2);
   dfree(p.stilde64); dfree(p.stilde); dfree(p.work64); dfree(p.dscratch);
-  dfree(p.work64b); dfree(p.dref_sig2); dfree(p.dref_scale); dfree(p.dref_part);
+  dfree(p.work64b); dfree(p.dref_sig2); dfree(p.dref_scale); dfree(p.dref_part); dfree(p.dref_done);
   dfree(p.zref); dfree(p.zbf_hi); dfree(p.zbf_lo); dfree(p.zh_hi); dfree(p.zh_lo);
   dfree(p.slots); dfree(p.counts); dfree(p.total); dfree(p.fc_work); dfree(p.counter);
   dfree(p.ols_tw32); dfree(p.ols_tw64); dfree(p.ols_ct32); dfree(p.ct64);
@@ -375,6 +375,9 @@ int rfd_plan_create(const double* psd, int64_t n_psd, double f_low, double fs, i
   TRY(dalloc(&p.dref_sig2, (size_t)max_refs));
   TRY(dalloc(&p.dref_scale, (size_t)kDechirpBatch));
   TRY(dalloc(&p.dref_part, (size_t)kDechirpBatch * kSigParts));
+  TRY(dalloc(&p.dref_done, (size_t)kDechirpBatch));
+  if (hipMemsetAsync(p.dref_done, 0, kDechirpBatch * sizeof(unsigned int), p.stream) != hipSuccess)
+    TRY(fail(RFD_E_DEVICE, "plan initialisation failed"));
   TRY(dalloc(&p.fcz_list, (size_t)kFcZList));
   TRY(dalloc(&p.fcz_count, (size_t)1));
   TRY(dalloc(&p.counter, 1));

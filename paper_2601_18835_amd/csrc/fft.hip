@@ -793,10 +793,27 @@ __global__ __launch_bounds__(1024) void k_sigma_sq(const double* __restrict__ w,
 // sigma^2 of each reference of a batch in two steps of fixed order:
 // kSigParts workgroups per reference reduce contiguous bin ranges to
 // partial sums, then one wave per reference adds its partials and
-// stores sigma^2 by slot and the filter scale 1 / (sigma alpha).
+// stores sigma^2 by slot and the filter scale 1 / (sigma alpha): the workgroup that finishes last
+// (LAST), or k_sigma_final.  A launch of its own costs 3 us and the gap before it (16
+// FP32 templates on one reference: 76 us against 70 for the whole call), but each workgroup's release
+// of its partial writes its L2 back, which 1024 of them pay for (16 references: 44 us, 90 with LAST).
+// done: workgroups finished so far, a multiple of kSigParts between launches.
+__device__ __forceinline__ void sigma_store(DechirpRefs& r, int b, double s2, double* sig2_by_slot, double* scale,
+                                            double inv_alpha) {
+#pragma unroll
+  for (int o = kSigParts / 2; o > 0; o >>= 1) s2 += __shfl_xor(s2, o);
+  if (threadIdx.x == 0) {
+    sig2_by_slot[r.slot[b]] = s2;
+    scale[b] = inv_alpha / sqrt(s2);
+  }
+}
+template <bool LAST>
 __global__ __launch_bounds__(256) void k_sigma_part(const double* __restrict__ w, DechirpRefs r, int64_t nb,
-                                                   double* __restrict__ part) {
-  __shared__ double red[256];
+                                                   double* part, unsigned int* done,
+                                                   double* __restrict__ sig2_by_slot, double* __restrict__ scale,
+                                                   double inv_alpha) {
+  __shared__ double red[4];
+  __shared__ bool last;
   const double2* hb = r.h[blockIdx.y];
   const int64_t chunk = (nb + kSigParts - 1) / kSigParts;
   const int64_t i0 = (int64_t)blockIdx.x * chunk, i1 = std::min<int64_t>(i0 + chunk, nb);
@@ -814,25 +831,29 @@ __global__ __launch_bounds__(256) void k_sigma_part(const double* __restrict__ w
     for (int k = 0; k < 8; ++k) acc += u[k] * (v[k].x * v[k].x + v[k].y * v[k].y);
   }
   for (; i < i1; i += 256) acc += w[i] * (hb[i].x * hb[i].x + hb[i].y * hb[i].y);
-  red[threadIdx.x] = acc;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
+  double* mine = part + blockIdx.y * kSigParts;
+  static_assert(kSigParts == 64, "one wave adds them (and the count wraps at a multiple)");
+  if (threadIdx.x == 0) {
+    mine[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+    if constexpr (LAST)
+      last = __hip_atomic_fetch_add(done + blockIdx.y, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) % kSigParts ==
+             kSigParts - 1;
   }
-  if (threadIdx.x == 0) part[blockIdx.y * kSigParts + blockIdx.x] = red[0];
+  if constexpr (LAST) {
+    __syncthreads();
+    if (!last || threadIdx.x >= kSigParts) return;
+    const double s2 = __hip_atomic_load(mine + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sigma_store(r, blockIdx.y, s2, sig2_by_slot, scale, inv_alpha);
+  }
 }
 __global__ __launch_bounds__(kSigParts) void k_sigma_final(DechirpRefs r, const double* __restrict__ part,
                                                          double* __restrict__ sig2_by_slot,
                                                          double* __restrict__ scale, double inv_alpha) {
-  const int b = blockIdx.x;
-  double s2 = part[b * kSigParts + threadIdx.x];
-#pragma unroll
-  for (int o = kSigParts / 2; o > 0; o >>= 1) s2 += __shfl_xor(s2, o);
-  if (threadIdx.x == 0) {
-    sig2_by_slot[r.slot[b]] = s2;
-    scale[b] = inv_alpha / sqrt(s2);
-  }
+  sigma_store(r, blockIdx.x, part[blockIdx.x * kSigParts + threadIdx.x], sig2_by_slot, scale, inv_alpha);
 }
 
 // F[i] = w_i conj(h_i) / (sigma * alpha), FP64 then rounded to FP32.
@@ -898,11 +919,18 @@ int launch_dechirp_refs(Plan& p, int n_refs, const int32_t* ref_ids, const doubl
       refs.h[b] = reinterpret_cast<const double2*>(h_refs[r0 + b]);
       refs.slot[b] = ref_ids[r0 + b];
     }
-    hipLaunchKernelGGL(k_sigma_part, dim3(kSigParts, (unsigned)nr), dim3(256), 0, p.stream, p.w, refs, p.nb,
-                       p.dref_part);
-    RFD_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_sigma_final, dim3((unsigned)nr), dim3(kSigParts), 0, p.stream, refs,
-                       (const double*)p.dref_part, p.dref_sig2, p.dref_scale, 1.0 / p.data_scale);
+    const double inv_alpha = 1.0 / p.data_scale;
+    const dim3 grid(kSigParts, (unsigned)nr);
+    if (nr <= 2) {
+      hipLaunchKernelGGL(k_sigma_part<true>, grid, dim3(256), 0, p.stream, p.w, refs, p.nb, p.dref_part, p.dref_done,
+                         p.dref_sig2, p.dref_scale, inv_alpha);
+    } else {
+      hipLaunchKernelGGL(k_sigma_part<false>, grid, dim3(256), 0, p.stream, p.w, refs, p.nb, p.dref_part, p.dref_done,
+                         p.dref_sig2, p.dref_scale, inv_alpha);
+      RFD_CHECK_LAUNCH();
+      hipLaunchKernelGGL(k_sigma_final, dim3((unsigned)nr), dim3(kSigParts), 0, p.stream, refs,
+                         (const double*)p.dref_part, p.dref_sig2, p.dref_scale, inv_alpha);
+    }
     RFD_CHECK_LAUNCH();
     LoadDechirpRefs ld{p.stilde64, p.w, refs, p.dref_scale, p.i_low, p.i_high};
     int rc;

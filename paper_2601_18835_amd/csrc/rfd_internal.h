@@ -58,6 +58,7 @@ struct Plan {
   double2* work64b = nullptr; size_t work64b_cap = 0;   // batched dechirp intermediates (grown)
   double* dref_sig2 = nullptr;    // sigma_ref^2 by reference slot [max_refs]
   double* dref_scale = nullptr;   // 1 / (sigma alpha) of a dechirp batch [kDechirpBatch]
+  unsigned int* dref_done = nullptr;   // finished workgroups of each norm [kDechirpBatch]
   double* dref_part = nullptr;    // partial sums of their norms [kDechirpBatch][kSigParts]
   double* dscratch = nullptr; // small FP64 scratch (sigma etc.)  [64]
   // reference series store, slot-major [max_refs][n]
