@@ -250,6 +250,86 @@ __device__ double tukey(int l, int T) {
   return 1.0;
 }
 
+// The same sweeps in launches, one per block row, for banks too small to fill the chip with a workgroup per
+// eight templates: a workgroup takes 64 rows of eight templates, forms the step's solution
+// (again in each, from the step's residual: 2 us of products) and takes its rows' share off their residual,
+// X_i -= M_ij X_j.  The step's own rows go to `x`, which no workgroup of the launch reads; src is
+// r, or the right-hand sides in the first step.  Bound by the latency of each launch, 5 to 7 us:
+// 256 templates at T = 1024 424 -> 290 us, one 400 -> 190.
+template <bool BACK>
+__global__ __launch_bounds__(256) void k_trsm_step(const double2* __restrict__ M, const double2* __restrict__ inv, int T,
+                                                 int j, const double2* src, int64_t src_stride, double2* r,
+                                                 double2* x, int64_t xstride, int64_t count) {
+  constexpr int TPW = 8, NC = 16, N = kTrsmBlock;
+  __shared__ double X[2][N * NC];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int kq = lane >> 4, col = lane & 15, mate = col ^ TPW;
+  const double sgn = col < TPW ? -1.0 : 1.0;
+  const int64_t t0 = (int64_t)blockIdx.x * TPW;
+  const int i = BACK ? j - (int)blockIdx.y : j + (int)blockIdx.y;
+  const int row = 16 * wave + col;                            // of the block: the one whose operands this lane holds
+  for (int e = threadIdx.x; e < N * TPW; e += 256) {
+    const int tt = e / N, k = e % N;
+    const double2 v = j * N + k < T && t0 + tt < count ? src[(t0 + tt) * src_stride + j * N + k] : make_double2(0.0, 0.0);
+    X[0][k * NC + tt] = v.x;
+    X[0][k * NC + TPW + tt] = v.y;
+  }
+  const double2* D = inv + (int64_t)j * N * N;
+  double2 dm[N / 4], m[N / 4];
+#pragma unroll
+  for (int u = 0; u < N / 4; ++u) dm[u] = BACK ? D[row * N + 4 * u + kq] : D[(4 * u + kq) * N + row];
+#pragma unroll
+  for (int u = 0; u < N / 4; ++u)
+    m[u] = M[(int64_t)min(j * N + 4 * u + kq, T - 1) * T + min(i * N + row, T - 1)];
+  // this lane's residuals: rows 16 wave + 4 v + kq of the block, real or imaginary part of template col % 8
+  const bool re = col < TPW;
+  const int64_t tmpl = t0 + col % TPW;
+  double have[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int g = i * N + 16 * wave + 4 * v + kq;
+    have[v] = 0.0;
+    if (g < T && tmpl < count && i != j) {
+      const double2 y = src[tmpl * src_stride + g];
+      have[v] = re ? y.x : y.y;
+    }
+  }
+  __syncthreads();
+  typedef f64x4 V;
+  V p = {0.0, 0.0, 0.0, 0.0}, q = p;
+#pragma unroll
+  for (int u = 0; u < N / 4; ++u) {
+    const double* y = X[0] + (4 * u + kq) * NC;
+    p = __builtin_amdgcn_mfma_f64_16x16x4f64(dm[u].x, y[col], p, 0, 0, 0);
+    q = __builtin_amdgcn_mfma_f64_16x16x4f64(BACK ? -dm[u].y : dm[u].y, sgn * y[mate], q, 0, 0, 0);
+  }
+  if (i == j) {
+    double* o = reinterpret_cast<double*>(x);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int g = i * N + 16 * wave + 4 * v + kq;
+      if (g < T && tmpl < count) o[2 * (tmpl * xstride + g) + (re ? 0 : 1)] = p[v] + q[v];
+    }
+    return;                                                   // (the whole workgroup)
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) X[1][(16 * wave + 4 * v + kq) * NC + col] = p[v] + q[v];
+  __syncthreads();
+  p = q = V{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int u = 0; u < N / 4; ++u) {
+    const double* y = X[1] + (4 * u + kq) * NC;
+    p = __builtin_amdgcn_mfma_f64_16x16x4f64(m[u].x, y[col], p, 0, 0, 0);
+    q = __builtin_amdgcn_mfma_f64_16x16x4f64(m[u].y, sgn * y[mate], q, 0, 0, 0);
+  }
+  double* o = reinterpret_cast<double*>(r);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int g = i * N + 16 * wave + 4 * v + kq;
+    if (g < T && tmpl < count) o[2 * (tmpl * (int64_t)T + g) + (re ? 0 : 1)] = have[v] - (p[v] + q[v]);
+  }
+}
+
 __global__ void k_window(const double2* __restrict__ b, int64_t bstride, int T, int64_t count,
                          double2* __restrict__ a, int64_t astride) {
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < count * T;
@@ -425,14 +505,37 @@ int taps_prepare_subbank(Plan& p, Taps& tp, int b, const double* h_ref, double e
 int taps_norm_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count);
 int taps_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count);
 
+// A launch per block row (k_trsm_step) or all rows in one (k_trsm), as long as the transform buffer holds the
+// residuals.  make_taps of a 2^15-sample segment, one launch and steps: T = 512 157 -> 130 us (1 template), 261 -> 243 (256),
+// 623 -> 714 (1000); T = 1024 454 -> 245 (1), 620 -> 490 (256); T = 2048 1593 -> 485 (1), 1845 -> 1172 (256); T = 384
+// 106 -> 100 (1), 198 -> 198 (256); T = 256 68 -> 73 (1), 150 -> 159 (256).
+static bool trsm_in_steps(const Taps& tp, int T, int64_t count) {
+  return T >= 512 && count <= 256 && tp.work64_cap >= (size_t)(2 * count * T);
+}
+
 int taps_solve_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count, int method) {
   SubBankTaps& s = tp.sb[b];
   const int T = s.T;
   double2* abase = tp.a64 + s.a_base + first * s.Tp;
   if (method == RFD_TAPS_LS) {
-    // eight templates per workgroup while their columns fit LDS (128 KiB at T = 1024), else four
-    const int Tn = (int)round_up(T, kTrsmBlock);
-    if (T <= 1024)
+    const int Tn = (int)round_up(T, kTrsmBlock), nb = Tn / kTrsmBlock;
+    if (trsm_in_steps(tp, T, count)) {
+      // forward residuals and solutions in the (now idle) transform buffer; the latter are the backward sweep's residuals
+      double2 *r = tp.work64, *y = tp.work64 + count * T;
+      const unsigned groups = (unsigned)((count + 7) / 8);
+      for (int j = 0; j < nb; ++j) {
+        hipLaunchKernelGGL(k_trsm_step<false>, dim3(groups, (unsigned)(nb - j)), dim3(256), 0, p.stream,
+                           (const double2*)s.L, (const double2*)s.Dinv, T, j, (const double2*)(j ? r : tp.bvec),
+                           (int64_t)T, r, y, (int64_t)T, count);
+        RFD_CHECK_LAUNCH();
+      }
+      for (int j = nb - 1; j >= 0; --j) {
+        hipLaunchKernelGGL(k_trsm_step<true>, dim3(groups, (unsigned)(j + 1)), dim3(256), 0, p.stream,
+                           (const double2*)s.U, (const double2*)s.Dinv, T, j, (const double2*)y, (int64_t)T, y, abase,
+                           (int64_t)s.Tp, count);
+        RFD_CHECK_LAUNCH();
+      }
+    } else if (T <= 1024)     // eight templates per workgroup while their columns fit LDS (128 KiB at T = 1024), else four
       hipLaunchKernelGGL(k_trsm<8>, dim3((unsigned)((count + 7) / 8)), dim3(256), (size_t)Tn * 16 * sizeof(double),
                          p.stream, s.L, s.U, s.Dinv, T, tp.bvec, (int64_t)T, abase, (int64_t)s.Tp, count);
     else
