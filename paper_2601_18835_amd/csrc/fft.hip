@@ -1101,6 +1101,8 @@ int launch_corr64(Plan& p, Taps& tp, int mode, const double* h_r, const double* 
 // ------------------------------------------------- lag of the correlation peak
 // Pass B's output b (natural order) and the largest |b|^2 of each workgroup's outputs with its
 // index, the lowest on exact ties.
+// (the correlations pass by the caches: little of them is read again, and they would evict the intermediates that
+// this pass and the next batch's read from the last-level cache: 8 templates at N = 2^20 57 + 53 us -> 50 + 49)
 struct StorePeak {
   double2* z;
   int64_t n;
@@ -1115,7 +1117,8 @@ struct StorePeak {
     }
   }
   __device__ __forceinline__ void operator()(int b, int64_t i, double2 v) {
-    z[(int64_t)b * n + i] = v;
+    typedef __attribute__((ext_vector_type(2))) double V;
+    __builtin_nontemporal_store(__builtin_bit_cast(V, v), reinterpret_cast<V*>(z + (int64_t)b * n + i));
     take(v.x * v.x + v.y * v.y, (int)i);
   }
   __device__ __forceinline__ void done(int b, int group, int groups) {
