@@ -18,10 +18,11 @@ struct ColFft {
   static constexpr int NT = C * J;              // threads of the workgroup
   static constexpr int R3 = L / 256;            // last radix
   // column stride in LDS: lanes go over columns first, then over neighbouring elements; the group
-  // of lanes that one LDS pass serves (16 of 16 bytes, 32 of 8) then meets each bank once when the
-  // stride is G / C modulo G
-  static constexpr int G = sizeof(V) == 16 ? 16 : 32;
-  static constexpr int LP = L + L / 16 + ((G / C - L - L / 16) % G + G) % G;
+  // of lanes that one LDS pass serves (8 of 16 bytes, 16 of 8: 128 bytes) then meets each bank once when the
+  // stride is G / C modulo G.  (Groups of 256 bytes had half of the FP32 passes' LDS cycles in conflicts: 32
+  // stretches of 3072 lags 124 -> 116 us without.)
+  static constexpr int G = sizeof(V) == 16 ? 8 : 16;
+  static constexpr int LP = L + L / 16 + (((C < G ? G / C : 1) - L - L / 16) % G + G) % G;
   static constexpr int LDS = C * LP;            // values
   static constexpr int TWB = 16 * kTwbStride;   // values of the second stage's twiddle table
   // the third stage's twiddles: 8 per thread in registers, or in FP64, where they would take 32
@@ -30,7 +31,7 @@ struct ColFft {
   static constexpr bool TW3_LDS = true;
   static constexpr int TW3 = TW3_LDS ? 256 * PER : 0;
   static constexpr size_t lds_bytes = (size_t)(LDS + TWB + TW3) * sizeof(V);
-  static_assert(C <= G && G % C == 0, "columns of a workgroup");
+  static_assert(G % C == 0 || C % G == 0, "columns of a workgroup");
 };
 
 // Twiddles of a thread.  All threads load them; a barrier must follow.  ct: (c, tau) of

@@ -685,7 +685,7 @@ __global__ __launch_bounds__(kNT) void k_corr_part(LD ld, V* __restrict__ part, 
 // The same shares with the transforms of col_fft.h: the workgroup's columns pass through their
 // stages in registers (as k_cols, batch entries [y JT, (y + 1) JT) in turn) and return to LDS in
 // natural order, where each lag finds its row.  (16 FP64 correlations at N = 2^20, T = 1024: 208 -> 73 us
-// against k_corr_part; 32 FP32 stretches of 3072 lags: 252 -> 122 us.)
+// against k_corr_part; 32 FP32 stretches of 3072 lags: 252 -> 116 us.)
 // FP32 columns of 512 and 1024 points do without the fetch ahead: two workgroups then fit a CU
 // (128 registers) and the one's loads pass under the other's lag sums (148 -> 122 us for those
 // stretches).  The other lengths would spill.
