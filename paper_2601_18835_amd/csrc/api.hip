@@ -886,12 +886,16 @@ int rfd_make_taps(rfd_plan* plan, rfd_taps* taps, int32_t subbank, const double*
     return fail(RFD_E_INVALID, "ridge_eps must be finite and >= 0");
   if (count == 0) return RFD_OK;
   const int T = s.T;
-  // FFT scratch for a chunk of templates (<= 256 MiB)
-  int64_t chunk = std::max<int64_t>(1, ((int64_t)256 << 20) / (p.n * (int64_t)sizeof(double2)));
-  chunk = std::min<int64_t>(chunk, 64);
-  if (centre) chunk = std::max<int64_t>(1, chunk / 2);     // as much again for the full correlations
+  // FFT scratch for a chunk of templates: up to 256 MiB of transforms (and as much again for the full
+  // correlations of centring), or 128 MiB of lag shares, which the last-level cache keeps until they are
+  // added.  make_taps, 500 templates, T = 256, N = 2^19: 16 chunks of 32, as many as transforms
+  // would allow, 1056 us; shares of 64 MiB 893, 128 MiB 863, 256 MiB 859; 250 at T = 1024, 2^20 1562, 1568, 1520, 1459.
+  const int64_t per = centre ? p.n : corr64_work(p, T);
+  int64_t chunk = std::max<int64_t>(1, ((int64_t)(per < p.n ? 128 : 256) << 20) / (per * (int64_t)sizeof(double2)));
+  chunk = std::min<int64_t>(chunk, per < p.n ? 4096 : 64);
+  if (centre) chunk = std::max<int64_t>(1, chunk / 2);
   chunk = std::min<int64_t>(chunk, count);
-  size_t need_w = (size_t)std::max<int64_t>(chunk, 1) * p.n;
+  const size_t need_w = (size_t)std::max<int64_t>(chunk * per, p.n);
   if (t.work64_cap < need_w) {
     RFD_HIP(hipStreamSynchronize(p.stream));
     dfree(t.work64);

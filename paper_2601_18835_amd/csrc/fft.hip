@@ -1020,11 +1020,19 @@ static int corr_columns(int n2) {
   }
 }
 
+// work-buffer values of one batch entry: the shares of its T lags, or its whole column transform
+static int corr_groups(const Plan& p, bool fp32) {
+  return p.n1 / (fp32 ? corr_columns<float2>(p.n2) : corr_columns<double2>(p.n2));
+}
+int64_t corr64_work(const Plan& p, int T) { return std::min<int64_t>((int64_t)corr_groups(p, false) * T, p.n); }
+
 int launch_corr64(Plan& p, Taps& tp, int mode, const double* h_r, const double* h_t, int64_t batch, int T,
                   int k0, double2* out, int64_t out_stride, int64_t lo, int64_t hi, const int32_t* k0s, bool fp32,
                   const double* bscale) {
-  size_t need = (size_t)batch * p.n;
-  if (tp.work64_cap < need) return fail(RFD_E_INVALID, "corr64: work buffer too small");
+  const int groups = corr_groups(p, fp32);
+  const bool shares = (int64_t)groups * T <= p.n;
+  if (tp.work64_cap < (size_t)(batch * (shares ? (int64_t)groups * T : p.n)))
+    return fail(RFD_E_INVALID, "corr64: work buffer too small");
   if (fp32 && mode == 0 && !bscale) return fail(RFD_E_INVALID, "corr64: FP32 integrands need their normalisation");
   // (a single-spectrum mode reads its spectrum as the second one too: the
   // loads need no branch on the mode)
@@ -1032,8 +1040,7 @@ int launch_corr64(Plan& p, Taps& tp, int mode, const double* h_r, const double* 
                 lo >= 0 ? lo : p.i_low, hi >= 0 ? hi : p.i_high, mode, mode == 0 ? bscale : nullptr};
   const double scale = mode == 2 ? 1.0 / (double)p.n : 1.0;
   // fused form: per-workgroup lag shares in the work buffer, then their sums
-  const int groups = p.n1 / (fp32 ? corr_columns<float2>(p.n2) : corr_columns<double2>(p.n2));
-  if ((int64_t)groups * T <= p.n) {
+  if (shares) {
     dim3 blk(kNT);
     const int jt = entries_per_wg(groups, (int)batch, p.n_cu, 2);
     const dim3 grid_r((unsigned)groups, (unsigned)((batch + jt - 1) / jt));

@@ -222,6 +222,7 @@ int launch_fc_cols_lds(Plan& p, const float2* filt, int nb, float2* Y, int n1, i
 // k0s (device, per batch entry, may be NULL) replaces k0 template by template.
 // fp32: FP32 column transforms of the integrand rounded once (shares and
 // sums in FP64); applies to the fused form, the row form stays FP64.
+int64_t corr64_work(const Plan& p, int T);   // FP64 work values per batch entry of launch_corr64
 int launch_corr64(Plan& p, Taps& tp, int mode, const double* h_r, const double* h_t, int64_t batch,
                   int T, int k0, double2* out, int64_t out_stride, int64_t lo = -1, int64_t hi = -1,
                   const int32_t* k0s = nullptr, bool fp32 = false, const double* bscale = nullptr);
