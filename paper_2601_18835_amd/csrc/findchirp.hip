@@ -76,6 +76,9 @@ struct FcCols {
   static constexpr int M2 = N2 >= 16 ? N2 / 16 : 1;
   static constexpr int CW = 256 / M2;
   static constexpr int V = N2 >= 16 ? 16 : N2;   // values per thread
+  // inputs among them: rows N2 / 2 and up are bins from N / 2 on, above every band.  Left out where a thread has
+  // sixteen rows (250 templates at N = 2^20: 65.6 -> 63.8 us per launch)
+  static constexpr int IN = M2 > 1 ? 8 : V;
 };
 
 struct FcColArgs {
@@ -97,16 +100,16 @@ struct FcColArgs {
 template <int N1, int N2>
 __global__ __launch_bounds__(256) void k_fc_cols(FcColArgs a) {
   using G = FcCols<N2>;
-  constexpr int M2 = G::M2, CW = G::CW, V = G::V;
+  constexpr int M2 = G::M2, CW = G::CW, V = G::V, IN = G::IN;
   const int c = threadIdx.x % CW, m = threadIdx.x / CW;
   const uint32_t i1 = blockIdx.x * CW + c;
   const int64_t b0 = (int64_t)blockIdx.y * a.JT;
   const int64_t b1 = std::min<int64_t>(b0 + a.JT, a.count);
-  // thread (c, m) holds x[m + M2 r] = Q[i1 + N1 (m + M2 r)], r < V
-  float2 sv[V];
-  int32_t off[V];                      // filter offset i - i_low, -1 outside the band
+  // thread (c, m) holds x[m + M2 r] = Q[i1 + N1 (m + M2 r)], r < IN
+  float2 sv[IN];
+  int32_t off[IN];                     // filter offset i - i_low, -1 outside the band
 #pragma unroll
-  for (int r = 0; r < V; ++r) {
+  for (int r = 0; r < IN; ++r) {
     const int64_t i = (int64_t)i1 + (int64_t)N1 * (m + M2 * r);
     const bool in = i >= a.i_low && i <= a.i_high;
     sv[r] = in ? a.s[i] : make_float2(0.f, 0.f);
@@ -153,21 +156,21 @@ __global__ __launch_bounds__(256) void k_fc_cols(FcColArgs a) {
       ts[s] = pw ? a.tw[pw * (4096 / N2)] : make_float2(1.f, 0.f);
     }
   }
-  float2 fv[V];
+  float2 fv[IN];
   if (b0 < b1) {
     const float2* fb = a.filt + b0 * a.n_band;
 #pragma unroll
-    for (int r = 0; r < V; ++r) fv[r] = off[r] >= 0 ? load_once(fb + off[r]) : make_float2(0.f, 0.f);
+    for (int r = 0; r < IN; ++r) fv[r] = off[r] >= 0 ? load_once(fb + off[r]) : make_float2(0.f, 0.f);
   }
   [[maybe_unused]] __shared__ float2 lds[M2 > 1 ? 16 * M2 * CW : 1];
   for (int64_t b = b0; b < b1; ++b) {
     float2 v[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] = r < V ? cmul(sv[r], fv[r]) : make_float2(0.f, 0.f);
+    for (int r = 0; r < 16; ++r) v[r] = r < IN ? cmul(sv[r], fv[r]) : make_float2(0.f, 0.f);
     if (b + 1 < b1) {
       const float2* fb = a.filt + (b + 1) * a.n_band;
 #pragma unroll
-      for (int r = 0; r < V; ++r) fv[r] = off[r] >= 0 ? load_once(fb + off[r]) : make_float2(0.f, 0.f);
+      for (int r = 0; r < IN; ++r) fv[r] = off[r] >= 0 ? load_once(fb + off[r]) : make_float2(0.f, 0.f);
     }
     float2* Yb = a.Y + b * N2 * N1;
     if constexpr (M2 == 1) {
@@ -176,7 +179,7 @@ __global__ __launch_bounds__(256) void k_fc_cols(FcColArgs a) {
       for (int s = 0; s < V; ++s) Yb[(int64_t)small_freq<V>(s) * N1 + i1] = cmul(v[s], ti[s]);
     } else {
       // radix 16 over r, twiddle, exchange, radix M2 over m
-      dft16<1>(v);
+      dft16_half<1>(v);
 #pragma unroll
       for (int s = 0; s < 16; ++s) lds[(dft16_freq(s) * M2 + m) * CW + c] = cmul(v[s], ts[s]);
       __syncthreads();
