@@ -32,8 +32,6 @@
 
 namespace rfd {
 
-constexpr int kFcN1 = 4096;    // row length when N > 4096
-
 // A filter value: read once per call, so marked to pass the caches by and leave them to the
 // intermediate (250 templates at N = 2^20: 1407 -> 1328 us).
 __device__ __forceinline__ float2 load_once(const float2* p) {

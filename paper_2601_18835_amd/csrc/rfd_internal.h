@@ -32,6 +32,7 @@ constexpr int kDechirpBatch = 32;               // references per batched dechir
 constexpr int kMaxRefSlots = 4096;              // reference-series slots of a plan, at most
 constexpr int kSigParts = 64;                   // partial sums per reference norm
 constexpr int kZParts = 32;                     // partial sums per FINDCHIRP trigger z
+constexpr int kFcN1 = 4096;                     // FINDCHIRP's row length when N > 4096
 constexpr int kFcZList = 4096;                  // firing slots listed with their z by FINDCHIRP
 constexpr int kMaxBands = 64;                   // bands of the chi^2 test, at most
 

@@ -308,10 +308,10 @@ struct FcZ {
 };
 __global__ __launch_bounds__(256) void k_fc_z_rows(const unsigned long long* __restrict__ slots, int64_t tmpl0, int count,
                                                  float thr2, int64_t nwin, int64_t W, const float2* __restrict__ Y,
-                                                 int64_t N1, int64_t N2, const double2* __restrict__ tab,
+                                                 int64_t N2, const double2* __restrict__ tab,
                                                  FcZ* __restrict__ list, unsigned long long* __restrict__ listed) {
-  __shared__ unsigned long long base;
   __shared__ double red[2][4];
+  __shared__ bool full;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   // a signal fires the same windows of every template: neighbouring workgroups, which run on
   // different compute units, take the same windows of different templates
@@ -320,21 +320,27 @@ __global__ __launch_bounds__(256) void k_fc_z_rows(const unsigned long long* __r
   const unsigned long long k = lane < kFcZSlots && q0 + lane < nwin ? slots[lane] : 0ull;   // (in every wave)
   unsigned long long mask = __ballot(slot_fires(k, thr2));
   if (mask == 0) return;
-  if (threadIdx.x == 0) base = atomicAdd(listed, (unsigned long long)__popcll(mask));
+  if (threadIdx.x == 0)                    // (no use for more z than the list takes)
+    full = __hip_atomic_load(listed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > (unsigned long long)kFcZList;
   __syncthreads();
-  for (unsigned long long e = base; mask != 0 && e < (unsigned long long)kFcZList; ++e, mask &= mask - 1) {
+  for (; mask != 0 && !full; mask &= mask - 1) {
     const int at = __ffsll(mask) - 1;
     const uint32_t off = 0xFFFFFFFFu - (uint32_t)__shfl((int)(uint32_t)(k & 0xFFFFFFFFull), at);
     const int64_t q = q0 + at, m = q * W + (int64_t)off;
-    const float2* __restrict__ row = Y + (b * N2 + (m & (N2 - 1))) * N1;
-    const uint32_t turn = (uint32_t)(m / N2);                     // of N1 (powers of two, at most 4096)
+    const float2* __restrict__ row = Y + (b * N2 + (m & (N2 - 1))) * kFcN1 + threadIdx.x;
+    const uint32_t turn = (uint32_t)(m / N2);                     // of N1: at most 4096
+    // a thread's values are 256 apart: their factors turn by a sixteenth root of unity
+    float2 y[kFcN1 / 256];
+#pragma unroll
+    for (int r = 0; r < kFcN1 / 256; ++r) y[r] = row[256 * r];
+    double2 w = tab[threadIdx.x * turn & (kFcN1 - 1)];
+    const double2 step = tab[256 * turn & (kFcN1 - 1)];
     double re = 0.0, im = 0.0;
-#pragma unroll 16
-    for (uint32_t i = threadIdx.x; i < (uint32_t)N1; i += 256) {
-      const float2 y = row[i];
-      const double2 w = tab[i * turn & (uint32_t)(N1 - 1)];
-      re += (double)y.x * w.x - (double)y.y * w.y;
-      im += (double)y.x * w.y + (double)y.y * w.x;
+#pragma unroll
+    for (int r = 0; r < kFcN1 / 256; ++r) {
+      re += (double)y[r].x * w.x - (double)y[r].y * w.y;
+      im += (double)y[r].x * w.y + (double)y[r].y * w.x;
+      w = cmul(w, step);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -346,9 +352,13 @@ __global__ __launch_bounds__(256) void k_fc_z_rows(const unsigned long long* __r
       red[1][wv] = im;
     }
     __syncthreads();
-    if (threadIdx.x == 0)
-      list[e] = FcZ{(long long)((tmpl0 + b) * nwin + q), make_float2((float)((red[0][0] + red[0][1]) + (red[0][2] + red[0][3])),
-                                                               (float)((red[1][0] + red[1][1]) + (red[1][2] + red[1][3])))};
+    if (threadIdx.x == 0) {
+      const unsigned long long e = atomicAdd(listed, 1ull);
+      full = e >= (unsigned long long)kFcZList;
+      if (e < (unsigned long long)kFcZList)
+        list[e] = FcZ{(long long)((tmpl0 + b) * nwin + q), make_float2((float)((red[0][0] + red[0][1]) + (red[0][2] + red[0][3])),
+                                                                   (float)((red[1][0] + red[1][1]) + (red[1][2] + red[1][3])))};
+    }
     __syncthreads();
   }
 }
@@ -555,8 +565,8 @@ int launch_fir_z(Plan& p, const Taps& tp, rfd_trigger* out, int64_t capacity) {
 }
 
 // The lists pay where a call's filters are much to read again and its slots few against its
-// intermediates.  250 templates of 2^20 samples, one trigger each and windows of 2048: 1260 -> 1103 us
-// (no trigger at all: 1020 -> 1034); windows of 64: 1267 -> 1142 (1033 -> 1092), of 16: 1376 -> 1332 (1091 -> 1293).
+// intermediates.  250 templates of 2^20 samples, one trigger each and windows of 2048: 1260 -> 1103 us, 1072 with
+// the sums' loads all in flight (no trigger at all: 1020 -> 1034); before that windows of 64: 1267 -> 1142 (1033 -> 1092), of 16: 1376 -> 1332 (1091 -> 1293).
 // 64 templates of 2^20: 384 -> 339; 250 of 2^18: 415 -> 379; 64 of 2^18: 147 -> 143 (119 -> 123); 8 of 2^20: 107 -> 110.
 static bool fc_z_lists(const Plan& p, int64_t n_templates, int64_t W) {
   return W >= 256 && n_templates * p.n >= (int64_t)1 << 25 && p.n > 4096;
@@ -566,7 +576,7 @@ int launch_findchirp_z_batch(Plan& p, int64_t n_templates, int64_t tmpl0, int co
                              int64_t nwin, float thr2) {
   if (!fc_z_lists(p, n_templates, W)) return RFD_OK;
   hipLaunchKernelGGL(k_fc_z_rows, dim3((unsigned)((nwin + kFcZSlots - 1) / kFcZSlots * count)), dim3(256), 0, p.stream,
-                     (const unsigned long long*)p.slots, tmpl0, count, thr2, nwin, W, (const float2*)p.fc_work, N1, N2,
+                     (const unsigned long long*)p.slots, tmpl0, count, thr2, nwin, W, (const float2*)p.fc_work, N2,
                      (const double2*)p.ols_tw64, (FcZ*)p.fcz_list, p.fcz_count);
   RFD_CHECK_LAUNCH();
   return RFD_OK;
