@@ -602,6 +602,8 @@ static int launch_ols_multi(Plan& p, const Taps& t, const int* sbs, int nsb, int
   return stage_end(p);
 }
 
+constexpr int64_t kOlsGroupBytes = (int64_t)128 << 20;
+
 int launch_ols(Plan& p, const Taps& t, int64_t W, int64_t nwin, float threshold, int64_t n_lo, int64_t n_hi,
                float2* x_scratch) {
   if (n_hi < 0) n_hi = p.n;
@@ -612,24 +614,28 @@ int launch_ols(Plan& p, const Taps& t, int64_t W, int64_t nwin, float threshold,
     if (!s.ols_valid || !(x_scratch ? x_scratch : s.ols_x)) return fail(RFD_E_STATE, "overlap-save spectra not prepared");
     ++active;
   }
-  // A short output range leaves each sub-bank's launch a small part of the
-  // chip: the sub-banks of one block size then share launches (their window
-  // keys are disjoint slots, their block spectra separate buffers).  Whole
-  // segments keep one launch per sub-bank, each filling the chip, so that a
-  // sub-bank's block spectra are used while still in the last-level cache.  A
-  // shared block-spectrum scratch keeps one launch per sub-bank as well.
-  if (!x_scratch && active > 1 && (n_hi - n_lo) * 8 <= p.n) {
-    std::vector<char> done(t.sb.size(), 0);
+  // Sub-banks of one block size share launches (their window keys are disjoint slots, their block spectra separate
+  // buffers): a launch each leaves the chip part empty at its end, and from its start where the sub-bank or the
+  // output range is small.  A launch takes as many as have kOlsGroupBytes of block spectra, which
+  // the last-level cache then holds until they are used.  16 uneven sub-banks of 250, N = 2^19: 2684 -> 2465 us; 8 of 512,
+  // T = 1024, N = 2^20: 5588 -> 5409 (5461 with 32 MiB, 5522 with 256); 16 of 300, T <= 100, N = 2^15: 404 -> 202; 2 of
+  // 2000, T = 512, N = 2^20: 4590 -> 4640.  A shared block-spectrum scratch keeps one launch per sub-bank.
+  std::vector<char> done(t.sb.size(), 0);
+  if (!x_scratch && active > 1) {
     for (size_t b0 = 0; b0 < t.sb.size(); ++b0) {
       const SubBankTaps& s0 = t.sb[b0];
       if (s0.count == 0 || done[b0]) continue;
       int sbs[kOlsMulti], nsb = 0;
+      int64_t bytes = 0;
       for (size_t b = b0; b < t.sb.size() && nsb < kOlsMulti; ++b) {
         const SubBankTaps& s = t.sb[b];
         if (s.count == 0 || done[b] || s.ols_K != s0.ols_K || s.ols_nf != s0.ols_nf) continue;
-        done[b] = 1;
+        bytes += (n_hi - n_lo + s.ols_L - 1) / s.ols_L * s.ols_K * (int64_t)sizeof(float2);
+        if (nsb > 0 && bytes > kOlsGroupBytes) break;
         sbs[nsb++] = (int)b;
       }
+      if (nsb == 1) continue;            // alone: below
+      for (int i = 0; i < nsb; ++i) done[sbs[i]] = 1;
       int rc;
       switch (s0.ols_K * 16 + s0.ols_nf) {
 #define OLS_CASE(KK, NN) \
@@ -640,12 +646,12 @@ int launch_ols(Plan& p, const Taps& t, int64_t W, int64_t nwin, float threshold,
 #undef OLS_CASE
         default: rc = fail(RFD_E_INVALID, "overlap-save block size must be 1024, 2048 or 4096");
       }
-      if (rc) return rc;     // sub-banks past kOlsMulti of this block size start the next chunk
+      if (rc) return rc;     // sub-banks past the group start the next one
     }
-    return RFD_OK;
   }
-  for (const SubBankTaps& s : t.sb) {
-    if (s.count == 0) continue;
+  for (size_t b = 0; b < t.sb.size(); ++b) {
+    const SubBankTaps& s = t.sb[b];
+    if (s.count == 0 || done[b]) continue;
     float2* X = x_scratch ? x_scratch : s.ols_x;
     int rc;
     switch (s.ols_K * 16 + s.ols_nf) {
