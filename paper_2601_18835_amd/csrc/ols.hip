@@ -289,8 +289,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 }
 
 // ------------------------------------------------- several sub-banks at once
-// A short output range gives each sub-bank a few blocks only: one launch then
-// covers up to kOlsMulti sub-banks of one block size, their workgroups laid
+// One launch covers up to kOlsMulti sub-banks of one block size, their workgroups laid
 // end to end (sub-bank s owns workgroups [wg0, wg0 + gx gy) of k_ols_multi and
 // [wgx0, wgx0 + gx) of k_ols_x_multi).  The descriptors travel by value in the
 // kernel arguments (nothing to upload, and a captured graph keeps them).
