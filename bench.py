@@ -299,14 +299,14 @@ def main():
     def ols_block(T):
         return rfd.rfd_ols_shape(s.plan, T)[0]
 
-    def ols_flops_per_launch():
-        """(5 log2 K + 6) K per (template, block) over one sub-bank's launch, averaged over the launches."""
-        tot = []
+    def ols_flops():
+        """(5 log2 K + 6) K per (template, block) over every sub-bank, and the block sizes."""
+        tot = 0.0
         for sb in bank.subbanks:
             K = ols_block(sb.taps)
             nB = -(-w.n // (K - sb.taps + 1))
-            tot.append(sb.size * nB * K * (5.0 * np.log2(K) + 6.0))
-        return float(np.mean(tot)), float(np.sum(tot)), sorted(set(ols_block(sb.taps) for sb in bank.subbanks))
+            tot += sb.size * nB * K * (5.0 * np.log2(K) + 6.0)
+        return tot, sorted(set(ols_block(sb.taps) for sb in bank.subbanks))
 
     selection = None
     if args.fir_form == "auto":
@@ -350,7 +350,8 @@ def main():
     if prec == "ols32":
         # the overlap-save algorithm's own work: per (template, block) a K-point
         # product and inverse FFT, (5 log2 K + 6) K flop
-        fl, fl_step, ks = ols_flops_per_launch()
+        fl_step, ks = ols_flops()
+        fl = fl_step / (n_launch / ne)         # (sub-banks of one block size share launches)
         achieved = fl / (kernel_ms * 1e-3) / 1e12
         roofline = {"bound": "alu", "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
                     "frac": round(achieved / peak, 4), "traffic": read_traffic(COUNTERS.get((w.name, prec))),
