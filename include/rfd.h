@@ -249,6 +249,10 @@ int rfd_taps_create(rfd_plan* plan, int32_t n_subbanks, const int64_t* offsets, 
  *              through the Hermitian Toeplitz normal equations by Cholesky
  *              (factor from the Toeplitz Schur recursion); RFD_E_INVALID when
  *              M + lam I is not positive definite (a reference zero in band).
+ *              The sub-bank keeps the factor: a later call of the same ridge
+ *              compares the autocorrelation of its reference under the plan's
+ *              PSD with the factor's, waits for the answer and factors again
+ *              where they differ (not on a stream under capture).
  *              RFD_TAPS_WINDOW: a_k = tukey_k (1/N) sum_i R_i exp(+2 pi i i
  *              (k0+k)/N) (ridge_eps ignored).
  *              Either route may carry RFD_TAPS_CENTRE (per-template lag

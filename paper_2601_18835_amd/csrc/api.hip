@@ -769,6 +769,7 @@ static void taps_free(Taps& t) {
     dfree(s.U);
     dfree(s.Dinv);
     dfree(s.g);
+    dfree(s.gf);
     dfree(s.ols_x);
     dfree(s.ols_g);
     dfree(s.band_f);
@@ -778,6 +779,10 @@ static void taps_free(Taps& t) {
   dfree(t.d_p16); dfree(t.d_p32); dfree(t.d_count);
   dfree(t.d_it_off); dfree(t.d_it_sb); dfree(t.d_it_S); dfree(t.d_it_nsg);
   dfree(t.d_shift); dfree(t.peak_z); dfree(t.k0buf); dfree(t.peak_part); dfree(t.peak_idx);
+  if (t.factor_differs) (void)hipHostFree(t.factor_differs);
+  if (t.factor_event) (void)hipEventDestroy(t.factor_event);
+  t.factor_differs = nullptr;
+  t.factor_event = nullptr;
 }
 
 int rfd_taps_create(rfd_plan* plan, int32_t n_subbanks, const int64_t* offsets, const int32_t* ref_id,
@@ -848,6 +853,15 @@ int rfd_taps_create(rfd_plan* plan, int32_t n_subbanks, const int64_t* offsets, 
   TRY(dalloc(&t.d_count, (size_t)n_subbanks));
   for (auto& s : t.sb) TRY(dalloc(&s.g, (size_t)s.T));
   TRY(dalloc(&t.d_shift, (size_t)std::max<int64_t>(t.n_templates, 1)));
+  if (hipHostMalloc((void**)&t.factor_differs, sizeof(int), hipHostMallocDefault) != hipSuccess) {
+    t.factor_differs = nullptr;
+    (void)hipGetLastError();
+    TRY(fail(RFD_E_NOMEM, "host allocation failed"));
+  }
+  if (hipEventCreateWithFlags(&t.factor_event, hipEventDisableTiming) != hipSuccess) {
+    t.factor_event = nullptr;
+    TRY(fail(RFD_E_DEVICE, "taps: hipEventCreate failed"));
+  }
 #undef TRY
   if (hipMemsetAsync(t.d_shift, 0, std::max<int64_t>(t.n_templates, 1) * sizeof(int32_t), p.stream) != hipSuccess ||
       hipMemsetAsync(t.pbf, 0, p16 * sizeof(uint4), p.stream) != hipSuccess ||
@@ -866,6 +880,12 @@ int rfd_taps_create(rfd_plan* plan, int32_t n_subbanks, const int64_t* offsets, 
   }
   *out = h;
   return RFD_OK;
+}
+
+static bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &status) != hipSuccess) (void)hipGetLastError();
+  return status != hipStreamCaptureStatusNone;
 }
 
 int rfd_make_taps(rfd_plan* plan, rfd_taps* taps, int32_t subbank, const double* h_ref, const double* h_tmpl,
@@ -913,23 +933,28 @@ int rfd_make_taps(rfd_plan* plan, rfd_taps* taps, int32_t subbank, const double*
     if (rc) return rc;
     t.bvec_cap = need_b;
   }
-  // reference autocorrelation g (always) and the Cholesky factor (LS)
-  const double eps = method == RFD_TAPS_LS ? ridge_eps : -1.0;
-  if (method == RFD_TAPS_LS && (!s.L || s.eps != ridge_eps)) {
-    int rc = RFD_OK;      // (each on its own: an earlier call may have stopped between them)
+  // the autocorrelation g of this call's reference under the plan's weights and, for least squares, the Cholesky
+  // factor that belongs to it: made here for a new ridge; one of the same ridge is compared with g on the device, and
+  // the answer waited for once the correlations, which need no factor, are queued
+  int rc = launch_corr64(p, t, 1, h_ref, nullptr, 1, T, 0, s.g, T);
+  if (rc) return rc;
+  bool compare = false;
+  if (method == RFD_TAPS_LS) {
+    // (each on its own: an earlier call may have stopped between them)
     if (!s.L) rc = dalloc(&s.L, (size_t)T * T);
     if (!rc && !s.U) rc = dalloc(&s.U, (size_t)T * T);
     if (!rc && !s.Dinv) rc = dalloc(&s.Dinv, (size_t)round_up(T, 64) * 64);
+    if (!rc && !s.gf) rc = dalloc(&s.gf, (size_t)T);
     if (rc) return rc;
-    rc = taps_prepare_subbank(p, t, subbank, h_ref, eps);
-    if (rc) return rc;
-  } else {
-    // g is cheap; refresh it so sigma_fit always uses this reference
-    int rc = launch_corr64(p, t, 1, h_ref, nullptr, 1, T, 0, s.g, T);
+    if (s.eps != ridge_eps) {
+      rc = taps_factor(p, t, subbank, ridge_eps);
+    } else if (!capturing(p.stream)) {      // (a stream being captured cannot be waited for: it keeps the factor)
+      compare = true;
+      rc = taps_factor_compare(p, t, subbank);
+    }
     if (rc) return rc;
   }
   // per-template lag windows: the peak of each template's full correlation
-  int32_t* dsh = t.d_shift + s.first + first;
   if (centre) {
     const size_t need_p = (size_t)chunk * p.n;
     if (t.peak_cap < need_p) {
@@ -959,15 +984,9 @@ int rfd_make_taps(rfd_plan* plan, rfd_taps* taps, int32_t subbank, const double*
       if (rc) return rc;
       t.k0buf_cap = (size_t)count;
     }
-  } else {
-    bool any = false;
-    for (int64_t i = first; i < first + count && !any; ++i) any = s.centred_mask[i] != 0;
-    if (any) RFD_HIP(hipMemsetAsync(dsh, 0, count * sizeof(int32_t), p.stream));
   }
-  {
-    int rc = stage_begin(p, kStTaps);
-    if (rc) return rc;
-  }
+  rc = stage_begin(p, kStTaps);
+  if (rc) return rc;
   // correlation FFTs in chunks bounded by the FP64 scratch, then one solve
   // launch over every template of the call
   for (int64_t c0 = 0; c0 < count; c0 += chunk) {
@@ -975,24 +994,35 @@ int rfd_make_taps(rfd_plan* plan, rfd_taps* taps, int32_t subbank, const double*
     const int32_t* k0s = nullptr;
     if (centre) {
       const bool ls = method == RFD_TAPS_LS;
-      int rc = launch_corr_peak(p, t, h_ref, h_tmpl + 2 * c0 * p.nb, cn, T, s.k0, t.peak_z, t.k0buf + c0, dsh + c0,
-                                ls ? t.bvec + c0 * T : nullptr);
+      rc = launch_corr_peak(p, t, h_ref, h_tmpl + 2 * c0 * p.nb, cn, T, t.peak_z, t.k0buf + c0,
+                            ls ? t.bvec + c0 * T : nullptr);
       if (rc) return rc;
       if (ls) continue;
       k0s = t.k0buf + c0;
     }
-    int rc = launch_corr64(p, t, method == RFD_TAPS_LS ? 0 : 2, h_ref, h_tmpl + 2 * c0 * p.nb, cn, T, s.k0,
-                           t.bvec + c0 * T, T, -1, -1, k0s);
+    rc = launch_corr64(p, t, method == RFD_TAPS_LS ? 0 : 2, h_ref, h_tmpl + 2 * c0 * p.nb, cn, T, s.k0,
+                       t.bvec + c0 * T, T, -1, -1, k0s);
     if (rc) return rc;
   }
-  {
-    int rc = taps_solve_and_pack(p, t, subbank, first, count, method);
+  if (compare) {
+    bool current = false;
+    rc = taps_factor_current(t, &current);
+    if (!rc && !current) rc = taps_factor(p, t, subbank, ridge_eps);
     if (rc) return rc;
   }
-  {
-    int rc = stage_end(p);
+  // from here on the call replaces the templates' taps and their lag windows
+  int32_t* dsh = t.d_shift + s.first + first;
+  if (centre) {
+    rc = launch_lag_shifts(p, t.k0buf, s.k0, count, dsh);
     if (rc) return rc;
+  } else {
+    bool any = false;
+    for (int64_t i = first; i < first + count && !any; ++i) any = s.centred_mask[i] != 0;
+    if (any) RFD_HIP(hipMemsetAsync(dsh, 0, count * sizeof(int32_t), p.stream));
   }
+  rc = taps_solve_and_pack(p, t, subbank, first, count, method);
+  if (!rc) rc = stage_end(p);
+  if (rc) return rc;
   for (int64_t i = first; i < first + count; ++i) {
     if (!s.made_mask[i]) {
       s.made_mask[i] = 1;

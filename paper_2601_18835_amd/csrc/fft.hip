@@ -1152,24 +1152,20 @@ struct StorePeak {
 
 // Per template: the lag of the largest |b[l]|^2 over all N lags (lowest
 // index 0..N-1 on exact ties) from its workgroups' maxima, mapped into
-// (-N/2, N/2]; the lag window k0_j = peak - floor(T/2) and its offset from the
-// sub-bank's k0; and (out not NULL) the T lags k0_j + l of its full correlation. 256 lags per workgroup, whose
+// (-N/2, N/2]; the lag window k0_j = peak - floor(T/2); and (out not NULL) the
+// T lags k0_j + l of its full correlation. 256 lags per workgroup, whose
 // waves each find the peak for themselves: one latency more in place of a launch before (4.7 + 4.6 us per
 // batch of 8 templates, now 5).
 __global__ __launch_bounds__(256) void k_peak(const double* __restrict__ pv, const int32_t* __restrict__ pi, int groups,
-                                            const double2* __restrict__ z, int64_t n, int T, int k0_sb,
-                                            int32_t* __restrict__ k0_out, int32_t* __restrict__ d_out,
-                                            double2* __restrict__ out) {
+                                            const double2* __restrict__ z, int64_t n, int T,
+                                            int32_t* __restrict__ k0_out, double2* __restrict__ out) {
   const int64_t t = blockIdx.y;
   StorePeak m{nullptr, 0, nullptr, nullptr};
   for (int c = threadIdx.x & 63; c < groups; c += 64) m.take(pv[t * groups + c], pi[t * groups + c]);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) m.take(__shfl_xor(m.best, o), __shfl_xor(m.at, o));
   const int k0 = (int)(m.at <= n / 2 ? m.at : m.at - n) - T / 2;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    k0_out[t] = k0;
-    if (d_out) d_out[t] = k0 - k0_sb;
-  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) k0_out[t] = k0;
   const int l = blockIdx.x * 256 + threadIdx.x;
   if (out && l < T) out[t * T + l] = z[t * n + (((int64_t)k0 + l) & (n - 1))];
 }
@@ -1189,8 +1185,8 @@ static int row_groups(const Plan& p) {
 // them (out, may be NULL) instead of transforming the templates again.  16 templates at
 // N = 2^20, T = 1024: 365 us while the row pass kept |b|^2 alone, a second pass searched it and the kept lags were
 // summed from a second column transform.
-int launch_corr_peak(Plan& p, Taps& tp, const double* h_r, const double* h_t, int64_t batch, int T, int k0_sb,
-                     double2* z, int32_t* k0_out, int32_t* d_out, double2* out) {
+int launch_corr_peak(Plan& p, Taps& tp, const double* h_r, const double* h_t, int64_t batch, int T, double2* z,
+                     int32_t* k0_out, double2* out) {
   if (tp.work64_cap < (size_t)batch * p.n) return fail(RFD_E_INVALID, "corr peak: work buffer too small");
   const int groups = row_groups(p);
   if (tp.peak_cap < (size_t)batch * p.n || tp.peak_parts_cap < (size_t)batch * kPeakParts || groups > kPeakParts)
@@ -1202,8 +1198,20 @@ int launch_corr_peak(Plan& p, Taps& tp, const double* h_r, const double* h_t, in
                               (int)batch);
   if (rc) return rc;
   hipLaunchKernelGGL(k_peak, dim3(out ? (unsigned)((T + 255) / 256) : 1u, (unsigned)batch), dim3(256), 0, p.stream,
-                     (const double*)tp.peak_part, (const int32_t*)tp.peak_idx, groups, (const double2*)z, p.n, T, k0_sb,
-                     k0_out, d_out, out);
+                     (const double*)tp.peak_part, (const int32_t*)tp.peak_idx, groups, (const double2*)z, p.n, T,
+                     k0_out, out);
+  RFD_CHECK_LAUNCH();
+  return RFD_OK;
+}
+
+// Offsets of the lag windows from the sub-bank's k0.  Not part of the peak search: a call that is refused after its
+// search leaves the offsets of the taps that stand.
+__global__ void k_lag_shifts(const int32_t* __restrict__ k0s, int k0_sb, int64_t n, int32_t* __restrict__ d) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) d[i] = k0s[i] - k0_sb;
+}
+int launch_lag_shifts(Plan& p, const int32_t* k0s, int k0_sb, int64_t count, int32_t* d_out) {
+  hipLaunchKernelGGL(k_lag_shifts, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, p.stream, k0s, k0_sb, count, d_out);
   RFD_CHECK_LAUNCH();
   return RFD_OK;
 }

@@ -148,6 +148,7 @@ struct SubBankTaps {
   double2* U = nullptr;             // L^H, column-major
   double2* Dinv = nullptr;          // inverses of L's 64 x 64 diagonal blocks, column-major
   double2* g = nullptr;             // autocorrelation g[0..T-1]
+  double2* gf = nullptr;            // the g that the cached factor was made from
   double eps = -1.0;                // ridge of the cached factor
   int64_t made = 0;                 // templates whose taps exist
   std::vector<uint8_t> made_mask;
@@ -199,6 +200,8 @@ struct Taps {
   double2* peak_z = nullptr; size_t peak_cap = 0;      // the full correlations (centring)
   double* peak_part = nullptr; int32_t* peak_idx = nullptr; size_t peak_parts_cap = 0;   // workgroup maxima
   int32_t* k0buf = nullptr; size_t k0buf_cap = 0;      // per-template k0 of one make_taps call
+  int* factor_differs = nullptr;    // pinned: the last taps_factor_compare's answer, complete at factor_event
+  hipEvent_t factor_event = nullptr;
 };
 
 // FIR tiling shared by packing and kernels
@@ -230,16 +233,20 @@ int launch_corr64(Plan& p, Taps& tp, int mode, const double* h_r, const double* 
 constexpr int kPeakParts = 512;  // workgroups per template of the row pass, at most
 // Per-template lag centring: the full weighted cross-correlation b (mode 0)
 // of each batch entry into z [batch][N], and its peak lag l in
-// (-N/2, N/2]: k0_out[t] = l - floor(T/2), d_out[t] = k0_out[t] - k0_sb.
+// (-N/2, N/2]: k0_out[t] = l - floor(T/2).
 // out (may be NULL) [batch][T]: b at the lags k0_out[t] + l, l < T.
-int launch_corr_peak(Plan& p, Taps& tp, const double* h_r, const double* h_t, int64_t batch, int T, int k0_sb,
-                     double2* z, int32_t* k0_out, int32_t* d_out, double2* out);
+int launch_corr_peak(Plan& p, Taps& tp, const double* h_r, const double* h_t, int64_t batch, int T, double2* z,
+                     int32_t* k0_out, double2* out);
+// d_out[t] = k0s[t] - k0_sb
+int launch_lag_shifts(Plan& p, const int32_t* k0s, int k0_sb, int64_t count, int32_t* d_out);
 // band series [n_bands][N] (FP32, normalised by sigma_ref) of one reference
 int launch_band_cols(Plan& p, const double* h_ref, const int32_t* edges, int b0, int nb, double2* work);
 int launch_band_rows(Plan& p, int b0, int nb, float2* out, const double2* work);
 
 // ---------------------------------------------------- launchers (taps.hip)
-int taps_prepare_subbank(Plan& p, Taps& tp, int b, const double* h_ref, double eps);
+int taps_factor(Plan& p, Taps& tp, int b, double eps);            // of M + eps g[0] I from the sub-bank's g
+int taps_factor_compare(Plan& p, Taps& tp, int b);                // queue: is the factor the one of g?
+int taps_factor_current(Taps& tp, bool* current);                 // wait for the answer
 int taps_solve_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count, int method);
 // sigma_fit of the taps in a64 (with the sub-bank's g), then the normalised packings
 int taps_norm_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count);

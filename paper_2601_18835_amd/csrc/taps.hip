@@ -475,30 +475,53 @@ __global__ __launch_bounds__(256) void k_pack(const double2* __restrict__ a, int
 }
 
 // ------------------------------------------------------------ launchers
-int taps_prepare_subbank(Plan& p, Taps& tp, int b, const double* h_ref, double eps) {
+int taps_factor(Plan& p, Taps& tp, int b, double eps) {
   SubBankTaps& s = tp.sb[b];
   const int T = s.T;
-  int rc = launch_corr64(p, tp, 1, h_ref, nullptr, 1, T, 0, s.g, T);
-  if (rc) return rc;
-  if (eps >= 0.0) {
-    if (T > RFD_MAX_TAPS) return fail(RFD_E_INVALID, "taps out of range");
-    int64_t el = (int64_t)T * T;
-    int blocks = (int)((el + 255) / 256 < 4096 ? (el + 255) / 256 : 4096);
-    int* info = reinterpret_cast<int*>(p.dscratch + 8);
-    RFD_HIP(hipMemsetAsync(info, 0, sizeof(int), p.stream));
-    hipLaunchKernelGGL(k_schur_chol, dim3(1), dim3(1024), 0, p.stream, s.g, T, eps, s.L, info);
-    RFD_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_upper, dim3(blocks), dim3(256), 0, p.stream, s.L, T, s.U);
-    RFD_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_diag_inv, dim3((unsigned)((T + kTrsmBlock - 1) / kTrsmBlock)), dim3(kTrsmBlock),
-                       (size_t)2 * kTrsmBlock * (kTrsmBlock + 1) * sizeof(double2), p.stream, s.L, T, s.Dinv);
-    RFD_CHECK_LAUNCH();
-    int hinfo = 0;
-    RFD_HIP(hipMemcpyAsync(&hinfo, info, sizeof(int), hipMemcpyDeviceToHost, p.stream));
-    RFD_HIP(hipStreamSynchronize(p.stream));
-    if (hinfo != 0) return fail(RFD_E_INVALID, "ridge-regularised Gram matrix is not positive definite");
-    s.eps = eps;
-  }
+  if (T > RFD_MAX_TAPS) return fail(RFD_E_INVALID, "taps out of range");
+  int64_t el = (int64_t)T * T;
+  int blocks = (int)((el + 255) / 256 < 4096 ? (el + 255) / 256 : 4096);
+  int* info = reinterpret_cast<int*>(p.dscratch + 8);
+  RFD_HIP(hipMemsetAsync(info, 0, sizeof(int), p.stream));
+  hipLaunchKernelGGL(k_schur_chol, dim3(1), dim3(1024), 0, p.stream, s.g, T, eps, s.L, info);
+  RFD_CHECK_LAUNCH();
+  hipLaunchKernelGGL(k_upper, dim3(blocks), dim3(256), 0, p.stream, s.L, T, s.U);
+  RFD_CHECK_LAUNCH();
+  hipLaunchKernelGGL(k_diag_inv, dim3((unsigned)((T + kTrsmBlock - 1) / kTrsmBlock)), dim3(kTrsmBlock),
+                     (size_t)2 * kTrsmBlock * (kTrsmBlock + 1) * sizeof(double2), p.stream, s.L, T, s.Dinv);
+  RFD_CHECK_LAUNCH();
+  int hinfo = 0;
+  RFD_HIP(hipMemcpyAsync(&hinfo, info, sizeof(int), hipMemcpyDeviceToHost, p.stream));
+  RFD_HIP(hipStreamSynchronize(p.stream));
+  if (hinfo != 0) return fail(RFD_E_INVALID, "ridge-regularised Gram matrix is not positive definite");
+  RFD_HIP(hipMemcpyAsync(s.gf, s.g, T * sizeof(double2), hipMemcpyDeviceToDevice, p.stream));
+  s.eps = eps;
+  return RFD_OK;
+}
+
+// The factor is a function of g and the ridge alone, and g of the plan's weights and the caller's reference: where
+// either has changed since, g has, and the factor with it.  The sums that make g have a fixed
+// order, so that unchanged inputs give the same bits.
+__global__ __launch_bounds__(256) void k_g_differs(const double2* __restrict__ g, const double2* __restrict__ gf, int T,
+                                                 int* __restrict__ differs) {
+  int d = 0;
+  for (int i = threadIdx.x; i < T; i += 256)
+    d |= __double_as_longlong(g[i].x) != __double_as_longlong(gf[i].x) ||
+         __double_as_longlong(g[i].y) != __double_as_longlong(gf[i].y);
+  d = __syncthreads_or(d);
+  if (threadIdx.x == 0) *differs = d;
+}
+int taps_factor_compare(Plan& p, Taps& tp, int b) {
+  const SubBankTaps& s = tp.sb[b];
+  hipLaunchKernelGGL(k_g_differs, dim3(1), dim3(256), 0, p.stream, (const double2*)s.g, (const double2*)s.gf, s.T,
+                     tp.factor_differs);
+  RFD_CHECK_LAUNCH();
+  RFD_HIP(hipEventRecord(tp.factor_event, p.stream));
+  return RFD_OK;
+}
+int taps_factor_current(Taps& tp, bool* current) {
+  RFD_HIP(hipEventSynchronize(tp.factor_event));
+  *current = *(volatile int*)tp.factor_differs == 0;
   return RFD_OK;
 }
 

@@ -1,0 +1,85 @@
+"""Least-squares taps made again by one taps object after what the cached Cholesky factor was made from has
+changed, against FP64 solves on the host."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import taps as otaps
+from test_gpu_taps_blocks import setup  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def _weights(n, fs, f_low, psd):
+    w = np.zeros(n // 2 + 1)
+    i_low = int(np.ceil(f_low / (fs / n)))
+    w[i_low:n // 2] = 4.0 * (fs / n) / psd[i_low:n // 2]
+    return w
+
+
+def _check(rfd, taps, ref, wts, H, T, eps):
+    """Every template's taps solve the normal equations and sigma_fit is their norm."""
+    n = 2 * (ref.size - 1)
+    M = otaps.gram(ref, wts, T)
+    A = M + eps * M[0, 0].real * np.eye(T)
+    for j in range(len(H)):
+        a, sig, _, k0 = rfd.rfd_taps_get(taps, j)
+        b = otaps.crosscorr(H[j], ref, wts, T, k0)
+        # backward error of the solve and of the correlations, in units of |A| |a| + |b|
+        res = np.linalg.norm(A @ a - b) / (A[0, 0].real * T * np.linalg.norm(a) + np.linalg.norm(b))
+        assert res <= 1e-14 * max(T, 64)
+        want = np.sqrt(np.real(np.conj(a) @ M @ a))
+        # rounding of |M| |a|^2
+        tol = 1e-15 * T * A[0, 0].real * T * np.linalg.norm(a) ** 2 / want ** 2 + 1e-12
+        assert abs(sig / want - 1) <= tol
+
+
+@pytest.mark.parametrize("T", [48, 320])
+@pytest.mark.parametrize("centre", [False, True])
+def test_factor_follows_the_psd_and_the_reference(rfd, setup, T, centre):  # noqa: F811
+    import torch
+    n, fs, f_low, psd, _, ref, H = setup
+    H, eps = H[:3], 1e-4
+    other = synth.taylorf2(synth.WaveformParams(6.4, 5.2), n, fs, f_low)
+    f = np.arange(n // 2 + 1) * (fs / n)
+    method = rfd.RFD_TAPS_LS | (rfd.RFD_TAPS_CENTRE if centre else 0)
+    plan = rfd.rfd_plan_create(psd, f_low, fs, n)
+    taps = rfd.rfd_taps_create(plan, [0, 3], [0], [T], [-(T // 2)])
+    h = torch.from_numpy(H).cuda()
+    first = None
+    for p, r in ((psd, ref), (2.0 * psd, ref), (np.where(f < 60.0, 3.0, 1.0) * psd, ref), (psd, other), (psd, ref)):
+        rfd.rfd_plan_set_psd(plan, p)
+        rfd.rfd_make_taps(plan, taps, 0, torch.from_numpy(r).cuda(), h, method=method, ridge_eps=eps)
+        _check(rfd, taps, r, _weights(n, fs, f_low, p), H, T, eps)
+        if first is None:
+            first = [rfd.rfd_taps_get(taps, j) for j in range(3)]
+    for j in range(3):                      # back to the first inputs: the first bits
+        a, sig, _, k0 = rfd.rfd_taps_get(taps, j)
+        assert np.array_equal(a, first[j][0]) and (sig, k0) == (first[j][1], first[j][3])
+    rfd.rfd_taps_destroy(taps)
+    rfd.rfd_plan_destroy(plan)
+
+
+def test_another_reference_in_the_same_buffer(rfd, setup):  # noqa: F811
+    import torch
+    n, fs, f_low, psd, wts, ref, H = setup
+    T, eps = 100, 1e-4
+    plan = rfd.rfd_plan_create(psd, f_low, fs, n)
+    taps = rfd.rfd_taps_create(plan, [0, 3], [0], [T], [-(T // 2)])
+    r, h = torch.from_numpy(ref).cuda(), torch.from_numpy(H[:3]).cuda()
+    rfd.rfd_make_taps(plan, taps, 0, r, h, ridge_eps=eps)
+    # a reference without power in band is refused, and the taps that stand keep their lag windows
+    before = [rfd.rfd_taps_get(taps, j) for j in range(3)]
+    with pytest.raises(rfd.RfdError) as e:
+        rfd.rfd_make_taps(plan, taps, 0, torch.zeros_like(r), h, method=rfd.RFD_TAPS_LS | rfd.RFD_TAPS_CENTRE,
+                          ridge_eps=eps)
+    assert e.value.code == rfd.RFD_E_INVALID
+    for j in range(3):
+        a, sig, _, k0 = rfd.rfd_taps_get(taps, j)
+        assert np.array_equal(a, before[j][0]) and (sig, k0) == (before[j][1], before[j][3])
+    other = synth.taylorf2(synth.WaveformParams(6.4, 5.2), n, fs, f_low)
+    r.copy_(torch.from_numpy(other))
+    rfd.rfd_make_taps(plan, taps, 0, r, h, ridge_eps=eps)
+    _check(rfd, taps, other, wts, H[:3], T, eps)
+    rfd.rfd_taps_destroy(taps)
+    rfd.rfd_plan_destroy(plan)
