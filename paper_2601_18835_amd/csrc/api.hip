@@ -946,7 +946,7 @@ int rfd_make_taps(rfd_plan* plan, rfd_taps* taps, int32_t subbank, const double*
     if (!rc && !s.Dinv) rc = dalloc(&s.Dinv, (size_t)round_up(T, 64) * 64);
     if (!rc && !s.gf) rc = dalloc(&s.gf, (size_t)T);
     if (rc) return rc;
-    if (s.eps != ridge_eps) {
+    if (!s.factored || s.eps != ridge_eps) {
       rc = taps_factor(p, t, subbank, ridge_eps);
     } else if (!capturing(p.stream)) {      // (a stream being captured cannot be waited for: it keeps the factor)
       compare = true;

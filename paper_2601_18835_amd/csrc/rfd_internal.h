@@ -150,6 +150,7 @@ struct SubBankTaps {
   double2* g = nullptr;             // autocorrelation g[0..T-1]
   double2* gf = nullptr;            // the g that the cached factor was made from
   double eps = -1.0;                // ridge of the cached factor
+  bool factored = false;            // L, U and Dinv are whole: a refused factorisation leaves parts of two
   int64_t made = 0;                 // templates whose taps exist
   std::vector<uint8_t> made_mask;
   int64_t n_centred = 0;            // templates whose lag window is their own (d != 0 possible)

@@ -1641,7 +1641,7 @@ int rfd_surrogate_create(rfd_plan* plan, rfd_taps* taps, int32_t subbank, int32_
   if (subbank < 0 || subbank >= (int)t.sb.size()) return fail(RFD_E_INVALID, "subbank out of range");
   SubBankTaps& sb = t.sb[subbank];
   if (sb.count < 2 || sb.made != sb.count) return fail(RFD_E_STATE, "training sub-bank needs >= 2 made tap sets");
-  if (!sb.U) return fail(RFD_E_STATE, "training taps must come from the least-squares route (Cholesky factor)");
+  if (!sb.factored) return fail(RFD_E_STATE, "training taps must come from the least-squares route (Cholesky factor)");
   if (sb.n_centred > 0)
     return fail(RFD_E_UNSUPPORTED, "training taps must share the sub-bank's lag window (no RFD_TAPS_CENTRE)");
   if (n_basis < 1 || n_basis > 2 * sb.T || n_basis > 1024) return fail(RFD_E_INVALID, "n_basis out of range");

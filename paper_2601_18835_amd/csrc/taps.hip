@@ -482,6 +482,7 @@ int taps_factor(Plan& p, Taps& tp, int b, double eps) {
   int64_t el = (int64_t)T * T;
   int blocks = (int)((el + 255) / 256 < 4096 ? (el + 255) / 256 : 4096);
   int* info = reinterpret_cast<int*>(p.dscratch + 8);
+  s.factored = false;
   RFD_HIP(hipMemsetAsync(info, 0, sizeof(int), p.stream));
   hipLaunchKernelGGL(k_schur_chol, dim3(1), dim3(1024), 0, p.stream, s.g, T, eps, s.L, info);
   RFD_CHECK_LAUNCH();
@@ -496,6 +497,7 @@ int taps_factor(Plan& p, Taps& tp, int b, double eps) {
   if (hinfo != 0) return fail(RFD_E_INVALID, "ridge-regularised Gram matrix is not positive definite");
   RFD_HIP(hipMemcpyAsync(s.gf, s.g, T * sizeof(double2), hipMemcpyDeviceToDevice, p.stream));
   s.eps = eps;
+  s.factored = true;
   return RFD_OK;
 }
 

@@ -83,3 +83,30 @@ def test_another_reference_in_the_same_buffer(rfd, setup):  # noqa: F811
     _check(rfd, taps, other, wts, H[:3], T, eps)
     rfd.rfd_taps_destroy(taps)
     rfd.rfd_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("T", [48, 320])
+def test_a_refused_ridge_leaves_no_factor_behind(rfd, setup, T):  # noqa: F811
+    import torch
+    n, fs, f_low, psd, wts, ref, H = setup
+    plan = rfd.rfd_plan_create(psd, f_low, fs, n)
+    taps = rfd.rfd_taps_create(plan, [0, 3], [0], [T], [-(T // 2)])
+    r, h = torch.from_numpy(ref).cuda(), torch.from_numpy(H[:3]).cuda()
+    rfd.rfd_make_taps(plan, taps, 0, r, h, ridge_eps=1e-4)
+    first = [rfd.rfd_taps_get(taps, j) for j in range(3)]
+    def refused():
+        with pytest.raises(rfd.RfdError) as e:      # the band ends below fs / 2: M alone is singular to rounding
+            rfd.rfd_make_taps(plan, taps, 0, r, h, ridge_eps=0.0)
+        assert e.value.code == rfd.RFD_E_INVALID
+
+    refused()
+    rfd.rfd_make_taps(plan, taps, 0, r, h, ridge_eps=1e-4)
+    for j in range(3):
+        a, sig, _, k0 = rfd.rfd_taps_get(taps, j)
+        assert np.array_equal(a, first[j][0]) and (sig, k0) == (first[j][1], first[j][3])
+    refused()
+    with pytest.raises(rfd.RfdError) as e:          # nothing to whiten training taps with
+        rfd.rfd_surrogate_create(plan, taps, 0, 2, 32, 1)
+    assert e.value.code == rfd.RFD_E_STATE
+    rfd.rfd_taps_destroy(taps)
+    rfd.rfd_plan_destroy(plan)
