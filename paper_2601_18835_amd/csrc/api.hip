@@ -779,6 +779,7 @@ static void taps_free(Taps& t) {
   dfree(t.d_p16); dfree(t.d_p32); dfree(t.d_count);
   dfree(t.d_it_off); dfree(t.d_it_sb); dfree(t.d_it_S); dfree(t.d_it_nsg);
   dfree(t.d_shift); dfree(t.peak_z); dfree(t.k0buf); dfree(t.peak_part); dfree(t.peak_idx);
+  dfree(t.sig_part);
   if (t.factor_differs) (void)hipHostFree(t.factor_differs);
   if (t.factor_event) (void)hipEventDestroy(t.factor_event);
   t.factor_differs = nullptr;
@@ -853,6 +854,9 @@ int rfd_taps_create(rfd_plan* plan, int32_t n_subbanks, const int64_t* offsets, 
   TRY(dalloc(&t.d_count, (size_t)n_subbanks));
   for (auto& s : t.sb) TRY(dalloc(&s.g, (size_t)s.T));
   TRY(dalloc(&t.d_shift, (size_t)std::max<int64_t>(t.n_templates, 1)));
+  size_t n_part = 0;
+  for (auto& s : t.sb) n_part = std::max(n_part, sigma_part_values(s.T, s.count));
+  TRY(dalloc(&t.sig_part, n_part));
   if (hipHostMalloc((void**)&t.factor_differs, sizeof(int), hipHostMallocDefault) != hipSuccess) {
     t.factor_differs = nullptr;
     (void)hipGetLastError();

@@ -201,6 +201,7 @@ struct Taps {
   double2* peak_z = nullptr; size_t peak_cap = 0;      // the full correlations (centring)
   double* peak_part = nullptr; int32_t* peak_idx = nullptr; size_t peak_parts_cap = 0;   // workgroup maxima
   int32_t* k0buf = nullptr; size_t k0buf_cap = 0;      // per-template k0 of one make_taps call
+  double* sig_part = nullptr;                          // sums of sigma_fit^2 over parts of the taps (sigma_part_values)
   int* factor_differs = nullptr;    // pinned: the last taps_factor_compare's answer, complete at factor_event
   hipEvent_t factor_event = nullptr;
 };
@@ -251,6 +252,7 @@ int taps_factor_current(Taps& tp, bool* current);                 // wait for th
 int taps_solve_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count, int method);
 // sigma_fit of the taps in a64 (with the sub-bank's g), then the normalised packings
 int taps_norm_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count);
+size_t sigma_part_values(int T, int64_t count);                   // of the largest make_taps or renormalize call
 
 // ----------------------------------------------------- launchers (fir.hip)
 // n_len < 0: the whole segment; else output samples [n_start, n_start + n_len),

@@ -342,51 +342,132 @@ __global__ void k_window(const double2* __restrict__ b, int64_t bstride, int T, 
   }
 }
 
-// sigma_fit^2 = a^H M a with M[l,k] = g[l-k]; one workgroup per template.
+// sigma_fit^2 = a^H M a, M[l,k] = g[l-k], for eight templates per workgroup on the FP64 matrix cores: as in k_trsm their
+// taps are X = [Re | Im], M a is Re M [Re | Im] + Im M [-Im | Re], and the norm is the sum of its product with X.
+// M is Hermitian: what lies left of the 16 x 16 tiles on its diagonal counts twice, what lies right of them not at all.
+// A wave takes a row of tiles and its mirror (of the same work together, whichever the row); the taps pass through LDS in
+// panels, in runs along each template (as operands from L2 eight templates met one channel of it at a time, a power of two
+// apart).  T > 128 spreads a group's rows over workgroups, whose parts k_sigma_sum adds.  Bound by the matrix cores and,
+// at small T, by the latency of its panels: 256 templates at T = 1024 in 27 us (345 by products of one
+// row at a time, 41 from L2), 500 at T = 256 in 10, and 5 for the parts.
+// The sum over the normal equations, Re(a^H b) - lam |a|^2, has T products per template and not T^2, but its
+// error is the solve's residual at small ridges and a difference of large numbers at large ones: 3e-14
+// of the norm against 1e-15 at T = 200 and a ridge of 1e-4, 2e-10 against 2e-11 at 1e-8, 3e-9 against 1e-16 at 1e8.
+constexpr int kSigmaParts = RFD_MAX_TAPS / 16 / 2 / 4;
+constexpr int64_t kSigmaBatch = 4096;
+constexpr int kSigmaPanel = 128, kSigmaStride = 17;      // columns of a panel; values from one to the next (odd: banks)
+static int sigma_parts(int T) { return ((T + 15) / 16 + 7) / 8; }
+size_t sigma_part_values(int T, int64_t count) {
+  static_assert(kSigmaParts * 128 == RFD_MAX_TAPS, "a wave has a row of tiles and its mirror");
+  const int parts = sigma_parts(T);
+  return parts > 1 ? (size_t)(parts * std::min(count, kSigmaBatch)) : 0;
+}
+// part: [gridDim.y][count], or with one workgroup per group NULL and the norms to sigma
 __global__ __launch_bounds__(256) void k_sigma_fit(const double2* __restrict__ a, int64_t astride, int T,
-                                                 const double2* __restrict__ g, double* __restrict__ sigma) {
-  extern __shared__ double2 sh[];
-  double2* av = sh;
-  double2* gv = sh + T;
-  __shared__ double red[256];
-  const double2* ab = a + (int64_t)blockIdx.x * astride;
-  for (int i = threadIdx.x; i < T; i += 256) {
-    av[i] = ab[i];
-    gv[i] = g[i];
-  }
+                                                 const double2* __restrict__ g, int64_t count,
+                                                 double* __restrict__ part, double* __restrict__ sigma) {
+  constexpr int TPW = 8, PW = kSigmaPanel, ST = kSigmaStride;
+  extern __shared__ double2 gs[];                     // g, then two panels [PW][ST]
+  double* panels = reinterpret_cast<double*>(gs + T);
+  __shared__ double red[4][TPW];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int kq = lane >> 4, col = lane & 15;
+  const int64_t t0 = (int64_t)blockIdx.x * TPW;
+  double2 next[PW * TPW / 256];
+  auto fetch = [&](int c) {
+#pragma unroll
+    for (int i = 0; i < PW * TPW / 256; ++i) {
+      const int e = threadIdx.x + 256 * i, tt = e / PW, k = c + e % PW;
+      next[i] = k < T && t0 + tt < count ? a[(t0 + tt) * astride + k] : make_double2(0.0, 0.0);
+    }
+  };
+  auto store = [&](double* x) {
+#pragma unroll
+    for (int i = 0; i < PW * TPW / 256; ++i) {
+      const int e = threadIdx.x + 256 * i, tt = e / PW, k = e % PW;
+      x[k * ST + tt] = next[i].x;
+      x[k * ST + TPW + tt] = next[i].y;
+    }
+  };
+  fetch(0);
+  for (int i = threadIdx.x; i < T; i += 256) gs[i] = g[i];
+  store(panels);
   __syncthreads();
+  const int nt = (T + 15) / 16, unit = blockIdx.y * 4 + wave;
+  // first rows of the two tiles, T where the wave has none; the lane holds M operands of row r0 + col (of row T - 1
+  // past the end, where they meet zeros)
+  const int rows[2] = {2 * unit < nt ? 16 * unit : T, nt - 1 - unit > unit ? 16 * (nt - 1 - unit) : T};
+  f64x4 p[2], q[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) p[h] = q[h] = f64x4{0.0, 0.0, 0.0, 0.0};
+  const double sgn = col < TPW ? -1.0 : 1.0;
   double acc = 0.0;
-  for (int l = threadIdx.x; l < T; l += 256) {
-    double2 s = make_double2(0.0, 0.0);
-    for (int k = 0; k < T; ++k) s = cadd(s, cmul(gval(gv, l - k), av[k]));
-    acc += av[l].x * s.x + av[l].y * s.y;   // Re(conj(a_l) s)
-  }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+  for (int c0 = 0, b = 0; c0 < T; c0 += PW, b ^= 1) {
+    const double* x = panels + b * PW * ST;
+    if (c0 + PW < T) fetch(c0 + PW);
+    auto product = [&](int h, double2 m, int k) {      // column c0 + k
+      p[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(m.x, x[k * ST + col], p[h], 0, 0, 0);
+      q[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(m.y, x[k * ST + (col ^ TPW)], q[h], 0, 0, 0);
+    };
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int r0 = rows[h];
+      if (r0 >= T) continue;
+      const double2* m = gs + min(r0 + col, T - 1) - c0;
+      const int left = min(r0 - c0, PW);                // columns of the panel left of the diagonal tile
+      for (int k = 0; k < left; k += 16) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) product(h, m[-(k + kq + 4 * u)], k + kq + 4 * u);
+      }
+      if (r0 < c0 || r0 >= c0 + PW) continue;
+      p[h] *= 2.0;
+      q[h] *= 2.0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int d = col - kq - 4 * u;
+        double2 v = gs[min(abs(d), T - 1)];
+        if (d < 0) v.y = -v.y;
+        product(h, v, r0 - c0 + kq + 4 * u);
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc += x[(r0 - c0 + 4 * v + kq) * ST + col] * (p[h][v] + sgn * q[h][v]);
+    }
+    if (c0 + PW < T) store(panels + (b ^ 1) * PW * ST);
     __syncthreads();
   }
-  if (threadIdx.x == 0) sigma[blockIdx.x] = sqrt(red[0]);
-}
-
-// sigma_fit^2 = a^H M a of a least-squares solution: (M + lam I) a = b gives Re(a^H b) - lam |a|^2,
-// T products instead of T^2 (256 templates at T = 1024: 345 -> 6 us).  Both forms carry a rounding
-// error of about eps |M| |a|^2.  One wave per template.
-__global__ __launch_bounds__(64) void k_sigma_ls(const double2* __restrict__ a, int64_t astride,
-                                               const double2* __restrict__ b, int T, const double2* __restrict__ g,
-                                               double eps, double* __restrict__ sigma) {
-  const double2* ab = a + (int64_t)blockIdx.x * astride;
-  const double2* bb = b + (int64_t)blockIdx.x * T;
-  const double lam = eps * g[0].x;
-  double acc = 0.0;
-  for (int k = threadIdx.x; k < T; k += 64) {
-    const double2 x = ab[k], y = bb[k];
-    acc += x.x * (y.x - lam * x.x) + x.y * (y.y - lam * x.y);
+  acc += __shfl_xor(acc, TPW);
+  acc += __shfl_xor(acc, 16);
+  acc += __shfl_xor(acc, 32);
+  if (lane < TPW) red[wave][lane] = acc;
+  __syncthreads();
+  if (threadIdx.x < TPW && t0 + lane < count) {
+    const double s = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+    if (part) part[blockIdx.y * count + t0 + lane] = s;
+    else sigma[t0 + lane] = sqrt(s);
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-  if (threadIdx.x == 0) sigma[blockIdx.x] = sqrt(acc);
+}
+__global__ void k_sigma_sum(const double* __restrict__ part, int parts, int64_t count, double* __restrict__ sigma) {
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (t >= count) return;
+  double s = part[t];
+  for (int k = 1; k < parts; ++k) s += part[k * count + t];
+  sigma[t] = sqrt(s);
+}
+static int launch_sigma_fit(Plan& p, Taps& tp, const double2* a, int64_t astride, int T, const double2* g, int64_t count,
+                            double* sigma) {
+  const int parts = sigma_parts(T);
+  const int64_t batch = parts > 1 ? kSigmaBatch : count;
+  for (int64_t t0 = 0; t0 < count; t0 += batch) {
+    const int64_t cn = std::min(batch, count - t0);
+    hipLaunchKernelGGL(k_sigma_fit, dim3((unsigned)((cn + 7) / 8), (unsigned)parts), dim3(256),
+                       (size_t)T * sizeof(double2) + (size_t)2 * kSigmaPanel * kSigmaStride * sizeof(double), p.stream, a + t0 * astride, astride, T, g, cn, parts > 1 ? tp.sig_part : nullptr, sigma + t0);
+    RFD_CHECK_LAUNCH();
+    if (parts == 1) continue;
+    hipLaunchKernelGGL(k_sigma_sum, dim3((unsigned)((cn + 255) / 256)), dim3(256), 0, p.stream,
+                       (const double*)tp.sig_part, parts, cn, sigma + t0);
+    RFD_CHECK_LAUNCH();
+  }
+  return RFD_OK;
 }
 
 // Normalised taps c = conj(a) sigma_ref / sigma_fit, and their MFMA A-operand
@@ -573,22 +654,15 @@ int taps_solve_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count, 
                        (int64_t)s.Tp);
   }
   RFD_CHECK_LAUNCH();
-  if (method != RFD_TAPS_LS) return taps_norm_and_pack(p, tp, b, first, count);
-  hipLaunchKernelGGL(k_sigma_ls, dim3((unsigned)count), dim3(64), 0, p.stream, (const double2*)abase, (int64_t)s.Tp,
-                     (const double2*)tp.bvec, T, (const double2*)s.g, s.eps, tp.sigma_fit + s.first + first);
-  RFD_CHECK_LAUNCH();
-  return taps_pack(p, tp, b, first, count);
+  return taps_norm_and_pack(p, tp, b, first, count);
 }
 
 // sigma_fit of taps already in a64, then the normalised taps and MFMA packings.
 int taps_norm_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count) {
   SubBankTaps& s = tp.sb[b];
-  const int T = s.T;
-  double2* abase = tp.a64 + s.a_base + first * s.Tp;
-  double* sig = tp.sigma_fit + s.first + first;
-  hipLaunchKernelGGL(k_sigma_fit, dim3((unsigned)count), dim3(256), (size_t)2 * T * sizeof(double2), p.stream,
-                     abase, (int64_t)s.Tp, T, s.g, sig);
-  RFD_CHECK_LAUNCH();
+  int rc = launch_sigma_fit(p, tp, tp.a64 + s.a_base + first * s.Tp, s.Tp, s.T, s.g, count,
+                            tp.sigma_fit + s.first + first);
+  if (rc) return rc;
   return taps_pack(p, tp, b, first, count);
 }
 

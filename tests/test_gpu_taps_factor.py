@@ -110,3 +110,46 @@ def test_a_refused_ridge_leaves_no_factor_behind(rfd, setup, T):  # noqa: F811
     assert e.value.code == rfd.RFD_E_STATE
     rfd.rfd_taps_destroy(taps)
     rfd.rfd_plan_destroy(plan)
+
+
+def _norms(a, M):
+    """sqrt(a^H M a) in extended precision, and the error that rounding sums of |a| |M| |a| can leave."""
+    al, Ml = a.astype(np.clongdouble), M.astype(np.clongdouble)
+    sq = np.real(np.einsum("jl,jl->j", np.conj(al), al @ Ml.T)).astype(np.float64)
+    T, g0 = M.shape[0], M[0, 0].real
+    # 2 T products in a row, and g itself good to a few roundings of g[0] on either side
+    return np.sqrt(sq), 2.0 ** -52 * (2 * T + 32) * g0 * np.sum(np.abs(a), axis=1) ** 2 / sq
+
+
+@pytest.mark.parametrize("T,count", [(1, 3), (15, 8), (16, 9), (17, 3), (128, 3), (129, 3), (500, 3)])
+@pytest.mark.parametrize("eps", [1e-8, 1e-4, 1.0, 1e4, 1e8, 1e16])
+def test_norm_at_every_ridge(rfd, setup, T, count, eps):  # noqa: F811
+    import torch
+    n, fs, f_low, psd, wts, ref, H = setup
+    plan = rfd.rfd_plan_create(psd, f_low, fs, n)
+    taps = rfd.rfd_taps_create(plan, [0, count], [0], [T], [-(T // 2)])
+    rfd.rfd_make_taps(plan, taps, 0, torch.from_numpy(ref).cuda(), torch.from_numpy(H[:count]).cuda(), ridge_eps=eps)
+    got = [rfd.rfd_taps_get(taps, j)[:2] for j in range(count)]
+    want, tol = _norms(np.array([a for a, _ in got]), otaps.gram(ref, wts, T))
+    assert np.all(np.abs(np.array([s for _, s in got]) / want - 1) <= tol)
+    rfd.rfd_taps_destroy(taps)
+    rfd.rfd_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("T", [100, 144])
+def test_norms_of_more_templates_than_a_batch(rfd, T):
+    import torch
+    n, fs, f_low, count = 1 << 10, 1024.0, 20.0, 4101
+    rng = np.random.default_rng(5)
+    draw = lambda m: rng.standard_normal((m, n // 2 + 1)) + 1j * rng.standard_normal((m, n // 2 + 1))  # noqa: E731
+    ref, H = draw(1)[0], draw(count)
+    psd = rng.uniform(0.5, 2.0, n // 2 + 1)
+    plan = rfd.rfd_plan_create(psd, f_low, fs, n)
+    taps = rfd.rfd_taps_create(plan, [0, count], [0], [T], [-(T // 2)])
+    rfd.rfd_make_taps(plan, taps, 0, torch.from_numpy(ref).cuda(), torch.from_numpy(H).cuda())
+    picked = [0, 7, 8, 4095, 4096, 4099, 4100]
+    got = [rfd.rfd_taps_get(taps, j)[:2] for j in picked]
+    want, tol = _norms(np.array([a for a, _ in got]), otaps.gram(ref, _weights(n, fs, f_low, psd), T))
+    assert np.all(np.abs(np.array([s for _, s in got]) / want - 1) <= tol)
+    rfd.rfd_taps_destroy(taps)
+    rfd.rfd_plan_destroy(plan)
