@@ -142,11 +142,13 @@ __global__ __launch_bounds__(kTrsmBlock) void k_diag_inv(const double2* __restri
 // sweep with U = L^H in block rows of 64.  Off the diagonal a block row is a complex GEMM,
 // L X = Re L [Re | Im] + Im L [-Im | Re], one v_mfma_f64_16x16x4 for either part of four columns of L;
 // wave w takes 16 of the 64 rows, its operands come straight from L2 eight steps ahead.  The
-// diagonal block is a product with its inverse (64 rows: its condition is at most that of
-// the whole factor).  Bound by the matrix cores where count fills the chip: 2 T^2 / 4 / 16 / 4
-// pairs of 64-cycle instructions per wave, 0.2 ms at T = 1024 however few the templates.  256 templates at
-// T = 1024: 2836 us with one wave per template sweeping the factor's columns -> 424 us;
-// 500 at T = 256: 178 -> 46 us.
+// diagonal block is a product with its inverse, D, refined once: x = D r, x += D (r - L_ii x).  Without,
+// the residual of the solve carries the block's condition where a substitution's carries none (T = 64: 3e-16 of
+// |M| |a| against 2e-17 at a ridge of 1e-4, 2e-13 against 1e-17 at 1e-10), and the taps are 2 to 30 times further
+// from the exact solution.  Bound by the matrix cores where count fills the chip: 2 T^2 / 4 / 16 / 4
+// pairs of 64-cycle instructions per wave, 0.4 ms at T = 1024 however few the templates, and three more
+// block products per block row.  256 templates at T = 1024: 2836 us with one wave per template
+// sweeping the factor's columns -> 556 us (424 unrefined); 500 at T = 256: 178 -> 75 us (47 unrefined).
 typedef __attribute__((ext_vector_type(4))) double f64x4;
 template <int TPW>
 __global__ __launch_bounds__(256) void k_trsm(const double2* __restrict__ L, const double2* __restrict__ U,
@@ -199,38 +201,53 @@ __global__ __launch_bounds__(256) void k_trsm(const double2* __restrict__ L, con
     for (int s = 0; s < nb; ++s) {
       const int i = sweep ? nb - 1 - s : s;
       const int r0 = i * N + 16 * wave;                       // this wave's rows
-      // the diagonal block's operands (inv(L_ii) or its conjugate transpose), loaded ahead of the GEMM
-      const double2* D = inv + (int64_t)i * N * N;
-      double2 dm[N / 4];
+      // the diagonal block's operands (inv(L_ii) or its conjugate transpose, L_ii or U_ii), loaded ahead of the GEMM
+      const double2 *D = inv + (int64_t)i * N * N, *F = sweep ? U : L;
+      const int row = min(r0 + (lane & 15), T - 1);
+      double2 dm[N / 4], fm[N / 4];
 #pragma unroll
       for (int u = 0; u < N / 4; ++u) {
         const int k = 4 * u + kq, r = 16 * wave + (lane & 15);
         dm[u] = sweep ? D[r * N + k] : D[k * N + r];
+        if (sweep) dm[u].y = -dm[u].y;
+        fm[u] = F[(int64_t)min(i * N + k, T - 1) * T + row];
       }
       f64x4 p = {0.0, 0.0, 0.0, 0.0}, q = {0.0, 0.0, 0.0, 0.0};
-      if (sweep) gemm(U, min(r0 + (lane & 15), T - 1), (i + 1) * N, nb * N, p, q);
-      else gemm(L, min(r0 + (lane & 15), T - 1), 0, i * N, p, q);
-      if (mine) {
+      if (sweep) gemm(F, row, (i + 1) * N, nb * N, p, q);
+      else gemm(F, row, 0, i * N, p, q);
+      auto product = [&](const double2 (&m)[N / 4]) {         // with the block's rows of X; all of them are read on return
+        p = q = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int row = r0 + 4 * v + kq;
-          X[row * NC + col] = row < T ? X[row * NC + col] - (p[v] + q[v]) : 0.0;
+        for (int u = 0; u < N / 4; ++u) {
+          const double* x = X + (i * N + 4 * u + kq) * NC;
+          p = __builtin_amdgcn_mfma_f64_16x16x4f64(m[u].x, x[col], p, 0, 0, 0);
+          q = __builtin_amdgcn_mfma_f64_16x16x4f64(m[u].y, sgn * x[mate], q, 0, 0, 0);
         }
-      }
-      __syncthreads();
-      p = q = f64x4{0.0, 0.0, 0.0, 0.0};
+        __syncthreads();
+      };
+      auto put = [&](const double (&x)[4]) {                  // rows from T on stay zero
+        if (mine) {
 #pragma unroll
-      for (int u = 0; u < N / 4; ++u) {
-        const double* x = X + (i * N + 4 * u + kq) * NC;
-        p = __builtin_amdgcn_mfma_f64_16x16x4f64(dm[u].x, x[col], p, 0, 0, 0);
-        q = __builtin_amdgcn_mfma_f64_16x16x4f64(sweep ? -dm[u].y : dm[u].y, sgn * x[mate], q, 0, 0, 0);
-      }
-      __syncthreads();                                        // the residual has been read
-      if (mine) {
+          for (int v = 0; v < 4; ++v) X[(r0 + 4 * v + kq) * NC + col] = r0 + 4 * v + kq < T ? x[v] : 0.0;
+        }
+        __syncthreads();
+      };
+      double res[4], sol[4], x[4];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) X[(r0 + 4 * v + kq) * NC + col] = p[v] + q[v];
-      }
-      __syncthreads();
+      for (int v = 0; v < 4; ++v) res[v] = X[(r0 + 4 * v + kq) * NC + col] - (p[v] + q[v]);
+      put(res);
+      product(dm);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) sol[v] = p[v] + q[v];
+      put(sol);
+      product(fm);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) x[v] = res[v] - (p[v] + q[v]);
+      put(x);
+      product(dm);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) x[v] = sol[v] + (p[v] + q[v]);
+      put(x);
     }
   }
   for (int e = threadIdx.x; e < T * TPW; e += 256) {
@@ -251,11 +268,12 @@ __device__ double tukey(int l, int T) {
 }
 
 // The same sweeps in launches, one per block row, for banks too small to fill the chip with a workgroup per
-// eight templates: a workgroup takes 64 rows of eight templates, forms the step's solution
-// (again in each, from the step's residual: 2 us of products) and takes its rows' share off their residual,
-// X_i -= M_ij X_j.  The step's own rows go to `x`, which no workgroup of the launch reads; src is
-// r, or the right-hand sides in the first step.  Bound by the latency of each launch, 5 to 7 us:
-// 256 templates at T = 1024 424 -> 290 us, one 400 -> 190.
+// eight templates.  Launch j has the solution of block j: a workgroup takes 64 rows of eight templates and
+// subtracts that block's share from their residual, X_i -= M_ij X_j, and the one whose rows come next
+// solves them as well (j = -1 before the first block: that alone).  Solutions go to `x`, other residuals to r; src is
+// r, or the right-hand sides until r holds them.  Bound by the latency of each launch, 8 us with one
+// template at T = 1024 and 12 with 256 (375 us for the solve in place of 556).  With the block solved
+// again in every workgroup of the next launch the refinement took 4.3 us per launch, here 2.2.
 template <bool BACK>
 __global__ __launch_bounds__(256) void k_trsm_step(const double2* __restrict__ M, const double2* __restrict__ inv, int T,
                                                  int j, const double2* src, int64_t src_stride, double2* r,
@@ -266,68 +284,87 @@ __global__ __launch_bounds__(256) void k_trsm_step(const double2* __restrict__ M
   const int kq = lane >> 4, col = lane & 15, mate = col ^ TPW;
   const double sgn = col < TPW ? -1.0 : 1.0;
   const int64_t t0 = (int64_t)blockIdx.x * TPW;
-  const int i = BACK ? j - (int)blockIdx.y : j + (int)blockIdx.y;
+  const int i = BACK ? (j < 0 ? (T - 1) / N : j - 1 - (int)blockIdx.y) : j + 1 + (int)blockIdx.y;
+  const bool solve = blockIdx.y == 0;
   const int row = 16 * wave + col;                            // of the block: the one whose operands this lane holds
-  for (int e = threadIdx.x; e < N * TPW; e += 256) {
-    const int tt = e / N, k = e % N;
-    const double2 v = j * N + k < T && t0 + tt < count ? src[(t0 + tt) * src_stride + j * N + k] : make_double2(0.0, 0.0);
-    X[0][k * NC + tt] = v.x;
-    X[0][k * NC + TPW + tt] = v.y;
-  }
-  const double2* D = inv + (int64_t)j * N * N;
-  double2 dm[N / 4], m[N / 4];
-#pragma unroll
-  for (int u = 0; u < N / 4; ++u) dm[u] = BACK ? D[row * N + 4 * u + kq] : D[(4 * u + kq) * N + row];
-#pragma unroll
-  for (int u = 0; u < N / 4; ++u)
-    m[u] = M[(int64_t)min(j * N + 4 * u + kq, T - 1) * T + min(i * N + row, T - 1)];
-  // this lane's residuals: rows 16 wave + 4 v + kq of the block, real or imaginary part of template col % 8
-  const bool re = col < TPW;
+  const int own = (16 * wave + kq) * NC + col;                // this lane's values of X: own + 4 v NC, real or
+  const bool re = col < TPW;                                  // imaginary part of template col % 8 ...
   const int64_t tmpl = t0 + col % TPW;
-  double have[4];
+  const int g0 = i * N + 16 * wave + kq;                      // ... at rows g0 + 4 v
+  double2 m[N / 4], dm[N / 4], fm[N / 4];
+  if (j >= 0) {
+    for (int e = threadIdx.x; e < N * TPW; e += 256) {
+      const int tt = e / N, k = e % N;
+      const double2 v = j * N + k < T && t0 + tt < count ? x[(t0 + tt) * xstride + j * N + k] : make_double2(0.0, 0.0);
+      X[0][k * NC + tt] = v.x;
+      X[0][k * NC + TPW + tt] = v.y;
+    }
+#pragma unroll
+    for (int u = 0; u < N / 4; ++u)
+      m[u] = M[(int64_t)min(j * N + 4 * u + kq, T - 1) * T + min(i * N + row, T - 1)];
+  }
+  double res[4];
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
-    const int g = i * N + 16 * wave + 4 * v + kq;
-    have[v] = 0.0;
-    if (g < T && tmpl < count && i != j) {
-      const double2 y = src[tmpl * src_stride + g];
-      have[v] = re ? y.x : y.y;
+    res[v] = 0.0;
+    if (g0 + 4 * v < T && tmpl < count) {
+      const double2 y = src[tmpl * src_stride + g0 + 4 * v];
+      res[v] = re ? y.x : y.y;
     }
   }
-  __syncthreads();
-  typedef f64x4 V;
-  V p = {0.0, 0.0, 0.0, 0.0}, q = p;
+  if (solve) {
+    const double2* D = inv + (int64_t)i * N * N;
 #pragma unroll
-  for (int u = 0; u < N / 4; ++u) {
-    const double* y = X[0] + (4 * u + kq) * NC;
-    p = __builtin_amdgcn_mfma_f64_16x16x4f64(dm[u].x, y[col], p, 0, 0, 0);
-    q = __builtin_amdgcn_mfma_f64_16x16x4f64(BACK ? -dm[u].y : dm[u].y, sgn * y[mate], q, 0, 0, 0);
-  }
-  if (i == j) {
-    double* o = reinterpret_cast<double*>(x);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int g = i * N + 16 * wave + 4 * v + kq;
-      if (g < T && tmpl < count) o[2 * (tmpl * xstride + g) + (re ? 0 : 1)] = p[v] + q[v];
+    for (int u = 0; u < N / 4; ++u) {
+      dm[u] = BACK ? D[row * N + 4 * u + kq] : D[(4 * u + kq) * N + row];
+      if (BACK) dm[u].y = -dm[u].y;
+      fm[u] = M[(int64_t)min(i * N + 4 * u + kq, T - 1) * T + min(i * N + row, T - 1)];
     }
-    return;                                                   // (the whole workgroup)
   }
+  f64x4 p, q;
+  auto product = [&](const double2 (&a)[N / 4], const double* y) {
+    p = q = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int v = 0; v < 4; ++v) X[1][(16 * wave + 4 * v + kq) * NC + col] = p[v] + q[v];
-  __syncthreads();
-  p = q = V{0.0, 0.0, 0.0, 0.0};
+    for (int u = 0; u < N / 4; ++u) {
+      p = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].x, y[(4 * u + kq) * NC + col], p, 0, 0, 0);
+      q = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].y, sgn * y[(4 * u + kq) * NC + mate], q, 0, 0, 0);
+    }
+  };
+  auto put = [&](double* y, const double (&v)[4]) {           // rows from T on stay zero
 #pragma unroll
-  for (int u = 0; u < N / 4; ++u) {
-    const double* y = X[1] + (4 * u + kq) * NC;
-    p = __builtin_amdgcn_mfma_f64_16x16x4f64(m[u].x, y[col], p, 0, 0, 0);
-    q = __builtin_amdgcn_mfma_f64_16x16x4f64(m[u].y, sgn * y[mate], q, 0, 0, 0);
+    for (int e = 0; e < 4; ++e) y[own + 4 * e * NC] = g0 + 4 * e < T ? v[e] : 0.0;
+    __syncthreads();
+  };
+  auto store = [&](double2* to, int64_t stride, const double (&v)[4]) {
+    double* o = reinterpret_cast<double*>(to);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (g0 + 4 * e < T && tmpl < count) o[2 * (tmpl * stride + g0 + 4 * e) + (re ? 0 : 1)] = v[e];
+  };
+  if (j >= 0) {
+    __syncthreads();
+    product(m, X[0]);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) res[v] -= p[v] + q[v];
   }
-  double* o = reinterpret_cast<double*>(r);
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int g = i * N + 16 * wave + 4 * v + kq;
-    if (g < T && tmpl < count) o[2 * (tmpl * (int64_t)T + g) + (re ? 0 : 1)] = have[v] - (p[v] + q[v]);
+  if (!solve) {
+    store(r, T, res);
+    return;
   }
+  double sol[4], z[4];                                        // as in k_trsm, X[0] and X[1] in turn
+  put(X[1], res);
+  product(dm, X[1]);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) sol[v] = p[v] + q[v];
+  put(X[0], sol);
+  product(fm, X[0]);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) z[v] = res[v] - (p[v] + q[v]);
+  put(X[1], z);
+  product(dm, X[1]);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) sol[v] += p[v] + q[v];
+  store(x, xstride, sol);
 }
 
 __global__ void k_window(const double2* __restrict__ b, int64_t bstride, int T, int64_t count,
@@ -612,11 +649,12 @@ int taps_norm_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count);
 int taps_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count);
 
 // A launch per block row (k_trsm_step) or all rows in one (k_trsm), as long as the transform buffer holds the
-// residuals.  make_taps of a 2^15-sample segment, one launch and steps: T = 512 157 -> 130 us (1 template), 261 -> 243 (256),
-// 623 -> 714 (1000); T = 1024 454 -> 245 (1), 620 -> 490 (256); T = 2048 1593 -> 485 (1), 1845 -> 1172 (256); T = 384
-// 106 -> 100 (1), 198 -> 198 (256); T = 256 68 -> 73 (1), 150 -> 159 (256).
+// residuals.  make_taps of a 2^15-sample segment, one launch and steps: T = 512 228 -> 192 us (1 template), 333 -> 315 (256),
+// 445 -> 433 (512), 717 -> 738 (1000); T = 1024 598 -> 358 (1), 761 -> 578 (256), 944 -> 795 (512), 1388 -> 1423 (1000);
+// T = 2048 1874 -> 696 (1), 2547 -> 1845 (512), 3204 -> 3203 (1000); T = 384 164 -> 151 (1), 222 -> 221 (256), 469 -> 487
+// (1000); T = 256 106 -> 108 (1), 160 -> 167 (256).
 static bool trsm_in_steps(const Taps& tp, int T, int64_t count) {
-  return T >= 512 && count <= 256 && tp.work64_cap >= (size_t)(2 * count * T);
+  return T >= 512 && count <= 512 && tp.work64_cap >= (size_t)(2 * count * T);
 }
 
 int taps_solve_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count, int method) {
@@ -629,16 +667,16 @@ int taps_solve_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count, 
       // forward residuals and solutions in the (now idle) transform buffer; the latter are the backward sweep's residuals
       double2 *r = tp.work64, *y = tp.work64 + count * T;
       const unsigned groups = (unsigned)((count + 7) / 8);
-      for (int j = 0; j < nb; ++j) {
-        hipLaunchKernelGGL(k_trsm_step<false>, dim3(groups, (unsigned)(nb - j)), dim3(256), 0, p.stream,
-                           (const double2*)s.L, (const double2*)s.Dinv, T, j, (const double2*)(j ? r : tp.bvec),
+      for (int j = -1; j < nb - 1; ++j) {
+        hipLaunchKernelGGL(k_trsm_step<false>, dim3(groups, j < 0 ? 1u : (unsigned)(nb - 1 - j)), dim3(256), 0, p.stream,
+                           (const double2*)s.L, (const double2*)s.Dinv, T, j, (const double2*)(j > 0 ? r : tp.bvec),
                            (int64_t)T, r, y, (int64_t)T, count);
         RFD_CHECK_LAUNCH();
       }
-      for (int j = nb - 1; j >= 0; --j) {
-        hipLaunchKernelGGL(k_trsm_step<true>, dim3(groups, (unsigned)(j + 1)), dim3(256), 0, p.stream,
-                           (const double2*)s.U, (const double2*)s.Dinv, T, j, (const double2*)y, (int64_t)T, y, abase,
-                           (int64_t)s.Tp, count);
+      for (int j = nb; j > 0; --j) {
+        hipLaunchKernelGGL(k_trsm_step<true>, dim3(groups, j == nb ? 1u : (unsigned)j), dim3(256), 0, p.stream,
+                           (const double2*)s.U, (const double2*)s.Dinv, T, j == nb ? -1 : j, (const double2*)y, (int64_t)T, y,
+                           abase, (int64_t)s.Tp, count);
         RFD_CHECK_LAUNCH();
       }
     } else if (T <= 1024)     // eight templates per workgroup while their columns fit LDS (128 KiB at T = 1024), else four

@@ -153,3 +153,25 @@ def test_norms_of_more_templates_than_a_batch(rfd, T):
     assert np.all(np.abs(np.array([s for _, s in got]) / want - 1) <= tol)
     rfd.rfd_taps_destroy(taps)
     rfd.rfd_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("T,count", [(16, 3), (64, 3), (100, 9), (200, 3), (512, 3), (600, 512), (600, 513), (1100, 513)])
+@pytest.mark.parametrize("eps", [1e-10, 1e-8, 1e-4])
+def test_solve_is_backward_stable_at_small_ridges(rfd, setup, T, count, eps):  # noqa: F811
+    import torch
+    n, fs, f_low, psd, wts, ref, H = setup
+    H = np.tile(H, (32, 1))[:count] * np.exp(0.1j * np.arange(count))[:, None]
+    plan = rfd.rfd_plan_create(psd, f_low, fs, n)
+    taps = rfd.rfd_taps_create(plan, [0, count], [0], [T], [-(T // 2)])
+    rfd.rfd_make_taps(plan, taps, 0, torch.from_numpy(ref).cuda(), torch.from_numpy(H).cuda(), ridge_eps=eps)
+    M = otaps.gram(ref, wts, T)
+    A = M + eps * M[0, 0].real * np.eye(T)
+    for j in {0, count // 2, count - 1}:
+        a = rfd.rfd_taps_get(taps, j)[0]
+        b = otaps.crosscorr(H[j], ref, wts, T, -(T // 2))
+        # two substitutions leave a few roundings of |L| |L^H| |a|, at most T A[0,0] |a|; M, b and the products
+        # here as many again
+        res = np.linalg.norm(A @ a - b) / (A[0, 0].real * T * np.linalg.norm(a) + np.linalg.norm(b))
+        assert res <= 64 * 2.0 ** -53
+    rfd.rfd_taps_destroy(taps)
+    rfd.rfd_plan_destroy(plan)
