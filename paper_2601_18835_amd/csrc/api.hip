@@ -919,7 +919,8 @@ int rfd_make_taps(rfd_plan* plan, rfd_taps* taps, int32_t subbank, const double*
   chunk = std::min<int64_t>(chunk, per < p.n ? 4096 : 64);
   if (centre) chunk = std::max<int64_t>(1, chunk / 2);
   chunk = std::min<int64_t>(chunk, count);
-  const size_t need_w = (size_t)std::max<int64_t>(chunk * per, p.n);
+  size_t need_w = (size_t)std::max<int64_t>(chunk * per, p.n);
+  if (method == RFD_TAPS_LS) need_w = std::max(need_w, taps_solve_work(T, count));
   if (t.work64_cap < need_w) {
     RFD_HIP(hipStreamSynchronize(p.stream));
     dfree(t.work64);

@@ -250,6 +250,7 @@ int taps_factor(Plan& p, Taps& tp, int b, double eps);            // of M + eps 
 int taps_factor_compare(Plan& p, Taps& tp, int b);                // queue: is the factor the one of g?
 int taps_factor_current(Taps& tp, bool* current);                 // wait for the answer
 int taps_solve_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count, int method);
+size_t taps_solve_work(int T, int64_t count);                     // values of work64 that a least-squares solve takes
 // sigma_fit of the taps in a64 (with the sub-bank's g), then the normalised packings
 int taps_norm_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count);
 size_t sigma_part_values(int T, int64_t count);                   // of the largest make_taps or renormalize call

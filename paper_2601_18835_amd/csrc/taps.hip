@@ -648,14 +648,14 @@ int taps_factor_current(Taps& tp, bool* current) {
 int taps_norm_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count);
 int taps_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count);
 
-// A launch per block row (k_trsm_step) or all rows in one (k_trsm), as long as the transform buffer holds the
-// residuals.  make_taps of a 2^15-sample segment, one launch and steps: T = 512 228 -> 192 us (1 template), 333 -> 315 (256),
+// A launch per block row (k_trsm_step) or all rows in one (k_trsm); by the call's sizes alone, so that equal calls give
+// equal bits.  make_taps of a 2^15-sample segment, one launch and steps: T = 512 228 -> 192 us (1 template), 333 -> 315 (256),
 // 445 -> 433 (512), 717 -> 738 (1000); T = 1024 598 -> 358 (1), 761 -> 578 (256), 944 -> 795 (512), 1388 -> 1423 (1000);
 // T = 2048 1874 -> 696 (1), 2547 -> 1845 (512), 3204 -> 3203 (1000); T = 384 164 -> 151 (1), 222 -> 221 (256), 469 -> 487
 // (1000); T = 256 106 -> 108 (1), 160 -> 167 (256).
-static bool trsm_in_steps(const Taps& tp, int T, int64_t count) {
-  return T >= 512 && count <= 512 && tp.work64_cap >= (size_t)(2 * count * T);
-}
+static bool trsm_in_steps(int T, int64_t count) { return T >= 512 && count <= 512; }
+// (the steps' residuals and forward solutions)
+size_t taps_solve_work(int T, int64_t count) { return trsm_in_steps(T, count) ? (size_t)(2 * count * T) : 0; }
 
 int taps_solve_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count, int method) {
   SubBankTaps& s = tp.sb[b];
@@ -663,7 +663,8 @@ int taps_solve_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count, 
   double2* abase = tp.a64 + s.a_base + first * s.Tp;
   if (method == RFD_TAPS_LS) {
     const int Tn = (int)round_up(T, kTrsmBlock), nb = Tn / kTrsmBlock;
-    if (trsm_in_steps(tp, T, count)) {
+    if (trsm_in_steps(T, count)) {
+      if (tp.work64_cap < taps_solve_work(T, count)) return fail(RFD_E_INVALID, "taps: work buffer too small");
       // forward residuals and solutions in the (now idle) transform buffer; the latter are the backward sweep's residuals
       double2 *r = tp.work64, *y = tp.work64 + count * T;
       const unsigned groups = (unsigned)((count + 7) / 8);

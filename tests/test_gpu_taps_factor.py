@@ -175,3 +175,22 @@ def test_solve_is_backward_stable_at_small_ridges(rfd, setup, T, count, eps):  #
         assert res <= 64 * 2.0 ** -53
     rfd.rfd_taps_destroy(taps)
     rfd.rfd_plan_destroy(plan)
+
+
+def test_taps_do_not_depend_on_earlier_calls(rfd):
+    import torch
+    n, fs, f_low = 1 << 10, 1024.0, 20.0
+    rng = np.random.default_rng(6)
+    draw = lambda m: torch.from_numpy(rng.standard_normal((m, n // 2 + 1)) + 1j * rng.standard_normal((m, n // 2 + 1))).cuda()  # noqa: E731,E501
+    ref, H, more = draw(1)[0], draw(256), draw(600)
+    plan = rfd.rfd_plan_create(rng.uniform(0.5, 2.0, n // 2 + 1), f_low, fs, n)
+    taps = rfd.rfd_taps_create(plan, [0, 256, 856], [0, 0], [512, 100], [-256, -50])
+    rfd.rfd_make_taps(plan, taps, 0, ref, H)
+    first = [rfd.rfd_taps_get(taps, j)[:2] for j in (0, 100, 255)]
+    rfd.rfd_make_taps(plan, taps, 1, ref, more)      # more scratch than the first call had
+    rfd.rfd_make_taps(plan, taps, 0, ref, H)
+    for (a, sig), j in zip(first, (0, 100, 255)):
+        got = rfd.rfd_taps_get(taps, j)
+        assert np.array_equal(got[0], a) and got[1] == sig
+    rfd.rfd_taps_destroy(taps)
+    rfd.rfd_plan_destroy(plan)
