@@ -602,6 +602,7 @@ static int launch_ols_multi(Plan& p, const Taps& t, const int* sbs, int nsb, int
 }
 
 constexpr int64_t kOlsGroupBytes = (int64_t)128 << 20;
+constexpr int64_t kOlsAlone = (int64_t)1 << 20;
 
 int launch_ols(Plan& p, const Taps& t, int64_t W, int64_t nwin, float threshold, int64_t n_lo, int64_t n_hi,
                float2* x_scratch) {
@@ -617,19 +618,25 @@ int launch_ols(Plan& p, const Taps& t, int64_t W, int64_t nwin, float threshold,
   // buffers): a launch each leaves the chip part empty at its end, and from its start where the sub-bank or the
   // output range is small.  A launch takes as many as have kOlsGroupBytes of block spectra, which
   // the last-level cache then holds until they are used.  16 uneven sub-banks of 250, N = 2^19: 2684 -> 2465 us; 8 of 512,
-  // T = 1024, N = 2^20: 5588 -> 5409 (5461 with 32 MiB, 5522 with 256); 16 of 300, T <= 100, N = 2^15: 404 -> 202; 2 of
-  // 2000, T = 512, N = 2^20: 4590 -> 4640.  A shared block-spectrum scratch keeps one launch per sub-bank.
+  // T = 1024, N = 2^20: 5588 -> 5409 (5461 with 32 MiB, 5522 with 256); 16 of 300, T <= 100, N = 2^15: 404 -> 202.  Not
+  // those of kOlsAlone block transforms and more: their ends are little of their time, and alone they keep the order
+  // of ols_tile, in which an XCD reads a tap spectrum once.  Alone and shared: 4 of 4000, T = 256, N = 2^19 (1.2 million
+  // transforms each) 8370 and 8570 us; 2 of 4000, T = 512, N = 2^20 (1.2) 8930 and 9060; 2 of 4000, T = 100, N = 2^19 (2.3)
+  // 3890 and 3880; below the line 3 of 2000, T = 512, N = 2^20 (0.6) 6730 and 6740; 2 of 2000, T = 256, N = 2^19 (0.6) 2163
+  // and 2151; 4 of 1000 (0.3) 2288 and 2145.  A shared block-spectrum scratch keeps one launch per sub-bank.
   std::vector<char> done(t.sb.size(), 0);
   if (!x_scratch && active > 1) {
+    const auto blocks = [&](const SubBankTaps& s) { return (n_hi - n_lo + s.ols_L - 1) / s.ols_L; };
+    const auto alone = [&](const SubBankTaps& s) { return blocks(s) * s.count >= kOlsAlone; };
     for (size_t b0 = 0; b0 < t.sb.size(); ++b0) {
       const SubBankTaps& s0 = t.sb[b0];
-      if (s0.count == 0 || done[b0]) continue;
+      if (s0.count == 0 || done[b0] || alone(s0)) continue;
       int sbs[kOlsMulti], nsb = 0;
       int64_t bytes = 0;
       for (size_t b = b0; b < t.sb.size() && nsb < kOlsMulti; ++b) {
         const SubBankTaps& s = t.sb[b];
-        if (s.count == 0 || done[b] || s.ols_K != s0.ols_K || s.ols_nf != s0.ols_nf) continue;
-        bytes += (n_hi - n_lo + s.ols_L - 1) / s.ols_L * s.ols_K * (int64_t)sizeof(float2);
+        if (s.count == 0 || done[b] || s.ols_K != s0.ols_K || s.ols_nf != s0.ols_nf || alone(s)) continue;
+        bytes += blocks(s) * s.ols_K * (int64_t)sizeof(float2);
         if (nsb > 0 && bytes > kOlsGroupBytes) break;
         sbs[nsb++] = (int)b;
       }
