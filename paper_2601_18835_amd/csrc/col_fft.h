@@ -25,11 +25,10 @@ struct ColFft {
   static constexpr int LP = L + L / 16 + (((C < G ? G / C : 1) - L - L / 16) % G + G) % G;
   static constexpr int LDS = C * LP;            // values
   static constexpr int TWB = 16 * kTwbStride;   // values of the second stage's twiddle table
-  // the third stage's twiddles: 8 per thread in registers, or in FP64, where they would take 32
-  // registers beside the 64 of the values, the 256 butterflies' own in LDS
+  // the third stage's twiddles are the 256 butterflies' own, in LDS: the 8 of a thread would take 16
+  // registers, or 32 in FP64, beside the 32 or 64 of the values
   static constexpr int PER = R3 > 1 ? kTw16 * R3 / 16 : 0;    // per butterfly
-  static constexpr bool TW3_LDS = true;
-  static constexpr int TW3 = TW3_LDS ? 256 * PER : 0;
+  static constexpr int TW3 = 256 * PER;
   static constexpr size_t lds_bytes = (size_t)(LDS + TWB + TW3) * sizeof(V);
   static_assert(G % C == 0 || C % G == 0, "columns of a workgroup");
 };
@@ -39,7 +38,6 @@ struct ColFft {
 template <class F, int SIGN>
 struct ColTw {
   typedef typename F::V V;
-  V c[F::R3 > 1 && !F::TW3_LDS ? kTw16 : 1];
   const V* b;      // second stage: the row of j % 16
   const V* t3;     // third stage: entries i of butterfly j + J g at t3[256 i + J g]
   static __device__ __forceinline__ V at(const V* __restrict__ ct, int m) {
@@ -52,19 +50,10 @@ struct ColTw {
       table[(e / kTw16) * kTwbStride + e % kTw16] = at(ct, tw_exponent<16>(e % kTw16, 16 * (e / kTw16)));
     b = table + (j % 16) * kTwbStride;
     t3 = table + F::TWB + j;
-    if constexpr (F::TW3_LDS) {
-      for (int e = threadIdx.x; e < F::TW3; e += F::NT)
-        table[F::TWB + e] = at(ct, tw_exponent<F::R3>(e / 256, (e % 256) * (4096 / F::L)));
-    } else if constexpr (F::R3 > 1) {
-#pragma unroll
-      for (int i = 0; i < kTw16; ++i)
-        c[i] = at(ct, tw_exponent<F::R3>(i % F::PER, (j + F::J * (i / F::PER)) * (4096 / F::L)));
-    }
+    for (int e = threadIdx.x; e < F::TW3; e += F::NT)
+      table[F::TWB + e] = at(ct, tw_exponent<F::R3>(e / 256, (e % 256) * (4096 / F::L)));
   }
-  __device__ __forceinline__ V third(int i) const {
-    if constexpr (F::TW3_LDS) return t3[256 * (i % F::PER) + F::J * (i / F::PER)];
-    else return c[i];
-  }
+  __device__ __forceinline__ V third(int i) const { return t3[256 * (i % F::PER) + F::J * (i / F::PER)]; }
 };
 
 // The stages after the first.  On entry v holds the first stage's DFT of the thread (c0, j0):
