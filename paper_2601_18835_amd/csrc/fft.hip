@@ -419,7 +419,8 @@ struct ColInput {
 // Pass A (as k_pass_a): columns [g C, (g + 1) C) of batch entries [y JT, (y + 1) JT), the next entry's
 // operands fetched during the current transform.  The inter-pass factor w_N^(i1 n2) of a
 // thread's outputs turns by constant angles from one to the next: FP64 rotations from three table
-// values, rounded to V.  Neighbouring column groups, whose runs share cache lines, go to one XCD.
+// values, rounded to V.  In FP64, where chains of up to 16 doubled the error of the correlations, every fourth factor
+// is a table product of its own.  Neighbouring column groups, whose runs share cache lines, go to one XCD.
 // Bound by memory where the batch is large: 16 FP64 correlations at N = 2^20 read 134 MB and write
 // 268 MB in 96 us (325 us with the radix-4 transform in LDS, k_pass_a, which the lengths
 // below 256 keep); 8 FP32 reference integrands 66 -> 36 us; the data transform 24 -> 13 us.
@@ -452,9 +453,10 @@ __global__ __launch_bounds__(F::NT) __attribute__((amdgpu_waves_per_eu(2))) void
     V* Yb = Y + (int64_t)b * n1 * F::L;
     int jo = j;                                      // formed anew: 16 row addresses carried through
     asm volatile("" : "+v"(jo));                     // the loop would take 32 registers
+    constexpr bool kAnew = sizeof(V) == 16;
     constexpr int RF = F::R3 == 1 ? 16 : F::R3;      // outputs per group, turn_f apart
     double2 wg = base;                               // (likewise: 16 factors would take 64)
-    asm volatile("" : "+v"(wg.x), "+v"(wg.y));
+    if constexpr (!kAnew) asm volatile("" : "+v"(wg.x), "+v"(wg.y));
 #pragma unroll
     for (int g = 0; g < 16 / RF; ++g) {
       double2 w = wg;
@@ -465,10 +467,14 @@ __global__ __launch_bounds__(F::NT) __attribute__((amdgpu_waves_per_eu(2))) void
         for (int s = 0; s < RF; ++s)
           if ((F::R3 == 1 ? dft16_freq(s) : dftr_freq<F::R3>(s)) == f) q = g * RF + s;
         const int n2 = jo + col_fft_step<F>(q);
+        if (kAnew && (g * RF + f) % 4 == 0) {
+          w = twiddle_n(coarse, fine, (uint32_t)i1 * (uint32_t)n2 & nmask, SIGN);
+          if (f == 0) wg = w;
+        }
         if (((n2 - row_lo) & (F::L - 1)) < row_cnt) Yb[(uint32_t)(n2 * n1 + i1)] = cmul(v[q], to_v(w, V{}));
-        if (f + 1 < RF) w = cmul(w, turn_f);
+        if (f + 1 < RF && !(kAnew && (f + 1) % 4 == 0)) w = cmul(w, turn_f);
       }
-      if (g + 1 < 16 / RF) wg = cmul(wg, turn_g);
+      if (g + 1 < 16 / RF && !(kAnew && (g + 1) * RF % 4 == 0)) wg = cmul(wg, turn_g);
     }
   }
 }
@@ -721,21 +727,34 @@ __global__ __launch_bounds__(F::NT) __attribute__((amdgpu_waves_per_eu(kLagAhead
     if (k0s) k0 = k0s[b];                  // per-template lag window
     V* pb = part + ((int64_t)b * gridDim.x + g) * T;
     // share of lag m = k0 + l: e^{+2 pi i c0 m / N} sum_c Y_c[m mod L] (e^{+2 pi i m / N})^c, the sum by Horner's
-    // rule and the factor before it turning from one of the thread's lags to its next, in FP64
+    // rule and the factor before it turning from one of the thread's lags to its next, in FP64.  FP64 columns are
+    // added four at a time: the error of e^{2 pi i m / N} grows with its power, at 16 to twice that of table products
     double2 base = twiddle_n(coarse, fine, (uint32_t)c0 * (uint32_t)(k0 + (int)threadIdx.x) & nmask, +1);
     for (int l = threadIdx.x; l < T; l += F::NT) {
       const uint32_t m = (uint32_t)(k0 + l) & nmask;
       const V* row = buf + lpad(m % F::L);
       const double2 step = twiddle_n(coarse, fine, m, +1);
-      double2 acc = make_double2(row[(F::C - 1) * F::LP].x, row[(F::C - 1) * F::LP].y);
+      constexpr int Q = sizeof(V) == 16 && F::C > 4 ? 4 : F::C;
+      auto horner = [&](double2 a, double2 w, V y) {
+        return make_double2(fma(a.x, w.x, fma(-a.y, w.y, (double)y.x)), fma(a.x, w.y, fma(a.y, w.x, (double)y.y)));
+      };
+      auto columns = [&](int k) {            // k .. k + Q - 1
+        double2 a = make_double2(row[(k + Q - 1) * F::LP].x, row[(k + Q - 1) * F::LP].y);
 #pragma unroll
-      for (int k = F::C - 2; k >= 0; --k) {
-        const V y = row[k * F::LP];
-        acc = make_double2(fma(acc.x, step.x, fma(-acc.y, step.y, (double)y.x)),
-                           fma(acc.x, step.y, fma(acc.y, step.x, (double)y.y)));
+        for (int i = Q - 2; i >= 0; --i) a = horner(a, step, row[(k + i) * F::LP]);
+        return a;
+      };
+      double2 acc = columns(F::C - Q);
+      if constexpr (Q < F::C) {
+        const double2 turn = twiddle_n(coarse, fine, Q * m & nmask, +1);
+#pragma unroll
+        for (int k = F::C - 2 * Q; k >= 0; k -= Q) acc = horner(acc, turn, columns(k));
       }
       pb[l] = to_v(cmul(acc, base), V{});
-      base = cmul(base, adv);
+      if (sizeof(V) == 16 && l / F::NT % 4 == 3 && l + F::NT < T)       // (and chains of four here)
+        base = twiddle_n(coarse, fine, (uint32_t)c0 * (uint32_t)(k0 + l + F::NT) & nmask, +1);
+      else
+        base = cmul(base, adv);
     }
     __syncthreads();                       // the next entry's first stage overwrites the rows
   }
