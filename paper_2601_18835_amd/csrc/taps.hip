@@ -112,29 +112,68 @@ __global__ void k_upper(const double2* __restrict__ L, int T, double2* __restric
   }
 }
 
-// Inverses of the 64 x 64 diagonal blocks of L, column-major, the last one padded with the
-// identity: one workgroup per block, a forward substitution per column in LDS.  Once per factor.
+// Inverses of the 64 x 64 diagonal blocks of L, column-major, the last one padded with the identity: one workgroup
+// per block, in LDS.  Its four 16 x 16 diagonal tiles by substitution, a column per lane; then, a row of tiles at a time,
+// X = -L_ii^-1 (L_i0 .. L_i,i-1) X above.  Bound by the latency of the substitutions and sums; a substitution over all 64
+// rows took 86 us, half of the first call for a sub-bank of short filters, now 24.
 constexpr int kTrsmBlock = 64;
-__global__ __launch_bounds__(kTrsmBlock) void k_diag_inv(const double2* __restrict__ L, int T,
-                                                        double2* __restrict__ inv) {
-  constexpr int N = kTrsmBlock, S = N + 1;
+__global__ __launch_bounds__(256) void k_diag_inv(const double2* __restrict__ L, int T, double2* __restrict__ inv) {
+  constexpr int N = kTrsmBlock, S = N + 1, B = 16;
   extern __shared__ double2 sh[];
   double2* blk = sh;               // [row][col]
   double2* x = sh + N * S;         // [row][col], the inverse
-  const int o = blockIdx.x * N, c = threadIdx.x;
-  for (int j = 0; j < N; ++j) {    // lane c loads row c of column j
-    double2 v = make_double2(c == j ? 1.0 : 0.0, 0.0);
-    if (o + c < T && o + j < T && c >= j) v = L[(int64_t)(o + j) * T + o + c];
-    blk[c * S + j] = v;
+  const int o = blockIdx.x * N;
+  for (int e = threadIdx.x; e < N * N; e += 256) {
+    const int r = e % N, c = e / N;
+    double2 v = make_double2(c == r ? 1.0 : 0.0, 0.0);
+    if (o + r < T && o + c < T && r >= c) v = L[(int64_t)(o + c) * T + o + r];
+    blk[r * S + c] = v;
+    x[r * S + c] = make_double2(0.0, 0.0);
   }
   __syncthreads();
-  for (int r = 0; r < N; ++r) {    // column c: every lane walks all rows, zero above the diagonal
-    double2 s = make_double2(r == c ? 1.0 : 0.0, 0.0);
-    for (int k = 0; k < r; ++k) s = csub(s, cmul(blk[r * S + k], x[k * S + c]));
-    const double d = 1.0 / blk[r * S + r].x;
-    x[r * S + c] = make_double2(s.x * d, s.y * d);
+  if (threadIdx.x < N) {
+    const int c = threadIdx.x, t0 = c / B * B;
+    const double2* tile = blk + t0 * S + t0;
+    double2 y[B];                          // (zero above the diagonal)
+#pragma unroll
+    for (int r = 0; r < B; ++r) {
+      double2 s = make_double2(t0 + r == c ? 1.0 : 0.0, 0.0);
+#pragma unroll
+      for (int k = 0; k < r; ++k) s = csub(s, cmul(tile[r * S + k], y[k]));
+      const double d = 1.0 / tile[r * S + r].x;
+      y[r] = make_double2(s.x * d, s.y * d);
+      x[(t0 + r) * S + c] = y[r];
+    }
   }
-  for (int r = 0; r < N; ++r) inv[((int64_t)blockIdx.x * N + c) * N + r] = x[r * S + c];
+  __syncthreads();
+#pragma unroll
+  for (int i = B; i < N; i += B) {         // rows i .. i + B - 1 of the columns before i
+    for (int e = threadIdx.x; e < B * i; e += 256) {
+      const int r = i + e / i, c = e % i;
+      double2 s = make_double2(0.0, 0.0);
+      for (int k0 = c / B * B; k0 < i; k0 += B)
+#pragma unroll
+        for (int k = k0; k < k0 + B; ++k) s = csub(s, cmul(blk[r * S + k], x[k * S + c]));
+      x[r * S + c] = s;
+    }
+    __syncthreads();
+    double2 y[B * (N - B) / 256];
+#pragma unroll
+    for (int u = 0; u < B * i / 256; ++u) {
+      const int e = threadIdx.x + 256 * u, r = i + e / i, c = e % i;
+      y[u] = make_double2(0.0, 0.0);
+#pragma unroll
+      for (int k = i; k < i + B; ++k) y[u] = cadd(y[u], cmul(x[r * S + k], x[k * S + c]));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < B * i / 256; ++u) {
+      const int e = threadIdx.x + 256 * u;
+      x[(i + e / i) * S + e % i] = y[u];
+    }
+    __syncthreads();
+  }
+  for (int e = threadIdx.x; e < N * N; e += 256) inv[(int64_t)blockIdx.x * N * N + e] = x[(e % N) * S + e / N];
 }
 
 // (L L^H) a = b for TPW templates per workgroup on the FP64 matrix cores: their right-hand sides stay
@@ -606,7 +645,7 @@ int taps_factor(Plan& p, Taps& tp, int b, double eps) {
   RFD_CHECK_LAUNCH();
   hipLaunchKernelGGL(k_upper, dim3(blocks), dim3(256), 0, p.stream, s.L, T, s.U);
   RFD_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_diag_inv, dim3((unsigned)((T + kTrsmBlock - 1) / kTrsmBlock)), dim3(kTrsmBlock),
+  hipLaunchKernelGGL(k_diag_inv, dim3((unsigned)((T + kTrsmBlock - 1) / kTrsmBlock)), dim3(256),
                      (size_t)2 * kTrsmBlock * (kTrsmBlock + 1) * sizeof(double2), p.stream, s.L, T, s.Dinv);
   RFD_CHECK_LAUNCH();
   int hinfo = 0;
