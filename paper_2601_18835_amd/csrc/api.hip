@@ -780,10 +780,8 @@ static void taps_free(Taps& t) {
   dfree(t.d_it_off); dfree(t.d_it_sb); dfree(t.d_it_S); dfree(t.d_it_nsg);
   dfree(t.d_shift); dfree(t.peak_z); dfree(t.k0buf); dfree(t.peak_part); dfree(t.peak_idx);
   dfree(t.sig_part);
-  if (t.factor_differs) (void)hipHostFree(t.factor_differs);
-  if (t.factor_event) (void)hipEventDestroy(t.factor_event);
-  t.factor_differs = nullptr;
-  t.factor_event = nullptr;
+  if (t.factor_answer) (void)hipHostFree(t.factor_answer);
+  t.factor_answer = nullptr;
 }
 
 int rfd_taps_create(rfd_plan* plan, int32_t n_subbanks, const int64_t* offsets, const int32_t* ref_id,
@@ -857,15 +855,12 @@ int rfd_taps_create(rfd_plan* plan, int32_t n_subbanks, const int64_t* offsets, 
   size_t n_part = 0;
   for (auto& s : t.sb) n_part = std::max(n_part, sigma_part_values(s.T, s.count));
   TRY(dalloc(&t.sig_part, n_part));
-  if (hipHostMalloc((void**)&t.factor_differs, sizeof(int), hipHostMallocDefault) != hipSuccess) {
-    t.factor_differs = nullptr;
+  if (hipHostMalloc((void**)&t.factor_answer, sizeof(unsigned int), hipHostMallocDefault) != hipSuccess) {
+    t.factor_answer = nullptr;
     (void)hipGetLastError();
     TRY(fail(RFD_E_NOMEM, "host allocation failed"));
   }
-  if (hipEventCreateWithFlags(&t.factor_event, hipEventDisableTiming) != hipSuccess) {
-    t.factor_event = nullptr;
-    TRY(fail(RFD_E_DEVICE, "taps: hipEventCreate failed"));
-  }
+  *t.factor_answer = 0;
 #undef TRY
   if (hipMemsetAsync(t.d_shift, 0, std::max<int64_t>(t.n_templates, 1) * sizeof(int32_t), p.stream) != hipSuccess ||
       hipMemsetAsync(t.pbf, 0, p16 * sizeof(uint4), p.stream) != hipSuccess ||
@@ -1011,7 +1006,7 @@ int rfd_make_taps(rfd_plan* plan, rfd_taps* taps, int32_t subbank, const double*
   }
   if (compare) {
     bool current = false;
-    rc = taps_factor_current(t, &current);
+    rc = taps_factor_current(p, t, &current);
     if (!rc && !current) rc = taps_factor(p, t, subbank, ridge_eps);
     if (rc) return rc;
   }

@@ -202,8 +202,8 @@ struct Taps {
   double* peak_part = nullptr; int32_t* peak_idx = nullptr; size_t peak_parts_cap = 0;   // workgroup maxima
   int32_t* k0buf = nullptr; size_t k0buf_cap = 0;      // per-template k0 of one make_taps call
   double* sig_part = nullptr;                          // sums of sigma_fit^2 over parts of the taps (sigma_part_values)
-  int* factor_differs = nullptr;    // pinned: the last taps_factor_compare's answer, complete at factor_event
-  hipEvent_t factor_event = nullptr;
+  unsigned int* factor_answer = nullptr;               // pinned: the last taps_factor_compare's answer (k_g_differs)
+  unsigned int compares = 0;                           // its number
 };
 
 // FIR tiling shared by packing and kernels
@@ -248,7 +248,7 @@ int launch_band_rows(Plan& p, int b0, int nb, float2* out, const double2* work);
 // ---------------------------------------------------- launchers (taps.hip)
 int taps_factor(Plan& p, Taps& tp, int b, double eps);            // of M + eps g[0] I from the sub-bank's g
 int taps_factor_compare(Plan& p, Taps& tp, int b);                // queue: is the factor the one of g?
-int taps_factor_current(Taps& tp, bool* current);                 // wait for the answer
+int taps_factor_current(Plan& p, Taps& tp, bool* current);        // wait for the answer
 int taps_solve_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count, int method);
 size_t taps_solve_work(int T, int64_t count);                     // values of work64 that a least-squares solve takes
 // sigma_fit of the taps in a64 (with the sub-bank's g), then the normalised packings

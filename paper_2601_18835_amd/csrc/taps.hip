@@ -15,6 +15,7 @@
 // The FIR applies c = conj(a) sigma_ref / sigma_fit to zhat = z_ref/sigma_ref,
 // so its output is directly the normalised SNR of h_fit.
 #include <algorithm>
+#include <chrono>
 
 #include "dev_common.h"
 #include "rfd_internal.h"
@@ -661,26 +662,36 @@ int taps_factor(Plan& p, Taps& tp, int b, double eps) {
 // The factor is a function of g and the ridge alone, and g of the plan's weights and the caller's reference: where
 // either has changed since, g has, and the factor with it.  The sums that make g have a fixed
 // order, so that unchanged inputs give the same bits.
+// answer: pinned, call << 1 | differs.
 __global__ __launch_bounds__(256) void k_g_differs(const double2* __restrict__ g, const double2* __restrict__ gf, int T,
-                                                 int* __restrict__ differs) {
+                                                 unsigned int call, unsigned int* __restrict__ answer) {
   int d = 0;
   for (int i = threadIdx.x; i < T; i += 256)
     d |= __double_as_longlong(g[i].x) != __double_as_longlong(gf[i].x) ||
          __double_as_longlong(g[i].y) != __double_as_longlong(gf[i].y);
   d = __syncthreads_or(d);
-  if (threadIdx.x == 0) *differs = d;
+  if (threadIdx.x == 0)
+    __hip_atomic_store(answer, call << 1 | (d ? 1u : 0u), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 int taps_factor_compare(Plan& p, Taps& tp, int b) {
   const SubBankTaps& s = tp.sb[b];
+  tp.compares = (tp.compares + 1) & 0x7FFFFFFFu;
   hipLaunchKernelGGL(k_g_differs, dim3(1), dim3(256), 0, p.stream, (const double2*)s.g, (const double2*)s.gf, s.T,
-                     tp.factor_differs);
+                     tp.compares, tp.factor_answer);
   RFD_CHECK_LAUNCH();
-  RFD_HIP(hipEventRecord(tp.factor_event, p.stream));
   return RFD_OK;
 }
-int taps_factor_current(Taps& tp, bool* current) {
-  RFD_HIP(hipEventSynchronize(tp.factor_event));
-  *current = *(volatile int*)tp.factor_differs == 0;
+// Read as it comes, for a while: it is mostly there when the correlations are queued.  (An event for it took 4 us of
+// a call's 43 at T = 8, 8 templates.)
+int taps_factor_current(Plan& p, Taps& tp, bool* current) {
+  const auto answered = [&] { return __atomic_load_n(tp.factor_answer, __ATOMIC_ACQUIRE) >> 1 == tp.compares; };
+  const auto end = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
+  while (!answered() && std::chrono::steady_clock::now() < end) {}
+  if (!answered()) {
+    RFD_HIP(hipStreamSynchronize(p.stream));
+    if (!answered()) return fail(RFD_E_DEVICE, "taps: the factor was not compared");
+  }
+  *current = (*tp.factor_answer & 1u) == 0;
   return RFD_OK;
 }
 
