@@ -16,6 +16,7 @@
 // so its output is directly the normalised SNR of h_fit.
 #include <algorithm>
 #include <chrono>
+#include <thread>
 
 #include "dev_common.h"
 #include "rfd_internal.h"
@@ -687,8 +688,15 @@ int taps_factor_current(Plan& p, Taps& tp, bool* current) {
   const auto answered = [&] { return __atomic_load_n(tp.factor_answer, __ATOMIC_ACQUIRE) >> 1 == tp.compares; };
   const auto end = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
   while (!answered() && std::chrono::steady_clock::now() < end) {}
-  if (!answered()) {
-    RFD_HIP(hipStreamSynchronize(p.stream));
+  // (earlier work on the stream: not its wait, which would take in the correlations too)
+  while (!answered()) {
+    const hipError_t e = hipStreamQuery(p.stream);
+    if (e == hipErrorNotReady) {
+      (void)hipGetLastError();             // (not one that a later launch check is to find)
+      std::this_thread::sleep_for(std::chrono::microseconds(50));
+      continue;
+    }
+    RFD_HIP(e);
     if (!answered()) return fail(RFD_E_DEVICE, "taps: the factor was not compared");
   }
   *current = (*tp.factor_answer & 1u) == 0;

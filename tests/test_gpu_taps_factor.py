@@ -194,3 +194,26 @@ def test_taps_do_not_depend_on_earlier_calls(rfd):
         assert np.array_equal(got[0], a) and got[1] == sig
     rfd.rfd_taps_destroy(taps)
     rfd.rfd_plan_destroy(plan)
+
+
+def test_calls_queued_behind_each_other(rfd, setup):  # noqa: F811
+    """Many calls in a row without a wait: each finds out about its factor while the ones before it still run."""
+    import torch
+    n, fs, f_low, psd, wts, ref, H = setup
+    T, count = 64, 1500
+    plan = rfd.rfd_plan_create(psd, f_low, fs, n)
+    taps = rfd.rfd_taps_create(plan, [0, count], [0], [T], [-(T // 2)])
+    other = synth.taylorf2(synth.WaveformParams(6.4, 5.2), n, fs, f_low)
+    h = torch.from_numpy(np.tile(H, (100, 1))[:count]).cuda()
+    r = [torch.from_numpy(x).cuda() for x in (ref, other)]
+    for k in range(40):
+        rfd.rfd_make_taps(plan, taps, 0, r[k // 20], h, method=rfd.RFD_TAPS_LS | rfd.RFD_TAPS_CENTRE)
+    M = otaps.gram(other, wts, T)
+    A = M + 1e-4 * M[0, 0].real * np.eye(T)
+    for j in (0, 700, count - 1):
+        a, _, _, k0 = rfd.rfd_taps_get(taps, j)
+        b = otaps.crosscorr(H[j % len(H)], other, wts, T, k0)
+        res = np.linalg.norm(A @ a - b) / (A[0, 0].real * T * np.linalg.norm(a) + np.linalg.norm(b))
+        assert res <= 1e-14 * T
+    rfd.rfd_taps_destroy(taps)
+    rfd.rfd_plan_destroy(plan)
