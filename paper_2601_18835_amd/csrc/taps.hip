@@ -150,6 +150,7 @@ __global__ __launch_bounds__(256) void k_diag_inv(const double2* __restrict__ L,
   __syncthreads();
 #pragma unroll
   for (int i = B; i < N; i += B) {         // rows i .. i + B - 1 of the columns before i
+    if (o + i >= T) break;                 // (those of the identity)
     for (int e = threadIdx.x; e < B * i; e += 256) {
       const int r = i + e / i, c = e % i;
       double2 s = make_double2(0.0, 0.0);
@@ -191,17 +192,18 @@ __global__ __launch_bounds__(256) void k_diag_inv(const double2* __restrict__ L,
 // block products per block row.  256 templates at T = 1024: 2836 us with one wave per template
 // sweeping the factor's columns -> 556 us (424 unrefined); 500 at T = 256: 178 -> 75 us (47 unrefined).
 typedef __attribute__((ext_vector_type(4))) double f64x4;
-template <int TPW>
-__global__ __launch_bounds__(256) void k_trsm(const double2* __restrict__ L, const double2* __restrict__ U,
+// N: rows of a block; 16, one wave, for T <= 16 (calls of 8 templates at T = 8: 39.7 -> 32.4 us each).
+template <int TPW, int N = kTrsmBlock>
+__global__ __launch_bounds__(4 * N) void k_trsm(const double2* __restrict__ L, const double2* __restrict__ U,
                                               const double2* __restrict__ inv, int T, const double2* __restrict__ b,
                                               int64_t bstride, double2* __restrict__ a, int64_t astride,
                                               int64_t count) {
-  constexpr int NC = 2 * TPW, N = kTrsmBlock;
+  constexpr int NC = 2 * TPW;
   extern __shared__ __align__(16) double X[];       // [nb N][NC]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nb = (T + N - 1) / N;
   const int64_t t0 = (int64_t)blockIdx.x * TPW;
-  for (int e = threadIdx.x; e < nb * N * TPW; e += 256) {
+  for (int e = threadIdx.x; e < nb * N * TPW; e += 4 * N) {
     const int tt = e / (nb * N), row = e % (nb * N);
     const double2 v = row < T && t0 + tt < count ? b[(t0 + tt) * bstride + row] : make_double2(0.0, 0.0);
     X[row * NC + tt] = v.x;
@@ -243,13 +245,13 @@ __global__ __launch_bounds__(256) void k_trsm(const double2* __restrict__ L, con
       const int i = sweep ? nb - 1 - s : s;
       const int r0 = i * N + 16 * wave;                       // this wave's rows
       // the diagonal block's operands (inv(L_ii) or its conjugate transpose, L_ii or U_ii), loaded ahead of the GEMM
-      const double2 *D = inv + (int64_t)i * N * N, *F = sweep ? U : L;
+      const double2 *D = inv + (int64_t)i * kTrsmBlock * kTrsmBlock, *F = sweep ? U : L;
       const int row = min(r0 + (lane & 15), T - 1);
       double2 dm[N / 4], fm[N / 4];
 #pragma unroll
       for (int u = 0; u < N / 4; ++u) {
         const int k = 4 * u + kq, r = 16 * wave + (lane & 15);
-        dm[u] = sweep ? D[r * N + k] : D[k * N + r];
+        dm[u] = sweep ? D[r * kTrsmBlock + k] : D[k * kTrsmBlock + r];
         if (sweep) dm[u].y = -dm[u].y;
         fm[u] = F[(int64_t)min(i * N + k, T - 1) * T + row];
       }
@@ -291,7 +293,7 @@ __global__ __launch_bounds__(256) void k_trsm(const double2* __restrict__ L, con
       put(x);
     }
   }
-  for (int e = threadIdx.x; e < T * TPW; e += 256) {
+  for (int e = threadIdx.x; e < T * TPW; e += 4 * N) {
     const int tt = e / T, row = e % T;
     if (t0 + tt < count) a[(t0 + tt) * astride + row] = make_double2(X[row * NC + tt], X[row * NC + TPW + tt]);
   }
@@ -738,7 +740,10 @@ int taps_solve_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count, 
                            abase, (int64_t)s.Tp, count);
         RFD_CHECK_LAUNCH();
       }
-    } else if (T <= 1024)     // eight templates per workgroup while their columns fit LDS (128 KiB at T = 1024), else four
+    } else if (T <= 16)
+      hipLaunchKernelGGL((k_trsm<8, 16>), dim3((unsigned)((count + 7) / 8)), dim3(64), (size_t)16 * 16 * sizeof(double),
+                         p.stream, s.L, s.U, s.Dinv, T, tp.bvec, (int64_t)T, abase, (int64_t)s.Tp, count);
+    else if (T <= 1024)       // eight templates per workgroup while their columns fit LDS (128 KiB at T = 1024), else four
       hipLaunchKernelGGL(k_trsm<8>, dim3((unsigned)((count + 7) / 8)), dim3(256), (size_t)Tn * 16 * sizeof(double),
                          p.stream, s.L, s.U, s.Dinv, T, tp.bvec, (int64_t)T, abase, (int64_t)s.Tp, count);
     else
