@@ -427,53 +427,55 @@ __global__ void k_window(const double2* __restrict__ b, int64_t bstride, int T, 
 // M is Hermitian: what lies left of the 16 x 16 tiles on its diagonal counts twice, what lies right of them not at all.
 // A wave takes a row of tiles and its mirror (of the same work together, whichever the row); the taps pass through LDS in
 // panels, in runs along each template (as operands from L2 eight templates met one channel of it at a time, a power of two
-// apart).  T > 128 spreads a group's rows over workgroups, whose parts k_sigma_sum adds.  Bound by the matrix cores and,
-// at small T, by the latency of its panels: 256 templates at T = 1024 in 27 us (345 by products of one
-// row at a time, 41 from L2), 500 at T = 256 in 10, and 5 for the parts.
+// apart).  Up to T = 128 a group's rows are one workgroup's of four waves, up to 256 of eight; beyond, they are spread
+// over workgroups, whose parts k_sigma_sum adds.  Bound by the matrix cores and, at small T, by the latency of its panels:
+// 256 templates at T = 1024 in 27 us and 5 for the parts (345 by products of one row at a time, 41 from L2), 500
+// at T = 256 in 13 (10 + 5 in parts).
 // The sum over the normal equations, Re(a^H b) - lam |a|^2, has T products per template and not T^2, but its
 // error is the solve's residual at small ridges and a difference of large numbers at large ones: 3e-14
 // of the norm against 1e-15 at T = 200 and a ridge of 1e-4, 2e-10 against 2e-11 at 1e-8, 3e-9 against 1e-16 at 1e8.
 constexpr int kSigmaParts = RFD_MAX_TAPS / 16 / 2 / 4;
 constexpr int64_t kSigmaBatch = 4096;
 constexpr int kSigmaPanel = 128, kSigmaStride = 17;      // columns of a panel; values from one to the next (odd: banks)
-static int sigma_parts(int T) { return ((T + 15) / 16 + 7) / 8; }
+static int sigma_parts(int T) { return T <= 256 ? 1 : ((T + 15) / 16 + 7) / 8; }
 size_t sigma_part_values(int T, int64_t count) {
   static_assert(kSigmaParts * 128 == RFD_MAX_TAPS, "a wave has a row of tiles and its mirror");
   const int parts = sigma_parts(T);
   return parts > 1 ? (size_t)(parts * std::min(count, kSigmaBatch)) : 0;
 }
 // part: [gridDim.y][count], or with one workgroup per group NULL and the norms to sigma
-__global__ __launch_bounds__(256) void k_sigma_fit(const double2* __restrict__ a, int64_t astride, int T,
+template <int W>
+__global__ __launch_bounds__(64 * W) void k_sigma_fit(const double2* __restrict__ a, int64_t astride, int T,
                                                  const double2* __restrict__ g, int64_t count,
                                                  double* __restrict__ part, double* __restrict__ sigma) {
-  constexpr int TPW = 8, PW = kSigmaPanel, ST = kSigmaStride;
+  constexpr int TPW = 8, PW = kSigmaPanel, ST = kSigmaStride, NT = 64 * W;
   extern __shared__ double2 gs[];                     // g, then two panels [PW][ST]
   double* panels = reinterpret_cast<double*>(gs + T);
-  __shared__ double red[4][TPW];
+  __shared__ double red[W][TPW];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int kq = lane >> 4, col = lane & 15;
   const int64_t t0 = (int64_t)blockIdx.x * TPW;
-  double2 next[PW * TPW / 256];
+  double2 next[PW * TPW / NT];
   auto fetch = [&](int c) {
 #pragma unroll
-    for (int i = 0; i < PW * TPW / 256; ++i) {
-      const int e = threadIdx.x + 256 * i, tt = e / PW, k = c + e % PW;
+    for (int i = 0; i < PW * TPW / NT; ++i) {
+      const int e = threadIdx.x + NT * i, tt = e / PW, k = c + e % PW;
       next[i] = k < T && t0 + tt < count ? a[(t0 + tt) * astride + k] : make_double2(0.0, 0.0);
     }
   };
   auto store = [&](double* x) {
 #pragma unroll
-    for (int i = 0; i < PW * TPW / 256; ++i) {
-      const int e = threadIdx.x + 256 * i, tt = e / PW, k = e % PW;
+    for (int i = 0; i < PW * TPW / NT; ++i) {
+      const int e = threadIdx.x + NT * i, tt = e / PW, k = e % PW;
       x[k * ST + tt] = next[i].x;
       x[k * ST + TPW + tt] = next[i].y;
     }
   };
   fetch(0);
-  for (int i = threadIdx.x; i < T; i += 256) gs[i] = g[i];
+  for (int i = threadIdx.x; i < T; i += NT) gs[i] = g[i];
   store(panels);
   __syncthreads();
-  const int nt = (T + 15) / 16, unit = blockIdx.y * 4 + wave;
+  const int nt = (T + 15) / 16, unit = blockIdx.y * W + wave;
   // first rows of the two tiles, T where the wave has none; the lane holds M operands of row r0 + col (of row T - 1
   // past the end, where they meet zeros)
   const int rows[2] = {2 * unit < nt ? 16 * unit : T, nt - 1 - unit > unit ? 16 * (nt - 1 - unit) : T};
@@ -521,7 +523,9 @@ __global__ __launch_bounds__(256) void k_sigma_fit(const double2* __restrict__ a
   if (lane < TPW) red[wave][lane] = acc;
   __syncthreads();
   if (threadIdx.x < TPW && t0 + lane < count) {
-    const double s = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < W; w += 4) s += (red[w][lane] + red[w + 1][lane]) + (red[w + 2][lane] + red[w + 3][lane]);
     if (part) part[blockIdx.y * count + t0 + lane] = s;
     else sigma[t0 + lane] = sqrt(s);
   }
@@ -539,8 +543,11 @@ static int launch_sigma_fit(Plan& p, Taps& tp, const double2* a, int64_t astride
   const int64_t batch = parts > 1 ? kSigmaBatch : count;
   for (int64_t t0 = 0; t0 < count; t0 += batch) {
     const int64_t cn = std::min(batch, count - t0);
-    hipLaunchKernelGGL(k_sigma_fit, dim3((unsigned)((cn + 7) / 8), (unsigned)parts), dim3(256),
-                       (size_t)T * sizeof(double2) + (size_t)2 * kSigmaPanel * kSigmaStride * sizeof(double), p.stream, a + t0 * astride, astride, T, g, cn, parts > 1 ? tp.sig_part : nullptr, sigma + t0);
+    const bool wide = T > 128 && parts == 1;
+    hipLaunchKernelGGL(wide ? k_sigma_fit<8> : k_sigma_fit<4>, dim3((unsigned)((cn + 7) / 8), (unsigned)parts),
+                       dim3(wide ? 512 : 256),
+                       (size_t)T * sizeof(double2) + (size_t)2 * kSigmaPanel * kSigmaStride * sizeof(double), p.stream,
+                       a + t0 * astride, astride, T, g, cn, parts > 1 ? tp.sig_part : nullptr, sigma + t0);
     RFD_CHECK_LAUNCH();
     if (parts == 1) continue;
     hipLaunchKernelGGL(k_sigma_sum, dim3((unsigned)((cn + 255) / 256)), dim3(256), 0, p.stream,

@@ -121,7 +121,7 @@ def _norms(a, M):
     return np.sqrt(sq), 2.0 ** -52 * (2 * T + 32) * g0 * np.sum(np.abs(a), axis=1) ** 2 / sq
 
 
-@pytest.mark.parametrize("T,count", [(1, 3), (15, 8), (16, 9), (17, 3), (128, 3), (129, 3), (500, 3)])
+@pytest.mark.parametrize("T,count", [(1, 3), (15, 8), (16, 9), (17, 3), (128, 3), (129, 3), (256, 17), (257, 3), (500, 3)])
 @pytest.mark.parametrize("eps", [1e-8, 1e-4, 1.0, 1e4, 1e8, 1e16])
 def test_norm_at_every_ridge(rfd, setup, T, count, eps):  # noqa: F811
     import torch
@@ -136,7 +136,7 @@ def test_norm_at_every_ridge(rfd, setup, T, count, eps):  # noqa: F811
     rfd.rfd_plan_destroy(plan)
 
 
-@pytest.mark.parametrize("T", [100, 144])
+@pytest.mark.parametrize("T", [100, 144, 260])
 def test_norms_of_more_templates_than_a_batch(rfd, T):
     import torch
     n, fs, f_low, count = 1 << 10, 1024.0, 20.0, 4101
