@@ -190,7 +190,7 @@ __global__ __launch_bounds__(256) void k_diag_inv(const double2* __restrict__ L,
 // from the exact solution.  Bound by the matrix cores where count fills the chip: 2 T^2 / 4 / 16 / 4
 // pairs of 64-cycle instructions per wave, 0.4 ms at T = 1024 however few the templates, and three more
 // block products per block row.  256 templates at T = 1024: 2836 us with one wave per template
-// sweeping the factor's columns -> 556 us (424 unrefined); 500 at T = 256: 178 -> 75 us (47 unrefined).
+// sweeping the factor's columns -> 520 us (424 unrefined); 500 at T = 256: 178 -> 70 us (47 unrefined).
 typedef __attribute__((ext_vector_type(4))) double f64x4;
 // N: rows of a block; 16, one wave, for T <= 16 (calls of 8 templates at T = 8: 39.7 -> 32.4 us each).
 template <int TPW, int N = kTrsmBlock>
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(4 * N) void k_trsm(const double2* __restrict__ L, c
       for (int u = 0; u < 8; ++u) {
         const double* x = X + (c + 4 * u + kq) * NC;
         p = __builtin_amdgcn_mfma_f64_16x16x4f64(m[u].x, x[col], p, 0, 0, 0);
-        q = __builtin_amdgcn_mfma_f64_16x16x4f64(m[u].y, sgn * x[mate], q, 0, 0, 0);
+        q = __builtin_amdgcn_mfma_f64_16x16x4f64(m[u].y, x[mate], q, 0, 0, 0);
       }
     };
     double2 m[8], n[8];
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(4 * N) void k_trsm(const double2* __restrict__ L, c
         for (int u = 0; u < N / 4; ++u) {
           const double* x = X + (i * N + 4 * u + kq) * NC;
           p = __builtin_amdgcn_mfma_f64_16x16x4f64(m[u].x, x[col], p, 0, 0, 0);
-          q = __builtin_amdgcn_mfma_f64_16x16x4f64(m[u].y, sgn * x[mate], q, 0, 0, 0);
+          q = __builtin_amdgcn_mfma_f64_16x16x4f64(m[u].y, x[mate], q, 0, 0, 0);
         }
         __syncthreads();
       };
@@ -277,19 +277,19 @@ __global__ __launch_bounds__(4 * N) void k_trsm(const double2* __restrict__ L, c
       };
       double res[4], sol[4], x[4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) res[v] = X[(r0 + 4 * v + kq) * NC + col] - (p[v] + q[v]);
+      for (int v = 0; v < 4; ++v) res[v] = X[(r0 + 4 * v + kq) * NC + col] - (p[v] + sgn * q[v]);
       put(res);
       product(dm);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) sol[v] = p[v] + q[v];
+      for (int v = 0; v < 4; ++v) sol[v] = p[v] + sgn * q[v];
       put(sol);
       product(fm);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) x[v] = res[v] - (p[v] + q[v]);
+      for (int v = 0; v < 4; ++v) x[v] = res[v] - (p[v] + sgn * q[v]);
       put(x);
       product(dm);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) x[v] = sol[v] + (p[v] + q[v]);
+      for (int v = 0; v < 4; ++v) x[v] = sol[v] + (p[v] + sgn * q[v]);
       put(x);
     }
   }
@@ -315,7 +315,7 @@ __device__ double tukey(int l, int T) {
 // subtracts that block's share from their residual, X_i -= M_ij X_j, and the one whose rows come next
 // solves them as well (j = -1 before the first block: that alone).  Solutions go to `x`, other residuals to r; src is
 // r, or the right-hand sides until r holds them.  Bound by the latency of each launch, 8 us with one
-// template at T = 1024 and 12 with 256 (375 us for the solve in place of 556).  With the block solved
+// template at T = 1024 and 11 with 256 (364 us for the solve in place of 520).  With the block solved
 // again in every workgroup of the next launch the refinement took 4.3 us per launch, here 2.2.
 template <bool BACK>
 __global__ __launch_bounds__(256) void k_trsm_step(const double2* __restrict__ M, const double2* __restrict__ inv, int T,
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(256) void k_trsm_step(const double2* __restrict__ M
 #pragma unroll
     for (int u = 0; u < N / 4; ++u) {
       p = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].x, y[(4 * u + kq) * NC + col], p, 0, 0, 0);
-      q = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].y, sgn * y[(4 * u + kq) * NC + mate], q, 0, 0, 0);
+      q = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].y, y[(4 * u + kq) * NC + mate], q, 0, 0, 0);
     }
   };
   auto put = [&](double* y, const double (&v)[4]) {           // rows from T on stay zero
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(256) void k_trsm_step(const double2* __restrict__ M
     __syncthreads();
     product(m, X[0]);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) res[v] -= p[v] + q[v];
+    for (int v = 0; v < 4; ++v) res[v] -= p[v] + sgn * q[v];
   }
   if (!solve) {
     store(r, T, res);
@@ -398,15 +398,15 @@ __global__ __launch_bounds__(256) void k_trsm_step(const double2* __restrict__ M
   put(X[1], res);
   product(dm, X[1]);
 #pragma unroll
-  for (int v = 0; v < 4; ++v) sol[v] = p[v] + q[v];
+  for (int v = 0; v < 4; ++v) sol[v] = p[v] + sgn * q[v];
   put(X[0], sol);
   product(fm, X[0]);
 #pragma unroll
-  for (int v = 0; v < 4; ++v) z[v] = res[v] - (p[v] + q[v]);
+  for (int v = 0; v < 4; ++v) z[v] = res[v] - (p[v] + sgn * q[v]);
   put(X[1], z);
   product(dm, X[1]);
 #pragma unroll
-  for (int v = 0; v < 4; ++v) sol[v] += p[v] + q[v];
+  for (int v = 0; v < 4; ++v) sol[v] += p[v] + sgn * q[v];
   store(x, xstride, sol);
 }
 
@@ -716,10 +716,10 @@ int taps_norm_and_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count);
 int taps_pack(Plan& p, Taps& tp, int b, int64_t first, int64_t count);
 
 // A launch per block row (k_trsm_step) or all rows in one (k_trsm); by the call's sizes alone, so that equal calls give
-// equal bits.  make_taps of a 2^15-sample segment, one launch and steps: T = 512 228 -> 192 us (1 template), 333 -> 315 (256),
-// 445 -> 433 (512), 717 -> 738 (1000); T = 1024 598 -> 358 (1), 761 -> 578 (256), 944 -> 795 (512), 1388 -> 1423 (1000);
-// T = 2048 1874 -> 696 (1), 2547 -> 1845 (512), 3204 -> 3203 (1000); T = 384 164 -> 151 (1), 222 -> 221 (256), 469 -> 487
-// (1000); T = 256 106 -> 108 (1), 160 -> 167 (256).
+// equal bits.  make_taps of a 2^15-sample segment, one launch and steps: T = 512 210 -> 180 us (1 template), 315 -> 302 (256),
+// 425 -> 422 (512), 704 -> 731 (1000); T = 1024 543 -> 339 (1), 712 -> 558 (256), 888 -> 775 (512), 1343 -> 1423 (1000);
+// T = 2048 1747 -> 663 (1), 2360 -> 1830 (512), 3024 -> 3212 (1000); T = 384 147 -> 142 (1), 210 -> 213 (256), 458 -> 479
+// (1000); T = 256 99 -> 103 (1), 151 -> 162 (256).
 static bool trsm_in_steps(int T, int64_t count) { return T >= 512 && count <= 512; }
 // (the steps' residuals and forward solutions)
 size_t taps_solve_work(int T, int64_t count) { return trsm_in_steps(T, count) ? (size_t)(2 * count * T) : 0; }
