@@ -183,6 +183,11 @@ def oracle_leg(args, w, bank, psd, seg, hrefs, np, synth):
                 shifts=shifts, centre=not args.no_lag_centre), cpu
 
 
+def ols_kernel(blocks, launches, subbanks):
+    """The overlap-save kernel of a step: k_ols_multi where sub-banks share launches."""
+    return ("k_ols_multi<" if launches < subbanks else "k_ols<") + ",".join(str(k) for k in blocks) + ">"
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -355,7 +360,7 @@ def main():
         achieved = fl / (kernel_ms * 1e-3) / 1e12
         roofline = {"bound": "alu", "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
                     "frac": round(achieved / peak, 4), "traffic": read_traffic(COUNTERS.get((w.name, prec))),
-                    "kernel": "k_ols<" + ",".join(str(k) for k in ks) + ">", "flops_per_launch": fl,
+                    "kernel": ols_kernel(ks, n_launch // ne, len(bank.subbanks)), "flops_per_launch": fl,
                     "avg_launch_ms": round(kernel_ms, 4), "launches_per_step": n_launch // ne,
                     "direct_form_equivalent_TFLOPs": round(flops_alg / (stages["fir_ms"] * 1e-3) / 1e12, 2)}
     else:
@@ -850,7 +855,7 @@ def surrogate_main(args):
     fl = (nt / n_launch) * nB * K * (5.0 * np.log2(K) + 6.0)
     achieved = fl / (kernel_ms * 1e-3) / 1e12
     roofline = {"bound": "alu", "achieved": round(achieved, 2), "peak": PEAK["ols32"], "unit": "TFLOP/s",
-                "frac": round(achieved / PEAK["ols32"], 4), "traffic": None, "kernel": f"k_ols<{K}>",
+                "frac": round(achieved / PEAK["ols32"], 4), "traffic": None, "kernel": ols_kernel([K], n_launch, len(sbs)),
                 "flops_per_launch": fl, "avg_launch_ms": round(kernel_ms, 4), "launches_per_step": n_launch}
     cpu = None
     if not args.no_cpu_baseline:

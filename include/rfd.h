@@ -81,8 +81,9 @@ typedef enum rfd_taps_method {
    * filter index m = n + d_j of each template: its cluster windows are
    * [qW, (q+1)W) in m, i.e. [qW - d_j, (q+1)W - d_j) mod N in samples, and
    * triggers report n (so they are ordered by (template, window), not
-   * necessarily by sample).  Costs one extra N-point FP64 transform per
-   * template at construction and nothing in the FIR. */
+   * necessarily by sample).  Costs a whole N-point FP64 transform per
+   * template at construction (for least squares in place of the partial
+   * one that the T lags take) and nothing in the FIR. */
   RFD_TAPS_CENTRE = 0x100
 } rfd_taps_method;
 
@@ -389,8 +390,7 @@ int rfd_plan_get_timing(rfd_plan* plan, rfd_timing* out);
  *   ols_aligned 1 (default): RFD_OLS32 may keep L = 256 nf outputs per block
  *               (nf = floor((K - T + 1) / 256)) instead of all K - T + 1,
  *               when that costs less per output: the discarded outputs
- *               are then never computed and interior blocks skip
- *               per-sample range tests; 0: always K - T + 1.
+ *               are then never computed; 0: always K - T + 1.
  * RFD_E_INVALID for values outside these sets.
  */
 typedef struct rfd_fir_config {

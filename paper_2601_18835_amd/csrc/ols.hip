@@ -270,16 +270,13 @@ __device__ __forceinline__ void ols_body(const OlsArgs& a, uint32_t bx, uint32_t
   }
 }
 
-// Bound by VALU issue: 596 VALU instructions per wave and template at K = 4096 and
-// NF = 12 (four cycles each; 342 x 512 transforms on 256 CUs then take 0.68 ms at
-// 2.4 GHz, measured 0.72), 552 at K = 2048 and NF = 7, 494 at K = 1024 and NF = 3.
-// With the twiddles taken as products between the stages and the slots' sample
-// numbers carried through the loop in 64 bits it was 685 at K = 4096 and 583 at 1024,
-// and 215 registers allowed two waves per SIMD; three now fit (143 to 161 registers,
-// none spilled).  Of the last steps, rho^2 formed only in waves that may fire and spectra in
-// the order of their 16-byte loads took 626 to 596.  Whole cases: 8 sub-banks of 512
-// templates, T = 1024, N = 2^20: 7.47 -> 5.99 ms; 4096 templates, T = 256, N = 2^19:
-// 2.73 -> 2.35 ms.
+// Bound by VALU issue: by its counters 602 VALU instructions per wave and template at K = 4096 and NF = 12 (four
+// cycles each: 342 x 512 transforms on 256 CUs then take 0.69 ms at 2.4 GHz; 0.67 measured, 11 such sub-banks in a
+// launch of k_ols_multi), 558 at K = 2048 and NF = 7.  With the twiddles taken as products between the stages and the
+// slots' sample numbers carried through the loop in 64 bits there were 80 more at K = 4096, and 215 registers allowed
+// two waves per SIMD; three now fit (143 to 161 registers, none spilled).  rho^2 formed only in waves that
+// may fire and spectra in the order of their 16-byte loads saved 30 of them.  Whole calls: 8 sub-banks of 512
+// templates, T = 1024, N = 2^20: 7.47 -> 5.47 ms; 4096 templates, T = 256, N = 2^19: 2.69 -> 2.20 ms.
 template <int K, int NF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_ols(OlsArgs a) {
   __shared__ float2 lds[BlockFft<K>::F * BlockFft<K>::LDS];
@@ -383,10 +380,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 }
 
 // ------------------------------------------------------------------ host
-// Measured throughput of each block size per unit of FFT work, relative to
-// K = 2048: the kernels run at the VALU issue limit, so it follows their
-// instructions per (5 log2 K + 6) K flops (70.1, 68.0 and 67.0 TFLOP/s at T = 256,
-// 67.0, 68.7 and 68.0 at T = 512, whole segments of 2^19 samples).
+// Throughput of each block size per unit of FFT work, relative to K = 2048: the kernels run at the VALU issue
+// limit, so it follows their instructions per (5 log2 K + 6) K flops.  Whole segments of 2^19 samples, T = 256: 70.1, 68.0
+// and 67.0 TFLOP/s (1.03 : 1 : 0.985).  At T = 512 67.0, 68.7 and 68.0 (0.975 : 1 : 0.99), but there K = 1024 keeps half of
+// each block and is not chosen at any of these ratios.
 static double ols_efficiency(int K) { return K == 1024 ? 1.02 : (K == 2048 ? 1.0 : 0.99); }
 // ... and the gain of an aligned output length (L = 256 NF): the discarded outputs
 // are never computed (12 of 608 instructions at K = 4096 and NF = 12).  With these
